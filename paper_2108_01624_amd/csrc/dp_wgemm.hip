@@ -679,25 +679,58 @@ __global__ __launch_bounds__(512) void wgemm_dma16_kernel(WgemmBatchArgs b) {
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be writing LDS when the workgroup ends
 
-    // MFMA tile (i, j): accumulator register r of lane l holds row 4*(l/16) + r, column l%16.
+    // MFMA tile (i, j): accumulator register r of lane l holds row 4*(l/16) + r, column l%16.  Buffer accesses over 16 rows of
+    // the output at a time: rows past d_in lie outside the resource, lanes of columns past d_out get an offset outside it, so
+    // there is no branch around an access.  The loads of two tile rows (32 a lane) are in flight while the two before them are
+    // stored: written as one "*dst += x" after the other, each of the 128 accesses of a lane waited for its own round trip,
+    // 40 us a workgroup (28 layers of 768 x 768, K = 1,024 rows: 95 -> 59 us a launch; 30,528 x 1,024, K = 5,120: 435 -> 368 us;
+    // 4 layers of 1024 x 4096, K = 65,536: 1,902 -> 1,871 us).
     float* base = b.L[layer].out + (EPI == EPI_STORE ? (size_t)split * a.d_in * a.d_out : (size_t)0);
+    uint32_t voff[NI];
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+    for (int j = 0; j < NI; ++j) {
+        const int q = q0 + wc * WN + 16 * j + (lane & 15);
+        voff[j] = q < a.d_out ? (uint32_t)(4 * (lane >> 4) * a.d_out + q) * 4u : 0x80000000u;  // + at most 3 rows: still outside
+    }
+    const uint32_t pitch = (uint32_t)a.d_out * 4u;
+    auto row_rsrc = [&](int i) {
+        const int p = p0 + wr * WM + 16 * i;
+        const int rows = a.d_in - p < 16 ? (a.d_in - p < 0 ? 0 : a.d_in - p) : 16;
+        // (the address comes out of an integer division in vector registers: made scalar by hand, or every access becomes a loop)
+        const uint64_t at = (uint64_t)(base + (size_t)p * a.d_out);
+        const uint64_t at_s = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) << 32 |
+                              (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+        return __builtin_amdgcn_make_buffer_rsrc((void*)at_s, 0, __builtin_amdgcn_readfirstlane((int)(rows * pitch)), 0x00020000);
+    };
+    float old[2][2][4][NI];
+    auto fetch = [&](int g) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int p = p0 + wr * WM + 16 * i + 4 * (lane >> 4) + r;
-            if (p < a.d_in) {
+        for (int u = 0; u < 2; ++u) {
+            const __amdgpu_buffer_rsrc_t rs = row_rsrc(2 * g + u);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    old[g & 1][u][r][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(voff[j] + r * pitch), 0, 0));
+        }
+    };
+    if (EPI == EPI_ADD) fetch(0);
+#pragma unroll
+    for (int g = 0; g < MI / 2; ++g) {
+        if (EPI == EPI_ADD && g + 1 < MI / 2) fetch(g + 1);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const __amdgpu_buffer_rsrc_t rs = row_rsrc(2 * g + u);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int j = 0; j < NI; ++j) {
-                    const int q = q0 + wc * WN + 16 * j + (lane & 15);
-                    if (q < a.d_out) {
-                        float* dst = base + (size_t)p * a.d_out + q;
-                        if (EPI == EPI_ADD) *dst += acc[i][j][r] * c_cur;
-                        else *dst = acc[i][j][r] * c_cur;
-                    }
+                    const float x = acc[2 * g + u][j][r] * c_cur;
+                    const float y = EPI == EPI_ADD ? old[g & 1][u][r][j] + x : x;
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, y), rs, (int)(voff[j] + r * pitch), 0, 0);
                 }
-            }
         }
+    }
     if (want_bias && lane < 16) {
         // every row of the ones-product equals the column sums; row 0 sits in register 0 of lanes 0..15
         float* bp = a.bias_part + ((size_t)(unit * a.tiles_m + pm) * 2 + wr) * a.d_out;
