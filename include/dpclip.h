@@ -147,10 +147,11 @@ dp_status dp_sqnorms_embedding(dp_ctx* ctx, const int32_t* ids, const void* G, d
  * ------------------------------------------------------------------------------------------------- */
 
 /* sum_W[p,q] += sum_i c_i sum_t A[i,t,p] G[i,t,q];  sum_b[q] += sum_i c_i sum_t G[i,t,q] (sum_b may be NULL).
- * DP_BF16, accumulation in fp32: for T a multiple of 64 and widths >= 256 the operands enter the matrix-core
- * contraction unscaled (exact bf16 products) and the accumulators are rescaled by c_prev / c_next where the
- * example changes; for other shapes the clip factor multiplies G in fp32 and the product is rounded back to
- * bf16 (round-to-nearest-even) before the contraction (relative error of the sum about 1e-3). */
+ * DP_BF16, accumulation in fp32: the operands enter the matrix-core contraction unscaled (exact bf16 products) and the
+ * accumulators are rescaled by c_prev / c_next where the example changes.  Where that would waste much of the work (T well
+ * below a multiple of 32, wide layers) the clip factor may instead multiply G in fp32 once, the product rounded back to
+ * bf16 (round-to-nearest-even) before the contraction (relative error of the sum about 1e-3); T a multiple of 32 above 32
+ * never takes that form.  The bias sums add fp32 products either way. */
 dp_status dp_clip_accumulate_dense(dp_ctx* ctx, const void* A, const void* G, dp_dtype dtype, int B, int T, int d_in,
                                    int d_out, float C, const float* sqnorms, float* sum_W, float* sum_b);
 

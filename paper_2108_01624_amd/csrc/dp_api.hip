@@ -635,7 +635,8 @@ dp_status dp_clip_accumulate_tied_embedding(dp_ctx* ctx, const int32_t* ids, con
         TRY(dpk_embedding_sums(ctx, ids, dY, dtype, B, T, d, V, ctx->cbuf, sum_E));
     }
     if (M == 0) return DP_OK;
-    return dpk_tied_projection_sums(ctx, H, dL, dtype, B, M, d, V, sqnorms, C, sum_E);
+    // the output projection's sum is a dense sum with input dL [B, M, V] and output gradient H [B, M, d]
+    return dpk_weighted_gemm(ctx, dL, H, dtype, B, M, V, d, sqnorms, C, sum_E, nullptr);
 }
 
 // Argument checks of the update; *why is set to a static text on failure.

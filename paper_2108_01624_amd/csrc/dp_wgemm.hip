@@ -54,6 +54,8 @@ struct WgemmArgs {
     int rect_m, rect_n;  // mode 2: the tile grid is cut into rect_m x rect_n rectangles, 8 / nsplit per split;
                          // modes 1 and 3: a unit's tiles are walked in rectangles of this size
     int* err;            // device error word: DP_ERRBIT_NORM is set when a clip factor is NaN (non-finite squared norm)
+    int bias_direct;     // direct-to-LDS kernel: no bias partials, the kernel adds to sum_b (one row split)
+    int flat;            // direct-to-LDS kernel: no clip factors (G holds c * g already), a unit is one run of rows
 };
 
 // Several layers of one shape in one launch (direct-to-LDS kernel): the unit of work distribution is the pair
@@ -368,26 +370,27 @@ __global__ __launch_bounds__(64 * WVM * WVN) void wgemm_bf16_kernel(WgemmArgs a)
 }
 
 // ------------------------------------------------------------------------------------------------
-// Fast path of the clip-weighted sum (T a multiple of BK, both widths >= 256): 256 x 256 tile, 8 waves
-// (2 x 4, wave tile 128 x 64, accumulators in VGPRs, two waves per SIMD).
+// The clip-weighted sum in bf16: block tiles of 256 or 128 by 256 or 128, 8 waves (2 x 4; at 256 x 256 a wave tile of
+// 128 x 64, accumulators in VGPRs, two waves per SIMD).
 //
 //  * Both operand tiles go from global memory straight into LDS (buffer_load ... lds, 16 bytes per lane, a wave
 //    fills two tile rows per instruction): no staging registers, no LDS store instructions, nothing for the
 //    VALU to do per element.  The loads are issued through inline assembly because the compiler would otherwise
 //    wait for ALL outstanding LDS-filling loads before every LDS read; here the wave waits (vmcnt) only for the
-//    stage it is about to publish and keeps the later stages in flight.  Ring of five 32 KiB stages: all of the CU's LDS.
+//    stage it is about to publish and keeps the later stages in flight.  Ring of five 32 KiB stages at 256 x 256: all of the CU's LDS.
 //  * The clip factor is not applied to the operands at all.  All rows of a stage belong to one example, so the
 //    accumulators carry sum_{j<=i} (c_j / c_i) A_j^T G_j: when the stage's example changes they are multiplied
 //    by c_prev / c_next (128 + 32 VALU multiplies per wave per example, spread over the two half-iterations
 //    around the boundary), and by the last c at the end.  The bf16 products are exact in fp32, so this path is
-//    more accurate than rounding c*g to bf16.  Needs whole examples of at least two stages per row split
-//    (T a multiple of 64; the host aligns the splits); other shapes take the register-staged kernel.
+//    more accurate than rounding c*g to bf16.  Row splits are whole examples.  The last stage of an example whose T is no
+//    multiple of 32 is filled up with zero rows by the range check of its buffer resource: up to 31 rows of work for nothing,
+//    still 2.2 times the rate of scaling G while it is staged (4 layers of 768 x 3072, B = 96, T = 100: 615 -> 255 us).
+//    Where that waste is large (T = 20: 12 rows of 32) scale_rows_kernel writes bf16(c*g) once and the rows are contracted as
+//    one run (1024 x 1024, B = 512, T = 20: 62 -> 50 us; a 30,528 x 1,024 table: 659 -> 308); the host prices both forms.
 //  * Bias gradient: column sums of G are one more MFMA with an all-ones A fragment.  Every wave takes that duty
 //    for one stage in 2*tiles_m (tile row pm, wave row wr: stages s with s % (2*tiles_m) == 2*pm + wr), so the
 //    extra work is spread evenly; the partial sums of (split, pm, wr) are added in a fixed order afterwards.
 // ------------------------------------------------------------------------------------------------
-constexpr int DMA_NS = 5;  // LDS ring stages (5 x 32 KiB = all 160 KiB of a CU's LDS)
-
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void dma_load16(i32x4_t rsrc, uint32_t lds_byte_addr, int voff, int soff) {
@@ -417,13 +420,20 @@ __device__ __forceinline__ i32x4_t make_rsrc(const void* base, uint32_t bytes) {
 // same pass, so the chunk swizzle also takes bit 3 of the row.
 __device__ __forceinline__ int swz16(int row) { return ((row & 3) << 2) | (((row >> 3) & 1) << 1); }
 
-template <int EPI>
-__global__ __launch_bounds__(512) void wgemm_dma16_kernel(WgemmBatchArgs b) {
-    constexpr int MI = 8, NI = 4, MH = 4, WVN = 4;  // 16 x 16 tiles per wave: MI x NI, worked on in two halves of MH tile rows
-    constexpr int WM = 128, WN = 64, BM = 256, BN = 256;
-    constexpr int LPS = 4;  // LDS-filling loads per wave per stage (2 for A, 2 for G)
-    __shared__ __attribute__((aligned(16))) uint16_t As[DMA_NS][BK * BM];
-    __shared__ __attribute__((aligned(16))) uint16_t Gs[DMA_NS][BK * BN];
+// 160 KiB of LDS in stages of (BM + BN) x 32 rows, at most 8 (a smaller tile leaves room for a second workgroup on the CU).
+constexpr int dma_stages(int bm, int bn) { return bm + bn >= 512 ? 5 : (bm + bn >= 384 ? 6 : 5); }
+
+// MI x NI tiles of 16 x 16 per wave, 2 x 4 waves: block tile 32 MI x 64 NI (256 or 128 wide either way).
+// ONE_STAGE: examples of one stage (T <= 32) with factors; every stage then rescales.
+template <int MI, int NI, int EPI, bool ONE_STAGE>
+__global__ __launch_bounds__(512, MI * NI <= 8 ? 4 : 2) void wgemm_dma16_kernel(WgemmBatchArgs b) {
+    constexpr int MH = MI / 2, WVN = 4;  // a stage is worked on in two halves of MH tile rows
+    constexpr int WM = 16 * MI, WN = 16 * NI, BM = 2 * WM, BN = 4 * WN;
+    constexpr int NS = dma_stages(BM, BN);
+    constexpr int LA = BM / 128, LG = BN / 128, LPS = LA + LG;  // LDS-filling loads per wave per stage
+    constexpr int CA = BM / 8, CG = BN / 8;                     // 16-byte chunks per tile row
+    __shared__ __attribute__((aligned(16))) uint16_t As[NS][BK * BM];
+    __shared__ __attribute__((aligned(16))) uint16_t Gs[NS][BK * BN];
     const WgemmArgs& a = b.base;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -466,42 +476,65 @@ __global__ __launch_bounds__(512) void wgemm_dma16_kernel(WgemmBatchArgs b) {
         tile = ((rect / rpr) * a.rect_m + r / a.rect_n) * a.tiles_n + (rect % rpr) * a.rect_n + r % a.rect_n;
     }
     const int layer = unit / a.nsplit, split = unit % a.nsplit;
-    const uint16_t* Aptr = b.L[layer].A;
-    const uint16_t* Gptr = b.L[layer].G;
     const int pm = tile / a.tiles_n, qn = tile % a.tiles_n;
     const int p0 = pm * BM, q0 = qn * BN;
     const long k_lo = (long)split * a.rows_per_split;
     const long k_hi = k_lo + a.rows_per_split < a.K ? k_lo + a.rows_per_split : a.K;
-    const int nrows = k_hi > k_lo ? (int)(k_hi - k_lo) : 0;
-    const int nsteps = (nrows + BK - 1) / BK;
+    const int nrows = __builtin_amdgcn_readfirstlane(k_hi > k_lo ? (int)(k_hi - k_lo) : 0);
+    // The unit's rows are n_ex examples of T rows, each cut into spe stages of 32 rows, the last one of T_last (the rows
+    // that follow belong to the next example: the stage's buffer resource ends at the example's last row, so they arrive
+    // as zeros and multiply nothing).  Without factors (a.flat) the unit is one run of nrows rows.
+    const int T = a.flat ? nrows : a.T;
+    const int spe = (T + BK - 1) / BK, T_last = T - (spe - 1) * BK;
+    const int n_ex = a.flat ? (nrows > 0 ? 1 : 0) : __builtin_amdgcn_readfirstlane(nrows / a.T);
 
-    const i32x4_t rA = make_rsrc(Aptr + (size_t)k_lo * a.d_in, (uint32_t)((size_t)nrows * a.d_in * 2));
-    const i32x4_t rG = make_rsrc(Gptr + (size_t)k_lo * a.d_out, (uint32_t)((size_t)nrows * a.d_out * 2));
+    // Resources over the rows of the stage that is issued next; advanced from stage to stage.  (The stage's start is part of
+    // the base: a scalar offset would have to be trusted to the resource's range check.)
+    i32x4_t rA = make_rsrc(b.L[layer].A + (size_t)k_lo * a.d_in, 0);
+    i32x4_t rG = make_rsrc(b.L[layer].G + (size_t)k_lo * a.d_out, 0);
+    int q_issue = 0, left = n_ex * spe;  // stage of its example, and stages still to issue
+    int rows_issue = 0;
+    auto stage_open = [&]() {   // past the last stage: no rows, the loads bring zeros and touch no memory
+        rows_issue = left > 0 ? (q_issue == spe - 1 ? T_last : BK) : 0;
+        rA[2] = __builtin_amdgcn_readfirstlane(rows_issue * a.d_in * 2);
+        rG[2] = __builtin_amdgcn_readfirstlane(rows_issue * a.d_out * 2);
+    };
+    auto advance = [](i32x4_t& r) {
+        const uint64_t p = ((uint64_t)(uint32_t)r[1] << 32 | (uint32_t)r[0]) + (uint32_t)r[2];
+        r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+        r[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
+    };
+    auto stage_close = [&]() {
+        advance(rA);
+        advance(rG);
+        q_issue = q_issue + 1 == spe ? 0 : q_issue + 1;
+        --left;
+    };
 
-    // Load j (0, 1) of this wave fills tile rows 4*wave + 2*j and + 1: lane l -> row + l/32, LDS chunk l%32,
-    // which holds global chunk (l%32) ^ swz16(row).
-    int voffA[2], voffG[2];
-    uint32_t ldsA[2], ldsG[2];
+    // Load j of this wave fills tile rows (LA * wave + j) * 64 / CA .. of A (G likewise): lane l -> row + l / CA, LDS chunk
+    // l % CA, which holds global chunk (l % CA) ^ swz16(row).  Columns past the layer width read neighbouring (valid or
+    // zero) data and only feed output columns that are never stored.
+    int voffA[LA], voffG[LG];
+    uint32_t ldsA[LA], ldsG[LG];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int row0 = 4 * wave + 2 * j, row = row0 + (lane >> 5);
-        const int cg = (lane & 31) ^ swz16(row);
-        voffA[j] = (row * a.d_in + p0 + cg * 8) * 2;
-        voffG[j] = (row * a.d_out + q0 + cg * 8) * 2;
+    for (int j = 0; j < LA; ++j) {
+        const int row0 = (LA * wave + j) * (64 / CA), row = row0 + lane / CA;
+        voffA[j] = (row * a.d_in + p0 + ((lane % CA) ^ swz16(row)) * 8) * 2;
         ldsA[j] = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)&As[0][row0 * BM];
+    }
+#pragma unroll
+    for (int j = 0; j < LG; ++j) {
+        const int row0 = (LG * wave + j) * (64 / CG), row = row0 + lane / CG;
+        voffG[j] = (row * a.d_out + q0 + ((lane % CG) ^ swz16(row)) * 8) * 2;
         ldsG[j] = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)&Gs[0][row0 * BN];
     }
-    auto issue = [&](int st, int buf) {
-        // stages past the range load the last stage again (never multiplied): the stage offset is not part of the
-        // buffer bounds check, so it must not run past the rows
-        const int stc = st < nsteps ? st : (nsteps > 0 ? nsteps - 1 : 0);
-        const int soffA = __builtin_amdgcn_readfirstlane(stc * BK * a.d_in * 2);
-        const int soffG = __builtin_amdgcn_readfirstlane(stc * BK * a.d_out * 2);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            dma_load16(rA, __builtin_amdgcn_readfirstlane(ldsA[j] + buf * (BK * BM * 2)), voffA[j], soffA);
-            dma_load16(rG, __builtin_amdgcn_readfirstlane(ldsG[j] + buf * (BK * BN * 2)), voffG[j], soffG);
-        }
+    // The LPS loads of a stage in the order A0, G0, A1, G1 (what exists of it).
+    auto fill = [&](int k, int slot) {
+        constexpr int MIN = LA < LG ? LA : LG;
+        const bool isA = k < 2 * MIN ? k % 2 == 0 : LA > LG;
+        const int j = k < 2 * MIN ? k / 2 : k - MIN;
+        if (isA) dma_load16(rA, __builtin_amdgcn_readfirstlane(ldsA[j < LA ? j : 0] + slot * (BK * BM * 2)), voffA[j < LA ? j : 0], 0);
+        else dma_load16(rG, __builtin_amdgcn_readfirstlane(ldsG[j < LG ? j : 0] + slot * (BK * BN * 2)), voffG[j < LG ? j : 0], 0);
     };
     // Operand of the 16x16x32 MFMA: lane l holds the 8 consecutive k = 8*(l/16) .. +7 of column l%16 of its tile.  The
     // transposing read hands lane i of a 16-lane group column i of the 4 rows x 16 columns that the group addresses
@@ -534,22 +567,28 @@ __global__ __launch_bounds__(512) void wgemm_dma16_kernel(WgemmBatchArgs b) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
     }
-    const bool want_bias = b.L[layer].sum_b != nullptr;
-    const int duty_mod = 2 * a.tiles_m, duty = 2 * pm + wr;
+    const bool want_bias = EPI != EPI_SQNORM && b.L[layer].sum_b != nullptr;
+    // bias_direct (one row split, few stages): the first wave row of tile row 0 takes every stage and adds its sums itself
+    const int duty_mod = a.bias_direct ? 1 : 2 * a.tiles_m, duty = 2 * pm + wr;
     const uint32_t one2 = 0x3F803F80u;  // two bf16 ones
     const bf16x8_t ones = __builtin_bit_cast(bf16x8_t, u32x4_t{one2, one2, one2, one2});
     auto mma_bias = [&](const bf16x8_t* fg) {
 #pragma unroll
         for (int j = 0; j < NI; ++j) bacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, fg[j], bacc[j], 0, 0, 0);
     };
-    // fragments of one stage: tile rows 0..3 (lo), 4..7 (hi) of A and the four tile columns of G
+    // fragments of one stage: the first (lo) and second (hi) half of the tile rows of A and the tile columns of G
     bf16x8_t fa_lo[MH], fa_hi[MH], fg[NI];
     float c_cur = 1.f;  // clip factor of the example being accumulated (set by the example's first stage)
 
-    // prologue: DMA_NS - 1 stages in flight; publish stage 0
-    constexpr int AHEAD = DMA_NS - 1;  // the newest stage in flight is AHEAD stages past the one being multiplied
+    // prologue: NS - 1 stages in flight; publish stage 0
+    constexpr int AHEAD = NS - 1;  // the newest stage in flight is AHEAD stages past the one being multiplied
 #pragma unroll
-    for (int st = 0; st < AHEAD; ++st) issue(st, st);
+    for (int st = 0; st < AHEAD; ++st) {
+        stage_open();
+#pragma unroll
+        for (int k = 0; k < LPS; ++k) fill(k, st);
+        stage_close();
+    }
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * LPS) : "memory");  // stage 0 has landed
     __syncthreads();
     int buf = 0;      // ring slot of the stage being multiplied
@@ -560,12 +599,11 @@ __global__ __launch_bounds__(512) void wgemm_dma16_kernel(WgemmBatchArgs b) {
 
     // One loop iteration = one stage = one barrier.
     int duty_ctr = 0;  // (index of the stage being multiplied) % duty_mod
-    const int spe = a.T / BK;                                  // stages per example (>= 2)
-    int ex_run = (int)((uint32_t)k_lo / (uint32_t)a.T);        // the next example to start (row splits begin on examples)
-    const int nex = (int)(a.K / a.T);
+    int ex_run = __builtin_amdgcn_readfirstlane(a.flat ? 0 : (int)((uint32_t)k_lo / (uint32_t)a.T));  // the next example to start (row splits begin on examples)
+    const int nex = a.flat ? 0 : (int)(a.K / a.T);
     // lane l: clip factor c_e of example e = (ex & ~63) + l and the rescaling ratio c_{e-1} / c_e that applies when
     // example e starts.  Two plain loads per 64 examples; the compiler's wait for them also waits for the
-    // LDS-filling loads in flight, a bubble once per 256 or more stages.
+    // LDS-filling loads in flight, a bubble once per 64 examples.
     float cvec = 1.f, rvec = 1.f;
     auto load_factors = [&](int ex) {
         const int e = (ex & ~63) + lane;
@@ -575,41 +613,42 @@ __global__ __launch_bounds__(512) void wgemm_dma16_kernel(WgemmBatchArgs b) {
         rvec = dp_clip_factor(n_p, a.C) / cvec;
         if (cvec != cvec) atomicOr(a.err, DP_ERRBIT_NORM);  // NaN factor: this unit's sums become NaN as well
     };
-    if (nsteps > 0) load_factors(ex_run);
-    int s_issue = AHEAD;
+    if (n_ex > 0 && !a.flat) load_factors(ex_run);
     // Rescaling at an example boundary (every accumulator register times c_prev / c_next) is spread over the two halves
     // around it: in the second half of the example's last stage (PRE) a tile of the first half is multiplied in every
     // MFMA slot and a tile of the second half two MFMAs after its own MFMA; the last two tiles directly before their
     // MFMAs in the second half of the next example's first stage (POST).  Every stage kind is a straight-line body.
-    constexpr int PLAIN = 0, POST = 1, PRE = 2;
+    // An example of one stage is both at once (ONE): the two ratios meet in different tiles.
+    constexpr int PLAIN = 0, POST = 1, PRE = 2, ONE = 3;
     float ratio = 1.f;  // c_prev / c_next of the boundary being worked on (set in PRE, used up in POST)
-    auto scale_tile = [&](int i, int j) {
+    auto scale_tile = [&](int i, int j, float by) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i][j][r] *= ratio;
+        for (int r = 0; r < 4; ++r) acc[i][j][r] *= by;
     };
     auto body = [&](auto kind_tag) {
         constexpr int KIND = decltype(kind_tag)::value;
-        const int buf1 = buf + 1 == DMA_NS ? 0 : buf + 1;
+        const float ratio_post = ratio;
+        const int buf1 = buf + 1 == NS ? 0 : buf + 1;
         const bool bias_now = want_bias && duty_ctr == duty;
         duty_ctr = duty_ctr + 1 == duty_mod ? 0 : duty_ctr + 1;
         load_fa(buf, 1, fa_hi);  // needed by the second half
-        if (KIND == POST) {
+        if (KIND & POST) {
             // first stage of example ex_run: take over the example's factor
             const int el = __builtin_amdgcn_readfirstlane(ex_run & 63);
             c_cur = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cvec), el));
             ++ex_run;
         }
-        // first half: tile rows 0..3, tile column by tile column
+        // first half, tile column by tile column
 #pragma unroll
         for (int t = 0; t < MH * NI; ++t) {
             const int i = t % MH, j = t / MH;
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa_lo[i], fg[j], acc[i][j], 0, 0, 0);
         }
-        if (KIND == POST) {
+        if (KIND & POST) {
 #pragma unroll
             for (int j = 0; j < NI; ++j)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) bacc[j][r] *= ratio;
+                for (int r = 0; r < 4; ++r) bacc[j][r] *= ratio_post;
         }
         if (bias_now) mma_bias(fg);
         __builtin_amdgcn_s_setprio(0);
@@ -618,66 +657,86 @@ __global__ __launch_bounds__(512) void wgemm_dma16_kernel(WgemmBatchArgs b) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 2) * LPS) : "memory");
         __syncthreads();
         load_fa(buf1, 0, fa_lo);  // the next stage's first half
-        if (KIND == PRE) {
+        if (KIND & PRE) {
             // last stage of example ex_run - 1; the factors of 64 examples sit in registers (lane = example mod 64)
             if ((ex_run & 63) == 0) load_factors(ex_run);
             const int el = __builtin_amdgcn_readfirstlane(ex_run & 63);
             ratio = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, rvec), el));
         }
-        // second half: tile rows 4..7.  When a tile column is done its G fragment makes room for the next stage's,
-        // and one of the four LDS-filling loads of the newest stage goes out (spread, not back to back: issued
-        // together by all eight waves they queue up in the address unit).
+        // second half.  When a tile column is done its G fragment makes room for the next stage's, and the LDS-filling
+        // loads of the newest stage go out one by one (spread, not back to back: issued together by all eight waves they
+        // queue up in the address unit).
         {
             // of the two waves that share a SIMD, the one in the half that also issues the fills goes first (+3 %
             // measured; raising the priority in the first half as well costs 1 %)
             __builtin_amdgcn_s_setprio(1);
-            const int stc = s_issue < nsteps ? s_issue : (nsteps > 0 ? nsteps - 1 : 0);
-            const int soffA = __builtin_amdgcn_readfirstlane(stc * BK * a.d_in * 2);
-            const int soffG = __builtin_amdgcn_readfirstlane(stc * BK * a.d_out * 2);
+            stage_open();
 #pragma unroll
             for (int t = 0; t < MH * NI; ++t) {
                 const int i = MH + t % MH, j = t / MH;
-                if (KIND == POST && t >= MH * NI - 2) {
+                if ((KIND & POST) && t >= MH * NI - 2) {
                     __builtin_amdgcn_sched_barrier(0);
-                    scale_tile(i, j);
+                    scale_tile(i, j, ratio_post);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa_hi[t % MH], fg[j], acc[i][j], 0, 0, 0);
                 if (t % MH == MH - 1) {
-                    const int jj = j >> 1;
                     __builtin_amdgcn_sched_barrier(0);
                     fg[j] = read_frag(&Gs[buf1][foffG[j]], BN);
-                    if ((j & 1) == 0)
-                        dma_load16(rA, __builtin_amdgcn_readfirstlane(ldsA[jj] + ibuf * (BK * BM * 2)), voffA[jj], soffA);
-                    else
-                        dma_load16(rG, __builtin_amdgcn_readfirstlane(ldsG[jj] + ibuf * (BK * BN * 2)), voffG[jj], soffG);
+#pragma unroll
+                    for (int k = 0; k < LPS; ++k)
+                        if (k * NI / LPS == j) fill(k, ibuf);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if (KIND == PRE) {
+                if (KIND & PRE) {
                     __builtin_amdgcn_sched_barrier(0);
-                    scale_tile(t % MH, t / MH);
-                    if (t >= 2) scale_tile(MH + (t - 2) % MH, (t - 2) / MH);
+                    scale_tile(t % MH, t / MH, ratio);
+                    if (t >= 2) scale_tile(MH + (t - 2) % MH, (t - 2) / MH, ratio);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
+            stage_close();
         }
         __builtin_amdgcn_s_setprio(0);
-        ++s_issue;
-        ibuf = ibuf + 1 == DMA_NS ? 0 : ibuf + 1;
+        ibuf = ibuf + 1 == NS ? 0 : ibuf + 1;
         buf = buf1;
     };
-    // The unit's rows are whole examples (the host aligns row splits to examples), at least two stages each.
-    const int n_ex_unit = nsteps / spe;
-    for (int e = 0; e + 1 < n_ex_unit; ++e) {
-        body(std::integral_constant<int, POST>{});
-        for (int q = 0; q < spe - 2; ++q) body(std::integral_constant<int, PLAIN>{});
-        body(std::integral_constant<int, PRE>{});
+    // The unit's rows are whole examples (the host aligns row splits to examples), or, flat, one run.
+    if (EPI != EPI_SQNORM) {
+        if constexpr (ONE_STAGE) {
+            for (int e = 0; e + 1 < n_ex; ++e) body(std::integral_constant<int, ONE>{});
+        } else {
+            for (int e = 0; e + 1 < n_ex; ++e) {
+                body(std::integral_constant<int, POST>{});
+                for (int q = 0; q < spe - 2; ++q) body(std::integral_constant<int, PLAIN>{});
+                body(std::integral_constant<int, PRE>{});
+            }
+        }
     }
-    if (n_ex_unit > 0) {
+    if (n_ex > 0) {
         body(std::integral_constant<int, POST>{});
         for (int q = 0; q < spe - 1; ++q) body(std::integral_constant<int, PLAIN>{});
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be writing LDS when the workgroup ends
+
+    if constexpr (EPI == EPI_SQNORM) {
+        // rows / columns past the layer's widths hold products of neighbouring data: leave them out
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int p = p0 + wr * WM + 16 * i + 4 * (lane >> 4) + r;
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    const float v = (p < a.d_in && q0 + wc * WN + 16 * j + (lane & 15) < a.d_out) ? acc[i][j][r] : 0.f;
+                    s += v * v;
+                }
+            }
+        const float tot = dp_block_sum<512>(s, reinterpret_cast<float*>(&As[0][0]));
+        if (tid == 0) a.out[((size_t)split * b.n_layers + layer) * ntiles + tile] = tot;
+        return;
+    }
 
     // MFMA tile (i, j): accumulator register r of lane l holds row 4*(l/16) + r, column l%16.  Buffer accesses over 16 rows of
     // the output at a time: rows past d_in lie outside the resource, lanes of columns past d_out get an offset outside it, so
@@ -731,13 +790,13 @@ __global__ __launch_bounds__(512) void wgemm_dma16_kernel(WgemmBatchArgs b) {
                 }
         }
     }
-    if (want_bias && lane < 16) {
-        // every row of the ones-product equals the column sums; row 0 sits in register 0 of lanes 0..15
-        float* bp = a.bias_part + ((size_t)(unit * a.tiles_m + pm) * 2 + wr) * a.d_out;
+    // every row of the ones-product equals the column sums; row 0 sits in register 0 of lanes 0..15
+    if (want_bias && lane < 16 && (!a.bias_direct || duty == 0)) {
+        float* bp = a.bias_direct ? b.L[layer].sum_b : a.bias_part + ((size_t)(unit * a.tiles_m + pm) * 2 + wr) * a.d_out;
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int q = q0 + wc * WN + 16 * j + lane;
-            if (q < a.d_out) bp[q] = bacc[j][0] * c_cur;
+            if (q < a.d_out) bp[q] = (a.bias_direct ? bp[q] : 0.f) + bacc[j][0] * c_cur;
         }
     }
 }
@@ -779,16 +838,81 @@ __global__ __launch_bounds__(512) void mfma_ceiling_kernel(int iters, float* __r
     sink[t] = s;
 }
 
-// sum_b[layer][q] += sum over the layer's nb partial rows, in row order (fixed order).  grid (n_layers, d_out/256).
+// sum_b[layer][q] += sum over the layer's nb partial rows.  64 columns x 4 groups of rows per workgroup: group g adds the rows
+// g, g + 4, ... in ascending order, eight loads in flight, and the four group sums are added as (0+1)+(2+3): fixed order.
+// (One thread per column walking all rows: 10 us for 32 rows; this way 5.)  grid (n_layers, d_out / 64).
 __global__ __launch_bounds__(256) void bias_finish_kernel(WgemmBatchArgs b, int nb) {
+    __shared__ float red[4][64];
     const int layer = blockIdx.x;
     float* dst = b.L[layer].sum_b;
-    const int q = blockIdx.y * 256 + threadIdx.x;
-    if (!dst || q >= b.base.d_out) return;
-    const float* src = b.base.bias_part + (size_t)layer * nb * b.base.d_out + q;
+    if (!dst) return;
+    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const int q = blockIdx.y * 64 + lane;
+    const size_t d = b.base.d_out;
     float t = 0.f;
-    for (int r = 0; r < nb; ++r) t += src[(size_t)r * b.base.d_out];
-    dst[q] += t;
+    if (q < b.base.d_out) {
+        const float* src = b.base.bias_part + (size_t)layer * nb * d + q;
+        int r = g;
+        for (; r + 28 < nb; r += 32) {
+            float p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p[u] = src[(size_t)(r + 4 * u) * d];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t += p[u];
+        }
+        for (; r < nb; r += 4) t += src[(size_t)r * d];
+    }
+    red[g][lane] = t;
+    __syncthreads();
+    if (g == 0 && q < b.base.d_out) dst[q] += (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+}
+
+// Operands for the GEMM without factors: Gs = bf16(c_i * G) (products formed in fp32, rounded to nearest even, as the
+// register-staged kernel rounds what it stages), rows of one example after the other, and the column sums of the fp32 products
+// of a run of rows for the bias (part[layer][run][d], if wanted).  8 columns a thread, 256 columns x 8 rows a workgroup.
+// Bound: HBM, 4 bytes per element.  grid (runs, d / 256, layers).
+struct ScaleBatch {
+    const uint16_t* G[MAX_BATCH];
+    uint16_t* Gs[MAX_BATCH];
+};
+__global__ __launch_bounds__(256) void scale_rows_kernel(ScaleBatch sb, const float* __restrict__ sqnorms, float C, int T, long K, int d,
+                                                         int rows_per, float* __restrict__ part, int* __restrict__ err) {
+    __shared__ float red[8][32][9];
+    const uint16_t* __restrict__ G = sb.G[blockIdx.z];
+    uint16_t* __restrict__ Gs = sb.Gs[blockIdx.z];
+    const int cl = threadIdx.x & 31, ry = threadIdx.x >> 5;
+    const int col = blockIdx.y * 256 + cl * 8;
+    const long r0 = (long)blockIdx.x * rows_per, r1 = r0 + rows_per < K ? r0 + rows_per : K;
+    float s[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s[e] = 0.f;
+    if (col < d) {
+#pragma unroll 4
+        for (long r = r0 + ry; r < r1; r += 8) {
+            const float c = dp_clip_factor(sqnorms[(uint32_t)r / (uint32_t)T], C);
+            if (c != c) atomicOr(err, DP_ERRBIT_NORM);
+            u32x4_t v = *reinterpret_cast<const u32x4_t*>(G + (size_t)r * d + col);
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const f32x2_t x = {dp_bf16_lo(v[w]) * c, dp_bf16_hi(v[w]) * c};
+                s[2 * w] += x[0];
+                s[2 * w + 1] += x[1];
+                v[w] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2_t));
+            }
+            *reinterpret_cast<u32x4_t*>(Gs + (size_t)r * d + col) = v;
+        }
+    }
+    if (!part) return;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[ry][cl][e] = s[e];
+    __syncthreads();
+    const int c2 = threadIdx.x >> 3, e2 = threadIdx.x & 7;
+    if (blockIdx.y * 256 + c2 * 8 < d) {
+        float t = 0.f;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) t += red[r][c2][e2];
+        part[((size_t)blockIdx.z * gridDim.x + blockIdx.x) * d + blockIdx.y * 256 + c2 * 8 + e2] = t;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -861,8 +985,6 @@ void wgemm_dispatch(dp_ctx* ctx, const WgemmArgs& a, unsigned grid, int cfg, boo
 
 // Tile shape: 256 x 256 when both dimensions are at least that large, otherwise 128 x 128.
 static inline bool big_tile(int d_in, int d_out) { return d_in >= 256 && d_out >= 256; }
-// The direct-to-LDS kernel serves the 256 x 256 tile when all rows of a stage share one example.
-static inline bool use_dma_path(int cfg, bool uniform) { return cfg != 0 && uniform; }
 static inline int tile_cfg(int d_in, int d_out) { return big_tile(d_in, d_out) ? 2 : 0; }
 
 // A split's rows of one operand must stay below 2^31 bytes (32-bit buffer offsets).
@@ -904,13 +1026,39 @@ __global__ __launch_bounds__(256) void reduce_layers_kernel(ReduceBatch rb, int 
 }
 }  // namespace
 
-// Row-split count of one launch of the direct-to-LDS kernel over `nl` layers of `ntiles` tiles: the count with the
-// smallest modelled time.  An XCD runs 32 workgroups at a time and gets an eighth of the launch's workgroups, so
-// the launch takes ceil(workgroups / 8 / 32) rounds of one workgroup's time (1 us per step of BK rows at the rate
-// the kernel sustains, plus 8 us of prologue and epilogue); more than one split sends partial sums through memory
-// (written once, read once, about 4 TB/s) and costs one reduction launch.  `spe`: stages per example
+static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, dp_dtype dt, int B, int T, int d_in, int d_out,
+                                     const float* sqnorms, float C, float* sum_W, float* sum_b);
+
+// What a launch of the direct-to-LDS kernel is made of: block tile, with or without factors, and layers per launch.
+constexpr long BIAS_DIRECT_STAGES = 64;
+
+struct DmaPlan {
+    int bm, bn;
+    bool flat;
+    int per_launch;
+};
+
+// What a workgroup of a tile costs in microseconds, measured over 16 layers of 1024 x 1024 and 28 of 768 x 768 with 1,024 to
+// 32,768 rows: a stage of BK rows (256 x 256: 0.94; 128 x 128: 0.61 with two workgroups on a CU and 0.40 alone; mixed tiles
+// 0.58: per flop the large tile is the fastest by a fifth, it reads the fewest fragment bytes from LDS), and prologue plus
+// epilogue, whose share that is bandwidth grows with the part of the chip that is at it.
+struct DmaCost {
+    int wgs;  // workgroups a CU holds
+    double t_stage, t_stage_alone, t_ends, t_ends_full;
+};
+static DmaCost dma_cost(int bm, int bn, bool one_stage) {
+    if (bm == 256 && bn == 256) return {1, 0.94, 0.94, 7.0, 13.0};
+    if (bm == 128 && bn == 128) return one_stage ? DmaCost{2, 0.9, 0.5, 5.0, 7.0} : DmaCost{2, 0.61, 0.40, 5.0, 7.0};
+    return {1, 0.58, 0.58, 6.0, 7.0};
+}
+
+// Row-split count of one launch over `nl` layers of `ntiles` tiles: the count with the smallest modelled time, in
+// microseconds to *t_out.  An XCD runs 32 * wgs workgroups at a time and gets an eighth of the launch's workgroups, so
+// the launch takes ceil(workgroups / 8 / (32 wgs)) rounds of one workgroup's time; more than one split sends partial sums
+// through memory and costs one reduction launch (which finds most of them in the cache: 4 layers of 768 x 3072 in three
+// splits, 190 MB in 30 us).  `spe`: stages per example
 // (splits start on examples).
-static long choose_nsplit_dma(int nl, int ntiles, long ksteps, long spe, int d_in, int d_out) {
+static long choose_nsplit_dma(int nl, int ntiles, long ksteps, long spe, int d_in, int d_out, const DmaCost& c, double* t_out) {
     const long max_split = ksteps / 8 < 1 ? 1 : ksteps / 8;
     long best = 1;
     double best_t = 0.0;
@@ -918,42 +1066,92 @@ static long choose_nsplit_dma(int nl, int ntiles, long ksteps, long spe, int d_i
         const long steps_per = ((ksteps + s - 1) / s + spe - 1) / spe * spe;
         const long se = (ksteps + steps_per - 1) / steps_per;  // the splits that are not empty
         if (se != s && s > 1) continue;                        // the same plan as a smaller s
-        const long per_xcd = ((long)nl * se * ntiles + 7) / 8;
-        const long rounds = (per_xcd + 31) / 32;
-        double t = (double)rounds * ((double)steps_per + 8.0);
-        if (se > 1) t += (double)nl * (double)(se + 2) * d_in * d_out * 4.0 / 4.0e6 + 6.0;
+        const long wg = (long)nl * se * ntiles;
+        const long per_xcd = (wg + 7) / 8;
+        const long rounds = (per_xcd + 32 * c.wgs - 1) / (32 * c.wgs);
+        const double fill = wg >= 256l * c.wgs ? 1.0 : (double)wg / (256.0 * c.wgs);
+        double t = (double)rounds * ((double)steps_per * (wg <= 256 ? c.t_stage_alone : c.t_stage) + c.t_ends + c.t_ends_full * fill);
+        if (se > 1) t += (double)nl * (double)(se + 2) * d_in * d_out * 4.0 / 8.0e6 + 5.0;
         if (s == 1 || t < best_t) {
             best = se;
             best_t = t;
         }
     }
+    *t_out = best_t;
     return best;
 }
 
-// Clip-weighted sums of n same-shaped dense layers.  Layers that the direct-to-LDS kernel can take (bf16, both
-// widths >= 256, T a multiple of the stage height) go out in launches of up to MAX_BATCH layers; anything else
-// falls back to one call per layer.
+// Tile and form for n layers: the smallest modelled time of the whole call.
+static DmaPlan choose_dma_plan(int n, int B, int T, int d_in, int d_out, size_t ws_bytes) {
+    DmaPlan best{0, 0, false, 1};
+    double best_t = 0.0;
+    const long K = (long)B * T;
+    for (int flat = 0; flat < 2; ++flat) {
+        if (flat && T % BK == 0 && T > BK) continue;  // whole stages: nothing to gain
+        size_t per_ws = MAX_BATCH;
+        if (flat) {
+            // layers whose scaled output gradients fit half the workspace (their bias partials are a sixteenth of that)
+            per_ws = ws_bytes / 2 < 1024 ? 0 : (ws_bytes / 2 - 1024) / ((size_t)K * d_out * 2 + 256);
+            if (per_ws < 1) continue;
+        }
+        const long spe = flat ? 1 : (T + BK - 1) / BK;
+        const long ksteps = flat ? (K + BK - 1) / BK : (long)B * spe;
+        const bool one_stage = !flat && T <= BK;
+        for (int bm = one_stage ? 128 : 256; bm >= 128; bm -= 128)
+            for (int bn = one_stage ? 128 : 256; bn >= 128; bn -= 128) {
+                const DmaCost c = dma_cost(bm, bn, one_stage);
+                const int ntiles = ((d_in + bm - 1) / bm) * ((d_out + bn - 1) / bn);
+                // layers per launch: enough to give every CU its workgroups, but no more than one round of them when a
+                // layer has many tiles (workgroups that run at the same time share operands through L2; later rounds do not)
+                long per = 256l * c.wgs / ntiles;
+                if (per < 1) per = 1;
+                if (per > MAX_BATCH) per = MAX_BATCH;
+                if (per > (long)per_ws) per = (long)per_ws;
+                double t = 0.0, tl;
+                const long full = n / per, rest = n % per;
+                if (full) {
+                    choose_nsplit_dma((int)per, ntiles, ksteps, spe, d_in, d_out, c, &tl);
+                    t += full * (tl + 4.0);
+                }
+                if (rest) {
+                    choose_nsplit_dma((int)rest, ntiles, ksteps, spe, d_in, d_out, c, &tl);
+                    t += tl + 4.0;
+                }
+                if (flat) t += (full + (rest ? 1 : 0)) * 4.0 + 4.0 * (double)K * d_out * n / 4.0e6;
+                if (!best.bm || t < best_t) {
+                    best = DmaPlan{bm, bn, flat != 0, (int)per};
+                    best_t = t;
+                }
+            }
+    }
+    return best;
+}
+
+template <int MI, int NI, bool ONE_STAGE>
+static void dma_launch(dp_ctx* ctx, const WgemmBatchArgs& b, unsigned grid, bool split) {
+    if (split) hipLaunchKernelGGL((wgemm_dma16_kernel<MI, NI, EPI_STORE, ONE_STAGE>), dim3(grid), dim3(512), 0, ctx->stream, b);
+    else hipLaunchKernelGGL((wgemm_dma16_kernel<MI, NI, EPI_ADD, ONE_STAGE>), dim3(grid), dim3(512), 0, ctx->stream, b);
+}
+
+// Clip-weighted sums of n same-shaped dense layers.  bf16 layers go out in launches of the direct-to-LDS kernel; fp32 layers
+// and layers without weights one by one.
 dp_status dpk_weighted_gemm_batched(dp_ctx* ctx, int n, const void* const* A, const void* const* G, dp_dtype dt, int B,
                                     int T, int d_in, int d_out, const float* sqnorms, float C, float* const* sum_W,
                                     float* const* sum_b) {
-    const bool dma = dt == DP_BF16 && d_in > 0 && use_dma_path(tile_cfg(d_in, d_out), T % (2 * BK) == 0);
-    if (!dma) {
-        for (int l = 0; l < n; ++l) {
-            dp_status st = dpk_weighted_gemm(ctx, A[l], G[l], dt, B, T, d_in, d_out, sqnorms, C, sum_W[l], sum_b ? sum_b[l] : nullptr);
-            if (st != DP_OK) return st;
-        }
-        return DP_OK;
+    if (dt != DP_BF16 || d_in == 0) {
+        dp_status st = DP_OK;
+        for (int l = 0; st == DP_OK && l < n; ++l)
+            st = weighted_sum_single(ctx, A[l], G[l], dt, B, T, d_in, d_out, sqnorms, C, sum_W[l], sum_b ? sum_b[l] : nullptr);
+        return st;
     }
+    const DmaPlan plan = choose_dma_plan(n, B, T, d_in, d_out, ctx->ws_bytes);
+    const bool one_stage = !plan.flat && T <= BK;
+    const DmaCost cost = dma_cost(plan.bm, plan.bn, one_stage);
     const long K = (long)B * T;
-    const long ksteps = (K + BK - 1) / BK;
-    // layers per launch: enough to give every CU one workgroup, but no more than one round of workgroups when a
-    // layer has many tiles (workgroups that run at the same time share operands through L2; later rounds do not)
-    const int tiles_per_layer = ((d_in + 255) / 256) * ((d_out + 255) / 256);
-    int per_launch = 256 / tiles_per_layer;
-    if (per_launch < 1) per_launch = 1;
-    if (per_launch > MAX_BATCH) per_launch = MAX_BATCH;
-    for (int l0 = 0; l0 < n; l0 += per_launch) {
-        const int nl = n - l0 < per_launch ? n - l0 : per_launch;
+    const long spe = plan.flat ? 1 : (T + BK - 1) / BK;  // row splits begin on examples: the kernel rescales across example boundaries only
+    const long ksteps = plan.flat ? (K + BK - 1) / BK : (long)B * spe;
+    for (int l0 = 0; l0 < n; l0 += plan.per_launch) {
+        const int nl = n - l0 < plan.per_launch ? n - l0 : plan.per_launch;
         WgemmBatchArgs b;
         WgemmArgs& a = b.base;
         a.A = nullptr;
@@ -962,41 +1160,65 @@ dp_status dpk_weighted_gemm_batched(dp_ctx* ctx, int n, const void* const* A, co
         a.sqnorms = sqnorms;
         a.C = C;
         a.err = ctx->err_word;
+        a.flat = plan.flat ? 1 : 0;
         a.T = T;
         a.d_in = d_in;
         a.d_out = d_out;
         a.K = K;
-        a.tiles_m = (d_in + 255) / 256;
-        a.tiles_n = (d_out + 255) / 256;
+        a.tiles_m = (d_in + plan.bm - 1) / plan.bm;
+        a.tiles_n = (d_out + plan.bn - 1) / plan.bn;
         const int ntiles = a.tiles_m * a.tiles_n;
-        const long spe = T / BK;  // row splits begin on examples: the kernel rescales across example boundaries only
-        long nsplit = choose_nsplit_dma(nl, ntiles, ksteps, spe, d_in, d_out);
-        while (!range_ok((ksteps + nsplit - 1) / nsplit * BK, d_in, d_out)) nsplit *= 2;
+        double t_model;
+        long nsplit = choose_nsplit_dma(nl, ntiles, ksteps, spe, d_in, d_out, cost, &t_model);
         bool any_bias = false;
         for (int l = 0; l < nl; ++l)
             if (sum_b && sum_b[l0 + l]) any_bias = true;
-        // partial sums [nl][nsplit][d_in][d_out] and bias partials (one row per unit, tile row and wave row):
-        // fewer splits until the workspace holds both
+        // flat: the scaled output gradients and their column sums per run of rows
+        ScaleBatch sb;
+        const int dblk = (d_out + 255) / 256;
+        long runs = 0, rows_per = 0;
         dp_ws_alloc ws(ctx);
-        float* part = nullptr;
         float* bias_part = nullptr;
+        if (plan.flat) {
+            runs = 2048 / ((long)dblk * nl) < 1 ? 1 : 2048 / ((long)dblk * nl);
+            if (runs > (K + 31) / 32) runs = (K + 31) / 32;
+            if (runs > 256) runs = 256;
+            rows_per = (K + runs - 1) / runs;
+            runs = (K + rows_per - 1) / rows_per;
+            for (int l = 0; l < MAX_BATCH; ++l) {  // (the plan has seen that they fit)
+                sb.G[l] = (const uint16_t*)G[l0 + (l < nl ? l : 0)];
+                sb.Gs[l] = l < nl ? ws.get<uint16_t>((size_t)K * d_out) : sb.Gs[0];
+            }
+            if (any_bias) bias_part = ws.get<float>((size_t)nl * runs * d_out);
+            if (!sb.Gs[nl - 1] || (any_bias && !bias_part)) {
+                DP_SET_ERR(ctx, "workspace too small for the scaled output gradients");
+                return DP_ERR_WORKSPACE;
+            }
+        }
+
+        const size_t ws_mark = ws.off;
+        // partial sums [nl][nsplit][d_in][d_out] and bias partials (one row per unit, tile row and wave row):
+        // fewer splits until the workspace holds both.  One split of few stages adds its bias sums itself: a launch less for
+        // an extra MFMA column in an eighth of the waves' work (and the form that needs no workspace at all).
+        float* part = nullptr;
+        a.bias_direct = 0;
         for (;;) {
-            ws.off = ctx->ws_base;
+            ws.off = ws_mark;
+            if (!plan.flat && any_bias && nsplit == 1 && ksteps <= BIAS_DIRECT_STAGES) {
+                a.bias_direct = 1;
+                break;
+            }
             part = nsplit > 1 ? ws.get<float>((size_t)nl * nsplit * d_in * d_out) : nullptr;
-            bias_part = any_bias ? ws.get<float>((size_t)nl * nsplit * a.tiles_m * 2 * d_out) : nullptr;
+            if (!plan.flat) bias_part = any_bias ? ws.get<float>((size_t)nl * nsplit * a.tiles_m * 2 * d_out) : nullptr;
             if ((nsplit == 1 || part) && (!any_bias || bias_part)) break;
             if (nsplit == 1) {
-                DP_SET_ERR(ctx, "workspace too small for the bias partials");
-                return DP_ERR_WORKSPACE;
+                a.bias_direct = 1;
+                break;
             }
             nsplit = nsplit > 8 ? nsplit - 8 : nsplit / 2;
         }
         const long steps_per = ((ksteps + nsplit - 1) / nsplit + spe - 1) / spe * spe;
-        a.rows_per_split = steps_per * BK;
-        if (!range_ok(a.rows_per_split, d_in, d_out)) {
-            DP_SET_ERR(ctx, "dp_clip_accumulate_dense: workspace too small to split %ld rows", K);
-            return DP_ERR_WORKSPACE;
-        }
+        a.rows_per_split = plan.flat ? steps_per * BK : steps_per / spe * T;
         nsplit = (ksteps + steps_per - 1) / steps_per;
         a.nsplit = (int)nsplit;
         const long nunits = (long)nl * nsplit;
@@ -1041,23 +1263,32 @@ dp_status dpk_weighted_gemm_batched(dp_ctx* ctx, int n, const void* const* A, co
             DP_SET_ERR(ctx, "dp_clip_accumulate_dense: too many tiles");
             return DP_ERR_SHAPE;
         }
+        if (plan.flat) {
+            hipLaunchKernelGGL(scale_rows_kernel, dim3((unsigned)runs, dblk, nl), dim3(256), 0, ctx->stream, sb, sqnorms, C, T, K, d_out,
+                               (int)rows_per, bias_part, ctx->err_word);
+            DP_LAUNCH_CHECK(ctx, "scale_rows");
+        }
         b.n_layers = nl;
         for (int l = 0; l < MAX_BATCH; ++l) {
             const int src = l0 + (l < nl ? l : 0);
             b.L[l].A = (const uint16_t*)A[src];
-            b.L[l].G = (const uint16_t*)G[src];
-            b.L[l].out = nsplit == 1 ? sum_W[src] : part + (size_t)l * nsplit * d_in * d_out;
-            b.L[l].sum_b = sum_b ? sum_b[src] : nullptr;
+            b.L[l].G = plan.flat ? sb.Gs[l] : (const uint16_t*)G[src];
+            b.L[l].out = nsplit == 1 ? sum_W[src] : part + (size_t)(l < nl ? l : 0) * nsplit * d_in * d_out;
+            b.L[l].sum_b = sum_b && !plan.flat ? sum_b[src] : nullptr;
         }
-        const int nb = (int)nsplit * a.tiles_m * 2;  // bias partial rows per layer
         a.bias_part = bias_part;
         {
             dp_prof_scope prof(ctx, DP_PROF_WGEMM, 2.0 * (double)K * d_in * d_out * nl);
-            const dim3 grid((unsigned)nwg), block(512);
-            if (nsplit == 1) hipLaunchKernelGGL((wgemm_dma16_kernel<EPI_ADD>), grid, block, 0, ctx->stream, b);
-            else hipLaunchKernelGGL((wgemm_dma16_kernel<EPI_STORE>), grid, block, 0, ctx->stream, b);
+            if (one_stage) dma_launch<4, 2, true>(ctx, b, (unsigned)nwg, nsplit > 1);
+            else if (plan.bm == 256 && plan.bn == 256) dma_launch<8, 4, false>(ctx, b, (unsigned)nwg, nsplit > 1);
+            else if (plan.bm == 256) dma_launch<8, 2, false>(ctx, b, (unsigned)nwg, nsplit > 1);
+            else if (plan.bn == 256) dma_launch<4, 4, false>(ctx, b, (unsigned)nwg, nsplit > 1);
+            else dma_launch<4, 2, false>(ctx, b, (unsigned)nwg, nsplit > 1);
         }
         DP_LAUNCH_CHECK(ctx, "wgemm_dma");
+        const int nb = !any_bias || a.bias_direct ? 0 : plan.flat ? (int)runs : (int)nsplit * a.tiles_m * 2;  // bias partial rows per layer
+        if (nb)
+            for (int l = 0; l < nl; ++l) b.L[l].sum_b = sum_b[l0 + l];
         if (nsplit > 1) {
             ReduceBatch rb;
             for (int l = 0; l < MAX_BATCH; ++l) {
@@ -1069,8 +1300,8 @@ dp_status dpk_weighted_gemm_batched(dp_ctx* ctx, int n, const void* const* A, co
                                rb, (int)nsplit, n4);
             DP_LAUNCH_CHECK(ctx, "reduce_layers");
         }
-        if (any_bias) {
-            hipLaunchKernelGGL(bias_finish_kernel, dim3(nl, (d_out + 255) / 256), dim3(256), 0, ctx->stream, b, nb);
+        if (nb) {
+            hipLaunchKernelGGL(bias_finish_kernel, dim3(nl, (d_out + 63) / 64), dim3(256), 0, ctx->stream, b, nb);
             DP_LAUNCH_CHECK(ctx, "bias_finish");
         }
     }
@@ -1115,124 +1346,23 @@ dp_status dpk_mfma_ceiling(dp_ctx* ctx, int iters, int launches, double* tflops)
 
 dp_status dpk_weighted_gemm(dp_ctx* ctx, const void* A, const void* G, dp_dtype dt, int B, int T, int d_in, int d_out,
                             const float* sqnorms, float C, float* sum_W, float* sum_b) {
-    const long K = (long)B * T;
-    if (dt == DP_F32) {
-        dp_status st = dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf);
-        if (st != DP_OK) return st;
-        if (d_in > 0) {
-            dim3 grid((d_out + 63) / 64, (d_in + 63) / 64);
-            hipLaunchKernelGGL(wgemm_f32_kernel, grid, dim3(256), 0, ctx->stream, (const float*)A, (const float*)G,
-                               ctx->cbuf, T, K, d_in, d_out, sum_W);
-            DP_LAUNCH_CHECK(ctx, "wgemm_f32");
-        }
-        if (sum_b) return dpk_colstat_sums(ctx, nullptr, G, dt, B, T, d_out, ctx->cbuf, nullptr, sum_b);
-        return DP_OK;
+    return dpk_weighted_gemm_batched(ctx, 1, &A, &G, dt, B, T, d_in, d_out, sqnorms, C, &sum_W, &sum_b);
+}
+
+// A layer in fp32, or one without weights.
+static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, dp_dtype dt, int B, int T, int d_in, int d_out,
+                                     const float* sqnorms, float C, float* sum_W, float* sum_b) {
+    if (dt != DP_F32 && !sum_b) return DP_OK;
+    dp_status st = dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf);
+    if (st != DP_OK) return st;
+    if (d_in > 0) {
+        dim3 grid((d_out + 63) / 64, (d_in + 63) / 64);
+        hipLaunchKernelGGL(wgemm_f32_kernel, grid, dim3(256), 0, ctx->stream, (const float*)A, (const float*)G,
+                           ctx->cbuf, T, (long)B * T, d_in, d_out, sum_W);
+        DP_LAUNCH_CHECK(ctx, "wgemm_f32");
     }
-    if (d_in == 0) {  // no weights: only the bias sums are left
-        if (!sum_b) return DP_OK;
-        dp_status st = dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf);
-        if (st != DP_OK) return st;
-        return dpk_colstat_sums(ctx, nullptr, G, dt, B, T, d_out, ctx->cbuf, nullptr, sum_b);
-    }
-    if (use_dma_path(tile_cfg(d_in, d_out), T % (2 * BK) == 0))
-        return dpk_weighted_gemm_batched(ctx, 1, &A, &G, dt, B, T, d_in, d_out, sqnorms, C, &sum_W, &sum_b);
-    const bool big = big_tile(d_in, d_out);
-    const int BM = big ? 256 : 128, BN = BM;
-    WgemmArgs a;
-    a.A = (const uint16_t*)A;
-    a.G = (const uint16_t*)G;
-    a.sqnorms = sqnorms;
-    a.C = C;
-    a.err = ctx->err_word;
-    a.T = T;
-    a.d_in = d_in;
-    a.d_out = d_out;
-    a.K = K;
-    a.tiles_m = (d_in + BM - 1) / BM;
-    a.tiles_n = (d_out + BN - 1) / BN;
-    const int ntiles = a.tiles_m * a.tiles_n;
-    // split the token rows so that about 256 workgroups exist (one per CU: the 256 x 256 tile's accumulators
-    // leave room for one workgroup per CU); splits come in multiples of 8 (one per XCD) once there are
-    // several, and each split keeps at least 256 rows.
-    const long ksteps = (K + BK - 1) / BK;
-    long nsplit = 1;
-    if (ntiles < 256) {
-        nsplit = (256 + ntiles - 1) / ntiles;
-        const long max_split = (ksteps + 7) / 8;
-        if (nsplit > max_split) nsplit = max_split;
-        if (nsplit >= 8) nsplit = (nsplit / 8) * 8;
-        else if (nsplit > 4) nsplit = max_split >= 8 ? 8 : 4;
-        else if (nsplit == 3) nsplit = 4;
-        if (nsplit > max_split) nsplit = max_split < 1 ? 1 : max_split;
-        if (nsplit < 1) nsplit = 1;
-    }
-    while (!range_ok((ksteps + nsplit - 1) / nsplit * BK, d_in, d_out)) nsplit *= 2;
-    // partial sums [nsplit][d_in][d_out] and bias partials [nsplit][d_out]: fewer splits until the workspace holds both
-    dp_ws_alloc ws(ctx);
-    float* part = nullptr;
-    float* bias_part = nullptr;
-    for (;;) {
-        ws.off = ctx->ws_base;
-        part = nsplit > 1 ? ws.get<float>((size_t)nsplit * d_in * d_out) : nullptr;
-        bias_part = sum_b ? ws.get<float>((size_t)nsplit * d_out) : nullptr;
-        if ((nsplit == 1 || part) && (!sum_b || bias_part)) break;
-        if (nsplit == 1) {
-            DP_SET_ERR(ctx, "workspace too small for the bias partials");
-            return DP_ERR_WORKSPACE;
-        }
-        nsplit = nsplit > 8 ? nsplit - 8 : nsplit / 2;
-    }
-    const long steps_per = (ksteps + nsplit - 1) / nsplit;
-    a.rows_per_split = steps_per * BK;
-    if (!range_ok(a.rows_per_split, d_in, d_out)) {
-        DP_SET_ERR(ctx, "dp_clip_accumulate_dense: workspace too small to split %ld rows", K);
-        return DP_ERR_WORKSPACE;
-    }
-    nsplit = (ksteps + steps_per - 1) / steps_per;
-    a.nsplit = (int)nsplit;
-    a.xcd_map = nsplit >= 8 ? 1 : 0;
-    a.rect_m = a.rect_n = 1;
-    if (nsplit < 8 && 8 % nsplit == 0) {
-        // 8 / nsplit rectangles per split: pick the cut with the smallest half-perimeter (operand bytes per XCD)
-        const int nrect = 8 / (int)nsplit;
-        int best = -1;
-        for (int rm = 1; rm <= nrect; ++rm) {
-            if (nrect % rm) continue;
-            const int rn = nrect / rm;
-            if (a.tiles_m % rm || a.tiles_n % rn) continue;
-            const int cost = a.tiles_m / rm + a.tiles_n / rn;
-            if (best < 0 || cost < best) {
-                best = cost;
-                a.rect_m = rm;
-                a.rect_n = rn;
-            }
-        }
-        if (best >= 0) a.xcd_map = 2;
-    }
-    a.bias_part = bias_part;
-    const long nwg = a.xcd_map == 1 ? ((nsplit + 7) / 8) * 8 * ntiles : nsplit * ntiles;
-    if (nwg > 0x7FFFFFFFl) {
-        DP_SET_ERR(ctx, "dp_clip_accumulate_dense: too many tiles");
-        return DP_ERR_SHAPE;
-    }
-    const bool uniform = T % BK == 0;
-    const double flops = 2.0 * (double)K * d_in * d_out;
-    const int cfg = tile_cfg(d_in, d_out);
-    if (nsplit == 1) {
-        a.out = sum_W;
-        dp_prof_scope prof(ctx, DP_PROF_WGEMM, flops);
-        wgemm_dispatch<EPI_ADD, true>(ctx, a, (unsigned)nwg, cfg, uniform);
-    } else {
-        a.out = part;
-        dp_prof_scope prof(ctx, DP_PROF_WGEMM, flops);
-        wgemm_dispatch<EPI_STORE, true>(ctx, a, (unsigned)nwg, cfg, uniform);
-    }
-    DP_LAUNCH_CHECK(ctx, "wgemm_bf16");
-    dp_status st = DP_OK;
-    if (nsplit > 1)
-        st = dpk_reduce_partials(ctx, part, (int)nsplit, (size_t)d_in * d_out, (size_t)d_in * d_out, sum_W);
-    if (st == DP_OK && sum_b) st = dpk_reduce_partials(ctx, a.bias_part, (int)nsplit, (size_t)d_out, (size_t)d_out, sum_b);
-    return st;
+    if (sum_b) return dpk_colstat_sums(ctx, nullptr, G, dt, B, T, d_out, ctx->cbuf, nullptr, sum_b);
+    return DP_OK;
 }
 
 dp_status dpk_materialise_sqnorms(dp_ctx* ctx, const void* A, const void* G, dp_dtype dt, int B, int T, int d_in,

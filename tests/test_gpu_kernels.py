@@ -899,6 +899,31 @@ def test_clip_accumulate_dense_batched(dp, n, B, T, d_in, d_out):
             assert_sums_close(host(Sb[l]).astype(np.float64) + 0.5, b_ref, 1e-3, f"layer {l} sum_b")
 
 
+@pytest.mark.parametrize("n,B,T,d_in,d_out", [
+    (1, 1, 1, 8, 8), (2, 300, 1, 64, 72),                    # examples of one row; more than 64 of them (factors are refilled)
+    (3, 9, 31, 136, 136), (1, 80, 32, 128, 128),             # one stage per example, ragged and full
+    (2, 70, 33, 264, 136), (1, 130, 65, 136, 320),           # a stage of one row at the end of every example; mixed tiles
+    (1, 33, 100, 640, 1032), (2, 5, 127, 256, 256),          # ragged last stages on the large tile
+    (1, 600, 20, 1024, 1024), (1, 333, 7, 1032, 520)])       # many short examples on wide layers: scaled operands, no factors
+def test_clip_accumulate_dense_any_row_count(dp, n, B, T, d_in, d_out):
+    """Every form of the bf16 sum: rows per example around the 32-row stage, tiles of 128 and 256.  c * g may be rounded to bf16
+    once (at most 2^-8 per term, on average well below 2^-9); the bias sums always add the fp32 products."""
+    C = 1.0
+    sq = syn.synthetic_sqnorms(B, C, 400)
+    c = orc.clip_factors(sq.astype(np.float64), C)
+    As = [gen((B, T, d_in), 1.0, 410 + l, "bf16") for l in range(n)]
+    Gs = [gen((B, T, d_out), 0.1, 440 + l, "bf16") for l in range(n)]
+    SW = [torch.full((d_in, d_out), 0.25, dtype=torch.float32, device=DEV) for _ in range(n)]
+    Sb = [torch.full((d_out,), -0.5, dtype=torch.float32, device=DEV) for l in range(n)]
+    dp.clip_accumulate_dense_batched([to_dev(a) for a in As], [to_dev(g) for g in Gs], C, f32_dev(sq), SW, Sb)
+    dp.sync()
+    for l in range(n):
+        W_ref, b_ref = orc.clip_accumulate_dense(As[l], Gs[l], c, True)
+        rel = np.linalg.norm(host(SW[l]).astype(np.float64) - 0.25 - W_ref) / np.linalg.norm(W_ref)
+        assert rel < 2.0 ** -9, (l, rel)
+        assert_sums_close(host(Sb[l]).astype(np.float64) + 0.5, b_ref, 1e-4, f"layer {l} sum_b")
+
+
 def test_batched_equals_single_layer_calls(dp):
     """The direct-to-LDS path keeps exact bf16 products: one layer alone and inside a batch agree closely."""
     n, B, T, d_in, d_out, C = 4, 32, 128, 256, 256, 1.0
