@@ -252,14 +252,16 @@ __global__ __launch_bounds__(256) void zero_f32_kernel(float* __restrict__ p, ui
     }
 }
 
-// sqnorms[i] += partial[i*J + 0] + ... + partial[i*J + J-1], in index order.
+// sqnorms[i] += partial[i*J + 0] + ... + partial[i*J + J-1]: one wave per example, lane l adds the partials l, l + 64, ... in
+// ascending order, then a fixed tree over the lanes.  (One thread per example walking its row: J dependent, uncoalesced reads.)
 __global__ __launch_bounds__(256) void finish_partials_kernel(const float* __restrict__ partial, int B, int J,
                                                               float* __restrict__ sqnorms) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (i >= B) return;
     float t = 0.f;
-    for (int j = 0; j < J; ++j) t += partial[(size_t)i * J + j];
-    sqnorms[i] += t;
+    for (int j = lane; j < J; j += 64) t += partial[(size_t)i * J + j];
+    t = dp_wave_sum(t);
+    if (lane == 0) sqnorms[i] += t;
 }
 
 __global__ __launch_bounds__(256) void clip_factors_kernel(const float* __restrict__ sqnorms, int B, float C,
@@ -442,7 +444,7 @@ dp_status dpk_zero_f32(dp_ctx* ctx, float* p, uint64_t n) {
 }
 
 dp_status dpk_finish_partials(dp_ctx* ctx, const float* partial, int B, int J, float* sqnorms) {
-    hipLaunchKernelGGL(finish_partials_kernel, dim3((B + 255) / 256), dim3(256), 0, ctx->stream, partial, B, J,
+    hipLaunchKernelGGL(finish_partials_kernel, dim3((B + 3) / 4), dim3(256), 0, ctx->stream, partial, B, J,
                        sqnorms);
     DP_LAUNCH_CHECK(ctx, "finish_partials");
     return DP_OK;

@@ -411,6 +411,15 @@ __device__ __forceinline__ i32x4_t make_rsrc(const void* base, uint32_t bytes) {
     return r;
 }
 
+// A resource for the buffer builtins whose address and size are the same in every lane but were computed in vector registers
+// (after an integer division, say): made scalar by hand, or every access becomes a loop over its distinct values.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void* base, uint32_t bytes) {
+    const uint64_t p = (uint64_t)base;
+    const uint64_t s = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32 |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)s, 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+}
+
 // The kernel uses the 16x16x32 MFMA.  Per flop it moves as many fragment bytes through LDS as 32x32x16 would, but the
 // matrix pipe draws less power: a loop of nothing but MFMAs on random operands sustains 2.1 PFLOP/s with this shape
 // against 1.4 with 32x32x16 (the chip holds 2.07 against 1.7 GHz; on zeros 2.47 against 1.63 PFLOP/s), and this kernel
@@ -755,11 +764,7 @@ __global__ __launch_bounds__(512, MI * NI <= 8 ? 4 : 2) void wgemm_dma16_kernel(
     auto row_rsrc = [&](int i) {
         const int p = p0 + wr * WM + 16 * i;
         const int rows = a.d_in - p < 16 ? (a.d_in - p < 0 ? 0 : a.d_in - p) : 16;
-        // (the address comes out of an integer division in vector registers: made scalar by hand, or every access becomes a loop)
-        const uint64_t at = (uint64_t)(base + (size_t)p * a.d_out);
-        const uint64_t at_s = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) << 32 |
-                              (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
-        return __builtin_amdgcn_make_buffer_rsrc((void*)at_s, 0, __builtin_amdgcn_readfirstlane((int)(rows * pitch)), 0x00020000);
+        return uniform_rsrc(base + (size_t)p * a.d_out, rows * pitch);
     };
     float old[2][2][4][NI];
     auto fetch = [&](int g) {
@@ -916,50 +921,197 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(ScaleBatch sb, const fl
 }
 
 // ------------------------------------------------------------------------------------------------
-// fp32 path (small shapes, fp32 inputs): 64 x 64 output tile per workgroup, 16 x 16 threads, 4 x 4 each.
+// fp32 inputs, on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: products and sums in fp32).  The contraction index is
+// the slow index of both operands in memory and the MFMA wants one k per half-wave: a lane's operand is simply the element
+// (row k + lane / 32, column lane % 32), 128 contiguous bytes a half-wave, straight from global memory into registers.  A
+// workgroup owns a tile of 32 TE x 32 TE; its 8 waves take the row pairs in turn (16 flop per byte of L2 at TE = 2: 10 TB/s at
+// the full matrix rate, a third of what L2 delivers) and their accumulators meet in LDS.  c_i multiplies G on the way in;
+// the workgroups of tile row 0 also add up the columns of c * G for the bias.
+// 1024 x 1024, 8,192 rows: 107 TFLOP/s of the 154 that the vendor's fp32 product reaches.
+// B * T = 2,048 rows, 768 x 768: 397 + 9 (bias) -> 46 us (16 x 16 threads with 4 x 4 sums each, before); 64 x 64, 512 rows: 70 -> 8 us.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void wgemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ G,
-                                                        const float* __restrict__ c, int T, long K, int d_in,
-                                                        int d_out, float* __restrict__ out) {
-    __shared__ float As[16][64 + 4];
-    __shared__ float Gs[16][64 + 4];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int p0 = blockIdx.y * 64, q0 = blockIdx.x * 64;
-    float acc[4][4];
+constexpr int F32_WAVES = 8;
+constexpr int F32_FACTORS = 1024;  // clip factors a workgroup forms itself; with more examples in its rows they come precomputed
+
+template <int TE, bool OWN>
+__global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ G,
+                                                                   const float* __restrict__ c_or_sq, float C, int T, long K,
+                                                                   int d_in, int d_out, long rows_per_split, int add, float* __restrict__ out,
+                                                                   float* __restrict__ out_b, int* __restrict__ err) {
+    constexpr int NR = TE * TE * 16;      // accumulator registers of a wave
+    constexpr int U = TE == 1 ? 16 : 8;   // row pairs a wave has in flight beside those it multiplies
+    __shared__ float part[F32_WAVES / 2][NR][64];
+    __shared__ float bpart[F32_WAVES][TE][64];
+    __shared__ float ctab[OWN ? F32_FACTORS : 1];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
+    const int p0 = blockIdx.y * 32 * TE, q0 = blockIdx.x * 32 * TE;
+    const long k_lo = (long)blockIdx.z * rows_per_split;
+    const long k_hi = k_lo + rows_per_split < K ? k_lo + rows_per_split : K;
+    int pc[TE], qc[TE];  // columns past the widths repeat the last one and feed entries that are never stored
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int e = 0; e < TE; ++e) {
+        const int p = p0 + 32 * e + (lane & 31), q = q0 + 32 * e + (lane & 31);
+        pc[e] = p < d_in ? p : d_in - 1;
+        qc[e] = q < d_out ? q : d_out - 1;
+    }
+    f32x16_t acc[TE][TE];
+    float bs[TE];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-    for (long k0 = 0; k0 < K; k0 += 16) {
-        for (int e = threadIdx.x; e < 16 * 64; e += 256) {
-            const int r = e >> 6, col = e & 63;
-            const long k = k0 + r;
-            const bool ok = k < K;
-            As[r][col] = (ok && p0 + col < d_in) ? A[(size_t)k * d_in + p0 + col] : 0.f;
-            Gs[r][col] = (ok && q0 + col < d_out) ? c[k / T] * G[(size_t)k * d_out + q0 + col] : 0.f;
+    for (int i = 0; i < TE; ++i) {
+        bs[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < TE; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    }
+    const bool do_bias = out_b != nullptr && blockIdx.y == 0;
+    if constexpr (OWN) {
+        const int e_lo = (int)((uint32_t)k_lo / (uint32_t)T), e_hi = k_hi > k_lo ? (int)((uint32_t)(k_hi - 1) / (uint32_t)T) : e_lo - 1;
+        for (int e = e_lo + threadIdx.x; e <= e_hi; e += 64 * F32_WAVES) {
+            const float ce = dp_clip_factor(c_or_sq[e], C);
+            ctab[e - e_lo] = ce;
+            if (ce != ce) atomicOr(err, DP_ERRBIT_NORM);
         }
-        __syncthreads();
+    }
+    // Rows of this lane, relative to k_lo: 2 * wave + half, then every 16th, in blocks of 16 U.  Buffer loads whose resource ends
+    // at the split's last row: a row past it arrives as zeros, and there is no branch or select around a load.
+    constexpr int BLK = 2 * F32_WAVES * U;
+    const int r_first = 2 * wave + half, n_rows = k_hi > k_lo ? (int)(k_hi - k_lo) : 0;
+    const uint32_t pitchA = (uint32_t)d_in * 4u, pitchG = (uint32_t)d_out * 4u;
+    uint32_t voffA[TE], voffG[TE];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float av[4], gv[4];
+    for (int e = 0; e < TE; ++e) {
+        voffA[e] = r_first * pitchA + pc[e] * 4u;
+        voffG[e] = r_first * pitchG + qc[e] * 4u;
+    }
+    struct Rows {
+        float a[U][TE], g[U][TE];
+    };
+    struct Src {
+        __amdgpu_buffer_rsrc_t A, G;
+    };
+    auto block = [&](int it) {  // resources over the rows of block `it`
+        const int left = n_rows - it * BLK, rows = left < 0 ? 0 : left < BLK ? left : BLK;
+        const size_t at = (size_t)k_lo + (size_t)it * BLK;
+        return Src{uniform_rsrc(A + at * d_in, rows * pitchA), uniform_rsrc(G + at * d_out, rows * pitchG)};
+    };
+    auto load = [&](Rows& x, const Src& s, int u) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) av[i] = As[r][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) gv[j] = Gs[r][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] += av[i] * gv[j];
+        for (int e = 0; e < TE; ++e) {
+            x.a[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(s.A, (int)(voffA[e] + u * 2 * F32_WAVES * pitchA), 0, 0));
+            x.g[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(s.G, (int)(voffG[e] + u * 2 * F32_WAVES * pitchG), 0, 0));
         }
-        __syncthreads();
+    };
+    // The factor of the lane's row.  One step of 16 rows passes one boundary at most when T >= 16: the example follows by
+    // comparison; shorter examples are found by division.  (Either way no memory access and no loop under a branch: the
+    // compiler's count of loads in flight would be lost at the join.)
+    const int e_off = OWN ? (int)((uint32_t)k_lo / (uint32_t)T) : 0;
+    int row = r_first;  // the next row to multiply
+    int ex = (int)((uint32_t)(k_lo + r_first < K ? k_lo + r_first : K - 1) / (uint32_t)T) - e_off;
+    long bound = (long)(ex + e_off + 1) * T - k_lo;  // first row of the next example
+    auto factors = [&](float (&w)[U]) {
+        int e[U];
+        if (T >= 2 * F32_WAVES) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool over = row + u * 2 * F32_WAVES >= bound && row + u * 2 * F32_WAVES < n_rows;
+                ex += over ? 1 : 0;
+                bound += over ? T : 0;
+                e[u] = ex;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int r = row + u * 2 * F32_WAVES < n_rows ? row + u * 2 * F32_WAVES : n_rows - 1;
+                e[u] = (int)((uint32_t)(k_lo + r) / (uint32_t)T) - e_off;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = OWN ? ctab[e[u]] : c_or_sq[e[u]];
+        row += BLK;
+    };
+    auto mma = [&](const Rows& x, int u, float w) {
+        float g[TE];
+#pragma unroll
+        for (int j = 0; j < TE; ++j) {
+            // zeros past the range stay zeros: the repeated factor is that of a row inside it, finite or NaN with it
+            g[j] = w * x.g[u][j];
+            bs[j] += g[j];
+        }
+#pragma unroll
+        for (int i = 0; i < TE; ++i)
+#pragma unroll
+            for (int j = 0; j < TE; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[u][i], g[j], acc[i][j], 0, 0, 0);
+    };
+    const int n_iter = (n_rows + BLK - 1) / BLK;  // (the same for every wave)
+    Rows x0, x1;
+    {
+        const Src s = block(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {  // (in order: the wait counts of the loop are only as tight as the order on entry is certain)
+            load(x0, s, u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if (OWN) __syncthreads();  // the factors are in place
+    auto step = [&](const Rows& now, Rows& next, int it_next) {  // multiply a block, the next one's loads spread between the MFMAs
+        float w[U];
+        factors(w);
+        const Src s = block(it_next);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            load(next, s, u);
+            mma(now, u, w[u]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    for (int it = 0; it < n_iter; it += 2) {
+        step(x0, x1, it + 1);
+        step(x1, x0, it + 2);
+    }
+    // waves w + 4 hand their tiles to waves w, whose four sums every wave then adds for an eighth of the registers
+    constexpr int HW = F32_WAVES / 2;
+#pragma unroll
+    for (int e = 0; e < TE; ++e) bpart[wave][e][lane] = bs[e];
+    if (wave >= HW) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) part[wave - HW][r][lane] = acc[r / (16 * TE)][r / 16 % TE][r % 16];
+    }
+    __syncthreads();
+    if (wave < HW) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) part[wave][r][lane] += acc[r / (16 * TE)][r / 16 % TE][r % 16];
+    }
+    __syncthreads();
+    float* __restrict__ dst = out + (size_t)blockIdx.z * (add ? 0 : (size_t)d_in * d_out);
+    constexpr int NK = NR / F32_WAVES;
+    float old[NK];
+    auto place = [&](int k, int& p, int& q) {  // accumulator register r of lane l: row 8*(r/4) + 4*(l/32) + r%4, column l%32 of its tile
+        const int r = wave * NK + k, rr = r % 16;
+        p = p0 + 32 * (r / (16 * TE)) + 8 * (rr >> 2) + 4 * half + (rr & 3);
+        q = q0 + 32 * (r / 16 % TE) + (lane & 31);
+        return p < d_in && q < d_out;
+    };
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {  // all the reads first: one after the other with the writes, each waits for its round trip
+        int p, q;
+        old[k] = place(k, p, q) && add ? dst[(size_t)p * d_out + q] : 0.f;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int k = 0; k < NK; ++k) {
+        const int r = wave * NK + k;
+        const float v = (part[0][r][lane] + part[1][r][lane]) + (part[2][r][lane] + part[3][r][lane]);
+        int p, q;
+        if (place(k, p, q)) dst[(size_t)p * d_out + q] = old[k] + v;
+    }
+    if (do_bias && threadIdx.x < 32 * TE && q0 + (int)threadIdx.x < d_out) {
+        const int e = threadIdx.x >> 5, l = threadIdx.x & 31;
+        float t = 0.f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int p = p0 + ty * 4 + i, q = q0 + tx * 4 + j;
-            if (p < d_in && q < d_out) out[(size_t)p * d_out + q] += acc[i][j];
-        }
+        for (int w = 0; w < F32_WAVES; ++w) t += bpart[w][e][l] + bpart[w][e][l + 32];
+        float* o = out_b + (size_t)blockIdx.z * (add ? 0 : d_out) + q0 + threadIdx.x;
+        *o = add ? *o + t : t;
+    }
 }
 
 template <int MI, int NI, int WVM, int WVN, int EPI, bool SCALE, bool UNIFORM_C>
@@ -1353,16 +1505,44 @@ dp_status dpk_weighted_gemm(dp_ctx* ctx, const void* A, const void* G, dp_dtype 
 static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, dp_dtype dt, int B, int T, int d_in, int d_out,
                                      const float* sqnorms, float C, float* sum_W, float* sum_b) {
     if (dt != DP_F32 && !sum_b) return DP_OK;
-    dp_status st = dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf);
-    if (st != DP_OK) return st;
-    if (d_in > 0) {
-        dim3 grid((d_out + 63) / 64, (d_in + 63) / 64);
-        hipLaunchKernelGGL(wgemm_f32_kernel, grid, dim3(256), 0, ctx->stream, (const float*)A, (const float*)G,
-                           ctx->cbuf, T, (long)B * T, d_in, d_out, sum_W);
-        DP_LAUNCH_CHECK(ctx, "wgemm_f32");
+    const bool own = d_in > 0 && B <= F32_FACTORS;
+    dp_status st = own ? DP_OK : dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf);
+    if (st != DP_OK || (d_in == 0 && !sum_b)) return st;
+    if (d_in == 0) return dpk_colstat_sums(ctx, nullptr, G, dt, B, T, d_out, ctx->cbuf, nullptr, sum_b);
+    // (fp32 from here.)  Tiles of 64 once they are enough for half the chip, of 32 below that; the rows are split when there are
+    // few tiles and many rows (partial sums through the workspace, one reduction launch each), as far as the workspace goes.
+    const long K = (long)B * T;
+    const long t64 = (long)((d_in + 63) / 64) * ((d_out + 63) / 64);
+    const int te = t64 >= 128 ? 2 : 1;
+    const int tm = (d_in + 32 * te - 1) / (32 * te), tn = (d_out + 32 * te - 1) / (32 * te);
+    long nsplit = 256 / ((long)tm * tn);
+    if (nsplit > K / 1024) nsplit = K / 1024;
+    float *part = nullptr, *bpart = nullptr;
+    if (nsplit > 1) {
+        dp_ws_alloc ws(ctx);
+        part = ws.get<float>((size_t)nsplit * d_in * d_out);
+        bpart = ws.get<float>((size_t)nsplit * d_out);
     }
-    if (sum_b) return dpk_colstat_sums(ctx, nullptr, G, dt, B, T, d_out, ctx->cbuf, nullptr, sum_b);
-    return DP_OK;
+    if (!part || !bpart) nsplit = 1;
+    const long rows = ((K + nsplit - 1) / nsplit + 1) / 2 * 2;
+    nsplit = (K + rows - 1) / rows;
+    const dim3 grid(tn, tm, (unsigned)nsplit), block(64 * F32_WAVES);
+    const int add = nsplit == 1 ? 1 : 0;
+    float* o = add ? sum_W : part;
+    float* ob = !sum_b ? nullptr : add ? sum_b : bpart;
+    auto launch = [&](auto te_tag, auto own_tag) {
+        hipLaunchKernelGGL((wgemm_f32_kernel<decltype(te_tag)::value, decltype(own_tag)::value>), grid, block, 0, ctx->stream, (const float*)A,
+                           (const float*)G, own ? sqnorms : ctx->cbuf, C, T, K, d_in, d_out, rows, add, o, ob, ctx->err_word);
+    };
+    if (te == 2 && own) launch(std::integral_constant<int, 2>{}, std::true_type{});
+    else if (te == 2) launch(std::integral_constant<int, 2>{}, std::false_type{});
+    else if (own) launch(std::integral_constant<int, 1>{}, std::true_type{});
+    else launch(std::integral_constant<int, 1>{}, std::false_type{});
+    DP_LAUNCH_CHECK(ctx, "wgemm_f32");
+    if (add) return DP_OK;
+    st = dpk_reduce_partials(ctx, part, (int)nsplit, (size_t)d_in * d_out, (size_t)d_in * d_out, sum_W);
+    if (st == DP_OK && sum_b) st = dpk_reduce_partials(ctx, bpart, (int)nsplit, (size_t)d_out, (size_t)d_out, sum_b);
+    return st;
 }
 
 dp_status dpk_materialise_sqnorms(dp_ctx* ctx, const void* A, const void* G, dp_dtype dt, int B, int T, int d_in,

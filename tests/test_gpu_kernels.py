@@ -924,6 +924,33 @@ def test_clip_accumulate_dense_any_row_count(dp, n, B, T, d_in, d_out):
         assert_sums_close(host(Sb[l]).astype(np.float64) + 0.5, b_ref, 1e-4, f"layer {l} sum_b")
 
 
+@pytest.mark.parametrize("B,T,d_in,d_out", [(1, 1, 1, 1), (3, 33, 33, 31), (5, 64, 130, 4), (2, 97, 260, 520), (40, 3, 65, 129),
+                                            (1100, 2, 36, 40),      # more examples than a workgroup forms factors for
+                                            (9, 700, 64, 32),       # rows split over workgroups
+                                            (2, 40, 1030, 600)])    # tiles of 64
+def test_dense_f32_forms(dp, B, T, d_in, d_out):
+    """fp32 norms (both paths) and sums around the 32-row cells, 32- and 64-wide tiles and 16-row steps.  Sums of K fp32 terms:
+    error about sqrt(K) 6e-8 relative to the terms' norm, 1e-5 with room for cancellation (as the other fp32 tests)."""
+    import paper_2108_01624_amd as pkg
+
+    A, G = gen((B, T, d_in), 1.0, 500, "f32"), gen((B, T, d_out), 0.1, 501, "f32")
+    A_d, G_d = to_dev(A), to_dev(G)
+    n_ref = orc.sqnorms_dense(A, G, True)
+    for path in (pkg.DP_PATH_GRAM, pkg.DP_PATH_MATERIALISE):
+        n = torch.full((B,), 2.0, dtype=torch.float32, device=DEV)
+        dp.sqnorms_dense(A_d, G_d, True, path, n)
+        dp.sync()
+        assert_norms_close(host(n), n_ref + 2.0, 1e-5, f"path {path}")
+    sq = syn.synthetic_sqnorms(B, 1.0, 502)
+    W_ref, b_ref = orc.clip_accumulate_dense(A, G, orc.clip_factors(sq.astype(np.float64), 1.0), True)
+    W = torch.full((d_in, d_out), 0.25, dtype=torch.float32, device=DEV)
+    b = torch.full((d_out,), -0.5, dtype=torch.float32, device=DEV)
+    dp.clip_accumulate_dense(A_d, G_d, 1.0, f32_dev(sq), W, b)
+    dp.sync()
+    assert_sums_close(host(W).astype(np.float64) - 0.25, W_ref, 1e-5, "sum_W")
+    assert_sums_close(host(b).astype(np.float64) + 0.5, b_ref, 1e-5, "sum_b")
+
+
 def test_batched_equals_single_layer_calls(dp):
     """The direct-to-LDS path keeps exact bf16 products: one layer alone and inside a batch agree closely."""
     n, B, T, d_in, d_out, C = 4, 32, 128, 256, 256, 1.0
