@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256, 2) void gram_bf16_kernel(const uint16_t* __res
 }
 
 // ------------------------------------------------------------------------------------------------
-// T <= 128 (one block per example), both widths multiples of 64: the same computation with the row panels
+// T <= 128 (one block per example): the same computation with the row panels
 // streamed straight into a four-stage LDS ring by LDS-filling buffer loads, three 16 KiB chunks in flight per
 // workgroup (the register-staged kernel above keeps one: at two workgroups per CU that is too few bytes in
 // flight to cover the HBM latency at full bandwidth).  The loads go through inline assembly so that the wave
@@ -215,6 +215,9 @@ __device__ __forceinline__ gram_i32x4 gram_rsrc(const void* base, uint32_t bytes
     return r;
 }
 
+// An offset outside every example's byte range (below 2^31): such a lane's 16 bytes of LDS receive zeros.
+constexpr int GRAM_OUTSIDE = (int)0x80000000u;
+
 // GDK: contraction chunk per stage (a row segment of 2*GDK bytes per load); NS: ring stages.
 // Up to GRAM_MAX_BATCH same-shaped layers per launch: workgroup g works on example g % B of layer g / B.  More
 // workgroups than the chip holds at once keep the memory pipeline full across examples (one round of 512
@@ -234,23 +237,33 @@ struct GramBatch {
 };
 
 // out: n_layers == 1: sqnorms, "+="; otherwise partials [B][n_layers], stored.
-template <int GDK, int NS, int WGS_PER_CU>
-__global__ __launch_bounds__(256, WGS_PER_CU) void gram_dma_kernel(GramBatch gb, int T, int d_in, int d_out,
+// ROWS: rows of a panel, 128 (four quadrants of 64 x 64, one of them the mirror of another) or 64 (one).  The WAVES waves are
+// dealt to the quadrants and, where that leaves several to a quadrant, to the k steps of a chunk (their accumulators meet in LDS
+// at the end): a wave alone on its SIMD waits for its fragments k step by k step, 1.4 us a chunk, so with 128 rows and a
+// workgroup or less per CU 8 waves take half the k steps each (12 layers of 768 x 3072, B = 8: 41 -> 36 us; a deeper ring
+// alone changed nothing), and with 64 rows, where one wave of four had work, all four take a quarter each (4 layers of
+// 192 x 2264, B = 106, T = 47: 42 -> 30 us).
+// RAGGED: a width that is no multiple of GDK; what lies past a row's end in its last chunk is left out lane by lane.
+template <int ROWS, int GDK, int NS, int WAVES, int WGS_PER_CU, bool RAGGED>
+__global__ __launch_bounds__(64 * WAVES, WGS_PER_CU * WAVES / 4) void gram_dma_kernel(GramBatch gb, int T, int d_in, int d_out,
                                                                    int has_bias, float* __restrict__ out) {
-    constexpr int STAGE = GB * GDK;        // bf16 elements per stage
+    constexpr int STAGE = ROWS * GDK;      // bf16 elements per stage
     constexpr int CPR = GDK / 8;           // 16-byte chunks per row (8 or 16)
     constexpr int RPI = 64 / CPR;          // rows filled by one wave-wide load
-    constexpr int LPS = GB / RPI / 4;      // loads per wave per stage
+    constexpr int LPS = ROWS / RPI / WAVES;  // loads per wave per stage
+    constexpr int NQ = ROWS == 128 ? 4 : 1, KS = WAVES / NQ;  // quadrants, waves that share a quadrant's k steps
+    static_assert(LPS >= 1 && GDK / 16 >= KS, "more waves than there is work");
+    static_assert(NS * STAGE * 2 >= NQ * 32 * 1024 || KS == 1, "the ring doubles as the exchange buffer");
     __shared__ __attribute__((aligned(16))) uint16_t ring[NS][STAGE];
-    __shared__ float wred[4];
+    __shared__ float wred[WAVES];
     const int layer = blockIdx.x / gb.B, i = blockIdx.x - layer * gb.B;
     const uint16_t* __restrict__ A = gb.A[layer];
     const uint16_t* __restrict__ G = gb.G[layer];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wr = wave >> 1, wc = wave & 1;
+    const int quad = KS == 1 ? wave : NQ == 1 ? 0 : wave % NQ, kg = KS == 1 ? 0 : wave / NQ, wr = quad >> 1, wc = quad & 1;
     const bool active = wr <= wc;  // the lower-left quadrant mirrors the upper-right one
     const bool diagw = wr == wc;   // ... and inside a diagonal quadrant the lower-left 32 x 32 tile the upper-right one
-    const int nchA = d_in / GDK, nchG1 = d_out / GDK, nch = nchA + gb.n_out * nchG1;
+    const int nchA = (d_in + GDK - 1) / GDK, nchG1 = (d_out + GDK - 1) / GDK, nch = nchA + gb.n_out * nchG1;
     // chunk position c of row r holds global chunk c ^ swz(r): 16 consecutive rows -> 64 distinct banks
     auto swz = [](int r) { return CPR == 8 ? (r >> 1) & 7 : r & 15; };
 
@@ -286,10 +299,14 @@ __global__ __launch_bounds__(256, WGS_PER_CU) void gram_dma_kernel(GramBatch gb,
         // one choice of the source per stage, then a straight run of loads (every descriptor is a variable of its own
         // and stays in scalar registers; with the choice inside the loop each load of an output-gradient stage went
         // through a chain of branches)
+        const int left = st >= nch ? 0 : (isA ? d_in : d_out) - cr * GDK;  // columns of the row from this chunk on; past the end: none
         auto run = [&](const gram_i32x4& rs, const int (&voff)[LPS], int so) {
 #pragma unroll
-            for (int j = 0; j < LPS; ++j)
-                gram_dma16<true>(rs, __builtin_amdgcn_readfirstlane(ldsoff[j] + ibuf * (STAGE * 2)), voff[j], so);
+            for (int j = 0; j < LPS; ++j) {
+                int v = voff[j];
+                if (RAGGED && ((lane % CPR) ^ swz((LPS * wave + j) * RPI + lane / CPR)) * 8 >= left) v = GRAM_OUTSIDE;  // past the row's end: zeros
+                gram_dma16<true>(rs, __builtin_amdgcn_readfirstlane(ldsoff[j] + ibuf * (STAGE * 2)), v, so);
+            }
         };
         if (isA) run(rA, voffA, soff);
         else if (st >= nch) run(rG, voffG, 0x7FFFFFF0);  // past the end: reads zeros, keeps the load count uniform
@@ -323,7 +340,8 @@ __global__ __launch_bounds__(256, WGS_PER_CU) void gram_dma_kernel(GramBatch gb,
         constexpr bool DG = decltype(diag_tag)::value;
         const uint16_t* st = ring[cbuf];
 #pragma unroll
-        for (int kk = 0; kk < GDK / 16; ++kk) {
+        for (int step = 0; step < GDK / 16 / KS; ++step) {
+            const int kk = step * KS + kg;
             bf16x8_t a0[2], b0[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -356,7 +374,36 @@ __global__ __launch_bounds__(256, WGS_PER_CU) void gram_dma_kernel(GramBatch gb,
     };
     phase(nchA, accA);
     phase(nch, accG);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be writing LDS when the workgroup ends
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be writing LDS when the workgroup ends, or when it is reused
+    if constexpr (KS > 1) {
+        float* part = reinterpret_cast<float*>(&ring[0][0]) + quad * (128 * 64);  // [A | G][2][2][register][lane]
+        for (int g = 1; g < KS; ++g) {  // the groups' sums are added in group order
+            __syncthreads();
+            if (kg == g) {
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            part[((a * 2 + b) * 16 + r) * 64 + lane] = accA[a][b][r];
+                            part[((4 + a * 2 + b) * 16 + r) * 64 + lane] = accG[a][b][r];
+                        }
+            }
+            __syncthreads();
+            if (kg == 0) {
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            accA[a][b][r] += part[((a * 2 + b) * 16 + r) * 64 + lane];
+                            accG[a][b][r] += part[((4 + a * 2 + b) * 16 + r) * 64 + lane];
+                        }
+            }
+        }
+    }
     const float bias_term = has_bias ? 1.f : 0.f;
     float sum = 0.f;
 #pragma unroll
@@ -366,8 +413,8 @@ __global__ __launch_bounds__(256, WGS_PER_CU) void gram_dma_kernel(GramBatch gb,
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 sum += (a == 0 && b == 1 && diagw ? 2.f : 1.f) * ((accA[a][b][r] + bias_term) * accG[a][b][r]);  // skipped tiles hold zeros
-    sum *= wr == wc ? 1.f : (wr < wc ? 2.f : 0.f);
-    const float tot = dp_block_sum<256>(sum, wred);
+    sum *= kg > 0 ? 0.f : wr == wc ? 1.f : (wr < wc ? 2.f : 0.f);
+    const float tot = dp_block_sum<64 * WAVES>(sum, wred);
     if (threadIdx.x == 0) {
         if (gb.n_layers == 1) out[i] += tot;
         else out[(size_t)i * gb.n_layers + layer] = tot;
@@ -375,7 +422,7 @@ __global__ __launch_bounds__(256, WGS_PER_CU) void gram_dma_kernel(GramBatch gb,
 }
 
 // ------------------------------------------------------------------------------------------------
-// T > 128, widths multiples of 64: the panels of a 64-wide contraction chunk go straight into an LDS ring (no staging
+// 128 < T <= 2048: the panels of a 64-wide contraction chunk go straight into an LDS ring (no staging
 // registers, no LDS store instructions), as in the kernel above.  At this size the contraction, not HBM, is the bound on
 // paper (T flop per byte against ~310 at the machine balance); in practice it is the path that fills the LDS (a CU takes
 // about 120 GB/s from L2 this way, and a panel costs 16 KiB per stage) together with the matrix pipe.  A
@@ -410,7 +457,7 @@ struct GramUnits {
 
 // NPL: panels filled per stage (1: a diagonal cell alone; 2: a diagonal block, a diagonal cell + one more of its row, or
 // one off-diagonal cell; 3: two off-diagonal cells).  BLK: the unit is a diagonal block (cells (R, R), (R, C2), (C2, C2)).
-template <int NPL, bool BLK>
+template <int NPL, bool BLK, bool RAGGED>
 __device__ __forceinline__ float gram_unit_ring(const uint16_t* __restrict__ A, const uint16_t* __restrict__ G, int T, int d_in,
                                                 int d_out, int R, int C1, int C2, float bias_term, uint16_t* ring) {
     static_assert(!BLK || NPL == 2, "a diagonal block has two panels");
@@ -427,7 +474,7 @@ __device__ __forceinline__ float gram_unit_ring(const uint16_t* __restrict__ A, 
     const bool active = BLK || (cell == 0 ? (!diag0 || wr <= wc) : two);
     const bool diagw = !BLK && cell == 0 && diag0 && wr == wc;  // a diagonal quadrant of a diagonal cell: tiles below its diagonal mirror those above
     const bool twodiag = BLK && wave >= 6;                      // two diagonal quadrants of a diagonal block
-    const int nchA = d_in / GU_K, nch = nchA + d_out / GU_K;
+    const int nchA = (d_in + GU_K - 1) / GU_K, nch = nchA + (d_out + GU_K - 1) / GU_K;
     auto swz = [](int r) { return (r >> 1) & 7; };
     // rows >= T lie outside the example's byte range and read as zero
     const gram_i32x4 rA = gram_rsrc(A, (uint32_t)((size_t)T * d_in * 2));
@@ -455,12 +502,16 @@ __device__ __forceinline__ float gram_unit_ring(const uint16_t* __restrict__ A, 
         // (rotating the chunk order by the example index, which pays in gram_dma_kernel, costs 1-2 % here: the units of an
         // example need their panels at the same time, and any order serves that)
         const int soff = __builtin_amdgcn_readfirstlane((isA ? stc : stc - nchA) * GU_K * 2);
+        const int left = isA ? d_in - stc * GU_K : d_out - (stc - nchA) * GU_K;  // columns of the row from this chunk on
         auto run = [&](const gram_i32x4& rs, const int (&voff)[NPL][LPP]) {  // (the choice of the source stays outside the run of loads)
 #pragma unroll
             for (int p = 0; p < NPL; ++p)
 #pragma unroll
-                for (int j = 0; j < LPP; ++j)
-                    gram_dma16<false>(rs, __builtin_amdgcn_readfirstlane(ldsoff[p][j] + ibuf * (STAGE * 2)), voff[p][j], soff);
+                for (int j = 0; j < LPP; ++j) {
+                    int v = voff[p][j];
+                    if (RAGGED && ((lane & 7) ^ swz((LPP * wave + j) * 8 + (lane >> 3))) * 8 >= left) v = GRAM_OUTSIDE;  // past the row's end: zeros
+                    gram_dma16<false>(rs, __builtin_amdgcn_readfirstlane(ldsoff[p][j] + ibuf * (STAGE * 2)), v, soff);
+                }
         };
         if (isA) run(rA, voffA);
         else run(rG, voffG);
@@ -593,6 +644,7 @@ __device__ __forceinline__ float gram_unit_ring(const uint16_t* __restrict__ A, 
 
 // out: partials [B][n_layers * n_units], stored.  Workgroup id g -> XCD g % 8; (layer, example) u = (g / 8 / n_units) * 8 + g % 8,
 // unit = (g / 8) % n_units: the units of one example share an XCD, so that each panel comes from HBM once.
+template <bool RAGGED>
 __global__ __launch_bounds__(512, 1) void gram_units_kernel(GramBatch gb, GramUnits gu, int T, int d_in, int d_out, int has_bias,
                                                             float* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) uint16_t ring[GU_LDS];
@@ -609,137 +661,36 @@ __global__ __launch_bounds__(512, 1) void gram_units_kernel(GramBatch gb, GramUn
     const float bias_term = has_bias ? 1.f : 0.f;
     const int npl = 1 + (C1 != R ? 1 : 0) + (C2 != 255 ? 1 : 0);
     float s;
-    if (blk) s = gram_unit_ring<2, true>(A, G, T, d_in, d_out, R, C1, C2, bias_term, ring);
-    else if (npl == 3) s = gram_unit_ring<3, false>(A, G, T, d_in, d_out, R, C1, C2, bias_term, ring);
-    else if (npl == 2) s = gram_unit_ring<2, false>(A, G, T, d_in, d_out, R, C1, C2, bias_term, ring);
-    else s = gram_unit_ring<1, false>(A, G, T, d_in, d_out, R, C1, C2, bias_term, ring);
+    if (blk) s = gram_unit_ring<2, true, RAGGED>(A, G, T, d_in, d_out, R, C1, C2, bias_term, ring);
+    else if (npl == 3) s = gram_unit_ring<3, false, RAGGED>(A, G, T, d_in, d_out, R, C1, C2, bias_term, ring);
+    else if (npl == 2) s = gram_unit_ring<2, false, RAGGED>(A, G, T, d_in, d_out, R, C1, C2, bias_term, ring);
+    else s = gram_unit_ring<1, false, RAGGED>(A, G, T, d_in, d_out, R, C1, C2, bias_term, ring);
     __syncthreads();  // the ring is free: its first floats serve the reduction
     const float tot = dp_block_sum<512>(s, reinterpret_cast<float*>(&ring[0]));
     if (threadIdx.x == 0) out[((size_t)i * gb.n_layers + layer) * gu.n_units + unit] = tot;
 }
 
 // ------------------------------------------------------------------------------------------------
-// T <= 32 (the output projection of a tied table has 20 rows per example and a 30K-wide input): one 32 x 32 Gram tile
-// per operand, so the 128-row kernels above would spend their time on empty rows.  One workgroup per example, the
-// contraction split over the 8 waves in chunks of 128 columns; fragments come straight from global memory (lane =
-// (row, half) reads 128 contiguous bytes per chunk, the two lanes of a row 256; the MFMA's k slots take the same
-// columns for both operands of X X^T, which are the same registers).  The waves' accumulators meet in LDS.
-// Bound: HBM, B*T*(d_in+d_out)*2 bytes read once.
+// T <= 32 (prediction slots: 20 rows per example; the output projection of a tied table has a 30K-wide input): one 32 x 32
+// Gram tile per operand, where the 128-row kernel above would spend its time on empty rows.  Fed like gram_dma_kernel: 128-byte
+// row segments of the 32 rows go straight into a ring of 4 KiB stages (one 16-byte-per-lane load per wave and stage, coalesced
+// over 8 rows), and wave w takes k step w of every stage: one fragment read and one MFMA per wave and stage; the waves'
+// accumulators meet in LDS.  NS - 1 stages in flight per workgroup, two workgroups per CU.  Workgroup g works on example
+// g % B of layer g / B, as above.
+// Bound: HBM, B*T*(d_in+d_out)*2 bytes read once: 646 MB in 98 us; one layer of 1024 x 1024, B = 512, T = 20: 28 us on the
+// 128-row kernel, 12 here.
 // ------------------------------------------------------------------------------------------------
-constexpr int GS_WAVES = 8;   // waves per workgroup
-constexpr int GS_CHUNK = 128;  // columns per wave and step (each lane: 64 columns = 128 contiguous bytes)
-
-__device__ __forceinline__ void gram_small_load(const uint16_t* __restrict__ row, bool valid, int d, int kb, int half,
-                                                gram_i32x4 f[8]) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int k = kb + half * 64 + j * 8;  // widths are multiples of 8: a fragment lies inside the row or outside
-        if (valid && k < d) f[j] = __builtin_nontemporal_load(reinterpret_cast<const gram_i32x4*>(row + k));  // read once
-        else f[j] = gram_i32x4{0, 0, 0, 0};
-    }
-}
-
-__device__ __forceinline__ void gram_small_mfma(const gram_i32x4 f[8], f32x16_t& acc) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const bf16x8_t x = __builtin_bit_cast(bf16x8_t, f[j]);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, x, acc, 0, 0, 0);
-    }
-}
-
-// The loads of the next step are issued before the MFMAs of the current one (the kernel lives on bytes in flight):
-// two register sets take turns.
-__device__ __forceinline__ void gram_small_accumulate(const uint16_t* __restrict__ row, bool valid, int d, int wave, int half,
-                                                      f32x16_t& acc) {
-    constexpr int STEP = GS_WAVES * GS_CHUNK;
-    gram_i32x4 f0[8], f1[8];
-    int kb = wave * GS_CHUNK;
-    if (kb >= d) return;
-    gram_small_load(row, valid, d, kb, half, f0);
-    while (true) {
-        if (kb + STEP < d) gram_small_load(row, valid, d, kb + STEP, half, f1);
-        gram_small_mfma(f0, acc);
-        kb += STEP;
-        if (kb >= d) break;
-        if (kb + STEP < d) gram_small_load(row, valid, d, kb + STEP, half, f0);
-        gram_small_mfma(f1, acc);
-        kb += STEP;
-        if (kb >= d) break;
-    }
-}
-
-__global__ __launch_bounds__(64 * GS_WAVES, 4) void gram_small_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ G,
-                                                                   int T, int d_in, int d_out, int has_bias,
-                                                                   float* __restrict__ out) {
-    __shared__ float part[GS_WAVES / 2][2][16][64];
-    __shared__ float wred[GS_WAVES];
-    const int i = blockIdx.x;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int r32 = lane & 31, half = lane >> 5;
-    const bool valid = r32 < T;  // rows from T on stay zero in both Gram tiles
-    const size_t row = (size_t)i * T + (valid ? r32 : 0);
-    f32x16_t accA, accG;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) accA[r] = 0.f;
-    gram_small_accumulate(A + row * d_in, valid, d_in, wave, half, accA);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) accG[r] = 0.f;
-    gram_small_accumulate(G + row * d_out, valid, d_out, wave, half, accG);
-    // waves w + 4 hand their tiles to waves w, then the four sums meet
-    constexpr int HW = GS_WAVES / 2;
-    if (wave >= HW) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            part[wave - HW][0][r][lane] = accA[r];
-            part[wave - HW][1][r][lane] = accG[r];
-        }
-    }
-    __syncthreads();
-    if (wave < HW) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            accA[r] += part[wave][0][r][lane];
-            accG[r] += part[wave][1][r][lane];
-        }
-    }
-    __syncthreads();
-    if (wave < HW) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            part[wave][0][r][lane] = accA[r];
-            part[wave][1][r][lane] = accG[r];
-        }
-    }
-    __syncthreads();
-    const float bias_term = has_bias ? 1.f : 0.f;
-    float s = 0.f;
-#pragma unroll
-    for (int q = 0; q < 16 / GS_WAVES; ++q) {  // wave w finishes accumulator registers 2w, 2w+1; partial tiles added in index order
-        const int r = wave * (16 / GS_WAVES) + q;
-        const float a = ((part[0][0][r][lane] + part[1][0][r][lane]) + part[2][0][r][lane]) + part[3][0][r][lane];
-        const float g = ((part[0][1][r][lane] + part[1][1][r][lane]) + part[2][1][r][lane]) + part[3][1][r][lane];
-        s += (a + bias_term) * g;
-    }
-    const float tot = dp_block_sum<64 * GS_WAVES>(s, wred);
-    if (threadIdx.x == 0) out[i] += tot;
-}
-
-// The same tile fed like gram_dma_kernel (widths multiples of 64): 128-byte row segments of the 32 rows go straight
-// into a ring of 4 KiB stages (one 16-byte-per-lane load per wave and stage, coalesced over 8 rows), and wave w takes
-// k step w of every stage: one fragment read and one MFMA per wave and stage.  Loading fragments from global memory
-// directly, as the kernel above does, touches 16 bytes of 40 different lines per instruction and was bound by L1/L2
-// traffic (1.9 TB/s); here every line crosses once.  NS - 1 stages in flight per workgroup, two workgroups per CU.
 template <int NS>
-__global__ __launch_bounds__(256, 2) void gram_small_dma_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ G,
-                                                                int T, int d_in, int d_out, int has_bias,
-                                                                float* __restrict__ out) {
+__global__ __launch_bounds__(256, 2) void gram_small_dma_kernel(GramBatch gb, int T, int d_in, int d_out, int has_bias, float* __restrict__ out) {
     constexpr int GDK = 64, ROWS = 32, STAGE = ROWS * GDK, CPR = 8, RPI = 8;  // 4 loads fill a stage: one per wave
     static_assert(NS * STAGE * 2 >= 4 * 2 * 16 * 64 * 4, "the ring doubles as the reduction buffer");
     __shared__ __attribute__((aligned(16))) uint16_t ring[NS][STAGE];
     __shared__ float wred[4];
-    const int i = blockIdx.x;
+    const int layer = blockIdx.x / gb.B, i = blockIdx.x - layer * gb.B;
+    const uint16_t* __restrict__ A = gb.A[layer];
+    const uint16_t* __restrict__ G = gb.G[layer];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nchA = d_in / GDK, nch = nchA + d_out / GDK;
+    const int nchA = (d_in + GDK - 1) / GDK, nch = nchA + (d_out + GDK - 1) / GDK;
     auto swz = [](int r) { return (r >> 1) & 7; };  // chunk position c of row r holds global chunk c ^ swz(r)
     // rows >= T lie outside the example's byte range and read as zero
     const gram_i32x4 rA = gram_rsrc(A + (size_t)i * T * d_in, (uint32_t)((size_t)T * d_in * 2));
@@ -753,9 +704,10 @@ __global__ __launch_bounds__(256, 2) void gram_small_dma_kernel(const uint16_t* 
         const bool isA = st < nchA;
         const int soff = __builtin_amdgcn_readfirstlane((isA ? st : st - nchA) * GDK * 2);
         const uint32_t dst = __builtin_amdgcn_readfirstlane(ldsoff + ibuf * (STAGE * 2));
-        if (isA) gram_dma16<true>(rA, dst, voffA, soff);
-        else if (st >= nch) gram_dma16<true>(rG, dst, voffG, 0x7FFFFFF0);  // past the end: reads zeros, keeps the load count uniform
-        else gram_dma16<true>(rG, dst, voffG, soff);
+        // columns past the row's end, and whole stages past the last, arrive as zeros (the load count stays uniform)
+        const int left = st >= nch ? 0 : isA ? d_in - st * GDK : d_out - (st - nchA) * GDK;
+        if (isA) gram_dma16<true>(rA, dst, cg * 8 < left ? voffA : GRAM_OUTSIDE, soff);
+        else gram_dma16<true>(rG, dst, cg * 8 < left ? voffG : GRAM_OUTSIDE, st >= nch ? 0 : soff);
         ibuf = ibuf + 1 == NS ? 0 : ibuf + 1;
     };
     const int r = lane & 31;
@@ -803,7 +755,10 @@ __global__ __launch_bounds__(256, 2) void gram_small_dma_kernel(const uint16_t* 
         sum += (a + bias_term) * g;
     }
     const float tot = dp_block_sum<256>(sum, wred);
-    if (threadIdx.x == 0) out[i] += tot;
+    if (threadIdx.x == 0) {
+        if (gb.n_layers == 1) out[i] += tot;
+        else out[(size_t)i * gb.n_layers + layer] = tot;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -966,21 +921,32 @@ __global__ __launch_bounds__(256) void materialise_f32_kernel(const float* __res
 
 }  // namespace
 
-// The LDS-ring kernel serves one 128 x 128 block per example and widths that are multiples of its row segment.
+// The LDS-ring kernels serve one block of up to 128 rows per example.
 static bool gram_dma_ok(int T, int d_in, int d_out) {
-    return T <= GB && d_in % GK == 0 && d_out % GK == 0 && d_in > 0 && d_out > 0 &&
-           (size_t)T * (d_in > d_out ? d_in : d_out) * 2 < (1u << 31);
+    return T <= GB && d_in > 0 && d_out > 0 && (size_t)GB * (d_in > d_out ? d_in : d_out) * 2 < (1u << 31);
 }
 
 static dp_status gram_dma_launch(dp_ctx* ctx, const GramBatch& gb, int T, int d_in, int d_out, int has_bias, float* out,
                                  double bytes) {
     dp_prof_scope prof(ctx, DP_PROF_GRAM, bytes);
-    const dim3 grid((unsigned)((long)gb.n_layers * gb.B)), block(256);
-    // 256-byte row segments (two stages of 32 KiB) when the widths allow, else 128-byte segments (four stages of 16 KiB)
-    if (d_in % 128 == 0 && d_out % 128 == 0)
-        hipLaunchKernelGGL((gram_dma_kernel<128, 2, 2>), grid, block, 0, ctx->stream, gb, T, d_in, d_out, has_bias, out);
-    else
-        hipLaunchKernelGGL((gram_dma_kernel<64, 4, 2>), grid, block, 0, ctx->stream, gb, T, d_in, d_out, has_bias, out);
+    const long wgs = (long)gb.n_layers * gb.B;
+    const dim3 grid((unsigned)wgs);
+    // 256-byte row segments (stages of 32 KiB) when the widths allow, else 128-byte segments (16 KiB)
+    const bool wide = d_in % 128 == 0 && d_out % 128 == 0, ragged = d_in % 64 != 0 || d_out % 64 != 0;
+    const bool few = wgs <= 256;  // a workgroup or less per CU: it may have all of the CU
+    auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, ctx->stream, gb, T, d_in, d_out, has_bias, out);
+    };
+    if (T <= 32 && gb.n_out == 1) launch(gram_small_dma_kernel<16>, 256);
+    else if (T <= 64 && wide) launch(gram_dma_kernel<64, 128, 4, 4, 2, false>, 256);
+    else if (T <= 64 && ragged) launch(gram_dma_kernel<64, 64, 8, 4, 2, true>, 256);
+    else if (T <= 64) launch(gram_dma_kernel<64, 64, 8, 4, 2, false>, 256);
+    else if (wide && few) launch(gram_dma_kernel<128, 128, 4, 8, 1, false>, 512);
+    else if (wide) launch(gram_dma_kernel<128, 128, 2, 4, 2, false>, 256);
+    else if (ragged && few) launch(gram_dma_kernel<128, 64, 9, 8, 1, true>, 512);
+    else if (ragged) launch(gram_dma_kernel<128, 64, 4, 4, 2, true>, 256);
+    else if (few) launch(gram_dma_kernel<128, 64, 9, 8, 1, false>, 512);
+    else launch(gram_dma_kernel<128, 64, 4, 4, 2, false>, 256);
     DP_LAUNCH_CHECK(ctx, "gram_dma");
     return DP_OK;
 }
@@ -1008,10 +974,10 @@ static GramUnits gram_make_units(int nblk) {
     return gu;
 }
 
-// The unit kernel: T up to GU_MAX_BLK cells of 128 rows, widths multiples of its 64-wide chunk.
+// The unit kernel: T up to GU_MAX_BLK cells of 128 rows.
 static bool gram_units_ok(int T, int d_in, int d_out) {
-    return T > GB && T <= GB * GU_MAX_BLK && d_in % GU_K == 0 && d_out % GU_K == 0 && d_in > 0 && d_out > 0 &&
-           (size_t)T * (d_in > d_out ? d_in : d_out) * 2 < (1u << 31);
+    return T > GB && T <= GB * GU_MAX_BLK && d_in > 0 && d_out > 0 &&
+           (size_t)((T + GB - 1) / GB * GB) * (d_in > d_out ? d_in : d_out) * 2 < (1u << 31);
 }
 
 dp_status dpk_gram_unit_plan(int T, uint32_t* units, int capacity, int* n_units) {
@@ -1041,8 +1007,10 @@ static dp_status gram_units_launch(dp_ctx* ctx, const GramBatch& gb, int T, int 
     }
     {
         dp_prof_scope prof(ctx, DP_PROF_GRAM, 2.0 * (double)gb.B * T * ((double)d_in + d_out) * gb.n_layers);
-        hipLaunchKernelGGL(gram_units_kernel, dim3((unsigned)nwg), dim3(512), 0, ctx->stream, gb, gu, T, d_in, d_out,
-                           has_bias, part);
+        if (d_in % GU_K == 0 && d_out % GU_K == 0)
+            hipLaunchKernelGGL((gram_units_kernel<false>), dim3((unsigned)nwg), dim3(512), 0, ctx->stream, gb, gu, T, d_in, d_out, has_bias, part);
+        else
+            hipLaunchKernelGGL((gram_units_kernel<true>), dim3((unsigned)nwg), dim3(512), 0, ctx->stream, gb, gu, T, d_in, d_out, has_bias, part);
     }
     DP_LAUNCH_CHECK(ctx, "gram_units");
     return dpk_finish_partials(ctx, part, gb.B, gu.n_units * gb.n_layers, sqnorms);
@@ -1074,15 +1042,19 @@ dp_status dpk_gram_sqnorms_batched(dp_ctx* ctx, int n_layers, const void* const*
         }
         return DP_OK;
     }
-    if (dt != DP_BF16 || !gram_dma_ok(T, d_in, d_out) || (long)B * GRAM_MAX_BATCH > 0x7FFFFFFFl) {
+    if (dt != DP_BF16 || !gram_dma_ok(T, d_in, d_out)) {
         for (int l = 0; l < n_layers; ++l) {
             dp_status st = dpk_gram_sqnorms(ctx, A[l], G[l], dt, B, T, d_in, d_out, has_bias, sqnorms);
             if (st != DP_OK) return st;
         }
         return DP_OK;
     }
-    for (int l0 = 0; l0 < n_layers; l0 += GRAM_MAX_BATCH) {
-        const int nl = n_layers - l0 < GRAM_MAX_BATCH ? n_layers - l0 : GRAM_MAX_BATCH;
+    for (int l0 = 0; l0 < n_layers;) {
+        int nl = n_layers - l0 < GRAM_MAX_BATCH ? n_layers - l0 : GRAM_MAX_BATCH;
+        if ((long)nl * B > 0x7FFFFFFFl) nl = 1;
+        dp_ws_alloc ws(ctx);
+        float* part = nl > 1 ? ws.get<float>((size_t)B * nl) : nullptr;
+        if (!part) nl = 1;  // one layer at a time adds to sqnorms itself
         GramBatch gb;
         for (int l = 0; l < GRAM_MAX_BATCH; ++l) {
             gb.A[l] = (const uint16_t*)A[l0 + (l < nl ? l : 0)];
@@ -1092,22 +1064,10 @@ dp_status dpk_gram_sqnorms_batched(dp_ctx* ctx, int n_layers, const void* const*
         gb.n_layers = nl;
         gb.n_out = 1;
         gb.B = B;
-        const double bytes = 2.0 * (double)B * T * ((double)d_in + d_out) * nl;
-        if (nl == 1) {
-            dp_status st = gram_dma_launch(ctx, gb, T, d_in, d_out, has_bias, sqnorms, bytes);
-            if (st != DP_OK) return st;
-            continue;
-        }
-        dp_ws_alloc ws(ctx);
-        float* part = ws.get<float>((size_t)B * nl);
-        if (!part) {
-            DP_SET_ERR(ctx, "workspace too small for %d x %d norm partials", B, nl);
-            return DP_ERR_WORKSPACE;
-        }
-        dp_status st = gram_dma_launch(ctx, gb, T, d_in, d_out, has_bias, part, bytes);
+        dp_status st = gram_dma_launch(ctx, gb, T, d_in, d_out, has_bias, part ? part : sqnorms, 2.0 * (double)B * T * ((double)d_in + d_out) * nl);
+        if (st == DP_OK && part) st = dpk_finish_partials(ctx, part, B, nl, sqnorms);   // layers added in index order
         if (st != DP_OK) return st;
-        st = dpk_finish_partials(ctx, part, B, nl, sqnorms);   // layers added in index order
-        if (st != DP_OK) return st;
+        l0 += nl;
     }
     return DP_OK;
 }
@@ -1188,20 +1148,8 @@ dp_status dpk_gram_sqnorms(dp_ctx* ctx, const void* A, const void* G, dp_dtype d
         DP_LAUNCH_CHECK(ctx, "gram_f32");
         return per > 1 ? dpk_finish_partials(ctx, part, B, per, sqnorms) : DP_OK;
     }
-    if (T <= 32 && d_in % 64 == 0 && d_out % 64 == 0 && 64l * (d_in > d_out ? d_in : d_out) < (1l << 31)) {
-        dp_prof_scope prof(ctx, DP_PROF_GRAM, 2.0 * (double)B * T * ((double)d_in + d_out));
-        hipLaunchKernelGGL((gram_small_dma_kernel<16>), dim3(B), dim3(256), 0, ctx->stream, (const uint16_t*)A,
-                           (const uint16_t*)G, T, d_in, d_out, has_bias, sqnorms);
-        DP_LAUNCH_CHECK(ctx, "gram_small_dma");
-        return DP_OK;
-    }
-    if (T <= 32) {
-        dp_prof_scope prof(ctx, DP_PROF_GRAM, 2.0 * (double)B * T * ((double)d_in + d_out));
-        hipLaunchKernelGGL(gram_small_kernel, dim3(B), dim3(64 * GS_WAVES), 0, ctx->stream, (const uint16_t*)A, (const uint16_t*)G, T,
-                           d_in, d_out, has_bias, sqnorms);
-        DP_LAUNCH_CHECK(ctx, "gram_small");
-        return DP_OK;
-    }
+    if (gram_dma_ok(T, d_in, d_out) || gram_units_ok(T, d_in, d_out))
+        return dpk_gram_sqnorms_batched(ctx, 1, &A, &G, dt, B, T, d_in, d_out, has_bias, sqnorms);
     const int nblk = (T + GB - 1) / GB;
     const long npairs = (long)nblk * (nblk + 1) / 2;
     const size_t lds = (size_t)2 * (nblk > 1 ? 2 : 1) * GB * GLD * sizeof(uint16_t);
@@ -1213,19 +1161,6 @@ dp_status dpk_gram_sqnorms(dp_ctx* ctx, const void* A, const void* G, dp_dtype d
         lds_attr_set = true;
     }
     const double bytes = 2.0 * (double)B * T * ((double)d_in + d_out);
-    if (gram_dma_ok(T, d_in, d_out) || gram_units_ok(T, d_in, d_out)) {
-        GramBatch gb;
-        for (int l = 0; l < GRAM_MAX_BATCH; ++l) {
-            gb.A[l] = (const uint16_t*)A;
-            gb.G[l] = (const uint16_t*)G;
-            gb.G2[l] = gb.G3[l] = gb.G[l];
-        }
-        gb.n_layers = 1;
-        gb.n_out = 1;
-        gb.B = B;
-        if (T > GB) return gram_units_launch(ctx, gb, T, d_in, d_out, has_bias, sqnorms);
-        return gram_dma_launch(ctx, gb, T, d_in, d_out, has_bias, sqnorms, bytes);
-    }
     if (npairs == 1) {
         dp_prof_scope prof(ctx, DP_PROF_GRAM, bytes);
         hipLaunchKernelGGL(gram_bf16_kernel, dim3(B), dim3(256), lds, ctx->stream, (const uint16_t*)A,
