@@ -333,7 +333,7 @@ dp_status dp_sqnorms_dense(dp_ctx* ctx, const void* A, const void* G, dp_dtype d
     }
     if (path == DP_PATH_AUTO) dp_choose_path(T, d_in, d_out, dtype, &path);
     if (path == DP_PATH_GRAM) return dpk_gram_sqnorms(ctx, A, G, dtype, B, T, d_in, d_out, has_bias, sqnorms);
-    return dpk_materialise_sqnorms(ctx, A, G, dtype, B, T, d_in, d_out, has_bias, sqnorms);
+    return dpk_materialise_sqnorms_batched(ctx, 1, &A, &G, dtype, B, T, d_in, d_out, has_bias, sqnorms);
 }
 
 dp_status dp_sqnorms_dense_batched(dp_ctx* ctx, int n_layers, const void* const* A, const void* const* G, dp_dtype dtype,
@@ -355,6 +355,8 @@ dp_status dp_sqnorms_dense_batched(dp_ctx* ctx, int n_layers, const void* const*
     if (path == DP_PATH_AUTO && d_in > 0) dp_choose_path(T, d_in, d_out, dtype, &path);
     if (path == DP_PATH_GRAM && d_in > 0)
         return dpk_gram_sqnorms_batched(ctx, n_layers, A, G, dtype, B, T, d_in, d_out, has_bias, sqnorms);
+    if (path == DP_PATH_MATERIALISE && d_in > 0)
+        return dpk_materialise_sqnorms_batched(ctx, n_layers, A, G, dtype, B, T, d_in, d_out, has_bias, sqnorms);
     for (int l = 0; l < n_layers; ++l)
         TRY(dp_sqnorms_dense(ctx, A[l], G[l], dtype, B, T, d_in, d_out, has_bias, path, sqnorms));
     return DP_OK;

@@ -763,8 +763,12 @@ dp_status dpk_colstat_sqnorms_batched(dp_ctx* ctx, int n, const void* const* X, 
     if (B == 0 || T == 0 || d == 0 || n == 0 || (!use_x && !use_1)) return DP_OK;
     bool v4 = true;
     for (int l = 0; l < n; ++l) v4 = v4 && vec4_ok(dt, d, use_x ? X[l] : G[l], G[l]);
-    for (int l0 = 0; l0 < n; l0 += COL_MAX_BATCH) {
-        const int L = n - l0 < COL_MAX_BATCH ? n - l0 : COL_MAX_BATCH;
+    // layers per launch: as many as one may hold and as have room for their partial norms (at least one)
+    const int vw = dt == DP_BF16 || v4 ? 4 : 1;
+    size_t per = ctx->ws_bytes / ((size_t)B * ((d + 64 * vw - 1) / (64 * vw)) * sizeof(float));
+    per = per < 1 ? 1 : per > COL_MAX_BATCH ? COL_MAX_BATCH : per;
+    for (int l0 = 0; l0 < n; l0 += (int)per) {
+        const int L = n - l0 < (int)per ? n - l0 : (int)per;
         const void* const* Xl = use_x ? X + l0 : nullptr;
         dp_status st;
         float* const* kl = keep ? keep + l0 : nullptr;

@@ -4,24 +4,15 @@
 // of one example's A_i^T G_i for the squared-norm path that sums squares of the entries.
 //
 // Both are "TN" contractions: the contraction index (token row k) is the SLOW index of both operands in
-// memory, while v_mfma_f32_32x32x16_bf16 wants each lane to hold 8 consecutive k for one output row/column.
+// memory, while the bf16 MFMA wants each lane to hold 8 consecutive k for one output row/column.
 // Tiles are staged in LDS as they lie in memory ([k][column], 16-byte chunks) and fragments are fetched
 // with the gfx950 transposing LDS read (ds_read_b64_tr_b16): inside a group of 16 lanes, lane i supplies
 // the address of 4 adjacent columns of row k0 + i/4 and receives column i of rows k0..k0+3, so two reads
 // give a lane its 8 consecutive k.  No permute instructions, natural output layout.
 //
 // LDS bank conflicts: the four rows a 16-lane group touches are one row pitch (512 B or 256 B) apart, i.e.
-// in the same banks.  The 16-byte chunk index is therefore XOR-ed with 4*(row % 4) when a chunk is stored,
+// in the same banks.  The 16-byte chunk index is therefore XOR-ed with bits of the row when a chunk is stored,
 // which spreads the four rows of a group, and the two groups of a half-wave, over 256 distinct bytes.
-//
-// Pipeline per workgroup of the register-staged kernel (8 waves as 2 x 4 on a 256 x 256 tile, or 4 waves as 2 x 2 on
-// 128 x 128): global -> registers up to four stages ahead (buffer loads: rows
-// past the split's range read as zero, so there is no branch around a load), registers -> LDS ring of
-// three stages, LDS -> fragments one 16-row step ahead of the MFMAs, also across the one barrier per stage.
-//
-// The clip factor c_i multiplies the rows of G in fp32 while they sit in registers between the global load
-// and the LDS store (once per element per workgroup); the product is rounded to bf16 (nearest even, by
-// v_cvt_pk_bf16_f32); accumulation is fp32 in the MFMA.
 //
 // Roofline: MFMA.  2*B*T*d_in*d_out flops per layer against (d_in + d_out)*B*T*2 bytes read once.
 #include <stdlib.h>
@@ -32,40 +23,36 @@
 
 namespace {
 
-constexpr int BK = 32;      // token rows per staged tile
-constexpr int NSTAGE = 3;   // LDS ring
+constexpr int BK = 32;  // token rows per staged tile
 
 enum { EPI_STORE = 0, EPI_ADD = 1, EPI_SQNORM = 2 };
 
 struct WgemmArgs {
-    const uint16_t* A;   // [K, d_in]
-    const uint16_t* G;   // [K, d_out]
     const float* sqnorms;  // [B] squared norms; c_i = min(1, C / sqrt(sqnorms[i])) (unused without scaling)
     float C;
-    float* bias_part;    // [nsplit][d_out] column sums of the scaled G rows (written by the tile row 0), or nullptr
+    float* bias_part;    // column sums of the scaled G rows, one row of d_out per (unit, tile row, wave row), or nullptr
     int T, d_in, d_out;
     long K;              // total rows
-    long rows_per_split; // multiple of BK (or T for the per-example materialisation)
+    long rows_per_split; // whole examples; without factors (flat) a multiple of BK, or T for the materialisation
     int tiles_m, tiles_n, nsplit;
-    float* out;          // EPI_STORE: [nsplit][d_in][d_out]; EPI_ADD: [d_in][d_out]; EPI_SQNORM: [nsplit][ntiles]
-    int xcd_map;         // 0: plain; 1: split index interleaved over the 8 XCDs; 2: each XCD owns one split and a
-                         // rect_m x rect_n-th sub-rectangle of the tile grid; 3 (direct-to-LDS kernel only): the
-                         // (unit, tile) sequence cut into 8 equal runs
-    int rect_m, rect_n;  // mode 2: the tile grid is cut into rect_m x rect_n rectangles, 8 / nsplit per split;
+    float* out;          // EPI_SQNORM: [nsplit][layers][ntiles] partial norms (the sums' outputs are per layer, below)
+    int xcd_map;         // 1: whole units dealt to the 8 XCDs; 2: each XCD owns one rect_m x rect_n-th sub-rectangle of a unit's
+                         // tile grid; 3: the (unit, tile) sequence cut into 8 equal runs
+    int rect_m, rect_n;  // mode 2: the tile grid is cut into rect_m x rect_n rectangles, 8 / units per unit;
                          // modes 1 and 3: a unit's tiles are walked in rectangles of this size
     int* err;            // device error word: DP_ERRBIT_NORM is set when a clip factor is NaN (non-finite squared norm)
-    int bias_direct;     // direct-to-LDS kernel: no bias partials, the kernel adds to sum_b (one row split)
-    int flat;            // direct-to-LDS kernel: no clip factors (G holds c * g already), a unit is one run of rows
+    int bias_direct;     // sums: no bias partials, the kernel adds to sum_b (one row split); norms: count the bias gradient
+    int flat;            // no clip factors (G holds c * g already, or the norms are wanted), a unit is one run of rows
 };
 
-// Several layers of one shape in one launch (direct-to-LDS kernel): the unit of work distribution is the pair
-// (layer, row split); `base` describes the common shape, and base.A / base.G / base.out are not used.
+// Several layers of one shape in one launch: the unit of work distribution is the pair (layer, row split); `base`
+// describes the common shape.
 constexpr int MAX_BATCH = 32;
 struct LayerPtrs {
     const uint16_t* A;
     const uint16_t* G;
     float* out;      // EPI_ADD: the layer's sum_W; EPI_STORE: the layer's first partial [nsplit][d_in][d_out]
-    float* sum_b;    // the layer's bias sum buffer or nullptr (device code only tests it; the finish kernel adds)
+    float* sum_b;    // the layer's bias sum buffer or nullptr
 };
 struct WgemmBatchArgs {
     WgemmArgs base;
@@ -79,19 +66,6 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ uint32_t scale_pair(uint32_t w, float s) {
-    const f32x2_t x = {dp_bf16_lo(w) * s, dp_bf16_hi(w) * s};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2_t));  // v_cvt_pk_bf16_f32 (RNE)
-}
-__device__ __forceinline__ u32x4_t scale_bf16x8(u32x4_t v, float s) {
-    u32x4_t o;
-    o[0] = scale_pair(v[0], s);
-    o[1] = scale_pair(v[1], s);
-    o[2] = scale_pair(v[2], s);
-    o[3] = scale_pair(v[3], s);
-    return o;
-}
-
 // 8 consecutive k (rows) of one column, as an MFMA operand: two transposing reads of 4 rows each.
 __device__ __forceinline__ bf16x8_t read_frag(const uint16_t* lds_lane_ptr, int row_pitch_elems) {
     typedef s16x4_t __attribute__((address_space(3))) * lptr;
@@ -99,274 +73,6 @@ __device__ __forceinline__ bf16x8_t read_frag(const uint16_t* lds_lane_ptr, int 
     const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(lds_lane_ptr + 4 * row_pitch_elems));
     const s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8_t, v);
-}
-
-// Workgroup = WVM x WVN waves; wave tile (32*MI) x (32*NI); block tile BM x BN = (32*MI*WVM) x (32*NI*WVN).
-// SCALE: multiply G rows by c.  UNIFORM_C: T % BK == 0, so all rows of a stage belong to one example.
-template <int MI, int NI, int WVM, int WVN, int EPI, bool SCALE, bool UNIFORM_C>
-__global__ __launch_bounds__(64 * WVM * WVN) void wgemm_bf16_kernel(WgemmArgs a) {
-    constexpr int NT = 64 * WVM * WVN;
-    constexpr int WM = 32 * MI, WN = 32 * NI;
-    constexpr int BM = WM * WVM, BN = WN * WVN;
-    constexpr int CA = BM / 8, CG = BN / 8;  // 16-byte chunks per tile row
-    constexpr int SA = BK * CA / NT, SG = BK * CG / NT;  // staging slots (16-byte chunks) per thread
-    static_assert(SA * NT == BK * CA && SG * NT == BK * CG, "tile must divide evenly over the threads");
-    __shared__ __attribute__((aligned(16))) uint16_t As[NSTAGE][BK * BM];
-    __shared__ __attribute__((aligned(16))) uint16_t Gs[NSTAGE][BK * BN];
-    __shared__ float wred[NT / 64];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave / WVN, wc = wave % WVN;
-    const int ntiles = a.tiles_m * a.tiles_n;
-    // Workgroup ids are dealt to the 8 XCDs round-robin (id % 8), each XCD with its own L2: give the workgroups
-    // of one XCD work that shares operand rows and columns, so that A and G come from HBM about once.
-    int tile, split;
-    if (a.xcd_map == 1) {
-        const int g = blockIdx.x, slot = g >> 3;
-        split = (slot / ntiles) * 8 + (g & 7);
-        tile = slot % ntiles;
-        if (split >= a.nsplit) return;
-    } else if (a.xcd_map == 2) {
-        const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-        const int nrect = a.rect_m * a.rect_n;
-        const int rect = xcd % nrect;
-        const int tm = a.tiles_m / a.rect_m, tn = a.tiles_n / a.rect_n;
-        split = xcd / nrect;
-        tile = ((rect / a.rect_n) * tm + slot / tn) * a.tiles_n + (rect % a.rect_n) * tn + slot % tn;
-    } else {
-        tile = blockIdx.x % ntiles;
-        split = blockIdx.x / ntiles;
-    }
-    const int pm = tile / a.tiles_n, qn = tile % a.tiles_n;
-    const int p0 = pm * BM, q0 = qn * BN;
-    const long k_lo = (long)split * a.rows_per_split;
-    const long k_hi = k_lo + a.rows_per_split < a.K ? k_lo + a.rows_per_split : a.K;
-    const int nrows = k_hi > k_lo ? (int)(k_hi - k_lo) : 0;
-    const int nsteps = (nrows + BK - 1) / BK;
-
-    // Buffer resources over this split's rows: any access past the last row returns zero.
-    const __amdgpu_buffer_rsrc_t rA = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a.A + (size_t)k_lo * a.d_in), 0, (int)((size_t)nrows * a.d_in * 2), 0x00020000);
-    const __amdgpu_buffer_rsrc_t rG = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a.G + (size_t)k_lo * a.d_out), 0, (int)((size_t)nrows * a.d_out * 2), 0x00020000);
-
-    // Per-thread staging slots: slot j moves the 16-byte chunk at tile row `row`, LDS chunk position `cpos`;
-    // the global chunk it holds is cpos ^ swizzle(row).  Columns past the layer width read neighbouring
-    // (valid or zero) data and only feed output columns that are never stored.
-    int voffA[SA], ldsA[SA], voffG[SG], ldsG[SG], rowG[SG];
-#pragma unroll
-    for (int j = 0; j < SA; ++j) {
-        const int id = tid + NT * j, row = id / CA, cpos = id % CA;
-        const int cg = cpos ^ ((row & 3) << 2);
-        voffA[j] = (row * a.d_in + p0 + cg * 8) * 2;
-        ldsA[j] = row * BM + cpos * 8;
-    }
-#pragma unroll
-    for (int j = 0; j < SG; ++j) {
-        const int id = tid + NT * j, row = id / CG, cpos = id % CG;
-        const int cg = cpos ^ ((row & 3) << 2);
-        voffG[j] = (row * a.d_out + q0 + cg * 8) * 2;
-        ldsG[j] = row * BN + cpos * 8;
-        rowG[j] = row;
-    }
-    // Fragment read offsets (elements) inside a stage for k step 0: lane l reads row 8*(l/32) + (l%16)/4
-    // (+4 for its second read), columns 32*i + 16*((l/16)%2) + 4*(l%4) .. +3 of operand tile i.
-    const int frow = 8 * (lane >> 5) + ((lane & 15) >> 2);
-    const int fsw = frow & 3;
-    int foffA[MI], foffG[NI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-        const int col = wr * WM + 32 * i + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-        foffA[i] = frow * BM + (((col >> 3) ^ (fsw << 2)) << 3) + (col & 7);
-    }
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int col = wc * WN + 32 * i + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-        foffG[i] = frow * BN + (((col >> 3) ^ (fsw << 2)) << 3) + (col & 7);
-    }
-
-    f32x16_t acc[MI][NI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    u32x4_t ra[2][SA], rg[2][SG];
-    float cs[2][SG];
-    // Bias gradient: the workgroups of tile row 0 also sum the scaled G rows they stage, column by column.
-    const bool do_bias = SCALE && a.bias_part != nullptr && pm == 0;
-    float bsum[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) bsum[e] = 0.f;
-    auto gload = [&](int set, int st) {  // stage st -> register set
-        const int soffA = st * BK * a.d_in * 2, soffG = st * BK * a.d_out * 2;
-#pragma unroll
-        for (int j = 0; j < SA; ++j) ra[set][j] = __builtin_amdgcn_raw_buffer_load_b128(rA, voffA[j], soffA, 0);
-#pragma unroll
-        for (int j = 0; j < SG; ++j) rg[set][j] = __builtin_amdgcn_raw_buffer_load_b128(rG, voffG[j], soffG, 0);
-        if constexpr (SCALE) {
-            if constexpr (UNIFORM_C) {
-                const long k = k_lo + (long)st * BK;
-                const float s = dp_clip_factor(a.sqnorms[(uint32_t)(k < a.K ? k : a.K - 1) / (uint32_t)a.T], a.C);
-                if (s != s && tid == 0) atomicOr(a.err, DP_ERRBIT_NORM);
-#pragma unroll
-                for (int j = 0; j < SG; ++j) cs[set][j] = s;
-            } else {
-#pragma unroll
-                for (int j = 0; j < SG; ++j) {
-                    long k = k_lo + (long)st * BK + rowG[j];
-                    if (k >= a.K) k = a.K - 1;
-                    cs[set][j] = dp_clip_factor(a.sqnorms[(uint32_t)k / (uint32_t)a.T], a.C);
-                    if (cs[set][j] != cs[set][j]) atomicOr(a.err, DP_ERRBIT_NORM);
-                }
-            }
-        }
-    };
-    auto lstore = [&](int set, int buf) {
-#pragma unroll
-        for (int j = 0; j < SA; ++j) *reinterpret_cast<u32x4_t*>(&As[buf][ldsA[j]]) = ra[set][j];
-#pragma unroll
-        for (int j = 0; j < SG; ++j) {
-            u32x4_t v = rg[set][j];
-            if constexpr (SCALE) {
-                if (do_bias) {
-                    // this thread always stages the same 8 columns (see the bias epilogue): add the fp32
-                    // products c*g to its running column sums before they are rounded to bf16
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        const float lo = dp_bf16_lo(v[w]) * cs[set][j], hi = dp_bf16_hi(v[w]) * cs[set][j];
-                        bsum[2 * w] += lo;
-                        bsum[2 * w + 1] += hi;
-                        const f32x2_t x = {lo, hi};
-                        v[w] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2_t));
-                    }
-                } else {
-                    v = scale_bf16x8(v, cs[set][j]);
-                }
-            }
-            *reinterpret_cast<u32x4_t*>(&Gs[buf][ldsG[j]]) = v;
-        }
-    };
-    auto load_frags = [&](int buf, int kk, bf16x8_t* fa, bf16x8_t* fg) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i) fa[i] = read_frag(&As[buf][kk * 16 * BM + foffA[i]], BM);
-#pragma unroll
-        for (int i = 0; i < NI; ++i) fg[i] = read_frag(&Gs[buf][kk * 16 * BN + foffG[i]], BN);
-    };
-    auto mma = [&](const bf16x8_t* fa, const bf16x8_t* fg) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fg[j], acc[i][j], 0, 0, 0);
-    };
-
-    // The stage count is rounded up to even so that the loop body can be unrolled twice with the register
-    // sets fixed at compile time; stages past the range load zeros (buffer bounds) and add nothing.
-    const int nsteps2 = (nsteps + 1) & ~1;
-
-    // ---- prologue: stages 0 and 1 into LDS, stages 2 and 3 in flight in registers ----
-    bf16x8_t fa0[MI], fg0[NI], fa1[MI], fg1[NI];
-    // (the scheduling barriers keep the loads in program order: the compiler's wait counts for the loop
-    // are only as tight as the load order on entry is certain)
-    gload(0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    gload(1, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    lstore(0, 0);
-    gload(0, 2);
-    __builtin_amdgcn_sched_barrier(0);
-    lstore(1, 1);
-    gload(1, 3);
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-    load_frags(0, 0, fa0, fg0);
-
-    // ---- main loop: iteration s computes stage s from LDS[s % 3]; stage s+1 is already visible in
-    // LDS[(s+1) % 3]; stage s+2 moves from register set s % 2 into LDS[(s+2) % 3] (the buffer read in
-    // iteration s-1, released by that iteration's barrier) and the set is reloaded with stage s+4.
-    // There is no branch in the body: everything past the last stage is zeros. ----
-    int buf = 0;
-    auto body = [&](int s, auto setc) {
-        constexpr int SET = decltype(setc)::value;
-        const int buf1 = buf == NSTAGE - 1 ? 0 : buf + 1;
-        const int buf2 = buf1 == NSTAGE - 1 ? 0 : buf1 + 1;
-        load_frags(buf, 1, fa1, fg1);
-        mma(fa0, fg0);
-        lstore(SET, buf2);
-        gload(SET, s + 4);
-        load_frags(buf1, 0, fa0, fg0);
-        mma(fa1, fg1);
-        __syncthreads();
-        // nothing of the next iteration may move above this point: its register set is still in flight
-        __builtin_amdgcn_sched_barrier(0);
-        buf = buf1;
-    };
-    for (int s = 0; s < nsteps2; s += 2) {
-        body(s, std::integral_constant<int, 0>());
-        body(s + 1, std::integral_constant<int, 1>());
-    }
-
-    if constexpr (SCALE) {
-        if (do_bias) {
-            // Thread t staged LDS chunk position t % CG of rows t / CG (+ multiples of NT / CG, a multiple of 4),
-            // i.e. always the global chunk (t % CG) ^ 4*((t / CG) % 4).  Gather the NT / CG row classes of every
-            // column in a fixed order.  The stage buffers are free: the loop ended with a barrier.
-            float* scratch = reinterpret_cast<float*>(&As[0][0]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) scratch[tid * 8 + e] = bsum[e];
-            __syncthreads();
-            if (tid < BN && q0 + tid < a.d_out) {
-                const int cgl = tid >> 3, e = tid & 7;
-                float t = 0.f;
-#pragma unroll 4
-                for (int r = 0; r < NT / CG; ++r) t += scratch[(r * CG + (cgl ^ ((r & 3) << 2))) * 8 + e];
-                a.bias_part[(size_t)split * a.d_out + q0 + tid] = t;
-            }
-        }
-    }
-
-    // MFMA tile (i, j): accumulator register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32.
-    if (EPI == EPI_SQNORM) {
-        // rows / columns past the layer's widths hold products of neighbouring data: leave them out
-        float s = 0.f;
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int p = p0 + wr * WM + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-#pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    const int q = q0 + wc * WN + 32 * j + (lane & 31);
-                    const float v = (p < a.d_in && q < a.d_out) ? acc[i][j][r] : 0.f;
-                    s += v * v;
-                }
-            }
-        const float tot = dp_block_sum<NT>(s, wred);
-        if (tid == 0) a.out[(size_t)split * ntiles + tile] = tot;
-        return;
-    }
-
-    float* base = a.out + (EPI == EPI_STORE ? (size_t)split * a.d_in * a.d_out : (size_t)0);
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int p = p0 + wr * WM + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            if (p < a.d_in) {
-#pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    const int q = q0 + wc * WN + 32 * j + (lane & 31);
-                    if (q < a.d_out) {
-                        float* dst = base + (size_t)p * a.d_out + q;
-                        if (EPI == EPI_ADD) *dst += acc[i][j][r];
-                        else *dst = acc[i][j][r];
-                    }
-                }
-            }
-        }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -576,8 +282,8 @@ __global__ __launch_bounds__(512, MI * NI <= 8 ? 4 : 2) void wgemm_dma16_kernel(
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
     }
-    const bool want_bias = EPI != EPI_SQNORM && b.L[layer].sum_b != nullptr;
-    // bias_direct (one row split, few stages): the first wave row of tile row 0 takes every stage and adds its sums itself
+    const bool want_bias = EPI == EPI_SQNORM ? a.bias_direct != 0 : b.L[layer].sum_b != nullptr;
+    // bias_direct (norms; sums with one row split and few stages): the first wave row of tile row 0 takes every stage
     const int duty_mod = a.bias_direct ? 1 : 2 * a.tiles_m, duty = 2 * pm + wr;
     const uint32_t one2 = 0x3F803F80u;  // two bf16 ones
     const bf16x8_t ones = __builtin_bit_cast(bf16x8_t, u32x4_t{one2, one2, one2, one2});
@@ -742,6 +448,14 @@ __global__ __launch_bounds__(512, MI * NI <= 8 ? 4 : 2) void wgemm_dma16_kernel(
                     s += v * v;
                 }
             }
+        // the bias gradient's entries (the columns of G summed: every row of the ones-product) count like a row of the weights
+        if (want_bias && duty == 0 && lane < 16) {
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                const float v = q0 + wc * WN + 16 * j + lane < a.d_out ? bacc[j][0] : 0.f;
+                s += v * v;
+            }
+        }
         const float tot = dp_block_sum<512>(s, reinterpret_cast<float*>(&As[0][0]));
         if (tid == 0) a.out[((size_t)split * b.n_layers + layer) * ntiles + tile] = tot;
         return;
@@ -1114,36 +828,7 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
     }
 }
 
-template <int MI, int NI, int WVM, int WVN, int EPI, bool SCALE, bool UNIFORM_C>
-void wgemm_launch(dp_ctx* ctx, const WgemmArgs& a, unsigned grid) {
-    hipLaunchKernelGGL((wgemm_bf16_kernel<MI, NI, WVM, WVN, EPI, SCALE, UNIFORM_C>), dim3(grid),
-                       dim3(64 * WVM * WVN), 0, ctx->stream, a);
-}
-
-// Tile configurations: 0 = 128 x 128 (4 waves of 64 x 64), 2 = 256 x 256 with 8 waves of 128 x 64 (two waves per
-// SIMD, which lets one wave's MFMAs run under the other's loads, conversions and waits).
-template <int EPI, bool SCALE>
-void wgemm_dispatch(dp_ctx* ctx, const WgemmArgs& a, unsigned grid, int cfg, bool uniform) {
-    if (cfg == 2) {
-        if (uniform) wgemm_launch<4, 2, 2, 4, EPI, SCALE, true>(ctx, a, grid);
-        else wgemm_launch<4, 2, 2, 4, EPI, SCALE, false>(ctx, a, grid);
-    } else {
-        if (uniform) wgemm_launch<2, 2, 2, 2, EPI, SCALE, true>(ctx, a, grid);
-        else wgemm_launch<2, 2, 2, 2, EPI, SCALE, false>(ctx, a, grid);
-    }
-}
-
 }  // namespace
-
-// Tile shape: 256 x 256 when both dimensions are at least that large, otherwise 128 x 128.
-static inline bool big_tile(int d_in, int d_out) { return d_in >= 256 && d_out >= 256; }
-static inline int tile_cfg(int d_in, int d_out) { return big_tile(d_in, d_out) ? 2 : 0; }
-
-// A split's rows of one operand must stay below 2^31 bytes (32-bit buffer offsets).
-static inline bool range_ok(long rows, int d_in, int d_out) {
-    const long w = d_in > d_out ? d_in : d_out;
-    return (rows + 4 * BK) * w * 2 < (1l << 31);
-}
 
 namespace {
 // The row splits' partial sums of all layers of a launch, added in one launch: blockIdx.y = layer,
@@ -1306,8 +991,6 @@ dp_status dpk_weighted_gemm_batched(dp_ctx* ctx, int n, const void* const* A, co
         const int nl = n - l0 < plan.per_launch ? n - l0 : plan.per_launch;
         WgemmBatchArgs b;
         WgemmArgs& a = b.base;
-        a.A = nullptr;
-        a.G = nullptr;
         a.out = nullptr;
         a.sqnorms = sqnorms;
         a.C = C;
@@ -1545,53 +1228,84 @@ static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, 
     return st;
 }
 
-dp_status dpk_materialise_sqnorms(dp_ctx* ctx, const void* A, const void* G, dp_dtype dt, int B, int T, int d_in,
-                                  int d_out, int has_bias, float* sqnorms) {
-    dp_status st;
+// Norms by materialisation: a unit of the kernel is one example, its tiles of A_i^T G_i are squared and summed as they leave the
+// accumulators; partial norms [B][layers * tiles] through the workspace.  Tile: the smallest time of a launch by the stage
+// costs above (a workgroup without a sum to add to takes about 3 us besides its stages).
+dp_status dpk_materialise_sqnorms_batched(dp_ctx* ctx, int n, const void* const* A, const void* const* G, dp_dtype dt, int B, int T,
+                                          int d_in, int d_out, int has_bias, float* sqnorms) {
+    dp_status st = DP_OK;
     if (dt == DP_F32) {
-        st = dpk_materialise_f32(ctx, (const float*)A, (const float*)G, B, T, d_in, d_out, sqnorms);
-    } else {
-        const bool big = big_tile(d_in, d_out);
-        const int BM = big ? 256 : 128, BN = BM;
-        WgemmArgs a;
-        a.A = (const uint16_t*)A;
-        a.G = (const uint16_t*)G;
-        a.sqnorms = nullptr;
-        a.C = 1.f;
+        for (int l = 0; st == DP_OK && l < n; ++l)
+            st = dpk_materialise_f32(ctx, (const float*)A[l], (const float*)G[l], B, T, d_in, d_out, sqnorms);
+        if (st == DP_OK && has_bias && n > 0) st = dpk_colstat_sqnorms_batched(ctx, n, nullptr, G, dt, B, T, d_out, 0, 1, sqnorms, nullptr);
+    }
+    for (int l0 = 0; dt == DP_BF16 && l0 < n;) {
+        int nl = n - l0 < MAX_BATCH ? n - l0 : MAX_BATCH, bm = 0, bn = 0;
+        float* part = nullptr;
+        for (;; nl = (nl + 1) / 2) {  // fewer layers, and at last the largest tile, until the partial norms fit
+            double best_t = 0.0;
+            for (int m = 256; m >= 128; m -= 128)
+                for (int k = 256; k >= 128; k -= 128) {
+                    const long wgs = (long)nl * B * ((d_in + m - 1) / m) * ((d_out + k - 1) / k);
+                    const DmaCost c = dma_cost(m, k, false);
+                    const double t = (double)((wgs + 256 * c.wgs - 1) / (256 * c.wgs)) * ((T + BK - 1) / BK * (wgs <= 256 ? c.t_stage_alone : c.t_stage) + 3.0);
+                    if (!bm || t < best_t) {
+                        bm = m;
+                        bn = k;
+                        best_t = t;
+                    }
+                }
+            dp_ws_alloc ws(ctx);
+            part = ws.get<float>((size_t)B * nl * ((d_in + bm - 1) / bm) * ((d_out + bn - 1) / bn));
+            if (!part && nl == 1) {
+                bm = d_in < 256 ? 128 : 256;
+                bn = d_out < 256 ? 128 : 256;
+                part = ws.get<float>((size_t)B * ((d_in + bm - 1) / bm) * ((d_out + bn - 1) / bn));
+            }
+            if ((part && (long)nl * B * ((d_in + bm - 1) / bm) * ((d_out + bn - 1) / bn) < 0x7FFFFFF0l) || nl == 1) break;
+            bm = 0;
+        }
+        WgemmBatchArgs b;
+        WgemmArgs& a = b.base;
+        a = WgemmArgs{};
         a.err = ctx->err_word;
-        a.bias_part = nullptr;
+        a.C = 1.f;
+        a.flat = 1;
+        a.bias_direct = has_bias ? 1 : 0;
         a.T = T;
         a.d_in = d_in;
         a.d_out = d_out;
         a.K = (long)B * T;
-        a.tiles_m = (d_in + BM - 1) / BM;
-        a.tiles_n = (d_out + BN - 1) / BN;
-        a.nsplit = B;  // one "split" per example: rows [i*T, (i+1)*T)
-        a.rows_per_split = T;
-        a.xcd_map = 0;
+        a.rows_per_split = T;  // one "split" per example
+        a.nsplit = B;
+        a.tiles_m = (d_in + bm - 1) / bm;
+        a.tiles_n = (d_out + bn - 1) / bn;
+        a.xcd_map = 3;
         a.rect_m = a.rect_n = 1;
-        if (!range_ok(T, d_in, d_out)) {
-            DP_SET_ERR(ctx, "dp_sqnorms_dense: one example's activations exceed 2 GiB");
-            return DP_ERR_SHAPE;
+        a.out = part;
+        const long ntiles = (long)a.tiles_m * a.tiles_n, nwg = ((long)nl * B * ntiles + 7) / 8 * 8;
+        if (!part) {
+            DP_SET_ERR(ctx, "workspace too small for %d x %ld materialise partials", B, ntiles);
+            return DP_ERR_WORKSPACE;
         }
-        const int ntiles = a.tiles_m * a.tiles_n;
-        const long nwg = (long)B * ntiles;
         if (nwg > 0x7FFFFFFFl) {
             DP_SET_ERR(ctx, "dp_sqnorms_dense: too many tiles");
             return DP_ERR_SHAPE;
         }
-        dp_ws_alloc ws(ctx);
-        float* part = ws.get<float>((size_t)B * ntiles);
-        if (!part) {
-            DP_SET_ERR(ctx, "workspace too small for %d x %d materialise partials", B, ntiles);
-            return DP_ERR_WORKSPACE;
+        b.n_layers = nl;
+        for (int l = 0; l < MAX_BATCH; ++l) {
+            const int src = l0 + (l < nl ? l : 0);
+            b.L[l] = LayerPtrs{(const uint16_t*)A[src], (const uint16_t*)G[src], nullptr, nullptr};
         }
-        a.out = part;
-        wgemm_dispatch<EPI_SQNORM, false>(ctx, a, (unsigned)nwg, tile_cfg(d_in, d_out), true);
-        DP_LAUNCH_CHECK(ctx, "wgemm_bf16 (materialise)");
-        st = dpk_finish_partials(ctx, part, B, ntiles, sqnorms);
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(512), 0, ctx->stream, b); };
+        if (bm == 256 && bn == 256) launch(wgemm_dma16_kernel<8, 4, EPI_SQNORM, false>);
+        else if (bm == 256) launch(wgemm_dma16_kernel<8, 2, EPI_SQNORM, false>);
+        else if (bn == 256) launch(wgemm_dma16_kernel<4, 4, EPI_SQNORM, false>);
+        else launch(wgemm_dma16_kernel<4, 2, EPI_SQNORM, false>);
+        DP_LAUNCH_CHECK(ctx, "wgemm_dma (materialise)");
+        st = dpk_finish_partials(ctx, part, B, (int)(nl * ntiles), sqnorms);
+        if (st != DP_OK) return st;
+        l0 += nl;
     }
-    if (st != DP_OK) return st;
-    if (has_bias) return dpk_colstat_sqnorms(ctx, nullptr, G, dt, B, T, d_out, 0, 1, sqnorms);
-    return DP_OK;
+    return st;
 }

@@ -951,6 +951,29 @@ def test_dense_f32_forms(dp, B, T, d_in, d_out):
     assert_sums_close(host(b).astype(np.float64) + 0.5, b_ref, 1e-5, "sum_b")
 
 
+@pytest.mark.parametrize("n,B,T,d_in,d_out", [
+    (1, 3, 1, 8, 8), (3, 5, 20, 72, 136), (17, 2, 32, 64, 64),        # up to 32 rows, one and several layers, ragged widths
+    (2, 7, 33, 72, 200), (1, 300, 64, 128, 128), (2, 4, 50, 128, 264),  # up to 64 rows: one quadrant
+    (1, 3, 65, 136, 72), (2, 140, 128, 64, 200), (3, 2, 100, 384, 128),  # up to 128 rows, few and many workgroups
+    (2, 3, 130, 200, 328), (1, 2, 300, 72, 1032),                     # units of the plane, ragged widths
+    (5, 3, 40, 264, 520)])
+@pytest.mark.parametrize("has_bias", [False, True])
+def test_sqnorms_dense_forms(dp, n, B, T, d_in, d_out, has_bias):
+    """Norms of a batch of layers, both paths: rows per example at the edges of the 32-, 64- and 128-row kernels and widths that
+    end inside a chunk.  bf16 products are exact in fp32; 1e-4 as in the other norm tests."""
+    import paper_2108_01624_amd as pkg
+
+    As = [gen((B, T, d_in), 1.0, 600 + l, "bf16") for l in range(n)]
+    Gs = [gen((B, T, d_out), 0.1, 640 + l, "bf16") for l in range(n)]
+    A_d, G_d = [to_dev(a) for a in As], [to_dev(g) for g in Gs]
+    ref = sum(orc.sqnorms_dense(a, g, has_bias) for a, g in zip(As, Gs)) + 3.0
+    for path in (pkg.DP_PATH_GRAM, pkg.DP_PATH_MATERIALISE):
+        sq = torch.full((B,), 3.0, dtype=torch.float32, device=DEV)
+        dp.sqnorms_dense_batched(A_d, G_d, has_bias, path, sq)
+        dp.sync()
+        assert_norms_close(host(sq), ref, 1e-4, f"path {path}")
+
+
 def test_batched_equals_single_layer_calls(dp):
     """The direct-to-LDS path keeps exact bf16 products: one layer alone and inside a batch agree closely."""
     n, B, T, d_in, d_out, C = 4, 32, 128, 256, 256, 1.0
