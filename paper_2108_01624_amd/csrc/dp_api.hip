@@ -571,8 +571,7 @@ dp_status dp_clip_accumulate_embedding(dp_ctx* ctx, const int32_t* ids, const vo
     TRY(check_f32(ctx, "sum_E", sum_E));
     TRY(check_clip(ctx, C, B));
     if (B == 0 || T == 0 || d == 0) return DP_OK;
-    TRY(dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf));
-    return dpk_embedding_sums(ctx, ids, G, dtype, B, T, d, V, ctx->cbuf, sum_E);
+    return dpk_embedding_sums(ctx, ids, G, dtype, B, T, d, V, sqnorms, C, sum_E);
 }
 
 dp_status dp_clip_accumulate_positions(dp_ctx* ctx, const void* G, dp_dtype dtype, int B, int T, int d, float C,
@@ -632,10 +631,7 @@ dp_status dp_clip_accumulate_tied_embedding(dp_ctx* ctx, const int32_t* ids, con
     if (dtype == DP_BF16 && ((uintptr_t)sum_E & 15)) FAIL(ctx, DP_ERR_ALIGN, "sum_E is not 16-byte aligned");
     TRY(check_clip(ctx, C, B));
     if (B == 0 || d == 0) return DP_OK;
-    if (T > 0) {
-        TRY(dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf));
-        TRY(dpk_embedding_sums(ctx, ids, dY, dtype, B, T, d, V, ctx->cbuf, sum_E));
-    }
+    if (T > 0) TRY(dpk_embedding_sums(ctx, ids, dY, dtype, B, T, d, V, sqnorms, C, sum_E));
     if (M == 0) return DP_OK;
     // the output projection's sum is a dense sum with input dL [B, M, V] and output gradient H [B, M, d]
     return dpk_weighted_gemm(ctx, dL, H, dtype, B, M, V, d, sqnorms, C, sum_E, nullptr);

@@ -680,13 +680,13 @@ __global__ __launch_bounds__(512, 1) void gram_units_kernel(GramBatch gb, GramUn
 // Bound: HBM, B*T*(d_in+d_out)*2 bytes read once: 646 MB in 98 us; one layer of 1024 x 1024, B = 512, T = 20: 28 us on the
 // 128-row kernel, 12 here.
 // ------------------------------------------------------------------------------------------------
-template <int NS>
+template <int NS, bool RAGGED>
 __global__ __launch_bounds__(256, 2) void gram_small_dma_kernel(GramBatch gb, int T, int d_in, int d_out, int has_bias, float* __restrict__ out) {
     constexpr int GDK = 64, ROWS = 32, STAGE = ROWS * GDK, CPR = 8, RPI = 8;  // 4 loads fill a stage: one per wave
     static_assert(NS * STAGE * 2 >= 4 * 2 * 16 * 64 * 4, "the ring doubles as the reduction buffer");
     __shared__ __attribute__((aligned(16))) uint16_t ring[NS][STAGE];
     __shared__ float wred[4];
-    const int layer = blockIdx.x / gb.B, i = blockIdx.x - layer * gb.B;
+    const int layer = __builtin_amdgcn_readfirstlane(blockIdx.x / gb.B), i = blockIdx.x - layer * gb.B;
     const uint16_t* __restrict__ A = gb.A[layer];
     const uint16_t* __restrict__ G = gb.G[layer];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -704,10 +704,11 @@ __global__ __launch_bounds__(256, 2) void gram_small_dma_kernel(GramBatch gb, in
         const bool isA = st < nchA;
         const int soff = __builtin_amdgcn_readfirstlane((isA ? st : st - nchA) * GDK * 2);
         const uint32_t dst = __builtin_amdgcn_readfirstlane(ldsoff + ibuf * (STAGE * 2));
-        // columns past the row's end, and whole stages past the last, arrive as zeros (the load count stays uniform)
-        const int left = st >= nch ? 0 : isA ? d_in - st * GDK : d_out - (st - nchA) * GDK;
-        if (isA) gram_dma16<true>(rA, dst, cg * 8 < left ? voffA : GRAM_OUTSIDE, soff);
-        else gram_dma16<true>(rG, dst, cg * 8 < left ? voffG : GRAM_OUTSIDE, st >= nch ? 0 : soff);
+        const int left = isA ? d_in - st * GDK : d_out - (st - nchA) * GDK;  // columns of the row from this chunk on
+        const bool cut = RAGGED && cg * 8 >= left;                          // past the row's end: zeros
+        if (isA) gram_dma16<true>(rA, dst, cut ? GRAM_OUTSIDE : voffA, soff);
+        else if (st >= nch) gram_dma16<true>(rG, dst, GRAM_OUTSIDE, 0);  // past the last: zeros, keeps the load count uniform
+        else gram_dma16<true>(rG, dst, cut ? GRAM_OUTSIDE : voffG, soff);
         ibuf = ibuf + 1 == NS ? 0 : ibuf + 1;
     };
     const int r = lane & 31;
@@ -937,7 +938,8 @@ static dp_status gram_dma_launch(dp_ctx* ctx, const GramBatch& gb, int T, int d_
     auto launch = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, ctx->stream, gb, T, d_in, d_out, has_bias, out);
     };
-    if (T <= 32 && gb.n_out == 1) launch(gram_small_dma_kernel<16>, 256);
+    if (T <= 32 && gb.n_out == 1 && ragged) launch(gram_small_dma_kernel<16, true>, 256);
+    else if (T <= 32 && gb.n_out == 1) launch(gram_small_dma_kernel<16, false>, 256);
     else if (T <= 64 && wide) launch(gram_dma_kernel<64, 128, 4, 4, 2, false>, 256);
     else if (T <= 64 && ragged) launch(gram_dma_kernel<64, 64, 8, 4, 2, true>, 256);
     else if (T <= 64) launch(gram_dma_kernel<64, 64, 8, 4, 2, false>, 256);

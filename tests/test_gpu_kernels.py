@@ -503,6 +503,11 @@ EMB_SHAPES = [("f32", 6, 20, 4, 13), ("f32", 3, 7, 6, 11), ("bf16", 8, 128, 1024
               ("bf16", 70, 128, 64, 50), ("bf16", 3, 512, 256, 1000)]
 
 
+# more than 256 sort chunks (bases from the scan), two workgroups of columns, runs over many chunks, three digits, ends of 16-row steps
+EMB_SHAPES += [("bf16", 520, 512, 8, 700), ("bf16", 4, 33, 2056, 7), ("f32", 40, 130, 5, 3), ("f32", 2, 16, 1032, 70000),
+               ("bf16", 1, 17, 1024, 9), ("f32", 9, 31, 1028, 20)]
+
+
 @pytest.mark.parametrize("dtype,B,T,d,V", EMB_SHAPES)
 def test_embedding_norms_and_sums(dp, dtype, B, T, d, V):
     ids = syn.zipf_ids(B, T, V, 1.1, 160)
