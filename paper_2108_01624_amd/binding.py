@@ -9,6 +9,7 @@ from ctypes import c_char_p, c_float, c_int, c_size_t, c_uint64, c_void_p
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libdpclip.so")
 _lib = None
+_float32 = _bfloat16 = _int32 = None  # torch's dtype objects, bound with the library
 
 DP_F32, DP_BF16 = 0, 1
 DP_PATH_AUTO, DP_PATH_GRAM, DP_PATH_MATERIALISE = 0, 1, 2
@@ -88,7 +89,7 @@ def load_library():
         return _lib
     # torch ships its own HIP runtime: import it first so that the library binds to the runtime that owns
     # the tensors' memory and streams instead of pulling in a second copy.
-    import torch  # noqa: F401
+    _bind_types()
 
     if not os.path.exists(_LIB_PATH):
         raise RuntimeError(f"{_LIB_PATH} is missing: build it with `python -m paper_2108_01624_amd.build` "
@@ -100,6 +101,13 @@ def load_library():
         fn.restype = _RESTYPES.get(name, c_int)
     _lib = lib
     return lib
+
+
+def _bind_types():
+    global _float32, _bfloat16, _int32
+    import torch
+
+    _float32, _bfloat16, _int32 = torch.float32, torch.bfloat16, torch.int32
 
 
 def _ptr(t):
@@ -114,9 +122,9 @@ def _f32(t):
     """Device pointer of an fp32 tensor (sums, norms, parameters); refuses any other element type."""
     if t is None or isinstance(t, int):
         return t
-    import torch
-
-    if t.dtype != torch.float32:
+    if _float32 is None:
+        _bind_types()
+    if t.dtype != _float32:
         raise TypeError(f"expected a float32 tensor, got {t.dtype}")
     return t.data_ptr()
 
@@ -124,21 +132,30 @@ def _f32(t):
 def _i32(t):
     if t is None or isinstance(t, int):
         return t
-    import torch
-
-    if t.dtype != torch.int32:
+    if _int32 is None:
+        _bind_types()
+    if t.dtype != _int32:
         raise TypeError(f"expected an int32 tensor, got {t.dtype}")
     return t.data_ptr()
 
 
 def _dtype_of(t) -> int:
-    import torch
+    return _dtype_code(t.dtype)
 
-    if t.dtype == torch.float32:
+
+def _dtype_code(dt) -> int:
+    if _float32 is None:
+        _bind_types()
+    if dt == _float32:
         return DP_F32
-    if t.dtype == torch.bfloat16:
+    if dt == _bfloat16:
         return DP_BF16
-    raise TypeError(f"unsupported tensor dtype {t.dtype}")
+    raise TypeError(f"unsupported tensor dtype {dt}")
+
+
+def _table(ptrs):
+    """HOST array of device pointers."""
+    return (c_void_p * len(ptrs))(*ptrs)
 
 
 def _check(ctx, st: int, where: str):
@@ -180,23 +197,57 @@ def dp_sqnorms_dense(ctx, A, G, has_bias, path, sqnorms, *, B=None, T=None):
     _check(ctx, st, "dp_sqnorms_dense")
 
 
+# Pointer-level forms of the batched calls: the caller has checked that all layers share one shape and dtype (`shape` is
+# (B, T, d_in, d_out) or (B, T, d), `dtype` a DP_* code) and hands over device addresses; one per layer, no tensor is touched again.
+def _sqnorms_dense_ptrs(ctx, As, Gs, dtype, shape, has_bias, path, sqnorms):
+    st = load_library().dp_sqnorms_dense_batched(ctx, len(As), _table(As), _table(Gs), dtype, *shape, int(has_bias), int(path),
+                                                 _f32(sqnorms))
+    _check(ctx, st, "dp_sqnorms_dense_batched")
+
+
+def _sqnorms_dense_shared_ptrs(ctx, As, n_out, Gs, dtype, shape, has_bias, sqnorms):
+    st = load_library().dp_sqnorms_dense_shared(ctx, len(As), _table(As), n_out, _table(Gs), dtype, *shape, int(has_bias),
+                                                _f32(sqnorms))
+    _check(ctx, st, "dp_sqnorms_dense_shared")
+
+
+def _clip_accumulate_dense_ptrs(ctx, As, Gs, dtype, shape, C, sqnorms, sum_Ws, sum_bs):
+    st = load_library().dp_clip_accumulate_dense_batched(ctx, len(As), _table(As), _table(Gs), dtype, *shape, float(C), _f32(sqnorms),
+                                                         _table(sum_Ws), _table(sum_bs) if sum_bs is not None else None)
+    _check(ctx, st, "dp_clip_accumulate_dense_batched")
+
+
+def _sqnorms_layernorm_keep_ptrs(ctx, Xhats, Gs, dtype, shape, sqnorms, grads):
+    st = load_library().dp_sqnorms_layernorm_keep(ctx, len(Xhats), _table(Xhats), _table(Gs), dtype, *shape, _f32(sqnorms), _table(grads))
+    _check(ctx, st, "dp_sqnorms_layernorm_keep")
+
+
+def _clip_accumulate_layernorm_kept_ptrs(ctx, grads, B, d, C, sqnorms, sum_gammas, sum_betas):
+    st = load_library().dp_clip_accumulate_layernorm_kept(ctx, len(grads), _table(grads), int(B), int(d), float(C), _f32(sqnorms),
+                                                          _table(sum_gammas), _table(sum_betas))
+    _check(ctx, st, "dp_clip_accumulate_layernorm_kept")
+
+
+def _dense_shape(As, Gs):
+    """(B, T, d_in, d_out) and the dtype code that all layers of a batch share."""
+    B, T, d_in = sA = As[0].shape
+    d_out = Gs[0].shape[-1]
+    dt, sG = As[0].dtype, (B, T, d_out)
+    for a, g in zip(As, Gs):
+        if a.shape != sA or g.shape != sG or a.dtype != dt:
+            raise ValueError("all layers of a batch must share one shape and dtype")
+    return (B, T, d_in, d_out), _dtype_code(dt)
+
+
 def dp_sqnorms_dense_batched(ctx, As, Gs, has_bias, path, sqnorms):
     """As, Gs: equally long lists of same-shaped tensors (one pair per layer)."""
-    n = len(As)
-    B, T, d_in = As[0].shape
-    d_out = Gs[0].shape[-1]
-    for a, g in zip(As, Gs):
-        if tuple(a.shape) != (B, T, d_in) or tuple(g.shape) != (B, T, d_out) or a.dtype != As[0].dtype:
-            raise ValueError("all layers of a batch must share one shape and dtype")
-    arr = lambda ptrs: (c_void_p * n)(*ptrs)
-    st = load_library().dp_sqnorms_dense_batched(ctx, n, arr([_ptr(t) for t in As]), arr([_ptr(t) for t in Gs]),
-                                                 _dtype_of(As[0]), B, T, d_in, d_out, int(has_bias), int(path), _f32(sqnorms))
-    _check(ctx, st, "dp_sqnorms_dense_batched")
+    shape, dt = _dense_shape(As, Gs)
+    _sqnorms_dense_ptrs(ctx, [_ptr(t) for t in As], [_ptr(t) for t in Gs], dt, shape, has_bias, path, sqnorms)
 
 
 def dp_sqnorms_dense_shared(ctx, As, Gs, has_bias, sqnorms):
     """As: one input tensor per group; Gs: per group a list of the output-gradient tensors of the layers sharing it."""
-    ng, n_out = len(As), len(Gs[0])
+    n_out = len(Gs[0])
     B, T, d_in = As[0].shape
     d_out = Gs[0][0].shape[-1]
     flat = []
@@ -207,11 +258,8 @@ def dp_sqnorms_dense_shared(ctx, As, Gs, has_bias, sqnorms):
             if tuple(g.shape) != (B, T, d_out) or g.dtype != a.dtype:
                 raise ValueError("all layers of a call must share one shape and dtype")
             flat.append(g)
-    pa = (c_void_p * ng)(*[_ptr(t) for t in As])
-    pg = (c_void_p * len(flat))(*[_ptr(t) for t in flat])
-    st = load_library().dp_sqnorms_dense_shared(ctx, ng, pa, n_out, pg, _dtype_of(As[0]), B, T, d_in, d_out, int(has_bias),
-                                                _f32(sqnorms))
-    _check(ctx, st, "dp_sqnorms_dense_shared")
+    _sqnorms_dense_shared_ptrs(ctx, [_ptr(t) for t in As], n_out, [_ptr(t) for t in flat], _dtype_of(As[0]), (B, T, d_in, d_out),
+                               has_bias, sqnorms)
 
 
 def dp_sqnorms_layernorm(ctx, Xhat, G, sqnorms):
@@ -240,18 +288,9 @@ def dp_clip_accumulate_dense(ctx, A, G, C, sqnorms, sum_W, sum_b=None):
 
 def dp_clip_accumulate_dense_batched(ctx, As, Gs, C, sqnorms, sum_Ws, sum_bs=None):
     """As, Gs, sum_Ws (and sum_bs, entries may be None): equally long lists of same-shaped tensors."""
-    n = len(As)
-    B, T, d_in = As[0].shape
-    d_out = Gs[0].shape[-1]
-    for a, g in zip(As, Gs):
-        if tuple(a.shape) != (B, T, d_in) or tuple(g.shape) != (B, T, d_out) or a.dtype != As[0].dtype:
-            raise ValueError("all layers of a batch must share one shape and dtype")
-    arr = lambda ptrs: (c_void_p * n)(*ptrs)
-    pb = arr([_f32(t) for t in sum_bs]) if sum_bs is not None else None
-    st = load_library().dp_clip_accumulate_dense_batched(ctx, n, arr([_ptr(t) for t in As]), arr([_ptr(t) for t in Gs]),
-                                                         _dtype_of(As[0]), B, T, d_in, d_out, float(C), _f32(sqnorms),
-                                                         arr([_f32(t) for t in sum_Ws]), pb)
-    _check(ctx, st, "dp_clip_accumulate_dense_batched")
+    shape, dt = _dense_shape(As, Gs)
+    _clip_accumulate_dense_ptrs(ctx, [_ptr(t) for t in As], [_ptr(t) for t in Gs], dt, shape, C, sqnorms, [_f32(t) for t in sum_Ws],
+                                [_f32(t) for t in sum_bs] if sum_bs is not None else None)
 
 
 def dp_clip_accumulate_layernorm(ctx, Xhat, G, C, sqnorms, sum_gamma, sum_beta):
@@ -306,24 +345,17 @@ def dp_clip_accumulate_layernorm_batched(ctx, Xhats, Gs, C, sqnorms, sum_gammas,
 
 def dp_sqnorms_layernorm_keep(ctx, Xhats, Gs, sqnorms, grads):
     """grads: one float32 tensor [B, 2, d] per layer, overwritten with every example's gain / offset gradient."""
-    n = len(Xhats)
     B, T, d = _same_shaped(Xhats, Gs)
     for g in grads:
         if g.numel() < B * 2 * d:
             raise ValueError("grads[l] must hold B x 2 x d floats")
-    arr = lambda ptrs: (c_void_p * n)(*ptrs)
-    st = load_library().dp_sqnorms_layernorm_keep(ctx, n, arr([_ptr(t) for t in Xhats]), arr([_ptr(t) for t in Gs]),
-                                                  _dtype_of(Gs[0]), B, T, d, _f32(sqnorms), arr([_f32(t) for t in grads]))
-    _check(ctx, st, "dp_sqnorms_layernorm_keep")
+    _sqnorms_layernorm_keep_ptrs(ctx, [_ptr(t) for t in Xhats], [_ptr(t) for t in Gs], _dtype_of(Gs[0]), (B, T, d), sqnorms,
+                                 [_f32(t) for t in grads])
 
 
 def dp_clip_accumulate_layernorm_kept(ctx, grads, B, d, C, sqnorms, sum_gammas, sum_betas):
-    n = len(grads)
-    arr = lambda ptrs: (c_void_p * n)(*ptrs)
-    st = load_library().dp_clip_accumulate_layernorm_kept(ctx, n, arr([_f32(t) for t in grads]), int(B), int(d), float(C),
-                                                          _f32(sqnorms), arr([_f32(t) for t in sum_gammas]),
-                                                          arr([_f32(t) for t in sum_betas]))
-    _check(ctx, st, "dp_clip_accumulate_layernorm_kept")
+    _clip_accumulate_layernorm_kept_ptrs(ctx, [_f32(t) for t in grads], B, d, C, sqnorms, [_f32(t) for t in sum_gammas],
+                                         [_f32(t) for t in sum_betas])
 
 
 def _tied_shapes(ids, dY, H, dL):

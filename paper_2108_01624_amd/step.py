@@ -28,6 +28,8 @@ class StepRunner:
                 off += n
             self.offsets.append(cur)
         self.P = off
+        # byte offsets of the tensors inside a flat buffer: what the batched calls need of a layer's sums
+        self._at = [[4 * o for o, _ in cur] for cur in self.offsets]
         self.S = torch.zeros(self.P, dtype=torch.float32, device=device)
         self.theta = torch.zeros(self.P, dtype=torch.float32, device=device)
         self.m = torch.zeros(self.P, dtype=torch.float32, device=device)
@@ -59,28 +61,39 @@ class StepRunner:
     @staticmethod
     def _ln_token(layers, nB):
         """Identifies the micro-batch whose LayerNorm gradients the keep buffers hold: batch size and input buffers."""
-        return (nB, tuple((l["X"].data_ptr(), l["G"].data_ptr()) for l in layers if l["kind"] == "layernorm"))
+        return (nB, [(l["X"].data_ptr(), l["G"].data_ptr()) for l in layers if l["kind"] == "layernorm"])
+
+    @staticmethod
+    def _dense_dims(key):
+        """(B, T, d_in, d_out) of a group of dense layers from its key, whose first entries are the shapes of A and G."""
+        (B, T, d_in), sG = key[0], key[1]
+        if tuple(sG[:-1]) != (B, T):
+            raise ValueError("A [B,T,d_in] and G [B,T,d_out] expected")
+        return B, T, d_in, sG[-1]
 
     def pass1(self, layers, path=B_.DP_PATH_AUTO, batch_dense=True):
         """Per-example squared global norms of one micro-batch: sqnorms[:B] = sum over all layers.  The norm is a sum
-        over layers, so dense layers of one shape, and LayerNorms of one shape, are handed over together."""
+        over layers, so dense layers of one shape, and LayerNorms of one shape, are handed over together (by address: a small
+        micro-batch is over on the GPU before Python has looked at 96 tensors twice)."""
         ctx = self.ctx
         nB = layers[0]["G"].shape[0]
         n = self.sqnorms[:nB]
         ctx.zero_f32(n)
         groups, ln_groups = {}, {}
         for k, l in enumerate(layers):
-            if l["kind"] == "dense":
+            kind = l["kind"]
+            if kind == "dense":
+                A, G = l["A"], l["G"]
                 if batch_dense:
-                    groups.setdefault((tuple(l["A"].shape), tuple(l["G"].shape), l["A"].dtype, bool(l["has_bias"])), []).append(l)
+                    groups.setdefault((A.shape, G.shape, A.dtype, bool(l["has_bias"])), []).append((A.data_ptr(), G.data_ptr(), G.dtype))
                 else:
-                    ctx.sqnorms_dense(l["A"], l["G"], l["has_bias"], path, n)
-            elif l["kind"] == "layernorm":
+                    ctx.sqnorms_dense(A, G, l["has_bias"], path, n)
+            elif kind == "layernorm":
                 if batch_dense:
-                    ln_groups.setdefault((tuple(l["X"].shape), l["X"].dtype), []).append(k)
+                    ln_groups.setdefault((l["X"].shape, l["X"].dtype), []).append(k)
                 else:
                     ctx.sqnorms_layernorm(l["X"], l["G"], n)
-            elif l["kind"] == "tied_embedding":   # lookup table that is also the output projection; G = dY
+            elif kind == "tied_embedding":   # lookup table that is also the output projection; G = dY
                 ctx.sqnorms_tied_embedding(l["ids"], l["G"], l["H"], l["dL"], n)
             else:
                 ctx.sqnorms_embedding(l["ids"], l["G"], l["V"], l["distinct"], n)
@@ -95,19 +108,25 @@ class StepRunner:
         if ln_groups and all(k[0][-1] % 4 == 0 for k in ln_groups):
             self._kept_for = self._ln_token(layers, nB)
         for key, ls in groups.items():
-            # layers reading the very same input tensor (query / key / value projections) share its Gram matrix
-            by_input = {}
-            for l in ls:
-                by_input.setdefault(l["A"].data_ptr(), []).append(l)
-            shared = [v for v in by_input.values() if len(v) in (2, 3)] if path == B_.DP_PATH_AUTO else []
-            for width in (3, 2):
-                sel = [v for v in shared if len(v) == width]
-                if sel:
-                    ctx.sqnorms_dense_shared([v[0]["A"] for v in sel], [[l["G"] for l in v] for v in sel], key[3], n)
-            taken = {id(l) for v in shared for l in v}
-            rest = [l for l in ls if id(l) not in taken]
+            dims, dt = self._dense_dims(key), B_._dtype_code(key[2])
+            rest = ls
+            if path == B_.DP_PATH_AUTO:
+                # layers reading the very same input tensor (query / key / value projections) share its Gram matrix
+                by_input = {}
+                for a, g, g_dt in ls:
+                    by_input.setdefault(a, []).append((g, g_dt))
+                shared = {a: gs for a, gs in by_input.items() if len(gs) in (2, 3)}
+                if any(g_dt != key[2] for gs in shared.values() for _, g_dt in gs):
+                    raise ValueError("all layers of a call must share one shape and dtype")
+                for width in (3, 2):
+                    sel = [(a, gs) for a, gs in shared.items() if len(gs) == width]
+                    if sel:
+                        B_._sqnorms_dense_shared_ptrs(ctx.handle, [a for a, _ in sel], width, [g for _, gs in sel for g, _ in gs], dt, dims,
+                                                      key[3], n)
+                if shared:
+                    rest = [x for x in ls if x[0] not in shared]
             if rest:
-                ctx.sqnorms_dense_batched([l["A"] for l in rest], [l["G"] for l in rest], key[3], path, n)
+                B_._sqnorms_dense_ptrs(ctx.handle, [x[0] for x in rest], [x[1] for x in rest], dt, dims, key[3], path, n)
         return n
 
     def pass2(self, layers, C, batch_dense=True):
@@ -116,20 +135,27 @@ class StepRunner:
         ctx = self.ctx
         nB = layers[0]["G"].shape[0]
         n = self.sqnorms[:nB]
+        S = B_._f32(self.S)
+        if self.S.numel() < self.P or not self.S.is_contiguous():
+            raise ValueError("S must be a contiguous buffer of all parameters")
         groups, ln_groups = {}, {}
         for k, l in enumerate(layers):
-            if l["kind"] == "dense":
+            kind = l["kind"]
+            if kind == "dense":
+                A, G = l["A"], l["G"]
                 if batch_dense:
-                    groups.setdefault((tuple(l["A"].shape), tuple(l["G"].shape), l["A"].dtype), []).append(k)
+                    at = self._at[k]
+                    groups.setdefault((A.shape, G.shape, A.dtype), []).append(
+                        (A.data_ptr(), G.data_ptr(), S + at[0], S + at[1] if l["has_bias"] else None))
                 else:
                     sb = self.view(self.S, k, 1) if l["has_bias"] else None
-                    ctx.clip_accumulate_dense(l["A"], l["G"], C, n, self.view(self.S, k, 0), sb)
-            elif l["kind"] == "layernorm":
+                    ctx.clip_accumulate_dense(A, G, C, n, self.view(self.S, k, 0), sb)
+            elif kind == "layernorm":
                 if batch_dense:
-                    ln_groups.setdefault((tuple(l["X"].shape), l["X"].dtype), []).append(k)
+                    ln_groups.setdefault((l["X"].shape, l["X"].dtype), []).append(k)
                 else:
                     ctx.clip_accumulate_layernorm(l["X"], l["G"], C, n, self.view(self.S, k, 0), self.view(self.S, k, 1))
-            elif l["kind"] == "tied_embedding":
+            elif kind == "tied_embedding":
                 ctx.clip_accumulate_tied_embedding(l["ids"], l["G"], l["H"], l["dL"], C, n, self.view(self.S, k, 0))
             elif l.get("distinct"):
                 ctx.clip_accumulate_positions(l["G"], C, n, self.view(self.S, k, 0))   # position ids: no sort needed
@@ -137,17 +163,15 @@ class StepRunner:
                 ctx.clip_accumulate_embedding(l["ids"], l["G"], l["V"], C, n, self.view(self.S, k, 0))
         kept = self._kept_for is not None and self._kept_for == self._ln_token(layers, nB)   # pass 1 of this very micro-batch left the LayerNorm gradients behind
         for sel in ln_groups.values():
-            sg, sb = [self.view(self.S, k, 0) for k in sel], [self.view(self.S, k, 1) for k in sel]
+            sg, sb = [S + self._at[k][0] for k in sel], [S + self._at[k][1] for k in sel]
             if kept:
                 d = layers[sel[0]]["X"].shape[-1]
                 ctx.clip_accumulate_layernorm_kept([self.ln_keep[k] for k in sel], nB, d, C, n, sg, sb)
             else:
                 ctx.clip_accumulate_layernorm_batched([layers[k]["X"] for k in sel], [layers[k]["G"] for k in sel], C, n, sg, sb)
-        for sel in groups.values():
-            ctx.clip_accumulate_dense_batched(
-                [layers[k]["A"] for k in sel], [layers[k]["G"] for k in sel], C, n,
-                [self.view(self.S, k, 0) for k in sel],
-                [self.view(self.S, k, 1) if layers[k]["has_bias"] else None for k in sel])
+        for key, ls in groups.items():
+            As, Gs, Ws, bs = (list(col) for col in zip(*ls))
+            B_._clip_accumulate_dense_ptrs(ctx.handle, As, Gs, B_._dtype_code(key[2]), self._dense_dims(key), C, n, Ws, bs)
 
     def update(self, *, sigma, C, seed, step, batch_size, lr, beta1, beta2, eps=1e-11, weight_decay, zero_sum=True,
                snr_sq=None):

@@ -190,3 +190,36 @@ def test_privacy_accounting_matches_the_oracle(lib):
     for bad in ((0.0, tol), (1.0, 0.0), (1.0, 1.0), (0.9 * math.log(1 / 2.89e-9) / 31, tol)):    # last: below the conversion term
         with pytest.raises(pkg.DpError):
             pkg.dp_rdp_noise_multiplier(q, steps, bad[0], 2.89e-9, 32, bad[1])
+
+
+def test_step_runner_refuses_what_the_addresses_cannot_carry():
+    """The step driver hands layers over by address: shapes that do not belong together and a sum buffer that cannot hold
+    every parameter are refused before the library is called."""
+    import torch
+
+    import dp_synth as syn
+    import paper_2108_01624_amd as pkg
+
+    class NoCalls:
+        handle = None
+
+        def __getattr__(self, name):
+            return lambda *a, **k: None
+
+    man = syn.single_dense_manifest(8, 16, True)
+    run = pkg.StepRunner(NoCalls(), man, 2, device="cpu")
+    A, G = torch.zeros(2, 3, 8), torch.zeros(2, 3, 16)
+    layer = lambda a, g: [dict(kind="dense", A=a, G=g, has_bias=True)]
+    for bad in (torch.zeros(2, 4, 16), torch.zeros(3, 3, 16)):
+        with pytest.raises(ValueError):
+            run.pass1(layer(A, bad))
+        with pytest.raises(ValueError):
+            run.pass2(layer(A, bad), 1.0)
+    full = run.S
+    for S in (full[:-1], torch.zeros(2 * full.numel())[::2]):
+        run.S = S
+        with pytest.raises(ValueError):
+            run.pass2(layer(A, G), 1.0)
+    run.S = full.double()
+    with pytest.raises(TypeError):
+        run.pass2(layer(A, G), 1.0)
