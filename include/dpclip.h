@@ -98,7 +98,7 @@ dp_status dp_sqnorms_dense(dp_ctx* ctx, const void* A, const void* G, dp_dtype d
 
 /* n_layers dense layers of one shape in one call: the result is that of n_layers calls of dp_sqnorms_dense
  * with the same arguments (each layer's norms added to sqnorms[i], layers in index order).  On the Gram path
- * with widths that are multiples of 64 the layers share launches of up to 16 layers, which keeps the memory
+ * the layers share launches of up to 64 layers, which keeps the memory
  * pipeline full across examples; their per-layer norms (for T > 128: per layer and unit of two or three 128 x 128 cells of the T x T plane) pass
  * through the library workspace and are added in a fixed order (DP_ERR_WORKSPACE if they do not fit).
  * A, G are HOST arrays of n_layers device pointers, read during the call only. */
@@ -121,7 +121,7 @@ dp_status dp_sqnorms_layernorm(dp_ctx* ctx, const void* Xhat, const void* G, dp_
                                float* sqnorms);
 
 /* n_layers LayerNorms of one shape in one call: the result of n_layers calls of dp_sqnorms_layernorm (layers added
- * in index order).  Up to 16 layers share a launch; their per-example partial norms pass through the library
+ * in index order).  Up to 32 layers share a launch; their per-example partial norms pass through the library
  * workspace (DP_ERR_WORKSPACE if they do not fit).  Xhat, G: HOST arrays of n_layers device pointers, read during the
  * call only. */
 dp_status dp_sqnorms_layernorm_batched(dp_ctx* ctx, int n_layers, const void* const* Xhat, const void* const* G,
@@ -169,7 +169,7 @@ dp_status dp_clip_accumulate_layernorm(dp_ctx* ctx, const void* Xhat, const void
                                        int d, float C, const float* sqnorms, float* sum_gamma, float* sum_beta);
 
 /* n_layers LayerNorms of one shape in one call: the result of n_layers calls of dp_clip_accumulate_layernorm, with
- * one evaluation of the clip factors and up to 16 layers per launch.  Xhat, G, sum_gamma, sum_beta: HOST arrays of
+ * one evaluation of the clip factors and up to 32 layers per launch.  Xhat, G, sum_gamma, sum_beta: HOST arrays of
  * n_layers device pointers (none NULL), read during the call only. */
 dp_status dp_clip_accumulate_layernorm_batched(dp_ctx* ctx, int n_layers, const void* const* Xhat, const void* const* G,
                                                dp_dtype dtype, int B, int T, int d, float C, const float* sqnorms,

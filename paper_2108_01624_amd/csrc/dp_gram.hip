@@ -221,8 +221,9 @@ constexpr int GRAM_OUTSIDE = (int)0x80000000u;
 // GDK: contraction chunk per stage (a row segment of 2*GDK bytes per load); NS: ring stages.
 // Up to GRAM_MAX_BATCH same-shaped layers per launch: workgroup g works on example g % B of layer g / B.  More
 // workgroups than the chip holds at once keep the memory pipeline full across examples (one round of 512
-// workgroups spends a fifth of its time filling and draining it).
-constexpr int GRAM_MAX_BATCH = 16;
+// workgroups spends a fifth of its time filling and draining it), and with few examples many layers are what fills the chip
+// at all (48 layers of 768 x 768, B = 8: three launches of 16 layers 53 us, one 27).
+constexpr int GRAM_MAX_BATCH = 64;
 struct GramBatch {
     const uint16_t* A[GRAM_MAX_BATCH];
     const uint16_t* G[GRAM_MAX_BATCH];

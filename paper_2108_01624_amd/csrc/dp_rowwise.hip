@@ -64,7 +64,7 @@ __device__ __forceinline__ void load_vec(const void* __restrict__ base, size_t i
 // ------------------------------------------------------------------------------------------------
 // Up to COL_MAX_BATCH same-shaped layers per launch (blockIdx.z = layer): the 48 LayerNorms of the model are 3 launches
 // per pass instead of 48, and their per-example partials meet in one ordered reduction.
-constexpr int COL_MAX_BATCH = 16;
+constexpr int COL_MAX_BATCH = 32;
 struct ColBatch {
     const void* X[COL_MAX_BATCH];
     const void* G[COL_MAX_BATCH];

@@ -47,7 +47,7 @@ struct WgemmArgs {
 
 // Several layers of one shape in one launch: the unit of work distribution is the pair (layer, row split); `base`
 // describes the common shape.
-constexpr int MAX_BATCH = 32;
+constexpr int MAX_BATCH = 64;
 struct LayerPtrs {
     const uint16_t* A;
     const uint16_t* G;
