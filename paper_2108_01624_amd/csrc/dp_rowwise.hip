@@ -361,103 +361,134 @@ __global__ __launch_bounds__(256) void reduce_partials_pair_kernel(const float4*
 }
 
 // ------------------------------------------------------------------------------------------------
-// embedding, per-example norms (pass 1): grid (B, ceil(d/(256*VW))), four waves per workgroup, each with 64*VW columns.
-// The workgroup ranks the example's T ids (stable counting rank in LDS), then every wave walks the rows in id order, adding
-// the square of every run of equal ids, column by column.  The next EMB_AHEAD rows are in flight while the last EMB_AHEAD are
-// added, and a run's end is a select, not a branch (behind a branch every row waited for the one before it).
-// B = 512, T = 128, d = 1024: 29 us (134 MB); with the partial norms of four workgroups per example added by a launch of their
-// own it was 31 + 5.
+// embedding, per-example norms (pass 1): one workgroup of W waves (8 or 16) per example and ncb blocks of 64*VW columns; the
+// W / ncb waves of a column block share the example's positions.
+// The workgroup ranks the T ids (stable counting rank in LDS: every key, the id above the position, against all others), then
+// every wave walks its run of sorted positions, EMB_AHEAD rows in flight, adding up rows of equal id; a run's end is a select,
+// not a branch.  Runs that are complete inside a wave are squared there; the sums of a wave's first and last run go to LDS, where
+// they are joined across the waves, column by column.
+// One wave walking all positions of its columns was a chain of T / 8 round trips: B = 23, T = 375, d = 832: 61 -> 23 us;
+// B = 512, T = 128, d = 1024 (134 MB): 31 + 5 -> 28.
 // ------------------------------------------------------------------------------------------------
 constexpr int EMB_AHEAD = 16;
 
-template <bool BF16, int VW, bool DISTINCT>
-__global__ __launch_bounds__(256) void embedding_sqnorms_kernel(const int32_t* __restrict__ ids,
-                                                                const void* __restrict__ G, int T, int d, int V,
-                                                                float* __restrict__ out, int J, int direct,
-                                                                int* __restrict__ err) {
-    extern __shared__ int32_t lds[];
-    __shared__ float wred[4];
-    int32_t* sid = lds;         // [T] ids of this example; after the ranking: in sorted order
-    int32_t* order = lds + T;   // [T] row index at each sorted position
+template <bool BF16, int VW, bool DISTINCT, int EMB_WAVES>
+__global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const int32_t* __restrict__ ids,
+                                                                           const void* __restrict__ G, int T, int d, int V, int ncb,
+                                                                           float* __restrict__ out, int J, int direct,
+                                                                           int* __restrict__ err) {
+    extern __shared__ uint32_t lds[];
+    __shared__ float head[EMB_WAVES][64 * VW], tail[EMB_WAVES][64 * VW];  // first and last run of a wave
+    __shared__ uint32_t whole[EMB_WAVES];                                 // the wave saw one run only: it is in head
+    __shared__ float wred[EMB_WAVES];
+    uint32_t* sid = lds;        // [T rounded up to 4] ids of this example
+    uint16_t* order = reinterpret_cast<uint16_t*>(lds + (T + 3) / 4 * 4);  // [T] row index at each sorted position (T <= 4096)
     const int i = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = ((blockIdx.y * 4 + wave) * 64 + lane) * VW;
     bool bad = false;
-    for (int t = threadIdx.x; t < T; t += 256) {
-        const int32_t v = ids[(size_t)i * T + t];
-        if (v < 0 || v >= V) bad = true;
-        sid[t] = v;
+    for (int t = threadIdx.x; t < (T + 3) / 4 * 4; t += 64 * EMB_WAVES) {
+        const int32_t v = t < T ? ids[(size_t)i * T + t] : 0;
+        if (t < T && (v < 0 || v >= V)) bad = true;
+        sid[t] = t < T ? (uint32_t)v : 0xFFFFFFFFu;  // (the padding ranks behind everything)
     }
     if (bad) atomicOr(err, 1);
     __syncthreads();
     if constexpr (!DISTINCT) {
-        for (int t = threadIdx.x; t < T; t += 256) {
-            const int32_t v = sid[t];
+        const uint4* s4 = reinterpret_cast<const uint4*>(sid);
+        for (int t = threadIdx.x; t < T; t += 64 * EMB_WAVES) {
+            const uint32_t v = sid[t];
+            // keys are unique as (id, position): before position t an equal id ranks lower, after it higher
             int rank = 0;
-#pragma unroll 8
-            for (int s = 0; s < T; ++s) {
-                const int32_t u = sid[s];
-                rank += (u < v) || (u == v && s < t);
+            const int t4 = t / 4;
+            for (int s = 0; s < t4; ++s) {
+                const uint4 u = s4[s];
+                rank += (u.x <= v) + (u.y <= v) + (u.z <= v) + (u.w <= v);
             }
-            order[rank] = t;
+            const uint4 u = s4[t4];
+            const int r = t % 4;
+            rank += (0 < r ? u.x <= v : u.x < v) + (1 < r ? u.y <= v : u.y < v) + (2 < r ? u.z <= v : u.z < v) + (u.w < v);
+            for (int s = t4 + 1; s < (T + 3) / 4; ++s) {
+                const uint4 w = s4[s];
+                rank += (w.x < v) + (w.y < v) + (w.z < v) + (w.w < v);
+            }
+            order[rank] = (uint16_t)t;
         }
         __syncthreads();
     }
-    float tot = 0.f;
-    if (col < d) {
+    const int parts = EMB_WAVES / ncb, cb = wave % ncb, part = wave / ncb;
+    const int col = ((blockIdx.y * ncb + cb) * 64 + lane) * VW;
+    const int per = (T + parts - 1) / parts, lo = part * per, hi = lo + per < T ? lo + per : T;  // this wave's positions
+    float tot = 0.f, run[VW], hd[VW];
+#pragma unroll
+    for (int k = 0; k < VW; ++k) run[k] = hd[k] = 0.f;
+    bool one = true;  // no run has ended yet
+    if (col < d && lo < hi) {
         const size_t base = (size_t)i * T * d + col;
-        float run[VW];
-#pragma unroll
-        for (int k = 0; k < VW; ++k) run[k] = 0.f;
-        int32_t prev = DISTINCT ? 0 : sid[order[0]];
-        struct Rows {
+        uint32_t prev = DISTINCT ? 0u : sid[order[lo]];
+        for (int p0 = lo; p0 < hi; p0 += EMB_AHEAD) {
             RawVec<BF16, VW> g[EMB_AHEAD];
-            int32_t id[EMB_AHEAD];
-        };
-        auto fetch = [&](Rows& x, int p0) {
+            uint32_t id[EMB_AHEAD];
 #pragma unroll
             for (int u = 0; u < EMB_AHEAD; ++u) {
-                const int p = p0 + u < T ? p0 + u : T - 1;
-                const int t = DISTINCT ? p : order[p];
-                x.id[u] = DISTINCT ? 0 : sid[t];
-                x.g[u] = load_raw<BF16, VW>(G, base + (size_t)t * d);
+                const int p = p0 + u < hi ? p0 + u : hi - 1;
+                const int t = DISTINCT ? p : (int)order[p];
+                id[u] = DISTINCT ? 0u : sid[t];
+                g[u] = load_raw<BF16, VW>(G, base + (size_t)t * d);
             }
-        };
-        auto add = [&](const Rows& x, int p0) {
 #pragma unroll
             for (int u = 0; u < EMB_AHEAD; ++u) {
-                const bool in = p0 + u < T;
-                const bool ends = !DISTINCT && in && x.id[u] != prev;  // the run before this row is complete
+                const bool in = p0 + u < hi;
+                const bool ends = !DISTINCT && in && id[u] != prev;  // the run before this row is complete
 #pragma unroll
                 for (int k = 0; k < VW; ++k) {
-                    const float g = in ? raw_value<BF16, VW>(x.g[u], k) : 0.f;
+                    const float x = in ? raw_value<BF16, VW>(g[u], k) : 0.f;
                     if constexpr (DISTINCT) {
-                        tot += g * g;
+                        tot += x * x;
                     } else {
-                        tot += ends ? run[k] * run[k] : 0.f;
-                        run[k] = (ends ? 0.f : run[k]) + g;
+                        hd[k] = ends && one ? run[k] : hd[k];
+                        tot += ends && !one ? run[k] * run[k] : 0.f;
+                        run[k] = (ends ? 0.f : run[k]) + x;
                     }
                 }
-                prev = in ? x.id[u] : prev;
+                one = one && !ends;
+                prev = in ? id[u] : prev;
             }
-        };
-        Rows x0, x1;
-        fetch(x0, 0);
-        for (int p0 = 0; p0 < T; p0 += 2 * EMB_AHEAD) {
-            if (p0 + EMB_AHEAD < T) fetch(x1, p0 + EMB_AHEAD);
-            __builtin_amdgcn_sched_barrier(0);
-            add(x0, p0);
-            if (p0 + EMB_AHEAD >= T) break;
-            if (p0 + 2 * EMB_AHEAD < T) fetch(x0, p0 + 2 * EMB_AHEAD);
-            __builtin_amdgcn_sched_barrier(0);
-            add(x1, p0 + EMB_AHEAD);
-        }
-        if constexpr (!DISTINCT) {
-#pragma unroll
-            for (int k = 0; k < VW; ++k) tot += run[k] * run[k];
         }
     }
-    tot = dp_block_sum<256>(tot, wred);
+    if constexpr (!DISTINCT) {
+#pragma unroll
+        for (int k = 0; k < VW; ++k) {
+            head[wave][lane * VW + k] = one ? run[k] : hd[k];
+            tail[wave][lane * VW + k] = run[k];
+        }
+        if (lane == 0) whole[wave] = one ? 1u : 0u;
+        __syncthreads();
+        if (part == 0 && col < d) {
+            // the parts of this column block in order of position: a part's first run continues the one before it when the ids agree
+            float carry[VW];
+#pragma unroll
+            for (int k = 0; k < VW; ++k) carry[k] = 0.f;
+            uint32_t carry_id = 0;
+            for (int q = 0; q < parts && q * per < T; ++q) {
+                const int w = q * ncb + cb, end = (q + 1) * per < T ? (q + 1) * per : T;
+                const bool joins = q > 0 && sid[order[q * per]] == carry_id, single = whole[w] != 0u;
+#pragma unroll
+                for (int k = 0; k < VW; ++k) {
+                    const float h = head[w][lane * VW + k];
+                    tot += joins ? 0.f : carry[k] * carry[k];
+                    carry[k] = joins ? carry[k] + h : h;
+                    if (!single) {
+                        tot += carry[k] * carry[k];
+                        carry[k] = tail[w][lane * VW + k];
+                    }
+                }
+                carry_id = sid[order[end - 1]];
+            }
+#pragma unroll
+            for (int k = 0; k < VW; ++k) tot += carry[k] * carry[k];
+        }
+    }
+    tot = dp_block_sum<64 * EMB_WAVES>(tot, wred);
     if (threadIdx.x == 0) {
         // (an out-of-range id only changes the grouping; the error itself is reported by dp_sync)
         if (direct) out[i] += tot;
@@ -1041,7 +1072,14 @@ dp_status dpk_colstat_sums(dp_ctx* ctx, const void* X, const void* G, dp_dtype d
 template <bool BF16, int VW>
 static dp_status embedding_sqnorms_launch(dp_ctx* ctx, const int32_t* ids, const void* G, int B, int T, int d, int V,
                                           int distinct, float* sqnorms) {
-    const int J = (d + 256 * VW - 1) / (256 * VW);
+    // Column blocks per workgroup: as many as there are (up to 4), so that the ids are ranked once and the example needs no
+    // reduction launch; one, and all waves on its positions, when the examples alone are too few for the chip.  16 waves of
+    // this kernel are what the registers of a CU hold: past one workgroup per CU, 8 waves each, so that two run side by side
+    // (B = 512: 36 us with 16, 28 with 8; B = 256: 21 with 16).
+    const int blocks = (d + 64 * VW - 1) / (64 * VW);
+    int ncb = blocks >= 3 ? 4 : blocks;
+    if ((long)B * ((blocks + ncb - 1) / ncb) < 128) ncb = 1;
+    int J = (blocks + ncb - 1) / ncb;
     float* out = sqnorms;
     int direct = 1;
     if (J > 1) {
@@ -1054,11 +1092,15 @@ static dp_status embedding_sqnorms_launch(dp_ctx* ctx, const int32_t* ids, const
         direct = 0;
     }
     dim3 grid(B, J);
-    const size_t lds = (size_t)2 * T * sizeof(int32_t);
-    if (distinct)
-        hipLaunchKernelGGL((embedding_sqnorms_kernel<BF16, VW, true>), grid, dim3(256), lds, ctx->stream, ids, G, T, d, V, out, J, direct, ctx->err_word);
-    else
-        hipLaunchKernelGGL((embedding_sqnorms_kernel<BF16, VW, false>), grid, dim3(256), lds, ctx->stream, ids, G, T, d, V, out, J, direct, ctx->err_word);
+    const size_t lds = ((size_t)T + 3) / 4 * 4 * sizeof(uint32_t) + (size_t)T * sizeof(uint16_t);
+    auto launch = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), lds, ctx->stream, ids, G, T, d, V, ncb, out, J, direct, ctx->err_word);
+    };
+    const bool many = (long)B * J > 256;
+    if (distinct && many) launch(embedding_sqnorms_kernel<BF16, VW, true, 8>, 8);
+    else if (distinct) launch(embedding_sqnorms_kernel<BF16, VW, true, 16>, 16);
+    else if (many) launch(embedding_sqnorms_kernel<BF16, VW, false, 8>, 8);
+    else launch(embedding_sqnorms_kernel<BF16, VW, false, 16>, 16);
     DP_LAUNCH_CHECK(ctx, "embedding_sqnorms");
     if (!direct) return dpk_finish_partials(ctx, out, B, J, sqnorms);
     return DP_OK;
