@@ -638,43 +638,36 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(ScaleBatch sb, const fl
 // fp32 inputs, on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: products and sums in fp32).  The contraction index is
 // the slow index of both operands in memory and the MFMA wants one k per half-wave: a lane's operand is simply the element
 // (row k + lane / 32, column lane % 32), 128 contiguous bytes a half-wave, straight from global memory into registers.  A
-// workgroup owns a tile of 32 TE x 32 TE; its 8 waves take the row pairs in turn (16 flop per byte of L2 at TE = 2: 10 TB/s at
-// the full matrix rate, a third of what L2 delivers) and their accumulators meet in LDS.  c_i multiplies G on the way in;
-// the workgroups of tile row 0 also add up the columns of c * G for the bias.
+// workgroup owns a tile of 32 TM x 32 TN; its 8 waves take the row pairs in turn (16 flop per byte of L2 at 2 x 2, 12 at 3 x 1: 10 and
+// 13 TB/s at the full matrix rate) and their accumulators meet in LDS.  c_i multiplies G on the way in; the workgroups of tile row
+// 0 also add up the columns of c * G for the bias.
 // 1024 x 1024, 8,192 rows: 107 TFLOP/s of the 154 that the vendor's fp32 product reaches.
-// B * T = 2,048 rows, 768 x 768: 397 + 9 (bias) -> 46 us (16 x 16 threads with 4 x 4 sums each, before); 64 x 64, 512 rows: 70 -> 8 us.
+// B * T = 2,048 rows, 768 x 768: 397 + 9 (bias) -> 38 us (16 x 16 threads with 4 x 4 sums each, before); 64 x 64, 512 rows: 70 -> 8 us.
 // ------------------------------------------------------------------------------------------------
 constexpr int F32_WAVES = 8;
 constexpr int F32_FACTORS = 1024;  // clip factors a workgroup forms itself; with more examples in its rows they come precomputed
 
-template <int TE, bool OWN>
+template <int TM, int TN, bool OWN>
 __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ G,
                                                                    const float* __restrict__ c_or_sq, float C, int T, long K,
                                                                    int d_in, int d_out, long rows_per_split, int add, float* __restrict__ out,
                                                                    float* __restrict__ out_b, int* __restrict__ err) {
-    constexpr int NR = TE * TE * 16;      // accumulator registers of a wave
-    constexpr int U = TE == 1 ? 16 : 8;   // row pairs a wave has in flight beside those it multiplies
+    constexpr int NR = TM * TN * 16;      // accumulator registers of a wave
+    constexpr int U = TM + TN < 3 ? 16 : 8;   // row pairs a wave has in flight beside those it multiplies
     __shared__ float part[F32_WAVES / 2][NR][64];
-    __shared__ float bpart[F32_WAVES][TE][64];
+    __shared__ float bpart[F32_WAVES][TN][64];
     __shared__ float ctab[OWN ? F32_FACTORS : 1];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
-    const int p0 = blockIdx.y * 32 * TE, q0 = blockIdx.x * 32 * TE;
+    const int p0 = blockIdx.y * 32 * TM, q0 = blockIdx.x * 32 * TN;
     const long k_lo = (long)blockIdx.z * rows_per_split;
     const long k_hi = k_lo + rows_per_split < K ? k_lo + rows_per_split : K;
-    int pc[TE], qc[TE];  // columns past the widths repeat the last one and feed entries that are never stored
+    f32x16_t acc[TM][TN];
+    float bs[TN];
 #pragma unroll
-    for (int e = 0; e < TE; ++e) {
-        const int p = p0 + 32 * e + (lane & 31), q = q0 + 32 * e + (lane & 31);
-        pc[e] = p < d_in ? p : d_in - 1;
-        qc[e] = q < d_out ? q : d_out - 1;
-    }
-    f32x16_t acc[TE][TE];
-    float bs[TE];
+    for (int j = 0; j < TN; ++j) {
+        bs[j] = 0.f;
 #pragma unroll
-    for (int i = 0; i < TE; ++i) {
-        bs[i] = 0.f;
-#pragma unroll
-        for (int j = 0; j < TE; ++j)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     }
@@ -692,14 +685,19 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
     constexpr int BLK = 2 * F32_WAVES * U;
     const int r_first = 2 * wave + half, n_rows = k_hi > k_lo ? (int)(k_hi - k_lo) : 0;
     const uint32_t pitchA = (uint32_t)d_in * 4u, pitchG = (uint32_t)d_out * 4u;
-    uint32_t voffA[TE], voffG[TE];
+    uint32_t voffA[TM], voffG[TN];  // columns past the widths repeat the last one and feed entries that are never stored
 #pragma unroll
-    for (int e = 0; e < TE; ++e) {
-        voffA[e] = r_first * pitchA + pc[e] * 4u;
-        voffG[e] = r_first * pitchG + qc[e] * 4u;
+    for (int e = 0; e < TM; ++e) {
+        const int p = p0 + 32 * e + (lane & 31);
+        voffA[e] = r_first * pitchA + (p < d_in ? p : d_in - 1) * 4u;
+    }
+#pragma unroll
+    for (int e = 0; e < TN; ++e) {
+        const int q = q0 + 32 * e + (lane & 31);
+        voffG[e] = r_first * pitchG + (q < d_out ? q : d_out - 1) * 4u;
     }
     struct Rows {
-        float a[U][TE], g[U][TE];
+        float a[U][TM], g[U][TN];
     };
     struct Src {
         __amdgpu_buffer_rsrc_t A, G;
@@ -711,10 +709,11 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
     };
     auto load = [&](Rows& x, const Src& s, int u) {
 #pragma unroll
-        for (int e = 0; e < TE; ++e) {
+        for (int e = 0; e < TM; ++e)
             x.a[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(s.A, (int)(voffA[e] + u * 2 * F32_WAVES * pitchA), 0, 0));
+#pragma unroll
+        for (int e = 0; e < TN; ++e)
             x.g[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(s.G, (int)(voffG[e] + u * 2 * F32_WAVES * pitchG), 0, 0));
-        }
     };
     // The factor of the lane's row.  One step of 16 rows passes one boundary at most when T >= 16: the example follows by
     // comparison; shorter examples are found by division.  (Either way no memory access and no loop under a branch: the
@@ -745,17 +744,17 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
         row += BLK;
     };
     auto mma = [&](const Rows& x, int u, float w) {
-        float g[TE];
+        float g[TN];
 #pragma unroll
-        for (int j = 0; j < TE; ++j) {
+        for (int j = 0; j < TN; ++j) {
             // zeros past the range stay zeros: the repeated factor is that of a row inside it, finite or NaN with it
             g[j] = w * x.g[u][j];
             bs[j] += g[j];
         }
 #pragma unroll
-        for (int i = 0; i < TE; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TE; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[u][i], g[j], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[u][i], g[j], acc[i][j], 0, 0, 0);
     };
     const int n_iter = (n_rows + BLK - 1) / BLK;  // (the same for every wave)
     Rows x0, x1;
@@ -786,15 +785,15 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
     // waves w + 4 hand their tiles to waves w, whose four sums every wave then adds for an eighth of the registers
     constexpr int HW = F32_WAVES / 2;
 #pragma unroll
-    for (int e = 0; e < TE; ++e) bpart[wave][e][lane] = bs[e];
+    for (int e = 0; e < TN; ++e) bpart[wave][e][lane] = bs[e];
     if (wave >= HW) {
 #pragma unroll
-        for (int r = 0; r < NR; ++r) part[wave - HW][r][lane] = acc[r / (16 * TE)][r / 16 % TE][r % 16];
+        for (int r = 0; r < NR; ++r) part[wave - HW][r][lane] = acc[r / (16 * TN)][r / 16 % TN][r % 16];
     }
     __syncthreads();
     if (wave < HW) {
 #pragma unroll
-        for (int r = 0; r < NR; ++r) part[wave][r][lane] += acc[r / (16 * TE)][r / 16 % TE][r % 16];
+        for (int r = 0; r < NR; ++r) part[wave][r][lane] += acc[r / (16 * TN)][r / 16 % TN][r % 16];
     }
     __syncthreads();
     float* __restrict__ dst = out + (size_t)blockIdx.z * (add ? 0 : (size_t)d_in * d_out);
@@ -802,8 +801,8 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
     float old[NK];
     auto place = [&](int k, int& p, int& q) {  // accumulator register r of lane l: row 8*(r/4) + 4*(l/32) + r%4, column l%32 of its tile
         const int r = wave * NK + k, rr = r % 16;
-        p = p0 + 32 * (r / (16 * TE)) + 8 * (rr >> 2) + 4 * half + (rr & 3);
-        q = q0 + 32 * (r / 16 % TE) + (lane & 31);
+        p = p0 + 32 * (r / (16 * TN)) + 8 * (rr >> 2) + 4 * half + (rr & 3);
+        q = q0 + 32 * (r / 16 % TN) + (lane & 31);
         return p < d_in && q < d_out;
     };
 #pragma unroll
@@ -818,7 +817,7 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
         int p, q;
         if (place(k, p, q)) dst[(size_t)p * d_out + q] = old[k] + v;
     }
-    if (do_bias && threadIdx.x < 32 * TE && q0 + (int)threadIdx.x < d_out) {
+    if (do_bias && threadIdx.x < 32 * TN && q0 + (int)threadIdx.x < d_out) {
         const int e = threadIdx.x >> 5, l = threadIdx.x & 31;
         float t = 0.f;
 #pragma unroll
@@ -1192,14 +1191,33 @@ static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, 
     dp_status st = own ? DP_OK : dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf);
     if (st != DP_OK || (d_in == 0 && !sum_b)) return st;
     if (d_in == 0) return dpk_colstat_sums(ctx, nullptr, G, dt, B, T, d_out, ctx->cbuf, nullptr, sum_b);
-    // (fp32 from here.)  Tiles of 64 once they are enough for half the chip, of 32 below that; the rows are split when there are
-    // few tiles and many rows (partial sums through the workspace, one reduction launch each), as far as the workspace goes.
+    // (fp32 from here.)  The tile with the smallest time of a launch: rounds of the 256 workgroups that run at once, at 4 us and, by
+    // tile (in units of 32), 7.0 (1 x 1), 10.7 (2 x 1), 14.8 (3 x 1) or 18.5 ns (2 x 2) a row.  Where one round is not filled the rows are
+    // split, at 1,024 and more each (partial sums through the workspace as far as it goes; the two reduction launches take 6 us).
+    // 2,048 rows: 768 x 768 (144 tiles of 2 x 2, 192 of 3 x 1) 46 -> 38 us; 512 x 512: 19 with 1 x 1, 28 with 2 x 2; 1024 x 1024: 43 with
+    // 2 x 2, 51 with 2 x 1; 768 x 3072: 128 -> 104 with 3 x 1.
     const long K = (long)B * T;
-    const long t64 = (long)((d_in + 63) / 64) * ((d_out + 63) / 64);
-    const int te = t64 >= 128 ? 2 : 1;
-    const int tm = (d_in + 32 * te - 1) / (32 * te), tn = (d_out + 32 * te - 1) / (32 * te);
-    long nsplit = 256 / ((long)tm * tn);
-    if (nsplit > K / 1024) nsplit = K / 1024;
+    static constexpr struct {
+        int m, n;
+        double ns_row;
+    } kTiles[] = {{2, 2, 18.5}, {3, 1, 14.8}, {2, 1, 10.7}, {1, 1, 7.0}};
+    int m32 = 0, n32 = 0, tm = 0, tn = 0;
+    long nsplit = 1;
+    double best = 0.0;
+    for (const auto& t : kTiles) {
+        const long a = (d_in + 32 * t.m - 1) / (32 * t.m), b = (d_out + 32 * t.n - 1) / (32 * t.n);
+        long ns = 256 / (a * b);
+        if (ns > K / 1024) ns = K / 1024;
+        if (ns < 1) ns = 1;
+        const double us = (double)((a * b * ns + 255) / 256) * ((double)((K + ns - 1) / ns) * t.ns_row * 1e-3 + 4.0) + (ns > 1 ? 6.0 : 0.0);
+        if (m32 && (us >= best || a > 65535)) continue;  // (a launch has at most 65,535 tile rows)
+        best = us;
+        m32 = t.m;
+        n32 = t.n;
+        tm = (int)a;
+        tn = (int)b;
+        nsplit = ns;
+    }
     float *part = nullptr, *bpart = nullptr;
     if (nsplit > 1) {
         dp_ws_alloc ws(ctx);
@@ -1213,14 +1231,22 @@ static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, 
     const int add = nsplit == 1 ? 1 : 0;
     float* o = add ? sum_W : part;
     float* ob = !sum_b ? nullptr : add ? sum_b : bpart;
-    auto launch = [&](auto te_tag, auto own_tag) {
-        hipLaunchKernelGGL((wgemm_f32_kernel<decltype(te_tag)::value, decltype(own_tag)::value>), grid, block, 0, ctx->stream, (const float*)A,
-                           (const float*)G, own ? sqnorms : ctx->cbuf, C, T, K, d_in, d_out, rows, add, o, ob, ctx->err_word);
+    auto launch = [&](auto m_tag, auto n_tag) {
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, ctx->stream, (const float*)A, (const float*)G, own ? sqnorms : ctx->cbuf, C, T, K, d_in,
+                               d_out, rows, add, o, ob, ctx->err_word);
+        };
+        constexpr int M = decltype(m_tag)::value, N = decltype(n_tag)::value;
+        if (own) go(wgemm_f32_kernel<M, N, true>);
+        else go(wgemm_f32_kernel<M, N, false>);
     };
-    if (te == 2 && own) launch(std::integral_constant<int, 2>{}, std::true_type{});
-    else if (te == 2) launch(std::integral_constant<int, 2>{}, std::false_type{});
-    else if (own) launch(std::integral_constant<int, 1>{}, std::true_type{});
-    else launch(std::integral_constant<int, 1>{}, std::false_type{});
+    using one = std::integral_constant<int, 1>;
+    using two = std::integral_constant<int, 2>;
+    using three = std::integral_constant<int, 3>;
+    if (m32 == 2 && n32 == 2) launch(two{}, two{});
+    else if (m32 == 3) launch(three{}, one{});
+    else if (m32 == 2) launch(two{}, one{});
+    else launch(one{}, one{});
     DP_LAUNCH_CHECK(ctx, "wgemm_f32");
     if (add) return DP_OK;
     st = dpk_reduce_partials(ctx, part, (int)nsplit, (size_t)d_in * d_out, (size_t)d_in * d_out, sum_W);

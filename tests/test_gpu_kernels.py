@@ -934,7 +934,9 @@ def test_clip_accumulate_dense_any_row_count(dp, n, B, T, d_in, d_out):
 @pytest.mark.parametrize("B,T,d_in,d_out", [(1, 1, 1, 1), (3, 33, 33, 31), (5, 64, 130, 4), (2, 97, 260, 520), (40, 3, 65, 129),
                                             (1100, 2, 36, 40),      # more examples than a workgroup forms factors for
                                             (9, 700, 64, 32),       # rows split over workgroups
-                                            (2, 40, 1030, 600)])    # tiles of 64
+                                            (2, 40, 1030, 600), (1100, 1, 705, 700),   # tiles of 96 x 32
+                                            (3, 40, 1000, 470), (1100, 1, 600, 500),   # of 64 x 32
+                                            (3, 33, 990, 890), (1100, 2, 990, 890)])   # of 64 x 64
 def test_dense_f32_forms(dp, B, T, d_in, d_out):
     """fp32 norms (both paths) and sums around the 32-row cells, 32- and 64-wide tiles and 16-row steps.  Sums of K fp32 terms:
     error about sqrt(K) 6e-8 relative to the terms' norm, 1e-5 with room for cancellation (as the other fp32 tests)."""
