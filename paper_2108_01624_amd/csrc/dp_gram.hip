@@ -673,20 +673,21 @@ __global__ __launch_bounds__(512, 1) void gram_units_kernel(GramBatch gb, GramUn
 
 // ------------------------------------------------------------------------------------------------
 // T <= 32 (prediction slots: 20 rows per example; the output projection of a tied table has a 30K-wide input): one 32 x 32
-// Gram tile per operand, where the 128-row kernel above would spend its time on empty rows.  Fed like gram_dma_kernel: 128-byte
-// row segments of the 32 rows go straight into a ring of 4 KiB stages (one 16-byte-per-lane load per wave and stage, coalesced
-// over 8 rows), and wave w takes k step w of every stage: one fragment read and one MFMA per wave and stage; the waves'
-// accumulators meet in LDS.  NS - 1 stages in flight per workgroup, two workgroups per CU.  Workgroup g works on example
-// g % B of layer g / B, as above.
-// Bound: HBM, B*T*(d_in+d_out)*2 bytes read once: 646 MB in 98 us; one layer of 1024 x 1024, B = 512, T = 20: 28 us on the
-// 128-row kernel, 12 here.
+// Gram tile per operand, where the 128-row kernel above would spend its time on empty rows.  Every wave works by itself: it fills
+// stages of its own (64 columns of the 32 rows, 4 KiB, four 16-byte-per-lane loads straight into LDS, coalesced over 8 rows each)
+// and multiplies them, wave w the chunks w, w + WAVES, ...; no barrier until the waves' accumulators meet in LDS.  (Stages that all
+// waves filled and shared cost a barrier each, 127 ns a chunk of 64 columns whatever the batch: 63 us for 31,552 columns.)  NS - 1
+// stages in flight per wave.  Workgroup g works on example g % B of layer g / B, as above.
+// Bound: HBM, B*T*(d_in+d_out)*2 bytes read once.  T = 20, 1024 + 30,528 columns: B = 256 (323 MB) 69 -> 52 us, B = 8 63 -> 29;
+// 1024 + 1024, B = 512: 28 us on the 128-row kernel, 11.5 with shared stages, 10.7.
 // ------------------------------------------------------------------------------------------------
-template <int NS, bool RAGGED>
-__global__ __launch_bounds__(256, 2) void gram_small_dma_kernel(GramBatch gb, int T, int d_in, int d_out, int has_bias, float* __restrict__ out) {
-    constexpr int GDK = 64, ROWS = 32, STAGE = ROWS * GDK, CPR = 8, RPI = 8;  // 4 loads fill a stage: one per wave
-    static_assert(NS * STAGE * 2 >= 4 * 2 * 16 * 64 * 4, "the ring doubles as the reduction buffer");
-    __shared__ __attribute__((aligned(16))) uint16_t ring[NS][STAGE];
-    __shared__ float wred[4];
+template <int WAVES, int NS, bool RAGGED>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void gram_small_dma_kernel(GramBatch gb, int T, int d_in, int d_out, int has_bias,
+                                                                                        float* __restrict__ out) {
+    constexpr int GDK = 64, ROWS = 32, STAGE = ROWS * GDK, RPI = 8, LOADS = ROWS / RPI;
+    static_assert(NS * STAGE * 2 >= 2 * 16 * 64 * 4, "a wave's ring doubles as its part of the reduction buffer");
+    __shared__ __attribute__((aligned(16))) uint16_t ring[WAVES][NS][STAGE];
+    __shared__ float wred[WAVES];
     const int layer = __builtin_amdgcn_readfirstlane(blockIdx.x / gb.B), i = blockIdx.x - layer * gb.B;
     const uint16_t* __restrict__ A = gb.A[layer];
     const uint16_t* __restrict__ G = gb.G[layer];
@@ -696,67 +697,86 @@ __global__ __launch_bounds__(256, 2) void gram_small_dma_kernel(GramBatch gb, in
     // rows >= T lie outside the example's byte range and read as zero
     const gram_i32x4 rA = gram_rsrc(A + (size_t)i * T * d_in, (uint32_t)((size_t)T * d_in * 2));
     const gram_i32x4 rG = gram_rsrc(G + (size_t)i * T * d_out, (uint32_t)((size_t)T * d_out * 2));
-    const int lrow = wave * RPI + lane / CPR;
-    const int cg = (lane % CPR) ^ swz(lrow);
-    const int voffA = (lrow * d_in + cg * 8) * 2, voffG = (lrow * d_out + cg * 8) * 2;
-    const uint32_t ldsoff = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)&ring[0][wave * RPI * GDK];
+    int cg[LOADS], voffA[LOADS], voffG[LOADS];
+#pragma unroll
+    for (int q = 0; q < LOADS; ++q) {
+        const int lrow = q * RPI + lane / 8;
+        cg[q] = (lane % 8) ^ swz(lrow);
+        voffA[q] = (lrow * d_in + cg[q] * 8) * 2;
+        voffG[q] = (lrow * d_out + cg[q] * 8) * 2;
+    }
+    const uint32_t ldsoff = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)&ring[wave][0][0];
     int ibuf = 0;  // buffer of the next stage to issue
     auto issue = [&](int st) {
         const bool isA = st < nchA;
         const int soff = __builtin_amdgcn_readfirstlane((isA ? st : st - nchA) * GDK * 2);
         const uint32_t dst = __builtin_amdgcn_readfirstlane(ldsoff + ibuf * (STAGE * 2));
         const int left = isA ? d_in - st * GDK : d_out - (st - nchA) * GDK;  // columns of the row from this chunk on
-        const bool cut = RAGGED && cg * 8 >= left;                          // past the row's end: zeros
-        if (isA) gram_dma16<true>(rA, dst, cut ? GRAM_OUTSIDE : voffA, soff);
-        else if (st >= nch) gram_dma16<true>(rG, dst, GRAM_OUTSIDE, 0);  // past the last: zeros, keeps the load count uniform
-        else gram_dma16<true>(rG, dst, cut ? GRAM_OUTSIDE : voffG, soff);
+        if (isA) {
+#pragma unroll
+            for (int q = 0; q < LOADS; ++q)  // past the row's end: zeros
+                gram_dma16<true>(rA, dst + q * RPI * GDK * 2, RAGGED && cg[q] * 8 >= left ? GRAM_OUTSIDE : voffA[q], soff);
+        } else if (st < nch) {
+#pragma unroll
+            for (int q = 0; q < LOADS; ++q)
+                gram_dma16<true>(rG, dst + q * RPI * GDK * 2, RAGGED && cg[q] * 8 >= left ? GRAM_OUTSIDE : voffG[q], soff);
+        } else {  // past the last: zeros, keeps the load count uniform
+#pragma unroll
+            for (int q = 0; q < LOADS; ++q) gram_dma16<true>(rG, dst + q * RPI * GDK * 2, GRAM_OUTSIDE, 0);
+        }
         ibuf = ibuf + 1 == NS ? 0 : ibuf + 1;
     };
     const int r = lane & 31;
-    const int fpos = r * GDK + (((2 * wave + (lane >> 5)) ^ swz(r)) << 3);  // this wave's k step of a stage
+    int fpos[GDK / 16];
+#pragma unroll
+    for (int k = 0; k < GDK / 16; ++k) fpos[k] = r * GDK + (((2 * k + (lane >> 5)) ^ swz(r)) << 3);
     f32x16_t accA, accG;
 #pragma unroll
     for (int q = 0; q < 16; ++q) accA[q] = accG[q] = 0.f;
 #pragma unroll
-    for (int st = 0; st < NS - 1; ++st) issue(st);
-    int cbuf = 0, s = 0;
+    for (int st = 0; st < NS - 1; ++st) issue(wave + st * WAVES);
+    int cbuf = 0, s = wave;
     auto phase = [&](int end, f32x16_t& acc) {
-        for (; s < end; ++s) {
-            // my load of stage s has landed (later ones may be in flight); after the barrier everyone's have, and
-            // everyone is done reading stage s-1, whose buffer the newest stage overwrites
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NS - 2) : "memory");
-            __syncthreads();
-            issue(s + NS - 1);
-            const bf16x8_t x = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(ring[cbuf] + fpos));
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, x, acc, 0, 0, 0);
+        for (; s < end; s += WAVES) {
+            // stage s has landed (later ones may be in flight), and the fragments of the one before it are in registers: the newest
+            // stage may overwrite its buffer
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * LOADS) : "memory");
+            issue(s + (NS - 1) * WAVES);
+            const uint16_t* buf = ring[wave][cbuf];
+            bf16x8_t x[GDK / 16];
+#pragma unroll
+            for (int k = 0; k < GDK / 16; ++k) x[k] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(buf + fpos[k]));
+#pragma unroll
+            for (int k = 0; k < GDK / 16; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[k], x[k], acc, 0, 0, 0);
             cbuf = cbuf + 1 == NS ? 0 : cbuf + 1;
         }
     };
     phase(nchA, accA);
     phase(nch, accG);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be writing LDS when the ring is reused
-    __syncthreads();
-    float* part = reinterpret_cast<float*>(&ring[0][0]);  // [wave][A|G][register][lane]
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // nothing may still be writing LDS when the ring is reused
+    // [wave][A|G][register][lane], each wave's part in its own ring
+    float* part = reinterpret_cast<float*>(&ring[0][0][0]);
+    constexpr int PITCH = NS * STAGE / 2;
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-        part[((wave * 2 + 0) * 16 + q) * 64 + lane] = accA[q];
-        part[((wave * 2 + 1) * 16 + q) * 64 + lane] = accG[q];
+        part[wave * PITCH + q * 64 + lane] = accA[q];
+        part[wave * PITCH + (16 + q) * 64 + lane] = accG[q];
     }
     __syncthreads();
     const float bias_term = has_bias ? 1.f : 0.f;
     float sum = 0.f;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {  // wave w finishes accumulator registers 4w .. 4w+3, the waves' partial tiles added in index order
-        const int reg = wave * 4 + q;
+    for (int q = 0; q < 16 / WAVES; ++q) {  // wave w finishes its share of the accumulator registers, the waves' partial tiles added in index order
+        const int reg = wave * (16 / WAVES) + q;
         float a = 0.f, g = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            a += part[((w * 2 + 0) * 16 + reg) * 64 + lane];
-            g += part[((w * 2 + 1) * 16 + reg) * 64 + lane];
+        for (int w = 0; w < WAVES; ++w) {
+            a += part[w * PITCH + reg * 64 + lane];
+            g += part[w * PITCH + (16 + reg) * 64 + lane];
         }
         sum += (a + bias_term) * g;
     }
-    const float tot = dp_block_sum<256>(sum, wred);
+    const float tot = dp_block_sum<64 * WAVES>(sum, wred);
     if (threadIdx.x == 0) {
         if (gb.n_layers == 1) out[i] += tot;
         else out[(size_t)i * gb.n_layers + layer] = tot;
@@ -939,8 +959,10 @@ static dp_status gram_dma_launch(dp_ctx* ctx, const GramBatch& gb, int T, int d_
     auto launch = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, ctx->stream, gb, T, d_in, d_out, has_bias, out);
     };
-    if (T <= 32 && gb.n_out == 1 && ragged) launch(gram_small_dma_kernel<16, true>, 256);
-    else if (T <= 32 && gb.n_out == 1) launch(gram_small_dma_kernel<16, false>, 256);
+    if (T <= 32 && gb.n_out == 1 && ragged && few) launch(gram_small_dma_kernel<8, 4, true>, 512);
+    else if (T <= 32 && gb.n_out == 1 && ragged) launch(gram_small_dma_kernel<4, 4, true>, 256);
+    else if (T <= 32 && gb.n_out == 1 && few) launch(gram_small_dma_kernel<8, 4, false>, 512);
+    else if (T <= 32 && gb.n_out == 1) launch(gram_small_dma_kernel<4, 4, false>, 256);
     else if (T <= 64 && wide) launch(gram_dma_kernel<64, 128, 4, 4, 2, false>, 256);
     else if (T <= 64 && ragged) launch(gram_dma_kernel<64, 64, 8, 4, 2, true>, 256);
     else if (T <= 64) launch(gram_dma_kernel<64, 64, 8, 4, 2, false>, 256);

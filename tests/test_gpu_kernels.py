@@ -962,6 +962,7 @@ def test_dense_f32_forms(dp, B, T, d_in, d_out):
 
 @pytest.mark.parametrize("n,B,T,d_in,d_out", [
     (1, 3, 1, 8, 8), (3, 5, 20, 72, 136), (17, 2, 32, 64, 64),        # up to 32 rows, one and several layers, ragged widths
+    (1, 300, 20, 72, 1032), (2, 140, 31, 128, 640), (1, 2, 20, 1032, 2056),  # ... few and many workgroups, many chunks a wave
     (2, 7, 33, 72, 200), (1, 300, 64, 128, 128), (2, 4, 50, 128, 264),  # up to 64 rows: one quadrant
     (1, 3, 65, 136, 72), (2, 140, 128, 64, 200), (3, 2, 100, 384, 128),  # up to 128 rows, few and many workgroups
     (2, 3, 130, 200, 328), (1, 2, 300, 72, 1032),                     # units of the plane, ragged widths
