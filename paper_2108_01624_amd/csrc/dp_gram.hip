@@ -244,6 +244,9 @@ struct GramBatch {
 // workgroup or less per CU 8 waves take half the k steps each (12 layers of 768 x 3072, B = 8: 41 -> 36 us; a deeper ring
 // alone changed nothing), and with 64 rows, where one wave of four had work, all four take a quarter each (4 layers of
 // 192 x 2264, B = 106, T = 47: 42 -> 30 us).
+// The next k step's fragments are read while one multiplies, those of a diagonal quadrant once for rows and columns, and a
+// stage's loads are issued behind the first fragments (12 layers of 768 x 3072, B = 8: 36.6 -> 34.6 us; one layer of 768 x 768,
+// B = 8: 16.7 -> 15.7; 8 layers of 1024 x 1024, B = 512: 322 -> 319, 6.7 TB/s).
 // RAGGED: a width that is no multiple of GDK; what lies past a row's end in its last chunk is left out lane by lane.
 template <int ROWS, int GDK, int NS, int WAVES, int WGS_PER_CU, bool RAGGED>
 __global__ __launch_bounds__(64 * WAVES, WGS_PER_CU * WAVES / 4) void gram_dma_kernel(GramBatch gb, int T, int d_in, int d_out,
@@ -340,23 +343,32 @@ __global__ __launch_bounds__(64 * WAVES, WGS_PER_CU * WAVES / 4) void gram_dma_k
     auto compute = [&](f32x16_t (&acc)[2][2], auto diag_tag) {
         constexpr bool DG = decltype(diag_tag)::value;
         const uint16_t* st = ring[cbuf];
-#pragma unroll
-        for (int step = 0; step < GDK / 16 / KS; ++step) {
+        constexpr int STEPS = GDK / 16 / KS;
+        bf16x8_t a[2][2], b[2][2];  // [step % 2]: the next step's fragments are on their way while one multiplies
+        auto fragments = [&](int step) {
             const int kk = step * KS + kg;
-            bf16x8_t a0[2], b0[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 // k chunk 2*kk + lane/32: its swizzled position differs from the kk = 0 one by XOR 2*kk
                 const int xr = fr[u] ^ ((2 * kk) << 3), xc = fc[u] ^ ((2 * kk) << 3);
-                a0[u] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(st + xr));
-                b0[u] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(st + xc));
+                a[step & 1][u] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(st + xr));
+                if (DG) b[step & 1][u] = a[step & 1][u];  // rows and columns of a diagonal quadrant are the same
+                else b[step & 1][u] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(st + xc));
             }
+        };
+        fragments(0);
+        issue(s + NS - 1);
+#pragma unroll
+        for (int step = 0; step < STEPS; ++step) {
+            if (step + 1 < STEPS) fragments(step + 1);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt)
                     if (!(DG && mt == 1 && nt == 0))
-                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[mt], b0[nt], acc[mt][nt], 0, 0, 0);
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[step & 1][mt], b[step & 1][nt], acc[mt][nt], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
     auto phase = [&](int end, f32x16_t (&acc)[2][2]) {
@@ -365,11 +377,9 @@ __global__ __launch_bounds__(64 * WAVES, WGS_PER_CU * WAVES / 4) void gram_dma_k
             // and everyone is done reading chunk s-1, whose buffer the newest chunk overwrites
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * LPS) : "memory");
             __syncthreads();
-            issue(s + NS - 1);
-            if (active) {
-                if (diagw) compute(acc, std::true_type{});
-                else compute(acc, std::false_type{});
-            }
+            if (!active) issue(s + NS - 1);
+            else if (diagw) compute(acc, std::true_type{});
+            else compute(acc, std::false_type{});
             cbuf = cbuf + 1 == NS ? 0 : cbuf + 1;
         }
     };
