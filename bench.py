@@ -279,7 +279,7 @@ def main():
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic,
                      "traffic_unit": "HBM bytes per launch (rocprofv3 --pmc FETCH_SIZE + WRITE_SIZE, profiles/)",
-                     "kernel": "wgemm_dma16_kernel (clip-weighted A^T diag(c) G, up to 32 same-shaped layers per launch)",
+                     "kernel": "wgemm_dma16_kernel (clip-weighted A^T diag(c) G, up to 64 same-shaped layers per launch)",
                      "avg_launch_ms": g_ms / max(1, g_n), "launches": int(g_n),
                      "sustained_mfma_only": mfma_ceiling,
                      "sustained_mfma_only_note": "TFLOP/s of a register-only loop of the same bf16 16x16x32 matrix "

@@ -586,8 +586,7 @@ __global__ __launch_bounds__(256) void bias_finish_kernel(WgemmBatchArgs b, int 
     if (g == 0 && q < b.base.d_out) dst[q] += (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
 }
 
-// Operands for the GEMM without factors: Gs = bf16(c_i * G) (products formed in fp32, rounded to nearest even, as the
-// register-staged kernel rounds what it stages), rows of one example after the other, and the column sums of the fp32 products
+// Operands for the GEMM without factors: Gs = bf16(c_i * G) (products formed in fp32, rounded to nearest even), rows of one example after the other, and the column sums of the fp32 products
 // of a run of rows for the bias (part[layer][run][d], if wanted).  8 columns a thread, 256 columns x 8 rows a workgroup.
 // Bound: HBM, 4 bytes per element.  grid (runs, d / 256, layers).
 struct ScaleBatch {
