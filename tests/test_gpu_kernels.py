@@ -839,7 +839,9 @@ def _tied_case(dtype, B, T, M, d, V, seed):
                                              ("bf16", 3, 16, 0, 64, 64), ("bf16", 16, 24, 20, 256, 520),
                                              # enough rows that the projection's GEMM splits them: partial sums next to
                                              # the pre-scaled H that the caller holds in the same workspace
-                                             ("bf16", 64, 24, 20, 256, 520)])
+                                             ("bf16", 64, 24, 20, 256, 520),
+                                             # many long examples: the entries of dL are gathered behind the contraction
+                                             ("bf16", 450, 5, 3, 512, 24)])
 def test_tied_embedding_norms_and_sums(dp, dtype, B, T, M, d, V):
     ids, dY, H, dL = _tied_case(dtype, B, T, M, d, V, 800)
     n0 = np.linspace(0.5, 1.5, B).astype(np.float32)     # the entry point adds to what is there
