@@ -293,6 +293,15 @@ dp_status dp_choose_path(int T, int d_in, int d_out, dp_dtype dtype, dp_path* ou
  *                 x > y stands for (y, x); C2 == 255: the cell (R, C1) alone.
  * DP_ERR_SHAPE if T is outside (128, 2048], DP_ERR_WORKSPACE if capacity is too small (70 words always suffice). */
 dp_status dp_gram_unit_plan(int T, uint32_t* units, int capacity, int* n_units);
+/* Host-only, pure: how dp_clip_accumulate_dense_batched cuts n_layers layers of these sizes, by a context with workspace_bytes of
+ * workspace (0: the default).  Writes six numbers to the HOST array `plan`:
+ *   [0], [1]  rows and columns of sum_W that a workgroup forms
+ *   [2]       1: bf16(c * g) is written first and contracted as one run of rows; 0: the operands enter unscaled
+ *   [3]       layers per launch
+ *   [4]       row splits of a full launch, whose partial sums pass through the workspace (fewer where it cannot hold them)
+ *   [5]       token rows that one 32-bit buffer resource covers; 0: 64-bit addresses
+ * The errors are those of the call itself for these sizes (DP_ERR_SHAPE, DP_ERR_DTYPE); all counts and widths at least 1. */
+dp_status dp_dense_sum_plan(dp_dtype dtype, int n_layers, int B, int T, int d_in, int d_out, size_t workspace_bytes, int32_t* plan);
 
 
 /* ---------------------------------------------------------------------------------------------------

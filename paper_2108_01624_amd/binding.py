@@ -61,6 +61,7 @@ SIGNATURES = {
     "dp_normal_f32": [c_void_p, c_void_p, c_uint64, c_uint64, c_uint64, c_uint64],
     "dp_choose_path": [c_int, c_int, c_int, c_int, ctypes.POINTER(c_int)],
     "dp_gram_unit_plan": [c_int, ctypes.POINTER(ctypes.c_uint32), c_int, ctypes.POINTER(c_int)],
+    "dp_dense_sum_plan": [c_int, c_int, c_int, c_int, c_int, c_int, c_size_t, ctypes.POINTER(ctypes.c_int32)],
     "dp_batch_size_schedule": [c_uint64, c_uint64, c_uint64, c_uint64, ctypes.c_uint32, ctypes.POINTER(c_uint64)],
     "dp_lr_schedule": [c_uint64, ctypes.c_double, c_uint64, c_uint64, ctypes.POINTER(ctypes.c_double)],
     "dp_rdp_sampled_gaussian": [ctypes.c_double, ctypes.c_double, c_int, ctypes.POINTER(ctypes.c_double)],
@@ -496,6 +497,15 @@ def dp_gram_unit_plan(T) -> list:
     if st != DP_OK:
         raise DpError(st, "dp_gram_unit_plan")
     return [int(buf[k]) for k in range(n.value)]
+
+
+def dp_dense_sum_plan(dtype, n_layers, B, T, d_in, d_out, workspace_bytes=0) -> dict:
+    """How a call of dp_clip_accumulate_dense_batched with these sizes is cut (host only)."""
+    buf = (ctypes.c_int32 * 6)()
+    st = load_library().dp_dense_sum_plan(dtype, n_layers, B, T, d_in, d_out, workspace_bytes, buf)
+    if st != DP_OK:
+        raise DpError(st, "dp_dense_sum_plan")
+    return dict(zip(("tile_m", "tile_n", "scaled", "layers", "splits", "block_rows"), map(int, buf)))
 
 
 def dp_profile_enable(ctx, enable: bool):

@@ -10,6 +10,7 @@ namespace {
 
 constexpr size_t DEFAULT_WORKSPACE = (size_t)512 << 20;
 constexpr int CBUF_CAP = 1 << 20;
+constexpr long MAX_ROWS = (long)INT_MAX - 4096;
 
 #define REQUIRE_CTX(ctx) \
     if (!(ctx)) return DP_ERR_NULL
@@ -44,7 +45,7 @@ dp_status check_f32(dp_ctx* ctx, const char* name, const void* p) {
 
 dp_status check_bt(dp_ctx* ctx, int B, int T) {
     if (B < 0 || T < 0) FAIL(ctx, DP_ERR_SHAPE, "negative B or T");
-    if ((long)B * T > (long)INT_MAX - 4096) FAIL(ctx, DP_ERR_SHAPE, "B*T = %ld exceeds 2^31", (long)B * T);
+    if ((long)B * T > MAX_ROWS) FAIL(ctx, DP_ERR_SHAPE, "B*T = %ld exceeds 2^31", (long)B * T);
     return DP_OK;
 }
 
@@ -194,6 +195,14 @@ dp_status dp_gram_unit_plan(int T, uint32_t* units, int capacity, int* n_units) 
     if (!units || !n_units) return DP_ERR_NULL;
     if (capacity < 0) return DP_ERR_SHAPE;
     return dpk_gram_unit_plan(T, units, capacity, n_units);
+}
+
+dp_status dp_dense_sum_plan(dp_dtype dtype, int n_layers, int B, int T, int d_in, int d_out, size_t workspace_bytes, int32_t* plan) {
+    if (!plan) return DP_ERR_NULL;
+    if (dtype != DP_F32 && dtype != DP_BF16) return DP_ERR_DTYPE;
+    if (n_layers < 1 || B < 1 || T < 1 || d_in < 1 || d_out < 1 || (long)B * T > MAX_ROWS) return DP_ERR_SHAPE;
+    if (dtype == DP_BF16 && (d_in % 8 || d_out % 8)) return DP_ERR_SHAPE;
+    return dpk_dense_sum_plan(dtype, n_layers, B, T, d_in, d_out, workspace_bytes ? workspace_bytes : DEFAULT_WORKSPACE, plan);
 }
 
 dp_status dp_choose_path(int T, int d_in, int d_out, dp_dtype dtype, dp_path* out) {

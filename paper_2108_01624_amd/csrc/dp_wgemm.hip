@@ -640,19 +640,25 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(ScaleBatch sb, const fl
 // workgroup owns a tile of 32 TM x 32 TN; its 8 waves take the row pairs in turn (16 flop per byte of L2 at 2 x 2, 12 at 3 x 1: 10 and
 // 13 TB/s at the full matrix rate) and their accumulators meet in LDS.  c_i multiplies G on the way in; the workgroups of tile row
 // 0 also add up the columns of c * G for the bias.
+// A block of rows is addressed by 32-bit offsets into one buffer resource; where a layer is so wide that a block's bytes do not
+// fit 32 bits (from 2^23 columns), WIDE forms 64-bit addresses per lane.
 // 1024 x 1024, 8,192 rows: 107 TFLOP/s of the 154 that the vendor's fp32 product reaches.
 // B * T = 2,048 rows, 768 x 768: 397 + 9 (bias) -> 38 us (16 x 16 threads with 4 x 4 sums each, before); 64 x 64, 512 rows: 70 -> 8 us.
 // ------------------------------------------------------------------------------------------------
 constexpr int F32_WAVES = 8;
 constexpr int F32_FACTORS = 1024;  // clip factors a workgroup forms itself; with more examples in its rows they come precomputed
 
-template <int TM, int TN, bool OWN>
+// Row pairs a wave of a TM x TN tile has in flight beside those it multiplies, and the rows of a workgroup's block of them.
+constexpr int f32_pairs(int tm, int tn) { return tm + tn < 3 ? 16 : 8; }
+constexpr int f32_block(int tm, int tn) { return 2 * F32_WAVES * f32_pairs(tm, tn); }
+
+template <int TM, int TN, bool OWN, bool WIDE>
 __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ G,
                                                                    const float* __restrict__ c_or_sq, float C, int T, long K,
                                                                    int d_in, int d_out, long rows_per_split, int add, float* __restrict__ out,
                                                                    float* __restrict__ out_b, int* __restrict__ err) {
     constexpr int NR = TM * TN * 16;      // accumulator registers of a wave
-    constexpr int U = TM + TN < 3 ? 16 : 8;   // row pairs a wave has in flight beside those it multiplies
+    constexpr int U = f32_pairs(TM, TN);
     __shared__ float part[F32_WAVES / 2][NR][64];
     __shared__ float bpart[F32_WAVES][TN][64];
     __shared__ float ctab[OWN ? F32_FACTORS : 1];
@@ -681,7 +687,7 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
     }
     // Rows of this lane, relative to k_lo: 2 * wave + half, then every 16th, in blocks of 16 U.  Buffer loads whose resource ends
     // at the split's last row: a row past it arrives as zeros, and there is no branch or select around a load.
-    constexpr int BLK = 2 * F32_WAVES * U;
+    constexpr int BLK = f32_block(TM, TN);
     const int r_first = 2 * wave + half, n_rows = k_hi > k_lo ? (int)(k_hi - k_lo) : 0;
     const uint32_t pitchA = (uint32_t)d_in * 4u, pitchG = (uint32_t)d_out * 4u;
     uint32_t voffA[TM], voffG[TN];  // columns past the widths repeat the last one and feed entries that are never stored
@@ -701,18 +707,43 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
     struct Src {
         __amdgpu_buffer_rsrc_t A, G;
     };
-    auto block = [&](int it) {  // resources over the rows of block `it`
-        const int left = n_rows - it * BLK, rows = left < 0 ? 0 : left < BLK ? left : BLK;
-        const size_t at = (size_t)k_lo + (size_t)it * BLK;
-        return Src{uniform_rsrc(A + at * d_in, rows * pitchA), uniform_rsrc(G + at * d_out, rows * pitchG)};
+    struct WideSrc {
+        long row;
     };
-    auto load = [&](Rows& x, const Src& s, int u) {
+    auto block = [&](int it) {  // resources over the rows of block `it`
+        if constexpr (WIDE) {
+            return WideSrc{(long)it * BLK + r_first};
+        } else {
+            const int left = n_rows - it * BLK, rows = left < 0 ? 0 : left < BLK ? left : BLK;
+            const size_t at = (size_t)k_lo + (size_t)it * BLK;
+            return Src{uniform_rsrc(A + at * d_in, rows * pitchA), uniform_rsrc(G + at * d_out, rows * pitchG)};
+        }
+    };
+    auto load = [&](Rows& x, const auto& s, int u) {
+        if constexpr (WIDE) {
+            const long r = s.row + u * 2 * F32_WAVES;
+            const bool in = r < n_rows;  // past the last row: that row is read, and zeros taken in its place
+            const size_t at = (size_t)k_lo + (size_t)(in ? r : n_rows - 1);
 #pragma unroll
-        for (int e = 0; e < TM; ++e)
-            x.a[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(s.A, (int)(voffA[e] + u * 2 * F32_WAVES * pitchA), 0, 0));
+            for (int e = 0; e < TM; ++e) {
+                const int p = p0 + 32 * e + (lane & 31);
+                const float v = A[at * d_in + (p < d_in ? p : d_in - 1)];
+                x.a[u][e] = in ? v : 0.f;
+            }
 #pragma unroll
-        for (int e = 0; e < TN; ++e)
-            x.g[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(s.G, (int)(voffG[e] + u * 2 * F32_WAVES * pitchG), 0, 0));
+            for (int e = 0; e < TN; ++e) {
+                const int q = q0 + 32 * e + (lane & 31);
+                const float v = G[at * d_out + (q < d_out ? q : d_out - 1)];
+                x.g[u][e] = in ? v : 0.f;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < TM; ++e)
+                x.a[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(s.A, (int)(voffA[e] + u * 2 * F32_WAVES * pitchA), 0, 0));
+#pragma unroll
+            for (int e = 0; e < TN; ++e)
+                x.g[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(s.G, (int)(voffG[e] + u * 2 * F32_WAVES * pitchG), 0, 0));
+        }
     };
     // The factor of the lane's row.  One step of 16 rows passes one boundary at most when T >= 16: the example follows by
     // comparison; shorter examples are found by division.  (Either way no memory access and no loop under a branch: the
@@ -758,7 +789,7 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
     const int n_iter = (n_rows + BLK - 1) / BLK;  // (the same for every wave)
     Rows x0, x1;
     {
-        const Src s = block(0);
+        const auto s = block(0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {  // (in order: the wait counts of the loop are only as tight as the order on entry is certain)
             load(x0, s, u);
@@ -769,7 +800,7 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
     auto step = [&](const Rows& now, Rows& next, int it_next) {  // multiply a block, the next one's loads spread between the MFMAs
         float w[U];
         factors(w);
-        const Src s = block(it_next);
+        const auto s = block(it_next);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             load(next, s, u);
@@ -1182,6 +1213,41 @@ dp_status dpk_weighted_gemm(dp_ctx* ctx, const void* A, const void* G, dp_dtype 
     return dpk_weighted_gemm_batched(ctx, 1, &A, &G, dt, B, T, d_in, d_out, sqnorms, C, &sum_W, &sum_b);
 }
 
+// Tile of the fp32 kernel (in units of 32) and row splits.
+struct F32Plan {
+    int m32, n32;
+    long nsplit;
+    bool wide;
+};
+
+// The tile with the smallest time of a launch: rounds of the 256 workgroups that run at once, at 4 us and, by
+// tile, 7.0 (1 x 1), 10.7 (2 x 1), 14.8 (3 x 1) or 18.5 ns (2 x 2) a row.  Where one round is not filled the rows are
+// split, at 1,024 and more each (partial sums through the workspace as far as it goes; the two reduction launches take 6 us).
+// 2,048 rows: 768 x 768 (144 tiles of 2 x 2, 192 of 3 x 1) 46 -> 38 us; 512 x 512: 19 with 1 x 1, 28 with 2 x 2; 1024 x 1024: 43 with
+// 2 x 2, 51 with 2 x 1; 768 x 3072: 128 -> 104 with 3 x 1.
+// A tile whose block of rows does not fit a 32-bit buffer resource is no candidate; without any, 2 x 2 with 64-bit addresses.
+static F32Plan choose_f32_plan(long K, int d_in, int d_out) {
+    static constexpr struct {
+        int m, n;
+        double ns_row;
+    } kTiles[] = {{2, 2, 18.5}, {3, 1, 14.8}, {2, 1, 10.7}, {1, 1, 7.0}};
+    const uint64_t width = d_in > d_out ? d_in : d_out;
+    F32Plan plan{0, 0, 1, false};
+    double best = 0.0;
+    for (const auto& t : kTiles) {
+        const long a = (d_in + 32l * t.m - 1) / (32 * t.m), b = (d_out + 32l * t.n - 1) / (32 * t.n);
+        const bool wide = (uint64_t)f32_block(t.m, t.n) * 4u * width > 0xFFFFFFFFu;
+        long ns = 256 / (a * b);
+        if (ns > K / 1024) ns = K / 1024;
+        if (ns < 1) ns = 1;
+        const double us = (double)((a * b * ns + 255) / 256) * ((double)((K + ns - 1) / ns) * t.ns_row * 1e-3 + 4.0) + (ns > 1 ? 6.0 : 0.0);
+        if (plan.m32 && (us >= best || a > 65535 || wide)) continue;  // (a launch has at most 65,535 tile rows)
+        best = us;
+        plan = F32Plan{t.m, t.n, ns, wide};
+    }
+    return plan;
+}
+
 // A layer in fp32, or one without weights.
 static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, dp_dtype dt, int B, int T, int d_in, int d_out,
                                      const float* sqnorms, float C, float* sum_W, float* sum_b) {
@@ -1190,33 +1256,10 @@ static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, 
     dp_status st = own ? DP_OK : dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf);
     if (st != DP_OK || (d_in == 0 && !sum_b)) return st;
     if (d_in == 0) return dpk_colstat_sums(ctx, nullptr, G, dt, B, T, d_out, ctx->cbuf, nullptr, sum_b);
-    // (fp32 from here.)  The tile with the smallest time of a launch: rounds of the 256 workgroups that run at once, at 4 us and, by
-    // tile (in units of 32), 7.0 (1 x 1), 10.7 (2 x 1), 14.8 (3 x 1) or 18.5 ns (2 x 2) a row.  Where one round is not filled the rows are
-    // split, at 1,024 and more each (partial sums through the workspace as far as it goes; the two reduction launches take 6 us).
-    // 2,048 rows: 768 x 768 (144 tiles of 2 x 2, 192 of 3 x 1) 46 -> 38 us; 512 x 512: 19 with 1 x 1, 28 with 2 x 2; 1024 x 1024: 43 with
-    // 2 x 2, 51 with 2 x 1; 768 x 3072: 128 -> 104 with 3 x 1.
+    // (fp32 from here)
     const long K = (long)B * T;
-    static constexpr struct {
-        int m, n;
-        double ns_row;
-    } kTiles[] = {{2, 2, 18.5}, {3, 1, 14.8}, {2, 1, 10.7}, {1, 1, 7.0}};
-    int m32 = 0, n32 = 0, tm = 0, tn = 0;
-    long nsplit = 1;
-    double best = 0.0;
-    for (const auto& t : kTiles) {
-        const long a = (d_in + 32 * t.m - 1) / (32 * t.m), b = (d_out + 32 * t.n - 1) / (32 * t.n);
-        long ns = 256 / (a * b);
-        if (ns > K / 1024) ns = K / 1024;
-        if (ns < 1) ns = 1;
-        const double us = (double)((a * b * ns + 255) / 256) * ((double)((K + ns - 1) / ns) * t.ns_row * 1e-3 + 4.0) + (ns > 1 ? 6.0 : 0.0);
-        if (m32 && (us >= best || a > 65535)) continue;  // (a launch has at most 65,535 tile rows)
-        best = us;
-        m32 = t.m;
-        n32 = t.n;
-        tm = (int)a;
-        tn = (int)b;
-        nsplit = ns;
-    }
+    const F32Plan plan = choose_f32_plan(K, d_in, d_out);
+    long nsplit = plan.nsplit;
     float *part = nullptr, *bpart = nullptr;
     if (nsplit > 1) {
         dp_ws_alloc ws(ctx);
@@ -1226,31 +1269,62 @@ static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, 
     if (!part || !bpart) nsplit = 1;
     const long rows = ((K + nsplit - 1) / nsplit + 1) / 2 * 2;
     nsplit = (K + rows - 1) / rows;
-    const dim3 grid(tn, tm, (unsigned)nsplit), block(64 * F32_WAVES);
+    const dim3 grid((unsigned)((d_out + 32 * plan.n32 - 1) / (32 * plan.n32)), (unsigned)((d_in + 32 * plan.m32 - 1) / (32 * plan.m32)),
+                    (unsigned)nsplit);
+    const dim3 block(64 * F32_WAVES);
     const int add = nsplit == 1 ? 1 : 0;
     float* o = add ? sum_W : part;
     float* ob = !sum_b ? nullptr : add ? sum_b : bpart;
-    auto launch = [&](auto m_tag, auto n_tag) {
+    auto launch = [&](auto m_tag, auto n_tag, auto wide_tag) {
         auto go = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, block, 0, ctx->stream, (const float*)A, (const float*)G, own ? sqnorms : ctx->cbuf, C, T, K, d_in,
                                d_out, rows, add, o, ob, ctx->err_word);
         };
         constexpr int M = decltype(m_tag)::value, N = decltype(n_tag)::value;
-        if (own) go(wgemm_f32_kernel<M, N, true>);
-        else go(wgemm_f32_kernel<M, N, false>);
+        constexpr bool W = decltype(wide_tag)::value;
+        if (own) go(wgemm_f32_kernel<M, N, true, W>);
+        else go(wgemm_f32_kernel<M, N, false, W>);
     };
     using one = std::integral_constant<int, 1>;
     using two = std::integral_constant<int, 2>;
     using three = std::integral_constant<int, 3>;
-    if (m32 == 2 && n32 == 2) launch(two{}, two{});
-    else if (m32 == 3) launch(three{}, one{});
-    else if (m32 == 2) launch(two{}, one{});
-    else launch(one{}, one{});
+    if (plan.wide) launch(two{}, two{}, std::true_type{});
+    else if (plan.m32 == 2 && plan.n32 == 2) launch(two{}, two{}, std::false_type{});
+    else if (plan.m32 == 3) launch(three{}, one{}, std::false_type{});
+    else if (plan.m32 == 2) launch(two{}, one{}, std::false_type{});
+    else launch(one{}, one{}, std::false_type{});
     DP_LAUNCH_CHECK(ctx, "wgemm_f32");
     if (add) return DP_OK;
     st = dpk_reduce_partials(ctx, part, (int)nsplit, (size_t)d_in * d_out, (size_t)d_in * d_out, sum_W);
     if (st == DP_OK && sum_b) st = dpk_reduce_partials(ctx, bpart, (int)nsplit, (size_t)d_out, (size_t)d_out, sum_b);
     return st;
+}
+
+// What dpk_weighted_gemm_batched does with these sizes, for its tests: tile rows and columns, flat, layers a launch, row splits of a
+// full launch (the workspace may hold fewer), rows that one 32-bit buffer resource covers (0: 64-bit addresses).
+dp_status dpk_dense_sum_plan(dp_dtype dt, int n, int B, int T, int d_in, int d_out, size_t ws_bytes, int32_t* out) {
+    const long K = (long)B * T;
+    if (dt == DP_F32) {
+        const F32Plan p = choose_f32_plan(K, d_in, d_out);
+        out[0] = 32 * p.m32;
+        out[1] = 32 * p.n32;
+        out[2] = 0;
+        out[3] = 1;
+        out[4] = (int32_t)p.nsplit;
+        out[5] = p.wide ? 0 : f32_block(p.m32, p.n32);
+        return DP_OK;
+    }
+    const DmaPlan p = choose_dma_plan(n, B, T, d_in, d_out, ws_bytes);
+    const long spe = p.flat ? 1 : (T + BK - 1) / BK, ksteps = p.flat ? (K + BK - 1) / BK : (long)B * spe;
+    const int ntiles = ((d_in + p.bm - 1) / p.bm) * ((d_out + p.bn - 1) / p.bn), nl = n < p.per_launch ? n : p.per_launch;
+    double t;
+    out[0] = p.bm;
+    out[1] = p.bn;
+    out[2] = p.flat ? 1 : 0;
+    out[3] = nl;
+    out[4] = (int32_t)choose_nsplit_dma(nl, ntiles, ksteps, spe, d_in, d_out, dma_cost(p.bm, p.bn, !p.flat && T <= BK), &t);
+    out[5] = BK;
+    return DP_OK;
 }
 
 // Norms by materialisation: a unit of the kernel is one example, its tiles of A_i^T G_i are squared and summed as they leave the

@@ -116,6 +116,31 @@ def test_gram_unit_plan_rejects_other_lengths(lib):
     assert lib.dp_gram_unit_plan(512, None, 2, ctypes.byref(n)) == -1
 
 
+@pytest.mark.parametrize("rows", [1, 40, 129, 1024, 4096])
+@pytest.mark.parametrize("d_in", [1, 32, 64, 1000])
+def test_fp32_sum_plan_fits_its_rows_into_32_bits(lib, rows, d_in):
+    """The bytes of a block of rows, and the offsets into it, are 32-bit numbers: at any width the block that the plan takes has to
+    fit, or the rows are addressed with 64 bits."""
+    import paper_2108_01624_amd as pkg
+
+    widths = [4, 1 << 20] + [w + e for w in (1 << 21, 1 << 22, 1 << 23, 1 << 24, 1 << 28) for e in (-1, 0, 1, 31)]
+    for w in widths:
+        for a, b in ((d_in, w), (min(w, 1 << 21), d_in)):
+            plan = pkg.dp_dense_sum_plan(pkg.DP_F32, 1, 1, rows, a, b)
+            assert plan["block_rows"] * 4 * max(a, b) < 1 << 32, (a, b, plan)
+            assert plan["block_rows"] > 0 or max(a, b) >= 1 << 23, (a, b, plan)
+            assert -(-a // plan["tile_m"]) <= 65535, (a, b, plan)
+
+
+def test_dense_sum_plan_refuses_what_the_call_refuses(lib):
+    import paper_2108_01624_amd as pkg
+
+    for bad in ((7, 1, 1, 1, 8, 8), (1, 0, 1, 1, 8, 8), (1, 1, 0, 1, 8, 8), (1, 1, 1, 1, 8, 12), (0, 1, 1 << 16, 1 << 15, 8, 8)):
+        with pytest.raises(pkg.DpError):
+            pkg.dp_dense_sum_plan(*bad)
+    assert lib.dp_dense_sum_plan(0, 1, 1, 1, 8, 8, 0, None) == -1
+
+
 def test_null_context_is_rejected_without_a_gpu(lib):
     assert lib.dp_sync(None) == -1
     assert lib.dp_destroy(None) == -1

@@ -962,6 +962,30 @@ def test_dense_f32_forms(dp, B, T, d_in, d_out):
     assert_sums_close(host(b).astype(np.float64) + 0.5, b_ref, 1e-5, "sum_b")
 
 
+@pytest.mark.parametrize("d_in,d_out", [(3, (1 << 23) - 8), (3, (1 << 23) + 40), (66, 1 << 23)])
+def test_dense_f32_sums_of_very_wide_layers(dp, d_in, d_out):
+    """Two blocks of rows, whose bytes just fit 32 bits, or no longer do.  The reference in fp64 on the device, in pieces of the
+    columns; 130 fp32 terms an entry: 1e-5 as above."""
+    import paper_2108_01624_amd as pkg
+
+    B, T, step = 13, 10, 1 << 20
+    assert (pkg.dp_dense_sum_plan(pkg.DP_F32, 1, B, T, d_in, d_out)["block_rows"] == 0) == (d_out >= 1 << 23)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(520)
+    A, G = torch.randn((B, T, d_in), generator=g, device=DEV), torch.randn((B, T, d_out), generator=g, device=DEV)
+    sq = f32_dev(syn.synthetic_sqnorms(B, 1.0, 521))
+    W, b = torch.full((d_in, d_out), 0.25, device=DEV), torch.full((d_out,), -0.5, device=DEV)
+    dp.clip_accumulate_dense(A, G, 1.0, sq, W, b)
+    dp.sync()
+    c = torch.where(sq > 1, 1 / sq.double().sqrt(), torch.ones_like(sq, dtype=torch.float64))
+    At = (A.double() * c[:, None, None]).reshape(B * T, d_in).t().contiguous()
+    for q in range(0, d_out, step):
+        Gq = G[:, :, q:q + step].reshape(B * T, -1).double()
+        for got, ref in ((W[:, q:q + step].double() - 0.25, At @ Gq),
+                         (b[q:q + step].double() + 0.5, (Gq * c.repeat_interleave(T)[:, None]).sum(0))):
+            assert float((got - ref).norm() / ref.norm()) < 1e-5 and float((got - ref).abs().max() / ref.square().mean().sqrt()) < 1e-4, q
+
+
 @pytest.mark.parametrize("n,B,T,d_in,d_out", [
     (1, 3, 1, 8, 8), (3, 5, 20, 72, 136), (17, 2, 32, 64, 64),        # up to 32 rows, one and several layers, ragged widths
     (1, 300, 20, 72, 1032), (2, 140, 31, 128, 640), (1, 2, 20, 1032, 2056),  # ... few and many workgroups, many chunks a wave
