@@ -59,7 +59,7 @@ typedef enum { DP_PATH_AUTO = 0, DP_PATH_GRAM = 1, DP_PATH_MATERIALISE = 2 } dp_
 typedef enum {
     DP_OK = 0,
     DP_ERR_NULL = -1,      /* a required pointer is NULL */
-    DP_ERR_SHAPE = -2,     /* a size is negative, or not a multiple the dtype requires */
+    DP_ERR_SHAPE = -2,     /* a size is negative, not a multiple the dtype requires, or beyond what a kernel can address */
     DP_ERR_DTYPE = -3,     /* unknown dp_dtype / dp_path value */
     DP_ERR_ALIGN = -4,     /* pointer alignment */
     DP_ERR_VALUE = -5,     /* C <= 0, sigma < 0, batch_size == 0, step == 0, beta outside [0,1), eps < 0 ...; from dp_sync: a
@@ -151,7 +151,7 @@ dp_status dp_sqnorms_embedding(dp_ctx* ctx, const int32_t* ids, const void* G, d
  * accumulators are rescaled by c_prev / c_next where the example changes.  Where that would waste much of the work (T well
  * below a multiple of 32, wide layers) the clip factor may instead multiply G in fp32 once, the product rounded back to
  * bf16 (round-to-nearest-even) before the contraction (relative error of the sum about 1e-3); T a multiple of 32 above 32
- * never takes that form.  The bias sums add fp32 products either way. */
+ * never takes that form.  The bias sums add fp32 products either way.  Widths up to 33,554,424 (DP_ERR_SHAPE above). */
 dp_status dp_clip_accumulate_dense(dp_ctx* ctx, const void* A, const void* G, dp_dtype dtype, int B, int T, int d_in,
                                    int d_out, float C, const float* sqnorms, float* sum_W, float* sum_b);
 

@@ -55,6 +55,11 @@ dp_status check_clip(dp_ctx* ctx, float C, int B) {
     return DP_OK;
 }
 
+dp_status check_sum_width(dp_ctx* ctx, dp_dtype dt, int d_in, int d_out) {
+    if (!dp_sum_width_ok(dt, d_in, d_out)) FAIL(ctx, DP_ERR_SHAPE, "a width above %d (bf16)", DP_BF16_MAX_WIDTH);
+    return DP_OK;
+}
+
 #define TRY(expr)                    \
     do {                             \
         dp_status s__ = (expr);      \
@@ -202,6 +207,7 @@ dp_status dp_dense_sum_plan(dp_dtype dtype, int n_layers, int B, int T, int d_in
     if (dtype != DP_F32 && dtype != DP_BF16) return DP_ERR_DTYPE;
     if (n_layers < 1 || B < 1 || T < 1 || d_in < 1 || d_out < 1 || (long)B * T > MAX_ROWS) return DP_ERR_SHAPE;
     if (dtype == DP_BF16 && (d_in % 8 || d_out % 8)) return DP_ERR_SHAPE;
+    if (!dp_sum_width_ok(dtype, d_in, d_out)) return DP_ERR_SHAPE;
     return dpk_dense_sum_plan(dtype, n_layers, B, T, d_in, d_out, workspace_bytes ? workspace_bytes : DEFAULT_WORKSPACE, plan);
 }
 
@@ -443,6 +449,7 @@ dp_status dp_clip_accumulate_dense(dp_ctx* ctx, const void* A, const void* G, dp
     if (dtype == DP_BF16 && ((uintptr_t)sum_W & 15)) FAIL(ctx, DP_ERR_ALIGN, "sum_W is not 16-byte aligned");
     TRY(check_clip(ctx, C, B));
     if (B == 0 || T == 0 || d_out == 0) return DP_OK;
+    TRY(check_sum_width(ctx, dtype, d_in, d_out));
     return dpk_weighted_gemm(ctx, A, G, dtype, B, T, d_in, d_out, sqnorms, C, sum_W, sum_b);
 }
 
@@ -465,6 +472,7 @@ dp_status dp_clip_accumulate_dense_batched(dp_ctx* ctx, int n_layers, const void
     TRY(check_f32(ctx, "sqnorms", sqnorms));
     TRY(check_clip(ctx, C, B));
     if (B == 0 || T == 0 || d_out == 0) return DP_OK;
+    TRY(check_sum_width(ctx, dtype, d_in, d_out));
     return dpk_weighted_gemm_batched(ctx, n_layers, A, G, dtype, B, T, d_in, d_out, sqnorms, C, sum_W, sum_b);
 }
 
@@ -640,6 +648,7 @@ dp_status dp_clip_accumulate_tied_embedding(dp_ctx* ctx, const int32_t* ids, con
     if (dtype == DP_BF16 && ((uintptr_t)sum_E & 15)) FAIL(ctx, DP_ERR_ALIGN, "sum_E is not 16-byte aligned");
     TRY(check_clip(ctx, C, B));
     if (B == 0 || d == 0) return DP_OK;
+    if (M > 0) TRY(check_sum_width(ctx, dtype, V, d));  // before anything is added to sum_E
     if (T > 0) TRY(dpk_embedding_sums(ctx, ids, dY, dtype, B, T, d, V, sqnorms, C, sum_E));
     if (M == 0) return DP_OK;
     // the output projection's sum is a dense sum with input dL [B, M, V] and output gradient H [B, M, d]

@@ -179,6 +179,9 @@ dp_status dpk_materialise_sqnorms_batched(dp_ctx*, int n, const void* const* A, 
 // sum_W += sum_i c_i A_i^T G_i and, if sum_b, sum_b += sum_i c_i sum_t G_i[t,:], with c_i from (sqnorms, C)
 dp_status dpk_weighted_gemm(dp_ctx*, const void* A, const void* G, dp_dtype, int B, int T, int d_in, int d_out,
                             const float* sqnorms, float C, float* sum_W, float* sum_b);
+// widest layer whose 32-row stages, and 16 rows of its fp32 sum, have offsets below 2^31 bytes (with the overhang of a tile)
+constexpr int DP_BF16_MAX_WIDTH = ((1 << 30) - 256) / 32;
+static inline bool dp_sum_width_ok(dp_dtype dt, int d_in, int d_out) { return dt != DP_BF16 || (d_in > d_out ? d_in : d_out) <= DP_BF16_MAX_WIDTH; }
 dp_status dpk_dense_sum_plan(dp_dtype, int n, int B, int T, int d_in, int d_out, size_t ws_bytes, int32_t* out /* [6] */);
 
 dp_status dpk_mfma_ceiling(dp_ctx*, int iters, int launches, double* tflops);

@@ -954,6 +954,7 @@ static DmaPlan choose_dma_plan(int n, int B, int T, int d_in, int d_out, size_t 
     const long K = (long)B * T;
     for (int flat = 0; flat < 2; ++flat) {
         if (flat && T % BK == 0 && T > BK) continue;  // whole stages: nothing to gain
+        if (flat && d_out > 65535 * 256) continue;    // (scale_rows_kernel has a grid row per 256 columns)
         size_t per_ws = MAX_BATCH;
         if (flat) {
             // layers whose scaled output gradients fit half the workspace (their bias partials are a sixteenth of that)
@@ -1337,6 +1338,10 @@ dp_status dpk_materialise_sqnorms_batched(dp_ctx* ctx, int n, const void* const*
         for (int l = 0; st == DP_OK && l < n; ++l)
             st = dpk_materialise_f32(ctx, (const float*)A[l], (const float*)G[l], B, T, d_in, d_out, sqnorms);
         if (st == DP_OK && has_bias && n > 0) st = dpk_colstat_sqnorms_batched(ctx, n, nullptr, G, dt, B, T, d_out, 0, 1, sqnorms, nullptr);
+    }
+    if (!dp_sum_width_ok(dt, d_in, d_out)) {
+        DP_SET_ERR(ctx, "dp_sqnorms_dense: a width above %d (bf16, by materialisation)", DP_BF16_MAX_WIDTH);
+        return DP_ERR_SHAPE;
     }
     for (int l0 = 0; dt == DP_BF16 && l0 < n;) {
         int nl = n - l0 < MAX_BATCH ? n - l0 : MAX_BATCH, bm = 0, bn = 0;

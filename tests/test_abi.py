@@ -139,6 +139,15 @@ def test_dense_sum_plan_refuses_what_the_call_refuses(lib):
         with pytest.raises(pkg.DpError):
             pkg.dp_dense_sum_plan(*bad)
     assert lib.dp_dense_sum_plan(0, 1, 1, 1, 8, 8, 0, None) == -1
+    # bf16: offsets into a 32-row stage, (31 w + columns up to w + a tile's overhang) * 2 bytes, stay below 2^31
+    widest = ((1 << 30) - 256) // 32
+    assert (31 * widest + widest + 255) * 2 < 1 << 31 <= (32 * (widest + 8) + 256) * 2
+    for a, b in ((8, widest), (widest, 8)):
+        plan = pkg.dp_dense_sum_plan(pkg.DP_BF16, 1, 1, 20, a, b, 1 << 34)
+        assert not (plan["scaled"] and b > 65535 * 256), plan
+        for w in (widest + 8, 1 << 26):
+            with pytest.raises(pkg.DpError):
+                pkg.dp_dense_sum_plan(pkg.DP_BF16, 1, 1, 20, w if a > b else a, b if a > b else w)
 
 
 def test_null_context_is_rejected_without_a_gpu(lib):

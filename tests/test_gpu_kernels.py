@@ -658,6 +658,23 @@ def test_argument_errors(dp):
     assert not host(x).any()
 
 
+def test_bf16_sums_refuse_widths_past_their_offsets(dp):
+    """Widths whose 32-row stages need more than 31 bits of offset: refused before anything is launched."""
+    import paper_2108_01624_amd as pkg
+
+    lib, h = pkg.load_library(), dp.handle
+    x = torch.zeros(64, dtype=torch.float32, device=DEV)
+    p = x.data_ptr()
+    for w in (33554432, 1 << 26):
+        assert lib.dp_clip_accumulate_dense(h, p, p, 1, 1, 1, 8, w, 1.0, p, p, None) == -2
+        assert lib.dp_clip_accumulate_dense(h, p, p, 1, 1, 1, w, 8, 1.0, p, p, None) == -2
+        assert lib.dp_clip_accumulate_tied_embedding(h, p, p, p, p, 1, 1, 4, 2, 8, w, 1.0, p, p) == -2
+        assert lib.dp_sqnorms_dense(h, p, p, 1, 1, 1, 8, w, 0, 2, p) == -2
+        assert lib.dp_clip_accumulate_dense(h, p, p, 1, 0, 1, 8, w, 1.0, p, p, None) == 0   # empty batch: no-op
+    dp.sync()
+    assert not host(x).any()
+
+
 def test_small_workspace(dp):
     """A context with a 2 MiB workspace: the GEMM takes fewer row splits than it would like and still gives the
     oracle's sums; a call whose buffers cannot fit returns DP_ERR_WORKSPACE and leaves the context usable."""
