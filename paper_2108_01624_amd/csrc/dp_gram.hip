@@ -1051,6 +1051,13 @@ static dp_status gram_units_launch(dp_ctx* ctx, const GramBatch& gb, int T, int 
     return dpk_finish_partials(ctx, part, gb.B, gu.n_units * gb.n_layers, sqnorms);
 }
 
+// Layers of one launch: as many as it may hold and as have room for their partial norms; a single one adds to sqnorms itself.
+static int gram_layers_per_launch(const dp_ctx* ctx, int n, int B) {
+    int nl = n < GRAM_MAX_BATCH ? n : GRAM_MAX_BATCH;
+    while (nl > 1 && ((size_t)nl * B * sizeof(float) > ctx->ws_bytes || (long)nl * B > 0x7FFFFFFFl)) nl = (nl + 1) / 2;
+    return nl;
+}
+
 dp_status dpk_gram_sqnorms_batched(dp_ctx* ctx, int n_layers, const void* const* A, const void* const* G, dp_dtype dt,
                                    int B, int T, int d_in, int d_out, int has_bias, float* sqnorms) {
     if (dt == DP_BF16 && gram_units_ok(T, d_in, d_out)) {
@@ -1085,11 +1092,9 @@ dp_status dpk_gram_sqnorms_batched(dp_ctx* ctx, int n_layers, const void* const*
         return DP_OK;
     }
     for (int l0 = 0; l0 < n_layers;) {
-        int nl = n_layers - l0 < GRAM_MAX_BATCH ? n_layers - l0 : GRAM_MAX_BATCH;
-        if ((long)nl * B > 0x7FFFFFFFl) nl = 1;
+        const int nl = gram_layers_per_launch(ctx, n_layers - l0, B);
         dp_ws_alloc ws(ctx);
         float* part = nl > 1 ? ws.get<float>((size_t)B * nl) : nullptr;
-        if (!part) nl = 1;  // one layer at a time adds to sqnorms itself
         GramBatch gb;
         for (int l = 0; l < GRAM_MAX_BATCH; ++l) {
             gb.A[l] = (const uint16_t*)A[l0 + (l < nl ? l : 0)];
@@ -1111,8 +1116,7 @@ dp_status dpk_gram_sqnorms_batched(dp_ctx* ctx, int n_layers, const void* const*
 // group-major: G[g * n_out + j].
 dp_status dpk_gram_sqnorms_shared(dp_ctx* ctx, int n_groups, const void* const* A, int n_out, const void* const* G,
                                   dp_dtype dt, int B, int T, int d_in, int d_out, int has_bias, float* sqnorms) {
-    if (dt != DP_BF16 || n_out < 2 || n_out > 3 || !gram_dma_ok(T, d_in, d_out) ||
-        (long)B * GRAM_MAX_BATCH > 0x7FFFFFFFl) {
+    if (dt != DP_BF16 || n_out < 2 || n_out > 3 || !gram_dma_ok(T, d_in, d_out)) {
         for (int g = 0; g < n_groups; ++g)
             for (int j = 0; j < n_out; ++j) {
                 dp_status st = dpk_gram_sqnorms(ctx, A[g], G[(size_t)g * n_out + j], dt, B, T, d_in, d_out, has_bias, sqnorms);
@@ -1120,8 +1124,10 @@ dp_status dpk_gram_sqnorms_shared(dp_ctx* ctx, int n_groups, const void* const* 
             }
         return DP_OK;
     }
-    for (int g0 = 0; g0 < n_groups; g0 += GRAM_MAX_BATCH) {
-        const int ng = n_groups - g0 < GRAM_MAX_BATCH ? n_groups - g0 : GRAM_MAX_BATCH;
+    for (int g0 = 0; g0 < n_groups;) {
+        const int ng = gram_layers_per_launch(ctx, n_groups - g0, B);
+        dp_ws_alloc ws(ctx);
+        float* part = ng > 1 ? ws.get<float>((size_t)B * ng) : nullptr;
         GramBatch gb;
         for (int l = 0; l < GRAM_MAX_BATCH; ++l) {
             const size_t g = (size_t)g0 + (l < ng ? l : 0);
@@ -1134,21 +1140,10 @@ dp_status dpk_gram_sqnorms_shared(dp_ctx* ctx, int n_groups, const void* const* 
         gb.n_out = n_out;
         gb.B = B;
         const double bytes = 2.0 * (double)B * T * ((double)d_in + (double)n_out * d_out) * ng;
-        if (ng == 1) {
-            dp_status st = gram_dma_launch(ctx, gb, T, d_in, d_out, has_bias, sqnorms, bytes);
-            if (st != DP_OK) return st;
-            continue;
-        }
-        dp_ws_alloc ws(ctx);
-        float* part = ws.get<float>((size_t)B * ng);
-        if (!part) {
-            DP_SET_ERR(ctx, "workspace too small for %d x %d norm partials", B, ng);
-            return DP_ERR_WORKSPACE;
-        }
-        dp_status st = gram_dma_launch(ctx, gb, T, d_in, d_out, has_bias, part, bytes);
+        dp_status st = gram_dma_launch(ctx, gb, T, d_in, d_out, has_bias, part ? part : sqnorms, bytes);
+        if (st == DP_OK && part) st = dpk_finish_partials(ctx, part, B, ng, sqnorms);
         if (st != DP_OK) return st;
-        st = dpk_finish_partials(ctx, part, B, ng, sqnorms);
-        if (st != DP_OK) return st;
+        g0 += ng;
     }
     return DP_OK;
 }

@@ -714,6 +714,30 @@ def test_small_workspace(dp):
         np.testing.assert_array_equal(host(n), host(n_ref))
 
 
+@pytest.mark.parametrize("floats_per_example", [0, 1, 20])
+def test_many_layers_on_a_small_workspace(dp, floats_per_example):
+    """Forty layers, or groups that share an input, and room for the partial norms of none, one or twenty of them: fewer a launch.
+    Against the default context; the two add the same 40 positive partial norms in another grouping (40 x 2^-24)."""
+    import paper_2108_01624_amd as pkg
+
+    n, B, T, d = 40, 256, 9, 64
+    A = [to_dev(gen((B, T, d), 1.0, 700 + l, "bf16")) for l in range(n)]
+    G = [to_dev(gen((B, T, d), 0.1, 750 + l, "bf16")) for l in range(n)]
+    pairs = [[G[l], G[(l + 1) % n]] for l in range(n)]
+
+    def norms(ctx):
+        out = [torch.full((B,), 2.0, dtype=torch.float32, device=DEV) for _ in range(2)]
+        ctx.sqnorms_dense_batched(A, G, True, pkg.DP_PATH_GRAM, out[0])
+        ctx.sqnorms_dense_shared(A, pairs, True, out[1])
+        ctx.sync()
+        return [host(x) for x in out]
+
+    ref = norms(dp)
+    with pkg.Context(workspace_bytes=max(256, 4 * B * floats_per_example)) as small:
+        for got, want in zip(norms(small), ref):
+            np.testing.assert_allclose(got, want, rtol=40 * 2.0 ** -24)
+
+
 def test_tiny_workspace_every_entry_point_works_or_reports(dp):
     """4 KiB of workspace: every call either needs none of it and gives the default context's result, or returns
     DP_ERR_WORKSPACE without touching its outputs."""
