@@ -992,18 +992,25 @@ dp_status dpk_kept_sums_batched(dp_ctx* ctx, int n, float* const* keep, int B, i
     return DP_OK;
 }
 
+// Runs of rows that the column sums of a layer are cut into (`vw` columns a lane), and the rows of a run.
+static long colstat_runs(long nrows, int d, int vw, int* rows_per) {
+    const int J = (d + 64 * vw - 1) / (64 * vw);
+    long R = 1024 / J;  // about 1024 workgroups per layer
+    if (R < 1) R = 1;
+    const long maxR = (nrows + 63) / 64;
+    if (R > maxR) R = maxR;
+    *rows_per = (int)((nrows + R - 1) / R);
+    return (nrows + *rows_per - 1) / *rows_per;
+}
+
 // out_x / out_1: tables of L pointers, or NULL when that statistic is not wanted (the same for every layer of the call)
 template <bool BF16, int VW>
 static dp_status colstat_sums_launch(dp_ctx* ctx, int L, const void* const* X, const void* const* G, int B, int T, int d,
                                      const float* c, float* const* out_x, float* const* out_1) {
     const long nrows = (long)B * T;
     const int J = (d + 64 * VW - 1) / (64 * VW);
-    long R = 1024 / J;  // about 1024 workgroups per layer
-    if (R < 1) R = 1;
-    const long maxR = (nrows + 63) / 64;
-    if (R > maxR) R = maxR;
-    const int rows_per = (int)((nrows + R - 1) / R);
-    R = (nrows + rows_per - 1) / rows_per;
+    int rows_per;
+    const long R = colstat_runs(nrows, d, VW, &rows_per);
     dp_ws_alloc ws(ctx);
     float* part = ws.get<float>((size_t)L * R * 2 * d);
     if (!part) {
@@ -1050,8 +1057,12 @@ dp_status dpk_colstat_sums_batched(dp_ctx* ctx, int n, const void* const* X, con
     if (B == 0 || T == 0 || d == 0 || n == 0 || (!out_x && !out_1)) return DP_OK;
     bool v4 = true;
     for (int l = 0; l < n; ++l) v4 = v4 && vec4_ok(dt, d, out_x ? X[l] : G[l], G[l]);
-    for (int l0 = 0; l0 < n; l0 += COL_MAX_BATCH) {
-        const int L = n - l0 < COL_MAX_BATCH ? n - l0 : COL_MAX_BATCH;
+    // layers per launch: as many as one may hold and as have room for their partial sums (at least one)
+    int rows_per;
+    size_t per = ctx->ws_bytes / (colstat_runs((long)B * T, d, dt == DP_BF16 || v4 ? 4 : 1, &rows_per) * 2 * (size_t)d * sizeof(float));
+    per = per < 1 ? 1 : per > COL_MAX_BATCH ? COL_MAX_BATCH : per;
+    for (int l0 = 0; l0 < n; l0 += (int)per) {
+        const int L = n - l0 < (int)per ? n - l0 : (int)per;
         const void* const* Xl = out_x ? X + l0 : nullptr;
         float* const* ox = out_x ? out_x + l0 : nullptr;
         float* const* o1 = out_1 ? out_1 + l0 : nullptr;

@@ -738,6 +738,28 @@ def test_many_layers_on_a_small_workspace(dp, floats_per_example):
             np.testing.assert_allclose(got, want, rtol=40 * 2.0 ** -24)
 
 
+@pytest.mark.parametrize("layers_room", [1, 20])
+def test_many_layernorms_on_a_small_workspace(dp, layers_room):
+    """Forty LayerNorms and room for the partial sums of one or twenty of them: fewer a launch, the same sums bit for bit (a layer's
+    rows are cut alike)."""
+    import paper_2108_01624_amd as pkg
+
+    n, B, T, d = 40, 16, 64, 256
+    X, G = [to_dev(gen((B, T, d), 1.0, 800 + l, "bf16")) for l in range(n)], [to_dev(gen((B, T, d), 0.1, 850 + l, "bf16")) for l in range(n)]
+    sq = f32_dev(syn.synthetic_sqnorms(B, 1.0, 899))
+
+    def sums(ctx):
+        out = [torch.full((2, d), 0.5, dtype=torch.float32, device=DEV) for _ in range(n)]
+        ctx.clip_accumulate_layernorm_batched(X, G, 1.0, sq, [o[0] for o in out], [o[1] for o in out])
+        ctx.sync()
+        return [host(o) for o in out]
+
+    ref = sums(dp)
+    with pkg.Context(workspace_bytes=layers_room * (B * T // 64) * 2 * d * 4) as small:   # a run of 64 rows: 2 d partial sums
+        for l, (got, want) in enumerate(zip(sums(small), ref)):
+            np.testing.assert_array_equal(got, want, err_msg=f"layer {l}")
+
+
 def test_tiny_workspace_every_entry_point_works_or_reports(dp):
     """4 KiB of workspace: every call either needs none of it and gives the default context's result, or returns
     DP_ERR_WORKSPACE without touching its outputs."""
