@@ -506,8 +506,8 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
 constexpr int SORT_CHUNK = 1024;
 constexpr int SORT_INLINE = 256;  // chunks up to which every workgroup can afford to read the whole histogram (1 KiB a chunk)
 
-// A row of the histogram (one digit) is padded to a multiple of 4 chunks, the padding zero.
-__host__ __device__ inline int sort_pitch(int nchunks) { return (nchunks + 3) / 4 * 4; }
+// A row of the histogram (one digit) is padded to a multiple of 4 chunks where the workspace allows, the padding zero.
+inline int sort_pitch(int nchunks) { return (nchunks + 3) / 4 * 4; }
 
 // Key of position r: the id, or the sentinel V (sorts last and is skipped) for an id out of range.
 template <bool FIRST>
@@ -520,9 +520,9 @@ __device__ __forceinline__ uint32_t sort_key(const uint32_t* __restrict__ keys, 
 // additions does not matter).  FIRST: `keys` are the ids, range-checked here.
 template <bool FIRST>
 __global__ __launch_bounds__(256) void sort_hist(const uint32_t* __restrict__ keys, int N, int V, int shift,
-                                                 uint32_t* __restrict__ hist, int nchunks, int* __restrict__ err) {
+                                                 uint32_t* __restrict__ hist, int nchunks, int pitch, int* __restrict__ err) {
     __shared__ uint32_t cnt[256];
-    const int c = blockIdx.x, pitch = sort_pitch(nchunks);
+    const int c = blockIdx.x;
     const int n0 = c * SORT_CHUNK;
     const int valid = N - n0 < SORT_CHUNK ? N - n0 : SORT_CHUNK;
     cnt[threadIdx.x] = 0;
@@ -545,7 +545,7 @@ __global__ __launch_bounds__(256) void sort_hist(const uint32_t* __restrict__ ke
 }
 
 // In-place exclusive prefix sum of hist[0..n): one workgroup, thread t owns a contiguous slice, read and written as
-// 16-byte vectors, eight in flight (n is 256 digits x a multiple of 4 chunks).
+// 16-byte vectors, eight in flight, where it is a multiple of 4 (n is 256 digits x the row pitch).
 __global__ __launch_bounds__(256) void sort_scan(uint32_t* __restrict__ hist, int n) {
     __shared__ uint32_t tsum[256];
     const int per = (n + 255) / 256;  // n % 256 == 0: every slice is full
@@ -607,17 +607,17 @@ __global__ __launch_bounds__(256) void sort_scan(uint32_t* __restrict__ hist, in
 // Stable scatter of one chunk by the current digit.  The chunk is cut into groups of 64 consecutive keys (one wave
 // handles a group at a time): digit counts per group (LDS integer counters), an exclusive scan over the groups per
 // digit on top of the chunk's global base, and inside a group the rank of a key among the keys of equal digit at lower
-// positions, from eight ballots.  INLINE: `base` is the histogram itself; thread b adds up digit b's counts of all chunks and of
+// positions, from eight ballots.  INLINE: `base` is the histogram itself, its pitch a multiple of 4; thread b adds up digit b's counts of all chunks and of
 // the chunks before this one, and a scan over the digits makes them bases.  Otherwise it has been scanned.
 template <bool FIRST, bool INLINE>
 __global__ __launch_bounds__(256) void sort_scatter(const uint32_t* __restrict__ keys,
                                                     const uint32_t* __restrict__ vals, int N, int V, int shift,
-                                                    const uint32_t* __restrict__ base, int nchunks,
+                                                    const uint32_t* __restrict__ base, int pitch,
                                                     uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out) {
     constexpr int NG = SORT_CHUNK / 64;  // groups per chunk
     __shared__ uint32_t gcnt[NG][256];
     __shared__ uint32_t wtot[4];
-    const int c = blockIdx.x, pitch = sort_pitch(nchunks);
+    const int c = blockIdx.x;
     const int n0 = c * SORT_CHUNK;
     const int valid = N - n0 < SORT_CHUNK ? N - n0 : SORT_CHUNK;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1145,22 +1145,30 @@ static dp_status embedding_sums_launch(dp_ctx* ctx, const int32_t* ids, const vo
     uint32_t* k1 = ws.get<uint32_t>(N);
     uint32_t* v0 = ws.get<uint32_t>(N);
     uint32_t* v1 = ws.get<uint32_t>(N);
-    uint32_t* hist = ws.get<uint32_t>((size_t)256 * sort_pitch(nsort));
-    float* first = ws.get<float>((size_t)nseg * d);
-    float* last = ws.get<float>((size_t)nseg * d);
+    uint32_t* hist;
+    float *first, *last;
+    const size_t mark = ws.off;
+    int pitch = sort_pitch(nsort);
+    for (;; pitch = nsort) {  // without padding when there is no room for it: the scan takes any pitch
+        ws.off = mark;
+        hist = ws.get<uint32_t>((size_t)256 * pitch);
+        first = ws.get<float>((size_t)nseg * d);
+        last = ws.get<float>((size_t)nseg * d);
+        if ((hist && first && last) || pitch == nsort) break;
+    }
     if (!k0 || !k1 || !v0 || !v1 || !hist || !first || !last) {
         DP_SET_ERR(ctx, "workspace too small for the embedding sort of %d tokens", N);
         return DP_ERR_WORKSPACE;
     }
     const int bits = bit_length((uint32_t)V);  // the sentinel V itself must be representable
-    const bool scan = nsort > SORT_INLINE;
+    const bool scan = nsort > SORT_INLINE || pitch % 4 != 0;
     const dim3 grid(nsort), block(256);
     for (int shift = 0; shift < bits; shift += 8) {
         const uint32_t* kin = shift ? k0 : reinterpret_cast<const uint32_t*>(ids);
-        if (shift) hipLaunchKernelGGL((sort_hist<false>), grid, block, 0, ctx->stream, kin, N, V, shift, hist, nsort, ctx->err_word);
-        else hipLaunchKernelGGL((sort_hist<true>), grid, block, 0, ctx->stream, kin, N, V, shift, hist, nsort, ctx->err_word);
-        if (scan) hipLaunchKernelGGL(sort_scan, dim3(1), block, 0, ctx->stream, hist, 256 * sort_pitch(nsort));
-        auto scatter = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, ctx->stream, kin, v0, N, V, shift, hist, nsort, k1, v1); };
+        if (shift) hipLaunchKernelGGL((sort_hist<false>), grid, block, 0, ctx->stream, kin, N, V, shift, hist, nsort, pitch, ctx->err_word);
+        else hipLaunchKernelGGL((sort_hist<true>), grid, block, 0, ctx->stream, kin, N, V, shift, hist, nsort, pitch, ctx->err_word);
+        if (scan) hipLaunchKernelGGL(sort_scan, dim3(1), block, 0, ctx->stream, hist, 256 * pitch);
+        auto scatter = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, ctx->stream, kin, v0, N, V, shift, hist, pitch, k1, v1); };
         if (shift && scan) scatter(sort_scatter<false, false>);
         else if (shift) scatter(sort_scatter<false, true>);
         else if (scan) scatter(sort_scatter<true, false>);

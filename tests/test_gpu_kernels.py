@@ -760,6 +760,26 @@ def test_many_layernorms_on_a_small_workspace(dp, layers_room):
             np.testing.assert_array_equal(got, want, err_msg=f"layer {l}")
 
 
+@pytest.mark.parametrize("B,T,d,V", [(4, 25, 8, 50), (9, 128, 8, 300), (8, 512, 64, 70000)])
+def test_embedding_sums_in_the_least_workspace(dp, B, T, d, V):
+    """Room for two pairs of key and row lists, one counter per digit and 1,024 tokens, and two rows per 32 tokens is enough; the
+    sums do not depend on it."""
+    import paper_2108_01624_amd as pkg
+
+    N, up = B * T, lambda x: -(-x // 256) * 256
+    need = 4 * up(4 * N) + 1024 * -(-N // 1024) + up(4 * -(-N // 32) * d) + 4 * -(-N // 32) * d
+    ids, G = to_dev(syn.zipf_ids(B, T, V, 1.1, 860)), to_dev(gen((B, T, d), 0.1, 861, "bf16"))
+    sq = f32_dev(syn.synthetic_sqnorms(B, 1.0, 862))
+    ref, got = torch.zeros(V, d, dtype=torch.float32, device=DEV), torch.zeros(V, d, dtype=torch.float32, device=DEV)
+    dp.clip_accumulate_embedding(ids, G, V, 1.0, sq, ref)
+    dp.sync()
+    with pkg.Context(workspace_bytes=need) as least:
+        least.clip_accumulate_embedding(ids, G, V, 1.0, sq, got)
+        least.sync()
+    np.testing.assert_array_equal(host(got), host(ref))
+    assert host(ref).any()
+
+
 def test_tiny_workspace_every_entry_point_works_or_reports(dp):
     """4 KiB of workspace: every call either needs none of it and gives the default context's result, or returns
     DP_ERR_WORKSPACE without touching its outputs."""
