@@ -957,8 +957,12 @@ static DmaPlan choose_dma_plan(int n, int B, int T, int d_in, int d_out, size_t 
         if (flat && d_out > 65535 * 256) continue;    // (scale_rows_kernel has a grid row per 256 columns)
         size_t per_ws = MAX_BATCH;
         if (flat) {
-            // layers whose scaled output gradients fit half the workspace (their bias partials are a sixteenth of that)
-            per_ws = ws_bytes / 2 < 1024 ? 0 : (ws_bytes / 2 - 1024) / ((size_t)K * d_out * 2 + 256);
+            // layers whose scaled output gradients fit half the workspace, with room for their bias partials besides (one row for up
+            // to 32 token rows and no more than 256: a sixteenth of the gradients, but more than they take for a single row)
+            if (ws_bytes / 2 < 1024) continue;
+            const size_t scaled = (size_t)K * d_out * 2 + 256, bias = (size_t)((K + BK - 1) / BK < 256 ? (K + BK - 1) / BK : 256) * d_out * 4;
+            per_ws = (ws_bytes / 2 - 1024) / scaled;
+            if (per_ws > (ws_bytes - 1024) / (scaled + bias)) per_ws = (ws_bytes - 1024) / (scaled + bias);
             if (per_ws < 1) continue;
         }
         const long spe = flat ? 1 : (T + BK - 1) / BK;

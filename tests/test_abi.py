@@ -132,6 +132,23 @@ def test_fp32_sum_plan_fits_its_rows_into_32_bits(lib, rows, d_in):
             assert -(-a // plan["tile_m"]) <= 65535, (a, b, plan)
 
 
+@pytest.mark.parametrize("B,T,d_in,d_out", [(1, 1, 752, 113056), (1, 1, 3496, 3544), (40, 20, 1024, 1024), (33, 1, 256, 4096)])
+@pytest.mark.parametrize("n", [1, 5])
+def test_scaled_form_is_planned_only_where_its_buffers_fit(lib, n, B, T, d_in, d_out):
+    """bf16(c * g) of every layer of a launch, and a bias partial for every run of rows (at most one per 32 rows, at most 256)."""
+    import paper_2108_01624_amd as pkg
+
+    K, up, planned = B * T, lambda x: -(-x // 256) * 256, 0
+    for pct in range(50, 1300, 5):
+        ws = 2048 + 2 * K * d_out * pct // 100
+        plan = pkg.dp_dense_sum_plan(pkg.DP_BF16, n, B, T, d_in, d_out, ws)
+        if plan["scaled"]:
+            planned += 1
+            runs = min(256, -(-K // 32), max(1, 2048 // (-(-d_out // 256) * plan["layers"])))
+            assert plan["layers"] * (up(2 * K * d_out) + 4 * runs * d_out) <= ws, (ws, plan)
+    assert planned
+
+
 def test_dense_sum_plan_refuses_what_the_call_refuses(lib):
     import paper_2108_01624_amd as pkg
 
