@@ -159,7 +159,8 @@ dp_status dp_clip_accumulate_dense(dp_ctx* ctx, const void* A, const void* G, dp
  * sqnorms) in as few launches as possible: the layers' tiles fill the chip together, so the token rows need not
  * be split and no partial sums pass through memory.  A, G, sum_W, sum_b are HOST arrays of n_layers device
  * pointers (sum_b may be NULL, and so may any of its entries); they are read during the call only.
- * The result of each layer is what dp_clip_accumulate_dense gives, up to fp32 summation order. */
+ * The result of each layer is what dp_clip_accumulate_dense gives, up to fp32 summation order.  Distinct sum buffers are
+ * what lets layers share a launch; entries whose buffers overlap (one weight used twice) add to them launch after launch. */
 dp_status dp_clip_accumulate_dense_batched(dp_ctx* ctx, int n_layers, const void* const* A, const void* const* G,
                                            dp_dtype dtype, int B, int T, int d_in, int d_out, float C,
                                            const float* sqnorms, float* const* sum_W, float* const* sum_b);
@@ -170,7 +171,7 @@ dp_status dp_clip_accumulate_layernorm(dp_ctx* ctx, const void* Xhat, const void
 
 /* n_layers LayerNorms of one shape in one call: the result of n_layers calls of dp_clip_accumulate_layernorm, with
  * one evaluation of the clip factors and up to 32 layers per launch.  Xhat, G, sum_gamma, sum_beta: HOST arrays of
- * n_layers device pointers (none NULL), read during the call only. */
+ * n_layers device pointers (none NULL), read during the call only; entries whose sum buffers overlap do not share a launch. */
 dp_status dp_clip_accumulate_layernorm_batched(dp_ctx* ctx, int n_layers, const void* const* Xhat, const void* const* G,
                                                dp_dtype dtype, int B, int T, int d, float C, const float* sqnorms,
                                                float* const* sum_gamma, float* const* sum_beta);

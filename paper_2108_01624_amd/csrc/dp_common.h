@@ -93,6 +93,33 @@ struct dp_ws_alloc {
     }
 };
 
+// How many of the first n layers may share a launch that adds to a[l][0 .. na) and, if b and b[l], b[l][0 .. nb): those whose
+// buffers do not overlap an earlier layer's (at least one).  Layers that share a sum buffer then add to it launch after launch.
+static inline int dp_disjoint_layers(int n, float* const* a, size_t na, float* const* b, size_t nb) {
+    uintptr_t lo = UINTPTR_MAX, hi = 0;  // hull of the buffers so far: in a flat buffer's order every layer lies outside it
+    auto range = [&](int l, int which, uintptr_t& from, uintptr_t& to) {
+        float* const* t = which ? b : a;
+        from = t && t[l] ? (uintptr_t)t[l] : 0;
+        to = from ? from + (which ? nb : na) * sizeof(float) : 0;
+        return from != to;
+    };
+    for (int l = 0; l < n; ++l) {
+        uintptr_t f, t, f2, t2;
+        for (int w = 0; w < 2; ++w) {
+            if (!range(l, w, f, t) || t <= lo || f >= hi) continue;
+            for (int k = 0; k < l; ++k)
+                for (int v = 0; v < 2; ++v)
+                    if (range(k, v, f2, t2) && f < t2 && f2 < t) return l;
+        }
+        for (int w = 0; w < 2; ++w)
+            if (range(l, w, f, t)) {
+                lo = f < lo ? f : lo;
+                hi = t > hi ? t : hi;
+            }
+    }
+    return n;
+}
+
 // ------------------------------------------------------------------------------------------------
 // device helpers
 // ------------------------------------------------------------------------------------------------

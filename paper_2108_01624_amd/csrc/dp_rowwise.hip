@@ -977,8 +977,9 @@ dp_status dpk_colstat_sqnorms(dp_ctx* ctx, const void* X, const void* G, dp_dtyp
 dp_status dpk_kept_sums_batched(dp_ctx* ctx, int n, float* const* keep, int B, int d, const float* c, float* const* sum_x,
                                 float* const* sum_1) {
     if (B == 0 || d == 0 || n == 0) return DP_OK;
-    for (int l0 = 0; l0 < n; l0 += COL_MAX_BATCH) {
-        const int L = n - l0 < COL_MAX_BATCH ? n - l0 : COL_MAX_BATCH;
+    int L;
+    for (int l0 = 0; l0 < n; l0 += L) {
+        L = dp_disjoint_layers(n - l0 < COL_MAX_BATCH ? n - l0 : COL_MAX_BATCH, sum_x + l0, d, sum_1 + l0, d);
         ColKeep ck;
         ColOut co;
         for (int l = 0; l < COL_MAX_BATCH; ++l) {
@@ -1061,11 +1062,12 @@ dp_status dpk_colstat_sums_batched(dp_ctx* ctx, int n, const void* const* X, con
     int rows_per;
     size_t per = ctx->ws_bytes / (colstat_runs((long)B * T, d, dt == DP_BF16 || v4 ? 4 : 1, &rows_per) * 2 * (size_t)d * sizeof(float));
     per = per < 1 ? 1 : per > COL_MAX_BATCH ? COL_MAX_BATCH : per;
-    for (int l0 = 0; l0 < n; l0 += (int)per) {
-        const int L = n - l0 < (int)per ? n - l0 : (int)per;
+    int L;
+    for (int l0 = 0; l0 < n; l0 += L) {
         const void* const* Xl = out_x ? X + l0 : nullptr;
         float* const* ox = out_x ? out_x + l0 : nullptr;
         float* const* o1 = out_1 ? out_1 + l0 : nullptr;
+        L = dp_disjoint_layers(n - l0 < (int)per ? n - l0 : (int)per, ox, d, o1, d);
         dp_status st;
         if (dt == DP_BF16) st = colstat_sums_launch<true, 4>(ctx, L, Xl, G + l0, B, T, d, c, ox, o1);
         else if (v4) st = colstat_sums_launch<false, 4>(ctx, L, Xl, G + l0, B, T, d, c, ox, o1);

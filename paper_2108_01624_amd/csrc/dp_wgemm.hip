@@ -1021,8 +1021,10 @@ dp_status dpk_weighted_gemm_batched(dp_ctx* ctx, int n, const void* const* A, co
     const long K = (long)B * T;
     const long spe = plan.flat ? 1 : (T + BK - 1) / BK;  // row splits begin on examples: the kernel rescales across example boundaries only
     const long ksteps = plan.flat ? (K + BK - 1) / BK : (long)B * spe;
-    for (int l0 = 0; l0 < n; l0 += plan.per_launch) {
-        const int nl = n - l0 < plan.per_launch ? n - l0 : plan.per_launch;
+    int nl;
+    for (int l0 = 0; l0 < n; l0 += nl) {
+        nl = dp_disjoint_layers(n - l0 < plan.per_launch ? n - l0 : plan.per_launch, sum_W + l0, (size_t)d_in * d_out, sum_b ? sum_b + l0 : nullptr,
+                                d_out);
         WgemmBatchArgs b;
         WgemmArgs& a = b.base;
         a.out = nullptr;

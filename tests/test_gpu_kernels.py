@@ -1016,6 +1016,42 @@ def test_clip_accumulate_dense_any_row_count(dp, n, B, T, d_in, d_out):
         assert_sums_close(host(Sb[l]).astype(np.float64) + 0.5, b_ref, 1e-4, f"layer {l} sum_b")
 
 
+@pytest.mark.parametrize("dtype,B,T,d_in,d_out", [("bf16", 5, 50, 72, 136), ("bf16", 3, 64, 256, 264), ("bf16", 600, 20, 512, 512), ("f32", 5, 20, 36, 40)])
+def test_layers_that_share_a_sum_buffer(dp, dtype, B, T, d_in, d_out):
+    """Entries of a batched call that name the same sum buffer, or a part of it, add to it one after the other, whatever launches the
+    others share; dense layers, LayerNorms and kept LayerNorm gradients.  Five layers' sums in one buffer against the oracle."""
+    sq = syn.synthetic_sqnorms(B, 1.0, 470)
+    c, sq_d = orc.clip_factors(sq.astype(np.float64), 1.0), f32_dev(sq)
+    n, owner = 8, [0, 1, 0, 0, 2, 1, 0, 0]                        # the layers of owner 0 all add to buffer 0
+    As, Gs = [gen((B, T, d_in), 1.0, 471 + l, dtype) for l in range(n)], [gen((B, T, d_out), 0.1, 481 + l, dtype) for l in range(n)]
+    ref = [orc.clip_accumulate_dense(a, g, c, True) for a, g in zip(As, Gs)]
+    zeros = lambda *s: torch.zeros(*s, dtype=torch.float32, device=DEV)
+    W, b = [zeros(d_in, d_out) for _ in range(3)], [zeros(d_out) for _ in range(3)]
+    dp.clip_accumulate_dense_batched([to_dev(a) for a in As], [to_dev(g) for g in Gs], 1.0, sq_d, [W[o] for o in owner], [b[o] for o in owner])
+    dp.sync()
+    for o in range(3):
+        mine = [ref[l] for l in range(n) if owner[l] == o]
+        assert_sums_close(host(W[o]), sum(w for w, _ in mine), tol_of(dtype), f"sum_W {o}")
+        assert_sums_close(host(b[o]), sum(x for _, x in mine), 1e-4, f"sum_b {o}")
+    X = [to_dev(gen((B, T, d_out), 1.0, 491 + l, dtype)) for l in range(n)]
+    G = [to_dev(g) for g in Gs]
+    ref = [orc.clip_accumulate_layernorm(host(x.float()), host(g.float()), c) for x, g in zip(X, G)]
+    keep, sqn = [zeros(B, 2, d_out) for _ in range(n)], zeros(B)
+    dp.sqnorms_layernorm_keep(X, G, sqn, keep)
+    for kept in (False, True):
+        sg, sb = [zeros(d_out) for _ in range(3)], [zeros(d_out) for _ in range(3)]
+        tables = [sg[o] for o in owner], [sb[o] for o in owner]
+        if kept:
+            dp.clip_accumulate_layernorm_kept(keep, B, d_out, 1.0, sq_d, *tables)
+        else:
+            dp.clip_accumulate_layernorm_batched(X, G, 1.0, sq_d, *tables)
+        dp.sync()
+        for o in range(3):
+            mine = [ref[l] for l in range(n) if owner[l] == o]
+            for got, k in ((sg[o], 0), (sb[o], 1)):
+                assert_sums_close(host(got), sum(r[k] for r in mine), 1e-4, f"LayerNorm {kept} {o} {k}")
+
+
 @pytest.mark.parametrize("B,T,d_in,d_out", [(1, 1, 1, 1), (3, 33, 33, 31), (5, 64, 130, 4), (2, 97, 260, 520), (40, 3, 65, 129),
                                             (1100, 2, 36, 40),      # more examples than a workgroup forms factors for
                                             (9, 700, 64, 32),       # rows split over workgroups
