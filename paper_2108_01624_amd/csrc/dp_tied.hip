@@ -21,7 +21,6 @@ namespace {
 // 64-wide chunk of d, so that the two lanes of a row use a whole 128-byte line.  MFMA j of a chunk contracts the
 // 16 columns {chunk + half*32 + j*8 + 0..7}: the assignment of columns to the instruction's k slots is the
 // same for both operands, which is all a dot product needs.
-template <bool EARLY>
 __global__ __launch_bounds__(256) void tied_cross_bf16_kernel(const int32_t* __restrict__ ids,
                                                               const uint16_t* __restrict__ dY,
                                                               const uint16_t* __restrict__ H,
@@ -40,14 +39,13 @@ __global__ __launch_bounds__(256) void tied_cross_bf16_kernel(const int32_t* __r
         const bool va = row_t < T, vb = row_m < M;
         const uint16_t* pa = dY + ((size_t)i * T + (va ? row_t : 0)) * d;
         const uint16_t* pb = H + ((size_t)i * M + (vb ? row_m : 0)) * d;
-        // EARLY: the entries of dL first, their two round trips (id, entry) pass under the contraction.  The whole norm call: B = 256,
-        // T = 128, M = 20, d = 1,024, V = 30,528 102 -> 94 us, B = 128, T = 512, M = 80, d = 768 656 -> 553, B = 1,000, T = 33, M = 5,
-        // d = 256 44 -> 37.  Otherwise behind it.  (Several waves to a tile's columns gather each entry again: 177 us with one at
-        // B = 512, two 185, four 194.)
+        // The entries of dL first: their two round trips (id, entry) pass under the contraction.  The whole norm call, with the
+        // gathers behind it and in front: B = 256, T = 128, M = 20, d = 1,024, V = 30,528 102 -> 94 us, B = 128, T = 512, M = 80,
+        // d = 768 656 -> 553, B = 1,000, T = 33, M = 5, d = 256 44 -> 37 (B = 512, d = 1,024: 182 -> 184; B = 1,000, T = 64, M = 10, d = 512: 161 -> 162).
+        // (Several waves to a tile's columns gather each entry again: 177 us with one at B = 512, two 185, four 194.)
         uint16_t l[16];
         uint32_t there = 0;
-        auto gather = [&] {
-            if (!vb) return;
+        if (vb) {
             const uint16_t* prow = dL + ((size_t)i * M + row_m) * V;
             int32_t id[16];
 #pragma unroll
@@ -63,8 +61,7 @@ __global__ __launch_bounds__(256) void tied_cross_bf16_kernel(const int32_t* __r
                 there |= ok && t < T ? 1u << r : 0u;
                 l[r] = prow[ok ? id[r] : 0];
             }
-        };
-        if (EARLY) gather();
+        }
         f32x16_t acc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = 0.f;
@@ -81,7 +78,6 @@ __global__ __launch_bounds__(256) void tied_cross_bf16_kernel(const int32_t* __r
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fa[j]),
                                                               __builtin_bit_cast(bf16x8_t, fb[j]), acc, 0, 0, 0);
         }
-        if (!EARLY) gather();
         // acc[r] of this lane = P[t, m] with t = tb*32 + 8*(r/4) + 4*half + r%4 and m = mb*32 + lane%32
 #pragma unroll
         for (int r = 0; r < 16; ++r) tot += there >> r & 1 ? acc[r] * dp_bf16_bits_to_f32(l[r]) : 0.f;  // (t >= T, m >= M: left out)
@@ -128,11 +124,8 @@ dp_status dpk_tied_cross_sqnorms(dp_ctx* ctx, const int32_t* ids, const void* dY
                                  dp_dtype dt, int B, int T, int M, int d, int V, float* sqnorms) {
     if (B == 0 || T == 0 || M == 0 || d == 0) return DP_OK;
     if (dt == DP_BF16)
-        // with several workgroups to a CU and a long contraction in each, the gathers of one pass under the multiplies of another
-        // and the burst in front only gets in their way: B = 512, d = 1,024 180 us early, 177 late; B = 400 equal
-        hipLaunchKernelGGL((B > 448 && d >= 512 ? tied_cross_bf16_kernel<false> : tied_cross_bf16_kernel<true>), dim3(B), dim3(256), 0,
-                           ctx->stream, ids, (const uint16_t*)dY, (const uint16_t*)H, (const uint16_t*)dL, T, M, d, V, sqnorms,
-                           ctx->err_word);
+        hipLaunchKernelGGL(tied_cross_bf16_kernel, dim3(B), dim3(256), 0, ctx->stream, ids, (const uint16_t*)dY, (const uint16_t*)H,
+                           (const uint16_t*)dL, T, M, d, V, sqnorms, ctx->err_word);
     else
         hipLaunchKernelGGL(tied_cross_f32_kernel, dim3(B), dim3(256), 0, ctx->stream, ids, (const float*)dY,
                            (const float*)H, (const float*)dL, T, M, d, V, sqnorms, ctx->err_word);

@@ -920,10 +920,9 @@ def _tied_case(dtype, B, T, M, d, V, seed):
 @pytest.mark.parametrize("dtype,B,T,M,d,V", [("bf16", 6, 128, 20, 128, 1024), ("bf16", 3, 40, 5, 72, 200), ("bf16", 2, 160, 80, 64, 512),
                                              ("bf16", 4, 33, 33, 8, 64), ("f32", 5, 19, 7, 20, 50), ("f32", 2, 70, 3, 130, 33),
                                              ("bf16", 3, 16, 0, 64, 64), ("bf16", 16, 24, 20, 256, 520),
-                                             # enough rows that the projection's GEMM splits them: partial sums next to
-                                             # the pre-scaled H that the caller holds in the same workspace
+                                             # more rows: 1,280 of them, in the projection's GEMM
                                              ("bf16", 64, 24, 20, 256, 520),
-                                             # many long examples: the entries of dL are gathered behind the contraction
+                                             # more examples than the chip holds workgroups
                                              ("bf16", 450, 5, 3, 512, 24)])
 def test_tied_embedding_norms_and_sums(dp, dtype, B, T, M, d, V):
     ids, dY, H, dL = _tied_case(dtype, B, T, M, d, V, 800)
