@@ -276,12 +276,12 @@ ACC_SHAPES = [
     ("f32", 32, 16, 64, 64),
     ("f32", 3, 5, 7, 6),
     ("f32", 4, 40, 70, 130),
-    ("bf16", 8, 128, 256, 384),    # 256 x 256 tiles, ragged second tile column, split over rows
-    ("bf16", 6, 96, 72, 136),      # 128 x 128 tiles, ragged
-    ("bf16", 64, 128, 256, 256),   # 8192 rows: several XCD-interleaved splits
-    ("bf16", 3, 50, 512, 264),     # rows not a multiple of the staged tile height
+    ("bf16", 8, 128, 256, 384),    # 128 x 128 tiles (as all of these), four row splits
+    ("bf16", 6, 96, 72, 136),      # ragged widths
+    ("bf16", 64, 128, 256, 256),   # 8192 rows: 32 row splits
+    ("bf16", 3, 50, 512, 264),     # rows not a multiple of the stage height
     ("bf16", 2, 7, 8, 8),
-    ("bf16", 5, 128, 256, 256),    # 5 examples over 3 row splits (2 + 2 + 1 whole examples)
+    ("bf16", 5, 128, 256, 256),    # few rows: one split, which adds the bias sums itself
     ("bf16", 7, 64, 256, 512),     # two stages per example: every stage starts or ends one
     ("bf16", 3, 192, 320, 256),    # six stages per example, ragged tile row
 ]
@@ -361,8 +361,7 @@ def test_dense_pipeline_clip_invariant_and_determinism(dp):
     assert_sums_close(S_b, Sb_ref, TOL_BF16, "sum_b")
 
 
-@pytest.mark.parametrize("T", [128, 48])  # 128: operands straight into LDS, accumulators rescaled at example boundaries;
-                                          # 48: register-staged kernel, clip factor applied to the staged rows
+@pytest.mark.parametrize("T", [128, 48])  # whole stages, and a ragged last one: accumulators rescaled at example boundaries
 def test_dense_one_example_with_a_huge_norm(dp, T):
     """Finite inputs, one example whose gradient norm is 5e18 (its squared norm, 2.5e37, is near the top of the fp32 range)
     between neighbours with norms around 1: its clip factor is 2e-19, the ratios of neighbouring factors 5e18 and 2e-19, and
@@ -920,7 +919,7 @@ def _tied_case(dtype, B, T, M, d, V, seed):
 @pytest.mark.parametrize("dtype,B,T,M,d,V", [("bf16", 6, 128, 20, 128, 1024), ("bf16", 3, 40, 5, 72, 200), ("bf16", 2, 160, 80, 64, 512),
                                              ("bf16", 4, 33, 33, 8, 64), ("f32", 5, 19, 7, 20, 50), ("f32", 2, 70, 3, 130, 33),
                                              ("bf16", 3, 16, 0, 64, 64), ("bf16", 16, 24, 20, 256, 520),
-                                             # more rows: 1,280 of them, in the projection's GEMM
+                                             # 64 examples: the projection's GEMM in eight row splits
                                              ("bf16", 64, 24, 20, 256, 520),
                                              # more examples than the chip holds workgroups
                                              ("bf16", 450, 5, 3, 512, 24)])
@@ -967,10 +966,10 @@ def test_tied_embedding_out_of_range_id_is_reported(dp):
 # ------------------------------------------------------------------------------------------------
 @pytest.mark.parametrize("n,B,T,d_in,d_out", [(3, 8, 128, 256, 384), (18, 2, 32, 256, 256), (5, 16, 128, 512, 256),
                                               (2, 3, 50, 512, 264), (3, 4, 64, 72, 136),
-                                              # 9 and 36 tiles per layer: workgroup counts that are no multiple of 8
-                                              # (the balanced XCD mapping, with and without the rectangle walk)
+                                              # 36 and 144 tiles per layer and units that are no multiple of 8
+                                              # (the balanced XCD mapping, with the rectangle walk)
                                               (5, 12, 128, 768, 768), (3, 4, 128, 768, 3072),
-                                              # widths that end inside a 256-column tile, odd layer counts, T = one and three stages of 64 rows
+                                              # widths that end inside a tile, odd layer counts, T = two and six stages
                                               (7, 6, 64, 264, 520), (2, 20, 192, 1000, 256)])
 def test_clip_accumulate_dense_batched(dp, n, B, T, d_in, d_out):
     C = 1.0
@@ -993,11 +992,11 @@ def test_clip_accumulate_dense_batched(dp, n, B, T, d_in, d_out):
 @pytest.mark.parametrize("n,B,T,d_in,d_out", [
     (1, 1, 1, 8, 8), (2, 300, 1, 64, 72),                    # examples of one row; more than 64 of them (factors are refilled)
     (3, 9, 31, 136, 136), (1, 80, 32, 128, 128),             # one stage per example, ragged and full
-    (2, 70, 33, 264, 136), (1, 130, 65, 136, 320),           # a stage of one row at the end of every example; mixed tiles
-    (1, 33, 100, 640, 1032), (2, 5, 127, 256, 256),          # ragged last stages on the large tile
+    (2, 70, 33, 264, 136), (1, 130, 65, 136, 320),           # a stage of one row at the end of every example
+    (1, 33, 100, 640, 1032), (2, 5, 127, 256, 256),          # ragged last stages of four rows and of 31
     (1, 600, 20, 1024, 1024), (1, 333, 7, 1032, 520)])       # many short examples on wide layers: scaled operands, no factors
 def test_clip_accumulate_dense_any_row_count(dp, n, B, T, d_in, d_out):
-    """Every form of the bf16 sum: rows per example around the 32-row stage, tiles of 128 and 256.  c * g may be rounded to bf16
+    """Rows per example around the 32-row stage, on the 128 x 128 tile (and one scaled case on 256 x 128).  c * g may be rounded to bf16
     once (at most 2^-8 per term, on average well below 2^-9); the bias sums always add the fp32 products."""
     C = 1.0
     sq = syn.synthetic_sqnorms(B, C, 400)
@@ -1013,6 +1012,52 @@ def test_clip_accumulate_dense_any_row_count(dp, n, B, T, d_in, d_out):
         rel = np.linalg.norm(host(SW[l]).astype(np.float64) - 0.25 - W_ref) / np.linalg.norm(W_ref)
         assert rel < 2.0 ** -9, (l, rel)
         assert_sums_close(host(Sb[l]).astype(np.float64) + 0.5, b_ref, 1e-4, f"layer {l} sum_b")
+
+
+FACTORS, SCALED = 0, 1
+SUM_FORMS = [  # (tile, form, split over rows) and a call that takes it
+    ((128, 128), FACTORS, False, (1, 4, 96, 72, 72)), ((128, 128), FACTORS, False, (1, 3, 92, 72, 72)), ((128, 128), FACTORS, False, (1, 3, 1, 72, 72)),
+    ((128, 128), FACTORS, True, (1, 3, 256, 72, 72)), ((128, 128), FACTORS, True, (1, 14, 44, 72, 72)), ((128, 128), FACTORS, True, (1, 40, 10, 80, 72)),
+    ((128, 128), SCALED, False, (1, 12, 1, 72, 72)), ((128, 128), SCALED, True, (1, 539, 2, 136, 152)),
+    ((128, 256), FACTORS, False, (16, 13, 96, 1080, 136)), ((128, 256), FACTORS, False, (5, 18, 33, 296, 2456)),
+    ((128, 256), FACTORS, True, (8, 41, 256, 264, 136)), ((128, 256), FACTORS, True, (5, 296, 34, 296, 144)),
+    ((128, 256), SCALED, False, (16, 353, 3, 1072, 144)), ((128, 256), SCALED, True, (5, 120, 32, 1552, 136)),
+    ((256, 128), FACTORS, False, (8, 7, 160, 136, 2136)), ((256, 128), FACTORS, False, (8, 18, 39, 136, 2952)),
+    ((256, 128), FACTORS, True, (8, 70, 224, 136, 160)), ((256, 128), FACTORS, True, (16, 279, 33, 192, 72)),
+    ((256, 128), SCALED, False, (5, 270, 4, 3584, 136)), ((256, 128), SCALED, True, (16, 461, 19, 152, 176)),
+    ((256, 256), FACTORS, False, (16, 4, 64, 136, 2056)), ((256, 256), FACTORS, False, (16, 5, 41, 144, 2304)),
+    ((256, 256), FACTORS, True, (5, 36, 64, 136, 3336)), ((256, 256), FACTORS, True, (8, 57, 41, 152, 1400)), ((256, 256), FACTORS, True, (4, 96, 100, 768, 3072)),
+    ((256, 256), SCALED, False, (16, 4, 1, 144, 2256)), ((256, 256), SCALED, True, (3, 311, 11, 3640, 136))]
+
+
+@pytest.mark.parametrize("tile,form,split,shape", SUM_FORMS)
+def test_clip_accumulate_dense_every_form(dp, tile, form, split, shape):
+    """Every instance of the bf16 sum, on a call that the plan gives to it.  The reference in fp64 on the device.  With factors the
+    products are exact: fp32 sums and up to 300 roundings of a rescaled accumulator, 1e-5 in the 2-norm.  Scaled operands are rounded
+    to bf16 once: 2^-9.  The bias sums add fp32 products either way."""
+    import paper_2108_01624_amd as pkg
+
+    n, B, T, d_in, d_out = shape
+    plan = pkg.dp_dense_sum_plan(pkg.DP_BF16, n, B, T, d_in, d_out)
+    assert ((plan["tile_m"], plan["tile_n"]), plan["scaled"], plan["splits"] > 1) == (tile, form, split), plan
+    g = torch.Generator(device=DEV)
+    g.manual_seed(530)
+    rand = lambda *s: torch.randn(s, generator=g, device=DEV).to(torch.bfloat16)
+    As, Gs = [rand(B, T, d_in) for _ in range(n)], [rand(B, T, d_out) for _ in range(n)]
+    sq = f32_dev(syn.synthetic_sqnorms(B, 1.0, 531))
+    W, b = [torch.full((d_in, d_out), 0.25, device=DEV) for _ in range(n)], [torch.full((d_out,), -0.5, device=DEV) if l != 1 else None for l in range(n)]
+    dp.clip_accumulate_dense_batched(As, Gs, 1.0, sq, W, b)
+    dp.sync()
+    c = torch.where(sq > 1, 1 / sq.double().sqrt(), torch.ones_like(sq, dtype=torch.float64))
+    for l in range(n):
+        cg = (Gs[l].double() * c[:, None, None]).reshape(B * T, d_out)
+        ref = As[l].reshape(B * T, d_in).double().t().contiguous() @ cg
+        rel, worst = (2.0 ** -9, 3e-2) if form == SCALED else (1e-5, 1e-4)
+        checks = [(W[l].double() - 0.25, ref, rel, worst)] + ([(b[l].double() + 0.5, cg.sum(0), 1e-5, 1e-4)] if b[l] is not None else [])
+        for got, want, r, m in checks:
+            err = (got - want).abs()
+            assert float(err.norm() / want.norm()) < r, (l, float(err.norm() / want.norm()))
+            assert float((err / (want.abs() + want.square().mean().sqrt())).max()) < m, l
 
 
 @pytest.mark.parametrize("dtype,B,T,d_in,d_out", [("bf16", 5, 50, 72, 136), ("bf16", 3, 64, 256, 264), ("bf16", 600, 20, 512, 512), ("f32", 5, 20, 36, 40)])
