@@ -1173,6 +1173,26 @@ def test_sqnorms_dense_forms(dp, n, B, T, d_in, d_out, has_bias):
         assert_norms_close(host(sq), ref, 1e-4, f"path {path}")
 
 
+@pytest.mark.parametrize("d_in,d_out", [(256, 256), (256, 120), (104, 256), (128, 72), (250 // 8 * 8, 504)])
+@pytest.mark.parametrize("T", [20, 64, 77])
+def test_materialised_norms_on_every_tile(dp, T, d_in, d_out):
+    """A workspace with room for one partial norm an example and large tile takes the largest tile the widths reach (256 from 256
+    columns on), for one layer after the other.  fp32 sums of exact products: 1e-4 as the other norm tests."""
+    import paper_2108_01624_amd as pkg
+
+    n, B, large = 3, 70, lambda w: 256 if w >= 256 else 128
+    tiles = -(-d_in // large(d_in)) * -(-d_out // large(d_out))
+    As, Gs = [gen((B, T, d_in), 1.0, 660 + l, "bf16") for l in range(n)], [gen((B, T, d_out), 0.1, 670 + l, "bf16") for l in range(n)]
+    ref = sum(orc.sqnorms_dense(a, g, True) for a, g in zip(As, Gs)) + 3.0
+    A_d, G_d = [to_dev(a) for a in As], [to_dev(g) for g in Gs]
+    with pkg.Context(workspace_bytes=4 * B * tiles) as small:
+        for ctx in (dp, small):
+            sq = torch.full((B,), 3.0, dtype=torch.float32, device=DEV)
+            ctx.sqnorms_dense_batched(A_d, G_d, True, pkg.DP_PATH_MATERIALISE, sq)
+            ctx.sync()
+            assert_norms_close(host(sq), ref, 1e-4)
+
+
 def test_batched_equals_single_layer_calls(dp):
     """The direct-to-LDS path keeps exact bf16 products: one layer alone and inside a batch agree closely."""
     n, B, T, d_in, d_out, C = 4, 32, 128, 256, 256, 1.0
