@@ -215,6 +215,17 @@ __device__ __forceinline__ gram_i32x4 gram_rsrc(const void* base, uint32_t bytes
     return r;
 }
 
+// Waits until at most the newest min(m, K) stages of LPS loads are in flight (they land in the order they were issued).  Nothing is
+// issued past the last stage, so towards the end fewer than K are: stages of zeros that kept one count for all iterations cost a
+// layer of two chunks as much as its work (12 layers of 64 x 64, B = 500, T = 33: 78 -> 70 us; 8 x 100 x 72 x 136: 11.4 -> 10.9).
+template <int LPS, int K>
+__device__ __forceinline__ void gram_wait(int m) {
+    if constexpr (K > 0) {
+        if (m < K) return gram_wait<LPS, K - 1>(m);
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(K * LPS) : "memory");
+}
+
 // An offset outside every example's byte range (below 2^31): such a lane's 16 bytes of LDS receive zeros.
 constexpr int GRAM_OUTSIDE = (int)0x80000000u;
 
@@ -256,15 +267,17 @@ __global__ __launch_bounds__(64 * WAVES, WGS_PER_CU * WAVES / 4) void gram_dma_k
     constexpr int RPI = 64 / CPR;          // rows filled by one wave-wide load
     constexpr int LPS = ROWS / RPI / WAVES;  // loads per wave per stage
     constexpr int NQ = ROWS == 128 ? 4 : 1, KS = WAVES / NQ;  // quadrants, waves that share a quadrant's k steps
+    constexpr bool EXACT = WAVES < 8;  // nothing issued past the last stage (eight waves: many stages, where the test costs 2 % and gives nothing)
     static_assert(LPS >= 1 && GDK / 16 >= KS, "more waves than there is work");
-    static_assert(NS * STAGE * 2 >= NQ * 32 * 1024 || KS == 1, "the ring doubles as the exchange buffer");
+    constexpr int XCH = 2 * (NQ == 1 ? 3 : 4) * 16 * 64;  // floats that a wave hands over
+    static_assert(NS * STAGE * 2 >= NQ * (KS / 2) * XCH * 4, "the ring doubles as the exchange buffer");
     __shared__ __attribute__((aligned(16))) uint16_t ring[NS][STAGE];
     __shared__ float wred[WAVES];
     const int layer = blockIdx.x / gb.B, i = blockIdx.x - layer * gb.B;
     const uint16_t* __restrict__ A = gb.A[layer];
     const uint16_t* __restrict__ G = gb.G[layer];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int quad = KS == 1 ? wave : NQ == 1 ? 0 : wave % NQ, kg = KS == 1 ? 0 : wave / NQ, wr = quad >> 1, wc = quad & 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int quad = NQ == 1 ? 0 : KS == 1 ? wave : wave % NQ, kg = KS == 1 ? 0 : wave / NQ, wr = quad >> 1, wc = quad & 1;
     const bool active = wr <= wc;  // the lower-left quadrant mirrors the upper-right one
     const bool diagw = wr == wc;   // ... and inside a diagonal quadrant the lower-left 32 x 32 tile the upper-right one
     const int nchA = (d_in + GDK - 1) / GDK, nchG1 = (d_out + GDK - 1) / GDK, nch = nchA + gb.n_out * nchG1;
@@ -290,6 +303,7 @@ __global__ __launch_bounds__(64 * WAVES, WGS_PER_CU * WAVES / 4) void gram_dma_k
     int ibuf = 0;  // buffer of the next stage to issue
     const int rotA = i % nchA, rotG = i % nchG1;
     auto issue = [&](int st) {
+        if (EXACT && st >= nch) return;
         const bool isA = st < nchA;
         const int cgi = st - nchA;                                             // chunk index over all output gradients
         const int which = cgi >= 2 * nchG1 ? 2 : (cgi >= nchG1 ? 1 : 0);       // which of the (up to three) tensors
@@ -313,7 +327,7 @@ __global__ __launch_bounds__(64 * WAVES, WGS_PER_CU * WAVES / 4) void gram_dma_k
             }
         };
         if (isA) run(rA, voffA, soff);
-        else if (st >= nch) run(rG, voffG, 0x7FFFFFF0);  // past the end: reads zeros, keeps the load count uniform
+        else if (!EXACT && st >= nch) run(rG, voffG, 0x7FFFFFF0);  // past the end: reads zeros, keeps the load count uniform
         else if (which == 0) run(rG, voffG, soff);
         else if (which == 1) run(rG2, voffG, soff);
         else run(rG3, voffG, soff);
@@ -375,7 +389,8 @@ __global__ __launch_bounds__(64 * WAVES, WGS_PER_CU * WAVES / 4) void gram_dma_k
         for (; s < end; ++s) {
             // my loads of chunk s have landed (later chunks may be in flight); after the barrier everyone's have,
             // and everyone is done reading chunk s-1, whose buffer the newest chunk overwrites
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * LPS) : "memory");
+            if constexpr (EXACT) gram_wait<LPS, NS - 2>(nch - 1 - s);
+            else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * LPS) : "memory");
             __syncthreads();
             if (!active) issue(s + NS - 1);
             else if (diagw) compute(acc, std::true_type{});
@@ -386,34 +401,34 @@ __global__ __launch_bounds__(64 * WAVES, WGS_PER_CU * WAVES / 4) void gram_dma_k
     phase(nchA, accA);
     phase(nch, accG);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be writing LDS when the workgroup ends, or when it is reused
-    if constexpr (KS > 1) {
-        float* part = reinterpret_cast<float*>(&ring[0][0]) + quad * (128 * 64);  // [A | G][2][2][register][lane]
-        for (int g = 1; g < KS; ++g) {  // the groups' sums are added in group order
-            __syncthreads();
-            if (kg == g) {
+    // The k groups' sums meet pairwise: groups KS/2 .. hand theirs to groups 0 .., then the same with half as many.  (A wave whose
+    // quadrant is the whole plane leaves out the tile below the diagonal, which holds zeros.)
+    auto each = [&](auto f) {
+        int e = 0;
 #pragma unroll
-                for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-                    for (int b = 0; b < 2; ++b)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            part[((a * 2 + b) * 16 + r) * 64 + lane] = accA[a][b][r];
-                            part[((4 + a * 2 + b) * 16 + r) * 64 + lane] = accG[a][b][r];
-                        }
+            for (int b = 0; b < 2; ++b) {
+                if (NQ == 1 && a == 1 && b == 0) continue;
+                f(accA[a][b], e++);
+                f(accG[a][b], e++);
             }
-            __syncthreads();
-            if (kg == 0) {
+    };
 #pragma unroll
-                for (int a = 0; a < 2; ++a)
+    for (int half = KS / 2; half > 0; half /= 2) {
+        float* part = reinterpret_cast<float*>(&ring[0][0]) + (quad * half + kg % half) * XCH + lane;
+        __syncthreads();
+        if (kg >= half && kg < 2 * half)
+            each([&](f32x16_t& x, int e) {
 #pragma unroll
-                    for (int b = 0; b < 2; ++b)
+                for (int r = 0; r < 16; ++r) part[(e * 16 + r) * 64] = x[r];
+            });
+        __syncthreads();
+        if (kg < half)
+            each([&](f32x16_t& x, int e) {
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            accA[a][b][r] += part[((a * 2 + b) * 16 + r) * 64 + lane];
-                            accG[a][b][r] += part[((4 + a * 2 + b) * 16 + r) * 64 + lane];
-                        }
-            }
-        }
+                for (int r = 0; r < 16; ++r) x[r] += part[(e * 16 + r) * 64];
+            });
     }
     const float bias_term = has_bias ? 1.f : 0.f;
     float sum = 0.f;
@@ -718,6 +733,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void gram_small_dma
     const uint32_t ldsoff = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)&ring[wave][0][0];
     int ibuf = 0;  // buffer of the next stage to issue
     auto issue = [&](int st) {
+        if (st >= nch) return;
         const bool isA = st < nchA;
         const int soff = __builtin_amdgcn_readfirstlane((isA ? st : st - nchA) * GDK * 2);
         const uint32_t dst = __builtin_amdgcn_readfirstlane(ldsoff + ibuf * (STAGE * 2));
@@ -726,13 +742,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void gram_small_dma
 #pragma unroll
             for (int q = 0; q < LOADS; ++q)  // past the row's end: zeros
                 gram_dma16<true>(rA, dst + q * RPI * GDK * 2, RAGGED && cg[q] * 8 >= left ? GRAM_OUTSIDE : voffA[q], soff);
-        } else if (st < nch) {
+        } else {
 #pragma unroll
             for (int q = 0; q < LOADS; ++q)
                 gram_dma16<true>(rG, dst + q * RPI * GDK * 2, RAGGED && cg[q] * 8 >= left ? GRAM_OUTSIDE : voffG[q], soff);
-        } else {  // past the last: zeros, keeps the load count uniform
-#pragma unroll
-            for (int q = 0; q < LOADS; ++q) gram_dma16<true>(rG, dst + q * RPI * GDK * 2, GRAM_OUTSIDE, 0);
         }
         ibuf = ibuf + 1 == NS ? 0 : ibuf + 1;
     };
@@ -750,7 +763,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void gram_small_dma
         for (; s < end; s += WAVES) {
             // stage s has landed (later ones may be in flight), and the fragments of the one before it are in registers: the newest
             // stage may overwrite its buffer
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * LOADS) : "memory");
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            gram_wait<LOADS, NS - 2>((nch - 1 - s) / WAVES);
             issue(s + (NS - 1) * WAVES);
             const uint16_t* buf = ring[wave][cbuf];
             bf16x8_t x[GDK / 16];
@@ -966,6 +980,15 @@ static dp_status gram_dma_launch(dp_ctx* ctx, const GramBatch& gb, int T, int d_
     // 256-byte row segments (stages of 32 KiB) when the widths allow, else 128-byte segments (16 KiB)
     const bool wide = d_in % 128 == 0 && d_out % 128 == 0, ragged = d_in % 64 != 0 || d_out % 64 != 0;
     const bool few = wgs <= 256;  // a workgroup or less per CU: it may have all of the CU
+    const long nch = (d_in + 63) / 64 + (long)gb.n_out * ((d_out + 63) / 64);  // chunks of 64 columns
+    // Up to 64 rows one wave takes 0.8 us a chunk and four that share the k steps 0.2, but these spend 1 us on their exchange and hold
+    // four wave slots and 64 KiB of LDS, 512 workgroups on the chip: one wave for three chunks and less, and up to twelve where
+    // there are more workgroups than that (one | four, us: B = 200, T = 64, 64 x 64 8.1 | 9.2, 72 x 136 10.6 | 10.0; four layers of
+    // 320 x 320 20.5 | 25.7; twelve layers, B = 500, T = 33: 64 x 64 30 | 70, 544 x 152 85 | 108, 200 x 1000 133 | 147).
+    const bool one = T <= 64 && (nch <= 3 || (wgs > 512 && nch <= 12));
+    // Up to 128 rows, a workgroup or less per CU: eight waves and all of the LDS pay from so many chunks on (four | eight: 72 x 136 9.2 |
+    // 10.9, 128 x 256 9.9 | 10.4, 384 x 384 13.6 | 12.9, 448 x 704 17.6 | 18.3, 832 x 3136 46.2 | 41.5).
+    const bool eight = few && nch > (wide ? 8 : 32);
     auto launch = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, ctx->stream, gb, T, d_in, d_out, has_bias, out);
     };
@@ -973,14 +996,16 @@ static dp_status gram_dma_launch(dp_ctx* ctx, const GramBatch& gb, int T, int d_
     else if (T <= 32 && gb.n_out == 1 && ragged) launch(gram_small_dma_kernel<4, 4, true>, 256);
     else if (T <= 32 && gb.n_out == 1 && few) launch(gram_small_dma_kernel<8, 4, false>, 512);
     else if (T <= 32 && gb.n_out == 1) launch(gram_small_dma_kernel<4, 4, false>, 256);
+    else if (one && ragged) launch(gram_dma_kernel<64, 64, 4, 1, 4, true>, 64);
+    else if (one) launch(gram_dma_kernel<64, 64, 4, 1, 4, false>, 64);
     else if (T <= 64 && wide) launch(gram_dma_kernel<64, 128, 4, 4, 2, false>, 256);
     else if (T <= 64 && ragged) launch(gram_dma_kernel<64, 64, 8, 4, 2, true>, 256);
     else if (T <= 64) launch(gram_dma_kernel<64, 64, 8, 4, 2, false>, 256);
-    else if (wide && few) launch(gram_dma_kernel<128, 128, 4, 8, 1, false>, 512);
+    else if (wide && eight) launch(gram_dma_kernel<128, 128, 4, 8, 1, false>, 512);
     else if (wide) launch(gram_dma_kernel<128, 128, 2, 4, 2, false>, 256);
-    else if (ragged && few) launch(gram_dma_kernel<128, 64, 9, 8, 1, true>, 512);
+    else if (ragged && eight) launch(gram_dma_kernel<128, 64, 9, 8, 1, true>, 512);
     else if (ragged) launch(gram_dma_kernel<128, 64, 4, 4, 2, true>, 256);
-    else if (few) launch(gram_dma_kernel<128, 64, 9, 8, 1, false>, 512);
+    else if (eight) launch(gram_dma_kernel<128, 64, 9, 8, 1, false>, 512);
     else launch(gram_dma_kernel<128, 64, 4, 4, 2, false>, 256);
     DP_LAUNCH_CHECK(ctx, "gram_dma");
     return DP_OK;

@@ -1173,6 +1173,30 @@ def test_sqnorms_dense_forms(dp, n, B, T, d_in, d_out, has_bias):
         assert_norms_close(host(sq), ref, 1e-4, f"path {path}")
 
 
+@pytest.mark.parametrize("n,B,T,d_in,d_out", [
+    (1, 3, 40, 64, 64), (1, 3, 40, 8, 8), (2, 300, 64, 64, 192), (2, 300, 50, 72, 264), (2, 300, 33, 384, 384),  # up to 64 rows: one wave
+    (1, 5, 64, 128, 120), (1, 5, 64, 192, 64), (2, 300, 40, 448, 384),      # ... four
+    (1, 3, 100, 128, 256), (1, 2, 128, 640, 512),                           # up to 128 rows, a workgroup a CU: 256-byte segments, four and eight waves
+    (1, 3, 65, 136, 72), (1, 2, 100, 1032, 1096), (1, 2, 70, 1088, 1088)])  # ... 128-byte segments, four and eight
+def test_sqnorms_dense_few_and_many_chunks(dp, n, B, T, d_in, d_out):
+    """Gram norms at the edges of the choice of waves: fewer chunks than ring stages, and as many chunks and workgroups as each of
+    the forms takes; the layers alone, and in pairs that share their input.  1e-4 as in the other norm tests."""
+    import paper_2108_01624_amd as pkg
+
+    As = [gen((B, T, d_in), 1.0, 680 + l, "bf16") for l in range(n)]
+    Gs = [gen((B, T, d_out), 0.1, 690 + l, "bf16") for l in range(2 * n)]
+    A_d, G_d = [to_dev(a) for a in As], [to_dev(g) for g in Gs]
+    one = [orc.sqnorms_dense(As[l // 2], Gs[l], True) for l in range(2 * n)]
+    sq = torch.full((B,), 3.0, dtype=torch.float32, device=DEV)
+    dp.sqnorms_dense_batched(A_d, G_d[::2], True, pkg.DP_PATH_GRAM, sq)
+    dp.sync()
+    assert_norms_close(host(sq), sum(one[::2]) + 3.0, 1e-4, "alone")
+    sq = torch.full((B,), 3.0, dtype=torch.float32, device=DEV)
+    dp.sqnorms_dense_shared(A_d, [G_d[2 * l:2 * l + 2] for l in range(n)], True, sq)
+    dp.sync()
+    assert_norms_close(host(sq), sum(one) + 3.0, 1e-4, "shared")
+
+
 @pytest.mark.parametrize("d_in,d_out", [(256, 256), (256, 120), (104, 256), (128, 72), (250 // 8 * 8, 504)])
 @pytest.mark.parametrize("T", [20, 64, 77])
 def test_materialised_norms_on_every_tile(dp, T, d_in, d_out):
