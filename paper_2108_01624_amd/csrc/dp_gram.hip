@@ -1078,6 +1078,54 @@ static dp_status gram_units_launch(dp_ctx* ctx, const GramBatch& gb, int T, int 
     return dpk_finish_partials(ctx, part, gb.B, gu.n_units * gb.n_layers, sqnorms);
 }
 
+// One layer on the register-staged kernel: a workgroup per 128 x 128 block of the upper triangle.
+static dp_status gram_block_sqnorms(dp_ctx* ctx, const void* A, const void* G, int B, int T, int d_in, int d_out, int has_bias, float* sqnorms) {
+    const int nblk = (T + GB - 1) / GB;
+    const long npairs = (long)nblk * (nblk + 1) / 2;
+    const size_t lds = (size_t)2 * (nblk > 1 ? 2 : 1) * GB * GLD * sizeof(uint16_t);
+    static bool lds_attr_set = false;  // off-diagonal blocks stage two panels per step: 72 KiB of dynamic LDS
+    if (!lds_attr_set) {
+        DP_HIP_CHECK(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(gram_bf16_kernel),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize,
+                                              2 * 2 * GB * GLD * (int)sizeof(uint16_t)));
+        lds_attr_set = true;
+    }
+    const double bytes = 2.0 * (double)B * T * ((double)d_in + d_out);
+    if (npairs == 1) {
+        dp_prof_scope prof(ctx, DP_PROF_GRAM, bytes);
+        hipLaunchKernelGGL(gram_bf16_kernel, dim3(B), dim3(256), lds, ctx->stream, (const uint16_t*)A,
+                           (const uint16_t*)G, B, T, d_in, d_out, has_bias, nblk, 1, sqnorms, 1);
+        DP_LAUNCH_CHECK(ctx, "gram_bf16");
+        return DP_OK;
+    }
+    const long groups = (B + 7) / 8;
+    const long nwg = groups * 8 * npairs;
+    if (nwg > 0x7FFFFFFFl) {
+        DP_SET_ERR(ctx, "dp_sqnorms_dense: B * T^2 too large for one launch");
+        return DP_ERR_SHAPE;
+    }
+    dp_ws_alloc ws(ctx);
+    float* part = ws.get<float>((size_t)B * npairs);
+    if (!part) {
+        DP_SET_ERR(ctx, "workspace too small for %d x %ld Gram partials", B, npairs);
+        return DP_ERR_WORKSPACE;
+    }
+    {
+        dp_prof_scope prof(ctx, DP_PROF_GRAM, bytes);
+        hipLaunchKernelGGL(gram_bf16_kernel, dim3((unsigned)nwg), dim3(256), lds, ctx->stream, (const uint16_t*)A,
+                           (const uint16_t*)G, B, T, d_in, d_out, has_bias, nblk, (int)npairs, part, 0);
+    }
+    DP_LAUNCH_CHECK(ctx, "gram_bf16");
+    return dpk_finish_partials(ctx, part, B, (int)npairs, sqnorms);
+}
+
+// Whether that is the better one for a single layer of more than 128 rows: widths that end inside a chunk, and so few units that the
+// chip is three quarters idle (B = 24, T = 195, 544 x 152: 18.0 | 19.2 us; B = 4, T = 300, 72 x 136: 12.0 | 13.5).
+static bool gram_block_better(const dp_ctx* ctx, int B, int T, int d_in, int d_out) {
+    const long nblk = (T + GB - 1) / GB, npairs = nblk * (nblk + 1) / 2;
+    return (d_in % GU_K || d_out % GU_K) && (long)B * gram_make_units((int)nblk).n_units <= 96 && (size_t)B * npairs * sizeof(float) <= ctx->ws_bytes;
+}
+
 // Layers of one launch: as many as it may hold and as have room for their partial norms; a single one adds to sqnorms itself.
 static int gram_layers_per_launch(const dp_ctx* ctx, int n, int B) {
     int nl = n < GRAM_MAX_BATCH ? n : GRAM_MAX_BATCH;
@@ -1087,6 +1135,8 @@ static int gram_layers_per_launch(const dp_ctx* ctx, int n, int B) {
 
 dp_status dpk_gram_sqnorms_batched(dp_ctx* ctx, int n_layers, const void* const* A, const void* const* G, dp_dtype dt,
                                    int B, int T, int d_in, int d_out, int has_bias, float* sqnorms) {
+    if (dt == DP_BF16 && n_layers == 1 && gram_units_ok(T, d_in, d_out) && gram_block_better(ctx, B, T, d_in, d_out))
+        return gram_block_sqnorms(ctx, A[0], G[0], B, T, d_in, d_out, has_bias, sqnorms);
     if (dt == DP_BF16 && gram_units_ok(T, d_in, d_out)) {
         // enough layers per launch for a few rounds of workgroups, and partials that fit the workspace
         const int nblk = (T + GB - 1) / GB;
@@ -1143,6 +1193,20 @@ dp_status dpk_gram_sqnorms_batched(dp_ctx* ctx, int n_layers, const void* const*
 // group-major: G[g * n_out + j].
 dp_status dpk_gram_sqnorms_shared(dp_ctx* ctx, int n_groups, const void* const* A, int n_out, const void* const* G,
                                   dp_dtype dt, int B, int T, int d_in, int d_out, int has_bias, float* sqnorms) {
+    if (dt == DP_BF16 && gram_units_ok(T, d_in, d_out)) {  // (the units form every layer's input again, many layers a launch)
+        const void *a[GRAM_MAX_BATCH], *go[GRAM_MAX_BATCH];
+        int n = 0;
+        for (int g = 0; g < n_groups; ++g)
+            for (int j = 0; j < n_out; ++j) {
+                a[n] = A[g];
+                go[n++] = G[(size_t)g * n_out + j];
+                if (n < GRAM_MAX_BATCH && !(g + 1 == n_groups && j + 1 == n_out)) continue;
+                const dp_status st = dpk_gram_sqnorms_batched(ctx, n, a, go, dt, B, T, d_in, d_out, has_bias, sqnorms);
+                if (st != DP_OK) return st;
+                n = 0;
+            }
+        return DP_OK;
+    }
     if (dt != DP_BF16 || n_out < 2 || n_out > 3 || !gram_dma_ok(T, d_in, d_out)) {
         for (int g = 0; g < n_groups; ++g)
             for (int j = 0; j < n_out; ++j) {
@@ -1207,43 +1271,7 @@ dp_status dpk_gram_sqnorms(dp_ctx* ctx, const void* A, const void* G, dp_dtype d
     }
     if (gram_dma_ok(T, d_in, d_out) || gram_units_ok(T, d_in, d_out))
         return dpk_gram_sqnorms_batched(ctx, 1, &A, &G, dt, B, T, d_in, d_out, has_bias, sqnorms);
-    const int nblk = (T + GB - 1) / GB;
-    const long npairs = (long)nblk * (nblk + 1) / 2;
-    const size_t lds = (size_t)2 * (nblk > 1 ? 2 : 1) * GB * GLD * sizeof(uint16_t);
-    static bool lds_attr_set = false;  // off-diagonal blocks stage two panels per step: 72 KiB of dynamic LDS
-    if (!lds_attr_set) {
-        DP_HIP_CHECK(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(gram_bf16_kernel),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                                              2 * 2 * GB * GLD * (int)sizeof(uint16_t)));
-        lds_attr_set = true;
-    }
-    const double bytes = 2.0 * (double)B * T * ((double)d_in + d_out);
-    if (npairs == 1) {
-        dp_prof_scope prof(ctx, DP_PROF_GRAM, bytes);
-        hipLaunchKernelGGL(gram_bf16_kernel, dim3(B), dim3(256), lds, ctx->stream, (const uint16_t*)A,
-                           (const uint16_t*)G, B, T, d_in, d_out, has_bias, nblk, 1, sqnorms, 1);
-        DP_LAUNCH_CHECK(ctx, "gram_bf16");
-        return DP_OK;
-    }
-    const long groups = (B + 7) / 8;
-    const long nwg = groups * 8 * npairs;
-    if (nwg > 0x7FFFFFFFl) {
-        DP_SET_ERR(ctx, "dp_sqnorms_dense: B * T^2 too large for one launch");
-        return DP_ERR_SHAPE;
-    }
-    dp_ws_alloc ws(ctx);
-    float* part = ws.get<float>((size_t)B * npairs);
-    if (!part) {
-        DP_SET_ERR(ctx, "workspace too small for %d x %ld Gram partials", B, npairs);
-        return DP_ERR_WORKSPACE;
-    }
-    {
-        dp_prof_scope prof(ctx, DP_PROF_GRAM, bytes);
-        hipLaunchKernelGGL(gram_bf16_kernel, dim3((unsigned)nwg), dim3(256), lds, ctx->stream, (const uint16_t*)A,
-                           (const uint16_t*)G, B, T, d_in, d_out, has_bias, nblk, (int)npairs, part, 0);
-    }
-    DP_LAUNCH_CHECK(ctx, "gram_bf16");
-    return dpk_finish_partials(ctx, part, B, (int)npairs, sqnorms);
+    return gram_block_sqnorms(ctx, A, G, B, T, d_in, d_out, has_bias, sqnorms);
 }
 
 dp_status dpk_materialise_f32(dp_ctx* ctx, const float* A, const float* G, int B, int T, int d_in, int d_out,

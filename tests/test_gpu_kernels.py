@@ -1197,6 +1197,27 @@ def test_sqnorms_dense_few_and_many_chunks(dp, n, B, T, d_in, d_out):
     assert_norms_close(host(sq), sum(one) + 3.0, 1e-4, "shared")
 
 
+@pytest.mark.parametrize("B,T,d_in,d_out", [(2, 130, 72, 64), (3, 300, 136, 200), (100, 130, 72, 64), (2, 200, 128, 192)])
+def test_sqnorms_dense_of_long_examples_alone_and_in_groups(dp, B, T, d_in, d_out):
+    """More than 128 rows: a single layer (blocks or units of the plane, by their number) and 25 groups of three that share an input,
+    more layers than a launch holds.  1e-4 as in the other norm tests."""
+    import paper_2108_01624_amd as pkg
+
+    ng, no = 25, 3
+    As = [gen((B, T, d_in), 1.0, 700 + l, "bf16") for l in range(2)]
+    Gs = [gen((B, T, d_out), 0.1, 710 + l, "bf16") for l in range(no)]
+    A_d, G_d = [to_dev(a) for a in As], [to_dev(g) for g in Gs]
+    one = [[orc.sqnorms_dense(a, g, True) for g in Gs] for a in As]
+    sq = torch.full((B,), 3.0, dtype=torch.float32, device=DEV)
+    dp.sqnorms_dense(A_d[0], G_d[1], True, pkg.DP_PATH_GRAM, sq)
+    dp.sync()
+    assert_norms_close(host(sq), one[0][1] + 3.0, 1e-4, "alone")
+    sq = torch.full((B,), 3.0, dtype=torch.float32, device=DEV)
+    dp.sqnorms_dense_shared([A_d[g % 2] for g in range(ng)], [G_d for _ in range(ng)], True, sq)
+    dp.sync()
+    assert_norms_close(host(sq), sum(sum(one[g % 2]) for g in range(ng)) + 3.0, 1e-4, "groups")
+
+
 @pytest.mark.parametrize("d_in,d_out", [(256, 256), (256, 120), (104, 256), (128, 72), (250 // 8 * 8, 504)])
 @pytest.mark.parametrize("T", [20, 64, 77])
 def test_materialised_norms_on_every_tile(dp, T, d_in, d_out):
