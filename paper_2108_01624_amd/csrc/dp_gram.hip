@@ -812,14 +812,13 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void gram_small_dma
 // ------------------------------------------------------------------------------------------------
 // fp32 inputs, on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: products and sums in fp32).  The T x T plane of an
 // example is cut into 32 x 32 cells of which the upper triangle is formed; a workgroup takes the cells cell0, cell0 + gridDim.y,
-// ... of an example, its 8 waves split the contraction in blocks of 32 columns (128 bytes of a row: lane = (row, half), a half
+// ... of an example, its W waves (8, or as many as there are blocks) split the contraction in blocks of 32 columns (128 bytes of a row: lane = (row, half), a half
 // is 64 contiguous bytes; the MFMA's k slots take the same columns of both operands, which is all a dot product needs) and the
 // waves' accumulators meet in LDS.  Operands come straight from global memory, the next block in flight while one multiplies:
 // every panel is read once per cell it is in, out of L2 (8 flop per byte, 20 TB/s at the full matrix rate).
-// B = 16, T = 128, 768 x 768: 6,170 -> 16 us (one thread per pair of rows, scalar loads, before).
+// B = 16, T = 128, 768 x 768: 6,170 -> 16 us (one thread per pair of rows, scalar loads, before).  Waves without a
+// block only add to the exchange: T = 17, B = 600, 64 x 64 12.7 us with 8 waves, 7.1 with 2; 30 x 30 16.1 | 6.4 with 1.
 // ------------------------------------------------------------------------------------------------
-constexpr int GF_WAVES = 8;
-
 template <bool VEC>
 __device__ __forceinline__ void gram_f32_load(const float* __restrict__ row, bool valid, int d, int kb, float f[16]) {
 #pragma unroll
@@ -836,10 +835,10 @@ __device__ __forceinline__ void gram_f32_load(const float* __restrict__ row, boo
 }
 
 // This wave's share of the cell of X X^T with rows r (va: inside the example) and columns c.
-template <bool VEC>
+template <bool VEC, int W>
 __device__ __forceinline__ void gram_f32_cell(const float* __restrict__ r, bool va, const float* __restrict__ c, bool vb, bool diag, int d,
                                               int wave, int half, f32x16_t& acc) {
-    constexpr int STEP = GF_WAVES * 32;
+    constexpr int STEP = W * 32;
     float a0[16], b0[16], a1[16], b1[16];
     auto load = [&](int kb, float (&a)[16], float (&b)[16]) {
         gram_f32_load<VEC>(r, va, d, kb + 16 * half, a);
@@ -863,11 +862,12 @@ __device__ __forceinline__ void gram_f32_cell(const float* __restrict__ r, bool 
 }
 
 // out: gridDim.y == 1: sqnorms, "+="; otherwise partials [B][gridDim.y], stored.
-template <bool VEC>
-__global__ __launch_bounds__(64 * GF_WAVES) void gram_f32_kernel(const float* __restrict__ A, const float* __restrict__ G, int T, int d_in, int d_out,
-                                                       int has_bias, int nblk, float* __restrict__ out) {
-    __shared__ float part[GF_WAVES / 2][2][16][64];
-    __shared__ float wred[GF_WAVES];
+template <bool VEC, int W>
+__global__ __launch_bounds__(64 * W) void gram_f32_kernel(const float* __restrict__ A, const float* __restrict__ G, int T, int d_in, int d_out,
+                                                          int has_bias, int nblk, float* __restrict__ out) {
+    constexpr int H = W / 2;
+    __shared__ float part[H ? H : 1][2][16][64];
+    __shared__ float wred[W];
     const int i = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r32 = lane & 31, half = lane >> 5;
     const int ncells = nblk * (nblk + 1) / 2;
     const float bias_term = has_bias ? 1.f : 0.f;
@@ -885,37 +885,46 @@ __global__ __launch_bounds__(64 * GF_WAVES) void gram_f32_kernel(const float* __
         f32x16_t accA, accG;
 #pragma unroll
         for (int r = 0; r < 16; ++r) accA[r] = accG[r] = 0.f;
-        gram_f32_cell<VEC>(A + rt * d_in, va, A + ru * d_in, vb, diag, d_in, wave, half, accA);
-        gram_f32_cell<VEC>(G + rt * d_out, va, G + ru * d_out, vb, diag, d_out, wave, half, accG);
-        __syncthreads();  // the previous cell's readers are done
-        // waves w + 4 hand their tiles to waves w, then the four sums meet
-        if (wave >= GF_WAVES / 2) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                part[wave - GF_WAVES / 2][0][r][lane] = accA[r];
-                part[wave - GF_WAVES / 2][1][r][lane] = accG[r];
-            }
-        }
-        __syncthreads();
-        if (wave < GF_WAVES / 2) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                part[wave][0][r][lane] += accA[r];
-                part[wave][1][r][lane] += accG[r];
-            }
-        }
-        __syncthreads();
+        gram_f32_cell<VEC, W>(A + rt * d_in, va, A + ru * d_in, vb, diag, d_in, wave, half, accA);
+        gram_f32_cell<VEC, W>(G + rt * d_out, va, G + ru * d_out, vb, diag, d_out, wave, half, accG);
         float p = 0.f;
+        if constexpr (W == 1) {
 #pragma unroll
-        for (int q = 0; q < 16 / GF_WAVES; ++q) {  // wave w finishes accumulator registers 2w and 2w + 1, the parts added in a fixed order
-            const int r = 16 / GF_WAVES * wave + q;
-            const float a = (part[0][0][r][lane] + part[1][0][r][lane]) + (part[2][0][r][lane] + part[3][0][r][lane]);
-            const float g = (part[0][1][r][lane] + part[1][1][r][lane]) + (part[2][1][r][lane] + part[3][1][r][lane]);
-            p += (a + bias_term) * g;
+            for (int r = 0; r < 16; ++r) p += (accA[r] + bias_term) * accG[r];
+        } else {
+            __syncthreads();  // the previous cell's readers are done
+            // waves w + W / 2 hand their tiles to waves w, then the sums of these meet
+            if (wave >= H) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    part[wave - H][0][r][lane] = accA[r];
+                    part[wave - H][1][r][lane] = accG[r];
+                }
+            }
+            __syncthreads();
+            if (wave < H) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    part[wave][0][r][lane] += accA[r];
+                    part[wave][1][r][lane] += accG[r];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 16 / W; ++q) {  // wave w finishes its share of the accumulator registers, the parts added in a fixed order
+                const int r = 16 / W * wave + q;
+                float a = 0.f, g = 0.f;
+#pragma unroll
+                for (int h = 0; h < H; h += 2) {
+                    a += part[h][0][r][lane] + (h + 1 < H ? part[h + 1 < H ? h + 1 : h][0][r][lane] : 0.f);
+                    g += part[h][1][r][lane] + (h + 1 < H ? part[h + 1 < H ? h + 1 : h][1][r][lane] : 0.f);
+                }
+                p += (a + bias_term) * g;
+            }
         }
         s += diag ? p : 2.f * p;  // rows past T are zeros in G G^T
     }
-    const float tot = dp_block_sum<64 * GF_WAVES>(s, wred);
+    const float tot = dp_block_sum<64 * W>(s, wred);
     if (threadIdx.x == 0) {
         if (gridDim.y == 1) out[i] += tot;
         else out[(size_t)i * gridDim.y + blockIdx.y] = tot;
@@ -940,7 +949,7 @@ __global__ __launch_bounds__(256) void materialise_f32_kernel(const float* __res
         f32x16_t acc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-        for (int t0 = 0; t0 < T; t0 += 16) {
+        for (int t0 = 0; t0 < T && p0 < d_in && q0 < d_out; t0 += 16) {  // (a wave whose tile lies outside has nothing to do)
             float a[8], g[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
@@ -1240,9 +1249,12 @@ dp_status dpk_gram_sqnorms_shared(dp_ctx* ctx, int n_groups, const void* const* 
 }
 
 // Workgroups per example of the fp32 norm kernels: one per piece (cell or block) up to about 4,096 in all, as far as their
-// partial norms fit the workspace; one workgroup per example walks all its pieces and needs none of it.
-static float* f32_partials(dp_ctx* ctx, int B, long pieces, float* sqnorms, int* per) {
+// partial norms fit the workspace; one workgroup per example walks all its pieces and needs none of it.  So it does where
+// the examples, many of them above all, have a few short pieces each (`steps`: blocks of the contraction of all of them), which take less than the launch that
+// adds the partial norms.
+static float* f32_partials(dp_ctx* ctx, int B, long pieces, long steps, float* sqnorms, int* per) {
     long g = pieces < 4096 ? pieces : 4096;
+    if (steps <= (B >= 128 ? 8 : 3)) g = 1;
     if (g > 1 && (long)B * g > 4096) g = 4096 / B < 1 ? 1 : 4096 / B;
     float* part = nullptr;
     if (g > 1) {
@@ -1258,14 +1270,24 @@ dp_status dpk_gram_sqnorms(dp_ctx* ctx, const void* A, const void* G, dp_dtype d
     if (dt == DP_F32) {
         const int nblk = (T + 31) / 32;
         int per;
-        float* part = f32_partials(ctx, B, (long)nblk * (nblk + 1) / 2, sqnorms, &per);
+        const int blocks = ((d_in > d_out ? d_in : d_out) + 31) / 32;  // of the contraction: no more waves than these
+        const long cells = (long)nblk * (nblk + 1) / 2;
+        float* part = f32_partials(ctx, B, cells, cells * ((blocks + 7) / 8) * 2, sqnorms, &per);
         const bool vec = d_in % 4 == 0 && d_out % 4 == 0 && (((uintptr_t)A | (uintptr_t)G) & 15) == 0;
-        if (vec)
-            hipLaunchKernelGGL((gram_f32_kernel<true>), dim3(B, per), dim3(64 * GF_WAVES), 0, ctx->stream, (const float*)A, (const float*)G, T, d_in,
-                               d_out, has_bias, nblk, part);
-        else
-            hipLaunchKernelGGL((gram_f32_kernel<false>), dim3(B, per), dim3(64 * GF_WAVES), 0, ctx->stream, (const float*)A, (const float*)G, T, d_in,
-                               d_out, has_bias, nblk, part);
+        auto launch = [&](auto kernel, int waves) {
+            hipLaunchKernelGGL(kernel, dim3(B, per), dim3(64 * waves), 0, ctx->stream, (const float*)A, (const float*)G, T, d_in, d_out, has_bias,
+                               nblk, part);
+        };
+        const long share = 2048 / ((long)B * per), most = blocks < share ? blocks : share;  // ... nor than the chip runs at once
+        auto pick = [&](auto vec_tag) {
+            constexpr bool VEC = decltype(vec_tag)::value;
+            if (most <= 1) launch(gram_f32_kernel<VEC, 1>, 1);
+            else if (most <= 2) launch(gram_f32_kernel<VEC, 2>, 2);
+            else if (most <= 4) launch(gram_f32_kernel<VEC, 4>, 4);
+            else launch(gram_f32_kernel<VEC, 8>, 8);
+        };
+        if (vec) pick(std::true_type{});
+        else pick(std::false_type{});
         DP_LAUNCH_CHECK(ctx, "gram_f32");
         return per > 1 ? dpk_finish_partials(ctx, part, B, per, sqnorms) : DP_OK;
     }
@@ -1278,7 +1300,7 @@ dp_status dpk_materialise_f32(dp_ctx* ctx, const float* A, const float* G, int B
                               float* sqnorms) {
     const int tiles_m = (d_in + 63) / 64, tiles_n = (d_out + 63) / 64;
     int per;
-    float* part = f32_partials(ctx, B, (long)tiles_m * tiles_n, sqnorms, &per);
+    float* part = f32_partials(ctx, B, (long)tiles_m * tiles_n, (long)tiles_m * tiles_n * ((T + 15) / 16), sqnorms, &per);
     hipLaunchKernelGGL(materialise_f32_kernel, dim3(B, per), dim3(256), 0, ctx->stream, A, G, T, d_in, d_out, tiles_m, tiles_n, part);
     DP_LAUNCH_CHECK(ctx, "materialise_f32");
     return per > 1 ? dpk_finish_partials(ctx, part, B, per, sqnorms) : DP_OK;

@@ -1099,6 +1099,7 @@ def test_layers_that_share_a_sum_buffer(dp, dtype, B, T, d_in, d_out):
 @pytest.mark.parametrize("B,T,d_in,d_out", [(1, 1, 1, 1), (3, 33, 33, 31), (5, 64, 130, 4), (2, 97, 260, 520), (40, 3, 65, 129),
                                             (1100, 2, 36, 40),      # more examples than a workgroup forms factors for
                                             (9, 700, 64, 32),       # rows split over workgroups
+                                            (7, 17, 20, 30), (7, 70, 100, 31), (300, 70, 33, 20),   # norms on one wave, on four, cells in a row
                                             (2, 40, 1030, 600), (1100, 1, 705, 700),   # tiles of 96 x 32
                                             (3, 40, 1000, 470), (1100, 1, 600, 500),   # of 64 x 32
                                             (3, 33, 990, 890), (1100, 2, 990, 890)])   # of 64 x 64
