@@ -361,20 +361,22 @@ __global__ __launch_bounds__(256) void reduce_partials_pair_kernel(const float4*
 }
 
 // ------------------------------------------------------------------------------------------------
-// embedding, per-example norms (pass 1): one workgroup of W waves (8 or 16) per example and ncb blocks of 64*VW columns; the
-// W / ncb waves of a column block share the example's positions.
+// embedding, per-example norms (pass 1): one workgroup per example and ncb blocks of 64*VW columns; `parts` waves (as many as there
+// are pieces of EMB_AHEAD positions, up to 8 or 16 waves in all) share the example's positions in a column block.
 // The workgroup ranks the T ids (stable counting rank in LDS: every key, the id above the position, against all others), then
 // every wave walks its run of sorted positions, EMB_AHEAD rows in flight, adding up rows of equal id; a run's end is a select,
 // not a branch.  Runs that are complete inside a wave are squared there; the sums of a wave's first and last run go to LDS, where
 // they are joined across the waves, column by column.
 // One wave walking all positions of its columns was a chain of T / 8 round trips: B = 23, T = 375, d = 832: 61 -> 23 us;
-// B = 512, T = 128, d = 1024 (134 MB): 31 + 5 -> 28.
+// B = 512, T = 128, d = 1024 (134 MB): 31 + 5 -> 28.  Waves without positions would only make the joining of the parts longer: T = 16,
+// d = 256, B = 4 12 us with 16 waves, 6 with 1; B = 514 16 | 7.
 // ------------------------------------------------------------------------------------------------
 constexpr int EMB_AHEAD = 16;
 
+// EMB_WAVES: the most waves that a launch may have; it has ncb * parts.
 template <bool BF16, int VW, bool DISTINCT, int EMB_WAVES>
 __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const int32_t* __restrict__ ids,
-                                                                           const void* __restrict__ G, int T, int d, int V, int ncb,
+                                                                           const void* __restrict__ G, int T, int d, int V, int ncb, int parts,
                                                                            float* __restrict__ out, int J, int direct,
                                                                            int* __restrict__ err) {
     extern __shared__ uint32_t lds[];
@@ -384,9 +386,9 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
     uint32_t* sid = lds;        // [T rounded up to 4] ids of this example
     uint16_t* order = reinterpret_cast<uint16_t*>(lds + (T + 3) / 4 * 4);  // [T] row index at each sorted position (T <= 4096)
     const int i = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nt = 64 * ncb * parts;
     bool bad = false;
-    for (int t = threadIdx.x; t < (T + 3) / 4 * 4; t += 64 * EMB_WAVES) {
+    for (int t = threadIdx.x; t < (T + 3) / 4 * 4; t += nt) {
         const int32_t v = t < T ? ids[(size_t)i * T + t] : 0;
         if (t < T && (v < 0 || v >= V)) bad = true;
         sid[t] = t < T ? (uint32_t)v : 0xFFFFFFFFu;  // (the padding ranks behind everything)
@@ -395,7 +397,7 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
     __syncthreads();
     if constexpr (!DISTINCT) {
         const uint4* s4 = reinterpret_cast<const uint4*>(sid);
-        for (int t = threadIdx.x; t < T; t += 64 * EMB_WAVES) {
+        for (int t = threadIdx.x; t < T; t += nt) {
             const uint32_t v = sid[t];
             // keys are unique as (id, position): before position t an equal id ranks lower, after it higher
             int rank = 0;
@@ -415,7 +417,7 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
         }
         __syncthreads();
     }
-    const int parts = EMB_WAVES / ncb, cb = wave % ncb, part = wave / ncb;
+    const int cb = wave % ncb, part = wave / ncb;
     const int col = ((blockIdx.y * ncb + cb) * 64 + lane) * VW;
     const int per = (T + parts - 1) / parts, lo = part * per, hi = lo + per < T ? lo + per : T;  // this wave's positions
     float tot = 0.f, run[VW], hd[VW];
@@ -455,7 +457,10 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
             }
         }
     }
-    if constexpr (!DISTINCT) {
+    if (!DISTINCT && parts == 1) {  // nothing to join: the last run, and the first if another one followed it
+#pragma unroll
+        for (int k = 0; k < VW; ++k) tot += run[k] * run[k] + (one ? 0.f : hd[k] * hd[k]);
+    } else if constexpr (!DISTINCT) {
 #pragma unroll
         for (int k = 0; k < VW; ++k) {
             head[wave][lane * VW + k] = one ? run[k] : hd[k];
@@ -488,8 +493,11 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
             for (int k = 0; k < VW; ++k) tot += carry[k] * carry[k];
         }
     }
-    tot = dp_block_sum<64 * EMB_WAVES>(tot, wred);
+    tot = dp_wave_sum(tot);
+    if (lane == 0) wred[wave] = tot;
+    __syncthreads();
     if (threadIdx.x == 0) {
+        for (int w = 1; w < ncb * parts; ++w) tot += wred[w];  // in wave order
         // (an out-of-range id only changes the grouping; the error itself is reported by dp_sync)
         if (direct) out[i] += tot;
         else out[(size_t)i * J + blockIdx.y] = tot;
@@ -1086,12 +1094,12 @@ template <bool BF16, int VW>
 static dp_status embedding_sqnorms_launch(dp_ctx* ctx, const int32_t* ids, const void* G, int B, int T, int d, int V,
                                           int distinct, float* sqnorms) {
     // Column blocks per workgroup: as many as there are (up to 4), so that the ids are ranked once and the example needs no
-    // reduction launch; one, and all waves on its positions, when the examples alone are too few for the chip.  16 waves of
-    // this kernel are what the registers of a CU hold: past one workgroup per CU, 8 waves each, so that two run side by side
-    // (B = 512: 36 us with 16, 28 with 8; B = 256: 21 with 16).
-    const int blocks = (d + 64 * VW - 1) / (64 * VW);
+    // reduction launch; one, and all waves on its positions, when the examples alone are too few for the chip and long enough
+    // for 16 waves.  16 waves of this kernel are what the registers of a CU hold: they are shared by the workgroups that a CU gets
+    // (B = 512: 36 us with 16 waves, 28 with 8; B = 514, T = 128, d = 256: 21 with 8, 14 with 4; B = 256: 21 with 16).
+    const int blocks = (d + 64 * VW - 1) / (64 * VW), pieces = (T + EMB_AHEAD - 1) / EMB_AHEAD;
     int ncb = blocks >= 3 ? 4 : blocks;
-    if ((long)B * ((blocks + ncb - 1) / ncb) < 128) ncb = 1;
+    if ((long)B * ((blocks + ncb - 1) / ncb) < 128 && ncb * pieces > 16) ncb = 1;
     int J = (blocks + ncb - 1) / ncb;
     float* out = sqnorms;
     int direct = 1;
@@ -1106,14 +1114,15 @@ static dp_status embedding_sqnorms_launch(dp_ctx* ctx, const int32_t* ids, const
     }
     dim3 grid(B, J);
     const size_t lds = ((size_t)T + 3) / 4 * 4 * sizeof(uint32_t) + (size_t)T * sizeof(uint16_t);
-    auto launch = [&](auto kernel, int waves) {
-        hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), lds, ctx->stream, ids, G, T, d, V, ncb, out, J, direct, ctx->err_word);
+    const long per_cu = ((long)B * J + 255) / 256;
+    const int room = 16 / ncb / per_cu < 1 ? 1 : (int)(16 / ncb / per_cu), parts = pieces < room ? pieces : room, waves = ncb * parts;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), lds, ctx->stream, ids, G, T, d, V, ncb, parts, out, J, direct, ctx->err_word);
     };
-    const bool many = (long)B * J > 256;
-    if (distinct && many) launch(embedding_sqnorms_kernel<BF16, VW, true, 8>, 8);
-    else if (distinct) launch(embedding_sqnorms_kernel<BF16, VW, true, 16>, 16);
-    else if (many) launch(embedding_sqnorms_kernel<BF16, VW, false, 8>, 8);
-    else launch(embedding_sqnorms_kernel<BF16, VW, false, 16>, 16);
+    if (distinct && waves <= 8) launch(embedding_sqnorms_kernel<BF16, VW, true, 8>);
+    else if (distinct) launch(embedding_sqnorms_kernel<BF16, VW, true, 16>);
+    else if (waves <= 8) launch(embedding_sqnorms_kernel<BF16, VW, false, 8>);
+    else launch(embedding_sqnorms_kernel<BF16, VW, false, 16>);
     DP_LAUNCH_CHECK(ctx, "embedding_sqnorms");
     if (!direct) return dpk_finish_partials(ctx, out, B, J, sqnorms);
     return DP_OK;

@@ -506,6 +506,7 @@ EMB_SHAPES = [("f32", 6, 20, 4, 13), ("f32", 3, 7, 6, 11), ("bf16", 8, 128, 1024
 EMB_SHAPES += [("bf16", 520, 512, 8, 700), ("bf16", 4, 33, 2056, 7), ("f32", 40, 130, 5, 3), ("f32", 2, 16, 1032, 70000),
                ("bf16", 1, 17, 1024, 9), ("f32", 9, 31, 1028, 20),
                # positions of an example dealt to 1, 4 and 16 waves, runs across several of them, the longest example
+               ("bf16", 4, 16, 256, 5), ("bf16", 4, 64, 1024, 9), ("bf16", 130, 17, 520, 4), ("bf16", 600, 40, 256, 30), ("f32", 1100, 65, 12, 9),  # ... to 1 .. 5
                ("bf16", 2, 4096, 8, 3), ("bf16", 140, 37, 1024, 2), ("bf16", 3, 5, 512, 4), ("f32", 130, 100, 300, 6), ("bf16", 6, 90, 264, 1)]
 
 
