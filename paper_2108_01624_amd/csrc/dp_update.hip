@@ -252,16 +252,20 @@ __global__ __launch_bounds__(256) void zero_f32_kernel(float* __restrict__ p, ui
     }
 }
 
-// sqnorms[i] += partial[i*J + 0] + ... + partial[i*J + J-1]: one wave per example, lane l adds the partials l, l + 64, ... in
-// ascending order, then a fixed tree over the lanes.  (One thread per example walking its row: J dependent, uncoalesced reads.)
+// sqnorms[i] += partial[i*J + 0] + ... + partial[i*J + J-1]: L lanes per example, lane l adds the partials l, l + L, ... in
+// ascending order, then a fixed tree over the lanes.
+template <int L>
 __global__ __launch_bounds__(256) void finish_partials_kernel(const float* __restrict__ partial, int B, int J,
                                                               float* __restrict__ sqnorms) {
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (i >= B) return;
+    const long i = ((long)blockIdx.x * 256 + threadIdx.x) / L;
+    const int lane = threadIdx.x % L;
+    const bool there = i < B;
+    const float base = there && lane == 0 ? sqnorms[i] : 0.f;  // asked for with the partials, not behind them
     float t = 0.f;
-    for (int j = lane; j < J; j += 64) t += partial[(size_t)i * J + j];
-    t = dp_wave_sum(t);
-    if (lane == 0) sqnorms[i] += t;
+    for (int j = lane; there && j < J; j += L) t += partial[(size_t)i * J + j];
+#pragma unroll
+    for (int o = L / 2; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    if (there && lane == 0) sqnorms[i] = base + t;
 }
 
 __global__ __launch_bounds__(256) void clip_factors_kernel(const float* __restrict__ sqnorms, int B, float C,
@@ -443,9 +447,14 @@ dp_status dpk_zero_f32(dp_ctx* ctx, float* p, uint64_t n) {
     return DP_OK;
 }
 
+// One lane per example for up to two partials, sixteen up to 64, a wave beyond.
 dp_status dpk_finish_partials(dp_ctx* ctx, const float* partial, int B, int J, float* sqnorms) {
-    hipLaunchKernelGGL(finish_partials_kernel, dim3((B + 3) / 4), dim3(256), 0, ctx->stream, partial, B, J,
-                       sqnorms);
+    const int lanes = J <= 2 ? 1 : J <= 64 ? 16 : 64;
+    const dim3 grid((unsigned)(((long)B * lanes + 255) / 256));
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, ctx->stream, partial, B, J, sqnorms); };
+    if (lanes == 1) launch(finish_partials_kernel<1>);
+    else if (lanes == 16) launch(finish_partials_kernel<16>);
+    else launch(finish_partials_kernel<64>);
     DP_LAUNCH_CHECK(ctx, "finish_partials");
     return DP_OK;
 }

@@ -447,7 +447,7 @@ def test_layernorm_norms_and_sums(dp, dtype, B, T, d):
 
 
 @pytest.mark.parametrize("dtype,n,B,T,d", [("bf16", 3, 9, 128, 1024), ("bf16", 19, 4, 33, 264), ("f32", 2, 5, 17, 20), ("bf16", 1, 3, 8, 64),
-                                          ("f32", 17, 2, 9, 6)])
+                                          ("f32", 17, 2, 9, 6), ("bf16", 40, 7, 5, 520)])
 def test_layernorm_batched(dp, dtype, n, B, T, d):
     """Several LayerNorms of one shape in one call (more than one launch's worth at n > 16): each layer against the oracle,
     the norms against the sum over layers."""
