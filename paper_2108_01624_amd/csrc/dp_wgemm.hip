@@ -557,35 +557,6 @@ __global__ __launch_bounds__(512) void mfma_ceiling_kernel(int iters, float* __r
     sink[t] = s;
 }
 
-// sum_b[layer][q] += sum over the layer's nb partial rows.  64 columns x 4 groups of rows per workgroup: group g adds the rows
-// g, g + 4, ... in ascending order, eight loads in flight, and the four group sums are added as (0+1)+(2+3): fixed order.
-// (One thread per column walking all rows: 10 us for 32 rows; this way 5.)  grid (n_layers, d_out / 64).
-__global__ __launch_bounds__(256) void bias_finish_kernel(WgemmBatchArgs b, int nb) {
-    __shared__ float red[4][64];
-    const int layer = blockIdx.x;
-    float* dst = b.L[layer].sum_b;
-    if (!dst) return;
-    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int q = blockIdx.y * 64 + lane;
-    const size_t d = b.base.d_out;
-    float t = 0.f;
-    if (q < b.base.d_out) {
-        const float* src = b.base.bias_part + (size_t)layer * nb * d + q;
-        int r = g;
-        for (; r + 28 < nb; r += 32) {
-            float p[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) p[u] = src[(size_t)(r + 4 * u) * d];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) t += p[u];
-        }
-        for (; r < nb; r += 4) t += src[(size_t)r * d];
-    }
-    red[g][lane] = t;
-    __syncthreads();
-    if (g == 0 && q < b.base.d_out) dst[q] += (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
-}
-
 // Operands for the GEMM without factors: Gs = bf16(c_i * G) (products formed in fp32, rounded to nearest even), rows of one example after the other, and the column sums of the fp32 products
 // of a run of rows for the bias (part[layer][run][d], if wanted).  8 columns a thread, 256 columns x 8 rows a workgroup.
 // Bound: HBM, 4 bytes per element.  grid (runs, d / 256, layers).
@@ -860,35 +831,62 @@ __global__ __launch_bounds__(64 * F32_WAVES) void wgemm_f32_kernel(const float* 
 }  // namespace
 
 namespace {
-// The row splits' partial sums of all layers of a launch, added in one launch: blockIdx.y = layer,
-// out_l[j] += sum_{r<R} part_l[r*n4 + j] with r ascending (a fixed order).
-struct ReduceBatch {
+// What is left to add behind a launch of the GEMM, all layers in one launch (blockIdx.y = layer); the first w_blocks workgroups of
+// a layer add the row splits' partial sums, the others the bias partials:
+//   out_l[j] += sum_{r<R} part_l[r*n4 + j]         (float4 columns j < n4)
+//   sum_b_l[q] += sum_{r<nb} bias_part[(l*nb + r)*d_out + q]
+// Many partials of few columns (TALL, and the bias): 64 columns and four groups of partials a workgroup, group g adding
+// r = g, g + 4, ... with eight loads in flight, then (0 + 1) + (2 + 3).  Otherwise a thread per column, r ascending.  Fixed orders.
+// (One thread walking all partials of its column: 10 us for 32 bias rows, this way 5; 64 splits of 64 x 64 12 | 4.  As two launches,
+// one behind the other, a call of a small layer waits for the host: B = 147, T = 192, 72 x 136 22.5 us, 17.2 as one.)
+struct FinishArgs {
     const float4* part[MAX_BATCH];
     float4* out[MAX_BATCH];
+    float* sum_b[MAX_BATCH];
 };
-__global__ __launch_bounds__(256) void reduce_layers_kernel(ReduceBatch rb, int R, size_t n4) {
-    const size_t j = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (j >= n4) return;
-    const float4* __restrict__ part = rb.part[blockIdx.y];
-    float4* __restrict__ out = rb.out[blockIdx.y];
-    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-    int r = 0;
-    for (; r + 4 <= R; r += 4) {  // four independent 16-byte loads in flight; additions stay in order
-        float4 p[4];
+template <typename V>
+__device__ __forceinline__ V add_partials(const V* __restrict__ src, size_t stride, int first, int step, int n) {
+    V t{};
+    int r = first;
+    for (; r + 7 * step < n; r += 8 * step) {
+        V p[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) p[u] = part[(size_t)(r + u) * n4 + j];
+        for (int u = 0; u < 8; ++u) p[u] = src[(size_t)(r + u * step) * stride];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            t.x += p[u].x; t.y += p[u].y; t.z += p[u].z; t.w += p[u].w;
+        for (int u = 0; u < 8; ++u) t += p[u];
+    }
+    for (; r < n; r += step) t += src[(size_t)r * stride];
+    return t;
+}
+template <bool TALL>
+__global__ __launch_bounds__(256) void finish_layers_kernel(FinishArgs f, int R, size_t n4, int w_blocks, const float* __restrict__ bias_part,
+                                                            int nb, int d_out) {
+    __shared__ f32x4_t red[4][64];
+    __shared__ float bred[4][64];
+    const int layer = blockIdx.y, lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    if ((int)blockIdx.x >= w_blocks) {
+        float* dst = f.sum_b[layer];
+        if (!dst) return;
+        const int q = ((int)blockIdx.x - w_blocks) * 64 + lane;
+        bred[g][lane] = q < d_out ? add_partials(bias_part + (size_t)layer * nb * d_out + q, (size_t)d_out, g, 4, nb) : 0.f;
+        __syncthreads();
+        if (g == 0 && q < d_out) dst[q] += (bred[0][lane] + bred[1][lane]) + (bred[2][lane] + bred[3][lane]);
+        return;
+    }
+    const f32x4_t* __restrict__ part = reinterpret_cast<const f32x4_t*>(f.part[layer]);
+    f32x4_t* __restrict__ out = reinterpret_cast<f32x4_t*>(f.out[layer]);
+    if constexpr (TALL) {
+        const size_t j = (size_t)blockIdx.x * 64 + lane;
+        red[g][lane] = j < n4 ? add_partials(part + j, n4, g, 4, R) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        __syncthreads();
+        if (g == 0 && j < n4) out[j] += (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    } else {
+        const size_t j = (size_t)blockIdx.x * 256 + threadIdx.x;
+        if (j < n4) {
+            const f32x4_t old = out[j];  // asked for with the partials
+            out[j] = old + add_partials(part + j, n4, 0, 1, R);
         }
     }
-    for (; r < R; ++r) {
-        const float4 p = part[(size_t)r * n4 + j];
-        t.x += p.x; t.y += p.y; t.z += p.z; t.w += p.w;
-    }
-    float4 o = out[j];
-    o.x += t.x; o.y += t.y; o.z += t.z; o.w += t.w;
-    out[j] = o;
 }
 }  // namespace
 
@@ -902,6 +900,7 @@ struct DmaPlan {
     int bm, bn;
     bool flat;
     int per_launch;
+    long nsplit;  // of a launch of min(n, per_launch) layers
 };
 
 // What a workgroup of a tile costs in microseconds, measured over 16 layers of 1024 x 1024 and 28 of 768 x 768 with 1,024 to
@@ -949,7 +948,7 @@ static long choose_nsplit_dma(int nl, int ntiles, long ksteps, long spe, int d_i
 
 // Tile and form for n layers: the smallest modelled time of the whole call.
 static DmaPlan choose_dma_plan(int n, int B, int T, int d_in, int d_out, size_t ws_bytes) {
-    DmaPlan best{0, 0, false, 1};
+    DmaPlan best{0, 0, false, 1, 1};
     double best_t = 0.0;
     const long K = (long)B * T;
     for (int flat = 0; flat < 2; ++flat) {
@@ -980,17 +979,18 @@ static DmaPlan choose_dma_plan(int n, int B, int T, int d_in, int d_out, size_t 
                 if (per > (long)per_ws) per = (long)per_ws;
                 double t = 0.0, tl;
                 const long full = n / per, rest = n % per;
-                if (full) {
-                    choose_nsplit_dma((int)per, ntiles, ksteps, spe, d_in, d_out, c, &tl);
-                    t += full * (tl + 4.0);
-                }
+                long nsplit = 1;
                 if (rest) {
-                    choose_nsplit_dma((int)rest, ntiles, ksteps, spe, d_in, d_out, c, &tl);
+                    nsplit = choose_nsplit_dma((int)rest, ntiles, ksteps, spe, d_in, d_out, c, &tl);
                     t += tl + 4.0;
+                }
+                if (full) {
+                    nsplit = choose_nsplit_dma((int)per, ntiles, ksteps, spe, d_in, d_out, c, &tl);
+                    t += full * (tl + 4.0);
                 }
                 if (flat) t += (full + (rest ? 1 : 0)) * 4.0 + 4.0 * (double)K * d_out * n / 4.0e6;
                 if (!best.bm || t < best_t) {
-                    best = DmaPlan{bm, bn, flat != 0, (int)per};
+                    best = DmaPlan{bm, bn, flat != 0, (int)per, nsplit};
                     best_t = t;
                 }
             }
@@ -1040,7 +1040,8 @@ dp_status dpk_weighted_gemm_batched(dp_ctx* ctx, int n, const void* const* A, co
         a.tiles_n = (d_out + plan.bn - 1) / plan.bn;
         const int ntiles = a.tiles_m * a.tiles_n;
         double t_model;
-        long nsplit = choose_nsplit_dma(nl, ntiles, ksteps, spe, d_in, d_out, cost, &t_model);
+        long nsplit = nl == (n < plan.per_launch ? n : plan.per_launch) ? plan.nsplit
+                                                                       : choose_nsplit_dma(nl, ntiles, ksteps, spe, d_in, d_out, cost, &t_model);
         bool any_bias = false;
         for (int l = 0; l < nl; ++l)
             if (sum_b && sum_b[l0 + l]) any_bias = true;
@@ -1158,22 +1159,20 @@ dp_status dpk_weighted_gemm_batched(dp_ctx* ctx, int n, const void* const* A, co
         }
         DP_LAUNCH_CHECK(ctx, "wgemm_dma");
         const int nb = !any_bias || a.bias_direct ? 0 : plan.flat ? (int)runs : (int)nsplit * a.tiles_m * 2;  // bias partial rows per layer
-        if (nb)
-            for (int l = 0; l < nl; ++l) b.L[l].sum_b = sum_b[l0 + l];
-        if (nsplit > 1) {
-            ReduceBatch rb;
-            for (int l = 0; l < MAX_BATCH; ++l) {
-                rb.part[l] = reinterpret_cast<const float4*>(b.L[l < nl ? l : 0].out);
-                rb.out[l] = reinterpret_cast<float4*>(sum_W[l0 + (l < nl ? l : 0)]);
+        if (nsplit > 1 || nb) {
+            FinishArgs f;
+            for (int l = 0; l < nl; ++l) {
+                f.part[l] = reinterpret_cast<const float4*>(b.L[l].out);
+                f.out[l] = reinterpret_cast<float4*>(sum_W[l0 + l]);
+                f.sum_b[l] = nb ? sum_b[l0 + l] : nullptr;
             }
             const size_t n4 = (size_t)d_in * d_out / 4;  // d_out is a multiple of 8
-            hipLaunchKernelGGL(reduce_layers_kernel, dim3((unsigned)((n4 + 255) / 256), nl), dim3(256), 0, ctx->stream,
-                               rb, (int)nsplit, n4);
-            DP_LAUNCH_CHECK(ctx, "reduce_layers");
-        }
-        if (nb) {
-            hipLaunchKernelGGL(bias_finish_kernel, dim3(nl, (d_out + 63) / 64), dim3(256), 0, ctx->stream, b, nb);
-            DP_LAUNCH_CHECK(ctx, "bias_finish");
+            const bool tall = nsplit >= 16 && n4 * nl <= 16384;  // too few columns to fill the chip one a thread
+            const long w_blocks = nsplit > 1 ? (long)((n4 + (tall ? 63 : 255)) / (tall ? 64 : 256)) : 0, b_blocks = nb ? (d_out + 63) / 64 : 0;
+            const dim3 grid((unsigned)(w_blocks + b_blocks), nl);
+            if (tall) hipLaunchKernelGGL(finish_layers_kernel<true>, grid, dim3(256), 0, ctx->stream, f, (int)nsplit, n4, (int)w_blocks, bias_part, nb, d_out);
+            else hipLaunchKernelGGL(finish_layers_kernel<false>, grid, dim3(256), 0, ctx->stream, f, (int)nsplit, n4, (int)w_blocks, bias_part, nb, d_out);
+            DP_LAUNCH_CHECK(ctx, "finish_layers");
         }
     }
     return DP_OK;
@@ -1322,14 +1321,11 @@ dp_status dpk_dense_sum_plan(dp_dtype dt, int n, int B, int T, int d_in, int d_o
         return DP_OK;
     }
     const DmaPlan p = choose_dma_plan(n, B, T, d_in, d_out, ws_bytes);
-    const long spe = p.flat ? 1 : (T + BK - 1) / BK, ksteps = p.flat ? (K + BK - 1) / BK : (long)B * spe;
-    const int ntiles = ((d_in + p.bm - 1) / p.bm) * ((d_out + p.bn - 1) / p.bn), nl = n < p.per_launch ? n : p.per_launch;
-    double t;
     out[0] = p.bm;
     out[1] = p.bn;
     out[2] = p.flat ? 1 : 0;
-    out[3] = nl;
-    out[4] = (int32_t)choose_nsplit_dma(nl, ntiles, ksteps, spe, d_in, d_out, dma_cost(p.bm, p.bn, !p.flat && T <= BK), &t);
+    out[3] = n < p.per_launch ? n : p.per_launch;
+    out[4] = (int32_t)p.nsplit;
     out[5] = BK;
     return DP_OK;
 }
