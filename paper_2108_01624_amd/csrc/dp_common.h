@@ -87,10 +87,6 @@ struct dp_ws_alloc {
         off = end;
         return reinterpret_cast<T*>(ctx->ws + o);
     }
-    size_t remaining() const {
-        size_t o = dp_align_up(off, 256);
-        return o >= ctx->ws_bytes ? 0 : ctx->ws_bytes - o;
-    }
 };
 
 // How many of the first n layers may share a launch that adds to a[l][0 .. na) and, if b and b[l], b[l][0 .. nb): those whose
@@ -130,16 +126,6 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float dp_bf16_bits_to_f32(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
 __device__ __forceinline__ float dp_bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float dp_bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-
-// fp32 -> bf16 bits, round to nearest even (inputs here are finite products c*g).
-__device__ __forceinline__ uint32_t dp_f32_to_bf16_bits(float x) {
-    uint32_t u = __float_as_uint(x);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-__device__ __forceinline__ uint32_t dp_pack_bf16x2(float lo, float hi) {
-    return dp_f32_to_bf16_bits(lo) | (dp_f32_to_bf16_bits(hi) << 16);
-}
 
 __device__ __forceinline__ float dp_wave_sum(float v) {
 #pragma unroll

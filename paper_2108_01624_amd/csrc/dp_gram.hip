@@ -12,8 +12,6 @@
 //
 // Roofline: HBM at T = 128 (2*T*(d_in+d_out) bytes per example against 2*T^2*(d_in+d_out) flops, i.e.
 // T flop/B, below the machine balance of ~310 flop/B); each row panel is read once per block it is in.
-#include <stdlib.h>
-
 #include <type_traits>
 
 #include "dp_common.h"

@@ -10,7 +10,6 @@
 //
 // Roofline: HBM, B*(T+M)*d*E bytes read once plus B*T*M gathered elements (each its own 32-byte sector of dL);
 // 2*T*M*d flops per example are far below the machine balance.
-#include <stdlib.h>
 
 #include "dp_common.h"
 

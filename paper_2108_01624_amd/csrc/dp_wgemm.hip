@@ -15,7 +15,6 @@
 // which spreads the four rows of a group, and the two groups of a half-wave, over 256 distinct bytes.
 //
 // Roofline: MFMA.  2*B*T*d_in*d_out flops per layer against (d_in + d_out)*B*T*2 bytes read once.
-#include <stdlib.h>
 
 #include <type_traits>
 
