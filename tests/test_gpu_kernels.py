@@ -449,7 +449,7 @@ def test_layernorm_norms_and_sums(dp, dtype, B, T, d):
 @pytest.mark.parametrize("dtype,n,B,T,d", [("bf16", 3, 9, 128, 1024), ("bf16", 19, 4, 33, 264), ("f32", 2, 5, 17, 20), ("bf16", 1, 3, 8, 64),
                                           ("f32", 17, 2, 9, 6), ("bf16", 40, 7, 5, 520)])
 def test_layernorm_batched(dp, dtype, n, B, T, d):
-    """Several LayerNorms of one shape in one call (more than one launch's worth at n > 16): each layer against the oracle,
+    """Several LayerNorms of one shape in one call (more than one launch's worth at n > 32): each layer against the oracle,
     the norms against the sum over layers."""
     Xs = [gen((B, T, d), 1.0, 900 + l, dtype) for l in range(n)]
     Gs = [gen((B, T, d), 0.1 * (1 + l % 3), 950 + l, dtype) for l in range(n)]
@@ -971,7 +971,8 @@ def test_tied_embedding_out_of_range_id_is_reported(dp):
                                               # (the balanced XCD mapping, with the rectangle walk)
                                               (5, 12, 128, 768, 768), (3, 4, 128, 768, 3072),
                                               # widths that end inside a tile, odd layer counts, T = two and six stages
-                                              (7, 6, 64, 264, 520), (2, 20, 192, 1000, 256)])
+                                              (7, 6, 64, 264, 520), (2, 20, 192, 1000, 256),
+                                              (66, 2, 40, 64, 72)])  # more layers than the 64 of a launch
 def test_clip_accumulate_dense_batched(dp, n, B, T, d_in, d_out):
     C = 1.0
     sq = syn.synthetic_sqnorms(B, C, 300)
@@ -1258,10 +1259,11 @@ def test_batched_equals_single_layer_calls(dp):
 
 @pytest.mark.parametrize("n,B,T,d_in,d_out,has_bias", [(3, 5, 128, 256, 384, True), (18, 3, 96, 64, 128, False),
                                                         (2, 4, 100, 72, 136, True), (2, 2, 300, 128, 128, True),
-                                                        (1, 6, 128, 128, 64, True)])
+                                                        (1, 6, 128, 128, 64, True), (66, 2, 40, 64, 72, True),
+                                                        (65, 2, 140, 64, 128, False)])
 def test_sqnorms_dense_batched(dp, n, B, T, d_in, d_out, has_bias):
-    """n same-shaped layers in one call: fast-path shapes (shared launches, more than 16 layers), ragged shapes and
-    several Gram blocks (per-layer fallback); the norms of all layers add up, on top of what sqnorms held."""
+    """n same-shaped layers in one call: shared launches (also of more layers than the 64 of one), ragged shapes and
+    several Gram blocks; the norms of all layers add up, on top of what sqnorms held."""
     import paper_2108_01624_amd as pkg
 
     As = [gen((B, T, d_in), 1.0, 500 + l, "bf16") for l in range(n)]
@@ -1283,15 +1285,18 @@ def test_sqnorms_dense_batched(dp, n, B, T, d_in, d_out, has_bias):
         dp.sqnorms_dense(a, g, has_bias, pkg.DP_PATH_GRAM, seq)
     dp.sync()
     np.testing.assert_array_equal(host(one), host(two))
-    np.testing.assert_allclose(host(one), host(seq), rtol=1e-6)
+    # (n fp32 additions of positive terms differ by at most n half units in the last place of the sum, twice)
+    np.testing.assert_allclose(host(one), host(seq), rtol=1e-6 if n <= 18 else n * 2.0**-23)
 
 
 @pytest.mark.parametrize("ng,n_out,B,T,d_in,d_out,has_bias", [(2, 3, 5, 128, 256, 128, True), (1, 2, 3, 64, 64, 192, False),
                                                                (18, 3, 2, 32, 64, 64, True), (2, 3, 2, 300, 128, 128, True),
-                                                               (1, 3, 4, 100, 72, 136, True)])
+                                                               (1, 3, 4, 100, 72, 136, True), (65, 2, 2, 40, 64, 72, False),
+                                                               (23, 3, 2, 140, 64, 72, True)])
 def test_sqnorms_dense_shared_input(dp, ng, n_out, B, T, d_in, d_out, has_bias):
     """Groups of layers reading one input (query / key / value): the norms are those of ng * n_out separate layers
-    (the oracle knows nothing of the sharing); fast-path shapes, more than 16 groups, and per-layer fallbacks."""
+    (the oracle knows nothing of the sharing); groups of two and three, more groups than the 64 of one launch,
+    and long examples, whose layers share launches one by one (69 of them: two launches)."""
     As = [gen((B, T, d_in), 1.0, 600 + g, "bf16") for g in range(ng)]
     Gs = [[gen((B, T, d_out), 0.1, 640 + 4 * g + j, "bf16") for j in range(n_out)] for g in range(ng)]
     ref = sum(orc.sqnorms_dense(As[g], Gs[g][j], has_bias) for g in range(ng) for j in range(n_out))
