@@ -97,10 +97,12 @@ dp_status dp_sqnorms_dense(dp_ctx* ctx, const void* A, const void* G, dp_dtype d
                            int d_out, int has_bias, dp_path path, float* sqnorms);
 
 /* n_layers dense layers of one shape in one call: the result is that of n_layers calls of dp_sqnorms_dense
- * with the same arguments (each layer's norms added to sqnorms[i], layers in index order).  On the Gram path
- * the layers share launches of up to 64 layers, which keeps the memory
- * pipeline full across examples; their per-layer norms (for T > 128: per layer and unit of two or three 128 x 128 cells of the T x T plane) pass
- * through the library workspace and are added in a fixed order (DP_ERR_WORKSPACE if they do not fit).
+ * with the same arguments up to the rounding of fp32 sums: the layers' norms are added to sqnorms[i] in an order that is
+ * fixed for a shape, but not that of the single calls.  In bf16 the layers of either path share launches of up to 64
+ * layers, which keeps the memory pipeline full across examples; their per-layer norms (for T > 128 on the Gram path: per
+ * layer and unit of two or three 128 x 128 cells of the T x T plane) pass through the library workspace.  Where those of
+ * 64 layers do not fit, fewer share a launch; DP_ERR_WORKSPACE only if those of one layer do not (a single layer of
+ * T <= 128 needs none on the Gram path).
  * A, G are HOST arrays of n_layers device pointers, read during the call only. */
 dp_status dp_sqnorms_dense_batched(dp_ctx* ctx, int n_layers, const void* const* A, const void* const* G, dp_dtype dtype,
                                    int B, int T, int d_in, int d_out, int has_bias, dp_path path, float* sqnorms);
@@ -109,8 +111,9 @@ dp_status dp_sqnorms_dense_batched(dp_ctx* ctx, int n_layers, const void* const*
  * activations): n_groups groups of n_out same-shaped layers, group g's layers having input A[g] and output
  * gradients G[g * n_out + j], j < n_out.  The result is that of n_groups * n_out calls of dp_sqnorms_dense (every
  * layer with its own bias if has_bias).  Because sum_j <A A^T (+1), G_j G_j^T> = <A A^T (+1), sum_j G_j G_j^T>, the
- * Gram path (T <= 128, widths multiples of 64, n_out 2 or 3) forms A A^T once per group and reads A once: a
- * third fewer bytes and matrix operations for a query/key/value group.  Other shapes are served layer by layer.
+ * Gram path in bf16 (T <= 128, any width, n_out 2 or 3) forms A A^T once per group and reads A once: a third fewer
+ * bytes and matrix operations for a query/key/value group.  Longer examples share launches as separate layers; other
+ * calls (fp32, n_out 1 or above 3, shapes of the materialise path) are served layer by layer.
  * A (n_groups entries) and G (n_groups * n_out entries) are HOST arrays of device pointers, read during the call. */
 dp_status dp_sqnorms_dense_shared(dp_ctx* ctx, int n_groups, const void* const* A, int n_out, const void* const* G,
                                   dp_dtype dtype, int B, int T, int d_in, int d_out, int has_bias, float* sqnorms);
@@ -120,10 +123,10 @@ dp_status dp_sqnorms_dense_shared(dp_ctx* ctx, int n_groups, const void* const* 
 dp_status dp_sqnorms_layernorm(dp_ctx* ctx, const void* Xhat, const void* G, dp_dtype dtype, int B, int T, int d,
                                float* sqnorms);
 
-/* n_layers LayerNorms of one shape in one call: the result of n_layers calls of dp_sqnorms_layernorm (layers added
- * in index order).  Up to 32 layers share a launch; their per-example partial norms pass through the library
- * workspace (DP_ERR_WORKSPACE if they do not fit).  Xhat, G: HOST arrays of n_layers device pointers, read during the
- * call only. */
+/* n_layers LayerNorms of one shape in one call: the result of n_layers calls of dp_sqnorms_layernorm up to the rounding
+ * of fp32 sums (the order of the additions is fixed for a shape, but not that of the single calls).  Up to 32 layers
+ * share a launch, fewer where their per-example partial norms do not fit the library workspace (DP_ERR_WORKSPACE if
+ * those of one layer do not).  Xhat, G: HOST arrays of n_layers device pointers, read during the call only. */
 dp_status dp_sqnorms_layernorm_batched(dp_ctx* ctx, int n_layers, const void* const* Xhat, const void* const* G,
                                        dp_dtype dtype, int B, int T, int d, float* sqnorms);
 

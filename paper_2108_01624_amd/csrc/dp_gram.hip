@@ -177,13 +177,13 @@ __global__ __launch_bounds__(256, 2) void gram_bf16_kernel(const uint16_t* __res
 }
 
 // ------------------------------------------------------------------------------------------------
-// T <= 128 (one block per example): the same computation with the row panels
-// streamed straight into a four-stage LDS ring by LDS-filling buffer loads, three 16 KiB chunks in flight per
-// workgroup (the register-staged kernel above keeps one: at two workgroups per CU that is too few bytes in
-// flight to cover the HBM latency at full bandwidth).  The loads go through inline assembly so that the wave
+// T <= 128 (one block per example): the same computation with the row panels streamed straight into an LDS ring (2 to 9
+// stages of 8 to 32 KiB, by the form) by LDS-filling buffer loads, all but one stage in flight per workgroup (the
+// register-staged kernel above keeps one chunk: at two workgroups per CU that is too few bytes in flight to cover the
+// HBM latency at full bandwidth).  The loads go through inline assembly so that the wave
 // waits (vmcnt) for the chunk it is about to publish only, not for every load in flight.
-// LDS layout: [128 rows][8 chunks of 16 B], chunk position c of row r holds global chunk c ^ ((r >> 1) & 7):
-// the 16-byte reads of 16 consecutive rows then fall into 64 distinct banks.
+// LDS layout: [64 or 128 rows][8 or 16 chunks of 16 B], chunk position c of row r holds global chunk c ^ ((r >> 1) & 7), or
+// c ^ (r & 15) with 16 chunks: the 16-byte reads of 16 consecutive rows then fall into 64 distinct banks.
 // ------------------------------------------------------------------------------------------------
 typedef int gram_i32x4 __attribute__((ext_vector_type(4)));
 
@@ -257,7 +257,7 @@ struct GramBatch {
 // 192 x 2264, B = 106, T = 47: 42 -> 30 us).
 // The next k step's fragments are read while one multiplies, those of a diagonal quadrant once for rows and columns, and a
 // stage's loads are issued behind the first fragments (12 layers of 768 x 3072, B = 8: 36.6 -> 34.6 us; one layer of 768 x 768,
-// B = 8: 16.7 -> 15.7; 8 layers of 1024 x 1024, B = 512: 322 -> 319, 6.7 TB/s).
+// B = 8: 16.7 -> 15.7; 8 layers of 1024 x 1024, B = 512: the same within the runs of one side, 320 us, 6.7 TB/s).
 // RAGGED: a width that is no multiple of GDK; what lies past a row's end in its last chunk is left out lane by lane.
 template <int ROWS, int GDK, int NS, int WAVES, int WGS_PER_CU, bool RAGGED>
 __global__ __launch_bounds__(64 * WAVES, WGS_PER_CU * WAVES / 4) void gram_dma_kernel(GramBatch gb, int T, int d_in, int d_out,
@@ -790,7 +790,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void gram_small_dma
     const float bias_term = has_bias ? 1.f : 0.f;
     float sum = 0.f;
 #pragma unroll
-    for (int q = 0; q < 16 / WAVES; ++q) {  // wave w finishes its share of the accumulator registers, the waves' partial tiles added in index order
+    for (int q = 0; q < 16 / WAVES; ++q) {  // wave w finishes its share of the accumulator registers, the waves' partial tiles added in wave order
         const int reg = wave * (16 / WAVES) + q;
         float a = 0.f, g = 0.f;
 #pragma unroll
@@ -1058,7 +1058,7 @@ dp_status dpk_gram_unit_plan(int T, uint32_t* units, int capacity, int* n_units)
     return DP_OK;
 }
 
-// nl <= GRAM_MAX_BATCH same-shaped layers: partials [B][nl * n_units] through the workspace, added in index order.
+// nl <= GRAM_MAX_BATCH same-shaped layers: partials [B][nl * n_units] through the workspace, added in a fixed order.
 static dp_status gram_units_launch(dp_ctx* ctx, const GramBatch& gb, int T, int d_in, int d_out, int has_bias,
                                    float* sqnorms) {
     const GramUnits gu = gram_make_units((T + GB - 1) / GB);
@@ -1189,7 +1189,7 @@ dp_status dpk_gram_sqnorms_batched(dp_ctx* ctx, int n_layers, const void* const*
         gb.n_out = 1;
         gb.B = B;
         dp_status st = gram_dma_launch(ctx, gb, T, d_in, d_out, has_bias, part ? part : sqnorms, 2.0 * (double)B * T * ((double)d_in + d_out) * nl);
-        if (st == DP_OK && part) st = dpk_finish_partials(ctx, part, B, nl, sqnorms);   // layers added in index order
+        if (st == DP_OK && part) st = dpk_finish_partials(ctx, part, B, nl, sqnorms);   // (in an order fixed by nl)
         if (st != DP_OK) return st;
         l0 += nl;
     }

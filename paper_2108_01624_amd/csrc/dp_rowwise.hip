@@ -62,7 +62,7 @@ __device__ __forceinline__ void load_vec(const void* __restrict__ base, size_t i
 // column statistics, per example (pass 1)
 //   grid (B, ceil(d / (64*VW))), 256 threads = 4 row groups x 64 column lanes
 // ------------------------------------------------------------------------------------------------
-// Up to COL_MAX_BATCH same-shaped layers per launch (blockIdx.z = layer): the 48 LayerNorms of the model are 3 launches
+// Up to COL_MAX_BATCH same-shaped layers per launch (blockIdx.z = layer): the 48 LayerNorms of the model are 2 launches
 // per pass instead of 48, and their per-example partials meet in one ordered reduction.
 constexpr int COL_MAX_BATCH = 32;
 struct ColBatch {
@@ -949,7 +949,7 @@ static dp_status colstat_sqnorms_launch(dp_ctx* ctx, int L, const void* const* X
     else
         hipLaunchKernelGGL((colstat_sqnorms_kernel<BF16, VW, false, true, false>), grid, dim3(256), 0, ctx->stream, cb, ck, T, d, out, J, direct);
     DP_LAUNCH_CHECK(ctx, "colstat_sqnorms");
-    if (!direct) return dpk_finish_partials(ctx, out, B, L * J, sqnorms);  // layers, then column blocks, in index order
+    if (!direct) return dpk_finish_partials(ctx, out, B, L * J, sqnorms);  // (in an order fixed by L * J)
     return DP_OK;
 }
 

@@ -134,7 +134,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void* base,
 // same pass, so the chunk swizzle also takes bit 3 of the row.
 __device__ __forceinline__ int swz16(int row) { return ((row & 3) << 2) | (((row >> 3) & 1) << 1); }
 
-// 160 KiB of LDS in stages of (BM + BN) x 32 rows, at most 8 (a smaller tile leaves room for a second workgroup on the CU).
+// Stages of (BM + BN) columns x 32 rows in the ring: 256 x 256 takes 5 of 32 KiB, the whole 160 KiB of LDS, the mixed tiles 6 of
+// 24 KiB, and 128 x 128 5 of 16 KiB, which leaves room for a second workgroup on the CU.
 constexpr int dma_stages(int bm, int bn) { return bm + bn >= 512 ? 5 : (bm + bn >= 384 ? 6 : 5); }
 
 // MI x NI tiles of 16 x 16 per wave, 2 x 4 waves: block tile 32 MI x 64 NI (256 or 128 wide either way).
