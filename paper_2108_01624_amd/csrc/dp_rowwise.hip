@@ -19,19 +19,20 @@ template <bool BF16, int VW>
 struct RawVec {
     uint32_t w[BF16 ? VW / 2 : VW];
 };
+typedef const __attribute__((address_space(1))) char* rw_global;
 template <bool BF16, int VW>
-__device__ __forceinline__ RawVec<BF16, VW> load_raw(const void* __restrict__ base, size_t idx) {
+__device__ __forceinline__ RawVec<BF16, VW> load_raw(rw_global row, uint32_t byte) {  // row: the same for the wave
     RawVec<BF16, VW> r;
     if constexpr (BF16) {
         static_assert(VW == 4, "bf16 rows are read four elements at a time");
-        const rw_u32x2 t = __builtin_nontemporal_load(reinterpret_cast<const rw_u32x2*>(reinterpret_cast<const uint16_t*>(base) + idx));
+        const rw_u32x2 t = __builtin_nontemporal_load(reinterpret_cast<const __attribute__((address_space(1))) rw_u32x2*>(row + byte));
         r.w[0] = t[0]; r.w[1] = t[1];
     } else if constexpr (VW == 4) {
-        const f32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(base) + idx));
+        const f32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const __attribute__((address_space(1))) f32x4_t*>(row + byte));
 #pragma unroll
         for (int k = 0; k < 4; ++k) r.w[k] = __float_as_uint(t[k]);
     } else {
-        r.w[0] = __float_as_uint(__builtin_nontemporal_load(reinterpret_cast<const float*>(base) + idx));
+        r.w[0] = __float_as_uint(__builtin_nontemporal_load(reinterpret_cast<const __attribute__((address_space(1))) float*>(row + byte)));
     }
     return r;
 }
@@ -362,16 +363,19 @@ __global__ __launch_bounds__(256) void reduce_partials_pair_kernel(const float4*
 
 // ------------------------------------------------------------------------------------------------
 // embedding, per-example norms (pass 1): one workgroup per example and ncb blocks of 64*VW columns; `parts` waves (as many as there
-// are pieces of EMB_AHEAD positions, up to 8 or 16 waves in all) share the example's positions in a column block.
+// are pieces of EMB_PIECE positions, up to 8 or 16 waves in all) share the example's positions in a column block.
 // The workgroup ranks the T ids (stable counting rank in LDS: every key, the id above the position, against all others), then
-// every wave walks its run of sorted positions, EMB_AHEAD rows in flight, adding up rows of equal id; a run's end is a select,
-// not a branch.  Runs that are complete inside a wave are squared there; the sums of a wave's first and last run go to LDS, where
-// they are joined across the waves, column by column.
+// every wave walks its run of sorted positions, EMB_AHEAD rows in flight, adding up rows of equal id.  What the walk decides by
+// is the same for the wave: row addresses and run ends are formed 64 positions at a time, one a lane, and read back as scalars
+// (two LDS reads and 34 vector instructions a row, the ends as selects, kept short examples from the memory's rate: T = 128,
+// d = 2,048, B = 514 62 -> 56 us; T = 64, B = 400 26 -> 22).  Runs that are complete inside a wave are squared there; the sums of
+// a wave's first and last run go to LDS, where they are joined across the waves, column by column.
 // One wave walking all positions of its columns was a chain of T / 8 round trips: B = 23, T = 375, d = 832: 61 -> 23 us;
 // B = 512, T = 128, d = 1024 (134 MB): 31 + 5 -> 28.  Waves without positions would only make the joining of the parts longer: T = 16,
 // d = 256, B = 4 12 us with 16 waves, 6 with 1; B = 514 16 | 7.
 // ------------------------------------------------------------------------------------------------
-constexpr int EMB_AHEAD = 16;
+constexpr int EMB_AHEAD = 8;   // rows in flight of a wave
+constexpr int EMB_PIECE = 16;  // positions that are worth a wave
 
 // EMB_WAVES: the most waves that a launch may have; it has ncb * parts.
 template <bool BF16, int VW, bool DISTINCT, int EMB_WAVES>
@@ -386,84 +390,109 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
     uint32_t* sid = lds;        // [T rounded up to 4] ids of this example
     uint16_t* order = reinterpret_cast<uint16_t*>(lds + (T + 3) / 4 * 4);  // [T] row index at each sorted position (T <= 4096)
     const int i = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nt = 64 * ncb * parts;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nt = 64 * ncb * parts;
     bool bad = false;
     for (int t = threadIdx.x; t < (T + 3) / 4 * 4; t += nt) {
         const int32_t v = t < T ? ids[(size_t)i * T + t] : 0;
         if (t < T && (v < 0 || v >= V)) bad = true;
-        sid[t] = t < T ? (uint32_t)v : 0xFFFFFFFFu;  // (the padding ranks behind everything)
+        sid[t] = t >= T ? 0xFFFFFFFFu : v == -1 ? 0xFFFFFFFEu : (uint32_t)v;  // (the padding ranks behind everything, also behind -1)
     }
     if (bad) atomicOr(err, 1);
     __syncthreads();
     if constexpr (!DISTINCT) {
         const uint4* s4 = reinterpret_cast<const uint4*>(sid);
-        for (int t = threadIdx.x; t < T; t += nt) {
-            const uint32_t v = sid[t];
+        const int n4 = (T + 3) / 4;
+        for (int t0 = wave * 64; t0 < T; t0 += nt) {  // (the same bounds for all lanes: the reads stay in flight)
+            const int t = t0 + lane, mid = t0 / 4 + 16 < n4 ? t0 / 4 + 16 : n4;
+            const uint32_t v = sid[t < T ? t : T - 1];
             // keys are unique as (id, position): before position t an equal id ranks lower, after it higher
             int rank = 0;
-            const int t4 = t / 4;
-            for (int s = 0; s < t4; ++s) {
+#pragma unroll 4
+            for (int s = 0; s < t0 / 4; ++s) {
                 const uint4 u = s4[s];
                 rank += (u.x <= v) + (u.y <= v) + (u.z <= v) + (u.w <= v);
             }
-            const uint4 u = s4[t4];
-            const int r = t % 4;
-            rank += (0 < r ? u.x <= v : u.x < v) + (1 < r ? u.y <= v : u.y < v) + (2 < r ? u.z <= v : u.z < v) + (u.w < v);
-            for (int s = t4 + 1; s < (T + 3) / 4; ++s) {
-                const uint4 w = s4[s];
-                rank += (w.x < v) + (w.y < v) + (w.z < v) + (w.w < v);
+#pragma unroll 4
+            for (int s = t0 / 4; s < mid; ++s) {
+                const uint4 u = s4[s];
+                const int e = t - 4 * s;
+                rank += (u.x < v + (e > 0)) + (u.y < v + (e > 1)) + (u.z < v + (e > 2)) + (u.w < v + (e > 3));
             }
-            order[rank] = (uint16_t)t;
+#pragma unroll 4
+            for (int s = mid; s < n4; ++s) {
+                const uint4 u = s4[s];
+                rank += (u.x < v) + (u.y < v) + (u.z < v) + (u.w < v);
+            }
+            if (t < T) order[rank] = (uint16_t)t;
         }
         __syncthreads();
     }
     const int cb = wave % ncb, part = wave / ncb;
-    const int col = ((blockIdx.y * ncb + cb) * 64 + lane) * VW;
+    const int col0 = (blockIdx.y * ncb + cb) * 64 * VW, col = col0 + lane * VW;
     const int per = (T + parts - 1) / parts, lo = part * per, hi = lo + per < T ? lo + per : T;  // this wave's positions
-    float tot = 0.f, run[VW], hd[VW];
+    float sq[VW], run[VW];  // squares of the finished runs, the run at hand
 #pragma unroll
-    for (int k = 0; k < VW; ++k) run[k] = hd[k] = 0.f;
+    for (int k = 0; k < VW; ++k) sq[k] = run[k] = 0.f;
     bool one = true;  // no run has ended yet
-    if (col < d && lo < hi) {
-        const size_t base = (size_t)i * T * d + col;
-        uint32_t prev = DISTINCT ? 0u : sid[order[lo]];
-        for (int p0 = lo; p0 < hi; p0 += EMB_AHEAD) {
-            RawVec<BF16, VW> g[EMB_AHEAD];
-            uint32_t id[EMB_AHEAD];
+    if (col0 < d && lo < hi) {  // (whole waves: lanes past the width read its last columns again and drop them below)
+        constexpr int E = BF16 ? 2 : 4;
+        const uint32_t at = ((col < d ? col : d - VW) - col0) * E;
+        const char* base = reinterpret_cast<const char*>(G) + ((size_t)i * T * d + col0) * E;
+        for (int q0 = lo; q0 < hi; q0 += 64) {
+            // 64 positions, one a lane: the address of the row, and whether the run before it is complete
+            const int p = q0 + lane < hi ? q0 + lane : hi - 1, row = DISTINCT ? p : (int)order[p], n = hi - q0;
+            const uint64_t addr = (uint64_t)base + (uint64_t)row * ((uint64_t)d * E);
+            const int a_lo = (int)(uint32_t)addr, a_hi = (int)(addr >> 32);
+            const uint64_t ends = DISTINCT ? 0 : __ballot(q0 + lane < hi && p > lo && sid[row] != sid[order[p > lo ? p - 1 : lo]]);
+            for (int u0 = 0; u0 < 64 && u0 < n; u0 += EMB_AHEAD) {
+                RawVec<BF16, VW> g[EMB_AHEAD];
+                const int left = n - u0;
+                const uint32_t e = (uint32_t)(ends >> u0);
 #pragma unroll
-            for (int u = 0; u < EMB_AHEAD; ++u) {
-                const int p = p0 + u < hi ? p0 + u : hi - 1;
-                const int t = DISTINCT ? p : (int)order[p];
-                id[u] = DISTINCT ? 0u : sid[t];
-                g[u] = load_raw<BF16, VW>(G, base + (size_t)t * d);
-            }
+                for (int u = 0; u < EMB_AHEAD; ++u) {
+                    const uint64_t r = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(a_hi, u0 + u) << 32 | (uint32_t)__builtin_amdgcn_readlane(a_lo, u0 + u);
+                    g[u] = load_raw<BF16, VW>((rw_global)r, at);
+                }
 #pragma unroll
-            for (int u = 0; u < EMB_AHEAD; ++u) {
-                const bool in = p0 + u < hi;
-                const bool ends = !DISTINCT && in && id[u] != prev;  // the run before this row is complete
-#pragma unroll
-                for (int k = 0; k < VW; ++k) {
-                    const float x = in ? raw_value<BF16, VW>(g[u], k) : 0.f;
+                for (int u = 0; u < EMB_AHEAD; ++u) {
+                    if (u >= left) continue;
                     if constexpr (DISTINCT) {
-                        tot += x * x;
+#pragma unroll
+                        for (int k = 0; k < VW; ++k) sq[k] += raw_value<BF16, VW>(g[u], k) * raw_value<BF16, VW>(g[u], k);
+                    } else if (!(e & (1u << u))) {
+#pragma unroll
+                        for (int k = 0; k < VW; ++k) run[k] += raw_value<BF16, VW>(g[u], k);
                     } else {
-                        hd[k] = ends && one ? run[k] : hd[k];
-                        tot += ends && !one ? run[k] * run[k] : 0.f;
-                        run[k] = (ends ? 0.f : run[k]) + x;
+                        if (one && parts > 1) {
+#pragma unroll
+                            for (int k = 0; k < VW; ++k) head[wave][lane * VW + k] = run[k];
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < VW; ++k) sq[k] += run[k] * run[k];
+                        }
+                        one = false;
+#pragma unroll
+                        for (int k = 0; k < VW; ++k) run[k] = raw_value<BF16, VW>(g[u], k);
                     }
                 }
-                one = one && !ends;
-                prev = in ? id[u] : prev;
             }
         }
     }
-    if (!DISTINCT && parts == 1) {  // nothing to join: the last run, and the first if another one followed it
+    float tot = 0.f;
 #pragma unroll
-        for (int k = 0; k < VW; ++k) tot += run[k] * run[k] + (one ? 0.f : hd[k] * hd[k]);
+    for (int k = 0; k < VW; ++k) tot += sq[k];
+    if (col >= d) {
+        tot = 0.f;
+#pragma unroll
+        for (int k = 0; k < VW; ++k) run[k] = 0.f;
+    }
+    if (!DISTINCT && parts == 1) {  // nothing to join
+#pragma unroll
+        for (int k = 0; k < VW; ++k) tot += run[k] * run[k];
     } else if constexpr (!DISTINCT) {
 #pragma unroll
         for (int k = 0; k < VW; ++k) {
-            head[wave][lane * VW + k] = one ? run[k] : hd[k];
+            if (one) head[wave][lane * VW + k] = run[k];  // (its only run; otherwise the first is there already)
             tail[wave][lane * VW + k] = run[k];
         }
         if (lane == 0) whole[wave] = one ? 1u : 0u;
@@ -1097,7 +1126,7 @@ static dp_status embedding_sqnorms_launch(dp_ctx* ctx, const int32_t* ids, const
     // reduction launch; one, and all waves on its positions, when the examples alone are too few for the chip and long enough
     // for 16 waves.  16 waves of this kernel are what the registers of a CU hold: they are shared by the workgroups that a CU gets
     // (B = 512: 36 us with 16 waves, 28 with 8; B = 514, T = 128, d = 256: 21 with 8, 14 with 4; B = 256: 21 with 16).
-    const int blocks = (d + 64 * VW - 1) / (64 * VW), pieces = (T + EMB_AHEAD - 1) / EMB_AHEAD;
+    const int blocks = (d + 64 * VW - 1) / (64 * VW), pieces = (T + EMB_PIECE - 1) / EMB_PIECE;
     int ncb = blocks >= 3 ? 4 : blocks;
     if ((long)B * ((blocks + ncb - 1) / ncb) < 128 && ncb * pieces > 16) ncb = 1;
     int J = (blocks + ncb - 1) / ncb;

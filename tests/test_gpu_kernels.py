@@ -553,6 +553,29 @@ def test_embedding_counts_are_exact(dp, B, T, V):
     np.testing.assert_array_equal(host(n).astype(np.float64), ref_n)
 
 
+@pytest.mark.parametrize("dtype,B,T,d,V", [
+    ("bf16", 1100, 64, 264, 30522), ("bf16", 1100, 65, 264, 3), ("bf16", 1100, 130, 520, 40),  # one wave to a column block
+    ("f32", 1100, 129, 130, 1), ("f32", 4200, 71, 7, 30522),
+    ("bf16", 300, 700, 264, 40), ("f32", 300, 530, 264, 2), ("bf16", 2, 4096, 8, 7)])        # several, of more than 64 positions
+def test_embedding_norms_are_exact_on_whole_numbers(dp, dtype, B, T, d, V):
+    """Rows of whole numbers from -2 to 2: every run and its square is exact, so a row that is left out, taken twice or added to
+    another run shows.  The norms stay below 2^24, where fp32 holds whole numbers."""
+    rng = np.random.default_rng(T * d + V)
+    ids = rng.integers(0, V, (B, T)).astype(np.int32)
+    G = rng.integers(-2, 3, (B, T, d)).astype(np.float32)
+    ref = np.zeros(B)
+    for i in range(B):
+        _, inv = np.unique(ids[i], return_inverse=True)
+        order = np.argsort(inv, kind="stable")
+        sums = np.add.reduceat(G[i][order], np.flatnonzero(np.diff(inv[order], prepend=-1)), axis=0)
+        ref[i] = float((sums.astype(np.float64) ** 2).sum())
+    assert ref.max() < 2**24
+    n = torch.zeros(B, dtype=torch.float32, device=DEV)
+    dp.sqnorms_embedding(to_dev(ids), to_dev(syn.f32_to_bf16_bits(G) if dtype == "bf16" else G), V, False, n)
+    dp.sync()
+    np.testing.assert_array_equal(host(n).astype(np.float64), ref)
+
+
 @pytest.mark.parametrize("dtype,B,T,d", [("bf16", 6, 128, 1024), ("f32", 4, 9, 5), ("bf16", 300, 16, 64)])
 def test_position_embedding(dp, dtype, B, T, d):
     V = T + 3
