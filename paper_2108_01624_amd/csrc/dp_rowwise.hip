@@ -365,7 +365,7 @@ __global__ __launch_bounds__(256) void reduce_partials_pair_kernel(const float4*
 // embedding, per-example norms (pass 1): one workgroup per example and ncb blocks of 64*VW columns; `parts` waves (as many as there
 // are pieces of EMB_PIECE positions, up to 8 or 16 waves in all) share the example's positions in a column block.
 // The workgroup ranks the T ids (stable counting rank in LDS: every key, the id above the position, against all others), then
-// every wave walks its run of sorted positions, EMB_AHEAD rows in flight, adding up rows of equal id.  What the walk decides by
+// every wave walks its run of sorted positions, emb_ahead rows in flight, adding up rows of equal id.  What the walk decides by
 // is the same for the wave: row addresses and run ends are formed 64 positions at a time, one a lane, and read back as scalars
 // (two LDS reads and 34 vector instructions a row, the ends as selects, kept short examples from the memory's rate: T = 128,
 // d = 2,048, B = 514 62 -> 56 us; T = 64, B = 400 26 -> 22).  Runs that are complete inside a wave are squared there; the sums of
@@ -374,7 +374,8 @@ __global__ __launch_bounds__(256) void reduce_partials_pair_kernel(const float4*
 // B = 512, T = 128, d = 1024 (134 MB): 31 + 5 -> 28.  Waves without positions would only make the joining of the parts longer: T = 16,
 // d = 256, B = 4 12 us with 16 waves, 6 with 1; B = 514 16 | 7.
 // ------------------------------------------------------------------------------------------------
-constexpr int EMB_AHEAD = 8;   // rows in flight of a wave
+// Rows in flight of a wave; without runs to form, position rows of B = 256, T = 128, d = 1,024 take 12.6 us with 8 and 11.4 with 16.
+constexpr int emb_ahead(bool distinct) { return distinct ? 16 : 8; }
 constexpr int EMB_PIECE = 16;  // positions that are worth a wave
 
 // EMB_WAVES: the most waves that a launch may have; it has ncb * parts.
@@ -389,6 +390,7 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
     __shared__ float wred[EMB_WAVES];
     uint32_t* sid = lds;        // [T rounded up to 4] ids of this example
     uint16_t* order = reinterpret_cast<uint16_t*>(lds + (T + 3) / 4 * 4);  // [T] row index at each sorted position (T <= 4096)
+    constexpr int AHEAD = emb_ahead(DISTINCT);
     const int i = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nt = 64 * ncb * parts;
     bool bad = false;
@@ -444,17 +446,17 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
             const uint64_t addr = (uint64_t)base + (uint64_t)row * ((uint64_t)d * E);
             const int a_lo = (int)(uint32_t)addr, a_hi = (int)(addr >> 32);
             const uint64_t ends = DISTINCT ? 0 : __ballot(q0 + lane < hi && p > lo && sid[row] != sid[order[p > lo ? p - 1 : lo]]);
-            for (int u0 = 0; u0 < 64 && u0 < n; u0 += EMB_AHEAD) {
-                RawVec<BF16, VW> g[EMB_AHEAD];
+            for (int u0 = 0; u0 < 64 && u0 < n; u0 += AHEAD) {
+                RawVec<BF16, VW> g[AHEAD];
                 const int left = n - u0;
                 const uint32_t e = (uint32_t)(ends >> u0);
 #pragma unroll
-                for (int u = 0; u < EMB_AHEAD; ++u) {
+                for (int u = 0; u < AHEAD; ++u) {
                     const uint64_t r = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(a_hi, u0 + u) << 32 | (uint32_t)__builtin_amdgcn_readlane(a_lo, u0 + u);
                     g[u] = load_raw<BF16, VW>((rw_global)r, at);
                 }
 #pragma unroll
-                for (int u = 0; u < EMB_AHEAD; ++u) {
+                for (int u = 0; u < AHEAD; ++u) {
                     if (u >= left) continue;
                     if constexpr (DISTINCT) {
 #pragma unroll
