@@ -14,6 +14,7 @@ namespace {
 // ------------------------------------------------------------------------------------------------
 // (non-temporal: every input byte of these kernels is read once and by one workgroup)
 typedef uint32_t rw_u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t rw_u32x4 __attribute__((ext_vector_type(4)));
 // The same in two steps, for loads that stay in flight: raw bits (RawVec), then values.
 template <bool BF16, int VW>
 struct RawVec {
@@ -556,14 +557,17 @@ __device__ __forceinline__ uint32_t sort_key(const uint32_t* __restrict__ keys, 
 }
 
 // hist[b * pitch + c] = number of keys of chunk c whose digit is b (integer counters in LDS: the order of the
-// additions does not matter).  FIRST: `keys` are the ids, range-checked here.
+// additions does not matter).  FIRST: `keys` are the ids, range-checked here, and `tickets` is cleared for the sums.
 template <bool FIRST>
 __global__ __launch_bounds__(256) void sort_hist(const uint32_t* __restrict__ keys, int N, int V, int shift,
-                                                 uint32_t* __restrict__ hist, int nchunks, int pitch, int* __restrict__ err) {
+                                                 uint32_t* __restrict__ hist, int nchunks, int pitch, uint32_t* __restrict__ tickets, int n_tickets,
+                                                 int* __restrict__ err) {
     __shared__ uint32_t cnt[256];
     const int c = blockIdx.x;
     const int n0 = c * SORT_CHUNK;
     const int valid = N - n0 < SORT_CHUNK ? N - n0 : SORT_CHUNK;
+    if (FIRST)
+        for (int e = c * 256 + threadIdx.x; e < n_tickets; e += gridDim.x * 256) tickets[e] = 0;
     cnt[threadIdx.x] = 0;
     __syncthreads();
     bool bad = false;
@@ -740,173 +744,414 @@ __global__ __launch_bounds__(256) void sort_scatter(const uint32_t* __restrict__
     }
 }
 
-// Ordered segment sums over the sorted (id, row) list.  A workgroup owns the SEG_CHUNK sorted positions [pc*SEG_CHUNK, ...)
-// and 256*VW columns, 64*VW a wave.  A run of equal ids that lies wholly inside the chunk is added to sum_E directly (this
-// workgroup is its only writer).  A run that continues from the previous chunk goes to first[pc], a run that starts here
-// and continues into the next chunk goes to last[pc]; segment_fixup_kernel adds those pieces in chunk order.
-// The table row of a finished run is asked for when the run ends and written when the next one does, so that its round trip
-// hides behind the rows that follow.  Clip factors are formed here.  B * T = 65,536, d = 1024: 57 -> 41 us
-// (134 MB of rows, 80 MB of the table and 30 MB of pieces: near what memory gives).
-constexpr int SEG_CHUNK = 32;
+// One launch that brings the positions of equal ids together, for up to GROUP_MAX_N positions.  The ids are dealt to 2^lg buckets by
+// their low lg bits; a workgroup writes the positions of one of the PARTS of a bucket to their places.  Its waves share all positions; each
+// counts, over all of its own, those of lower buckets (the bucket's place in the output) and by digit (the bits above lg, an id of its own
+// each) those of the bucket, then writes those of the part: the bucket's digits in order, in a digit the waves, in a wave the parts, in a part
+// the groups of 64 positions, in these by ballots.  So equal ids keep the order of their positions; the order of the ids does not matter to the sums.
+// `tickets` is cleared for the sums.  Bound: the instructions of the count, which takes the low bytes of four groups at a time.
+// Us, with the four launches of a histogram and a scatter per digit of 8 bits that took its place before: 464 positions 4.2 | 18, 16,384 7.6 | 18,
+// 65,536 20.7 | 24 (of 30,522 ids); beyond, and with more than 65,408 ids, they still are the sort.
+constexpr int GROUP_DIGITS = 512, GROUP_WAVES = 16, GROUP_MAX_N = 64 * 64 * GROUP_WAVES, GROUP_MAX_V = (GROUP_DIGITS - 1) << 7;
+// Low bits: 64 buckets where there are as many ids, 128 where the digits do not suffice for the rest and for the one of ids out of range.
+inline int group_bits(int V) {
+    int lg = 0;
+    while (lg < 6 && (1 << lg) < V) ++lg;
+    while (((V - 1) >> lg) + 1 >= GROUP_DIGITS) ++lg;
+    return lg;
+}
 
-template <bool BF16, int VW>
-__global__ __launch_bounds__(256) void segment_sums_kernel(const uint32_t* __restrict__ keys,
-                                                           const uint32_t* __restrict__ vals,
-                                                           const void* __restrict__ G, const float* __restrict__ sqnorms, float C,
-                                                           int N, int T, int d, int V, float* __restrict__ sum_E,
-                                                           float* __restrict__ first, float* __restrict__ last, int* __restrict__ err) {
-    __shared__ uint32_t skey[SEG_CHUNK + 2];  // [0] = key before the chunk, [1..n] = chunk, [n+1] = key after
-    __shared__ uint32_t srow[SEG_CHUNK];
-    __shared__ float sc[SEG_CHUNK];
-    const int pc = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int p0 = pc * SEG_CHUNK;
-    const int n = N - p0 < SEG_CHUNK ? N - p0 : SEG_CHUNK;
-    const uint32_t NONE = 0xFFFFFFFFu;
-    if ((int)threadIdx.x < n) {
-        const int k = threadIdx.x;
-        skey[1 + k] = keys[p0 + k];
-        const uint32_t row = vals[p0 + k];
-        srow[k] = row;
-        const float c = dp_clip_factor(sqnorms[row / (uint32_t)T], C);
-        sc[k] = c;
-        if (c != c) atomicOr(err, DP_ERRBIT_NORM);
-    }
-    if (threadIdx.x == 64) skey[0] = p0 > 0 ? keys[p0 - 1] : NONE;
-    if (threadIdx.x == 65) skey[n + 1] = p0 + n < N ? keys[p0 + n] : NONE;
-    __syncthreads();
-    const int col = ((blockIdx.y * 4 + wave) * 64 + lane) * VW;
-    if (col >= d) return;
-    float acc[VW], pend[VW], old[VW];  // the run under way; a finished run and the table row it adds to
-    float* pdst = nullptr;
+// A wave has Q * PARTS groups of 64 positions, Q of them in each part.
+template <int Q, int PARTS>
+__global__ __launch_bounds__(64 * GROUP_WAVES) void group_ids_kernel(const int32_t* __restrict__ ids, int N, int V, int lg,
+                                                                     uint32_t* __restrict__ keys, uint32_t* __restrict__ rows,
+                                                                     uint32_t* __restrict__ tickets, int n_tickets, int* __restrict__ err) {
+    constexpr int W = GROUP_WAVES, QUAD = Q < 4 ? Q : 4;
+    __shared__ uint32_t cnt[2][W][GROUP_DIGITS];  // of a wave's own positions: in the parts before this one, in the others
+    __shared__ uint32_t below[W], wtot[GROUP_DIGITS / 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = blockIdx.x >> lg;
+    const uint32_t mask = (1u << lg) - 1u, b = blockIdx.x & mask, none = ((uint32_t)(V - 1) >> lg) + 1u;  // none: the digit of ids out of range
+    const int w0 = wave * (Q * PARTS * 64);
+    // Places past the last position hold an id out of range of the last bucket: they come behind everything and are not written.
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc((void*)ids, 0, N * 4, 0x00020000);
+    auto load = [&](uint32_t (&id)[Q], int q) {
 #pragma unroll
-    for (int k = 0; k < VW; ++k) acc[k] = pend[k] = old[k] = 0.f;
-    auto flush = [&]() {
-        if (pdst) {
-#pragma unroll
-            for (int e = 0; e < VW; ++e) pdst[e] = old[e] + pend[e];
-        }
+        for (int u = 0; u < Q; ++u) id[u] = __builtin_amdgcn_raw_buffer_load_b32(src, lane * 4 + (q * Q + u) * 256, w0 * 4, 0);
     };
-    int seg_start = 0;
-    constexpr int AHEAD = 16;
-    for (int k0 = 0; k0 < n; k0 += AHEAD) {
-        float g[AHEAD][VW];
+    auto close = [&](uint32_t (&id)[Q], int q) {
+        if (w0 + (q * Q + Q) * 64 <= N) return;
 #pragma unroll
-        for (int u = 0; u < AHEAD; ++u) {
-            const int k = k0 + u < n ? k0 + u : n - 1;
-            load_vec<BF16, VW>(G, (size_t)srow[k] * d + col, g[u]);
-        }
+        for (int u = 0; u < Q; ++u) id[u] = w0 + (q * Q + u) * 64 + lane < N ? id[u] : 0xFFFFFFFFu;
+    };
+    auto digit = [&](uint32_t k) { return k < (uint32_t)V ? k >> lg : none; };
+    uint32_t mine[Q], id[2][Q];
+    load(id[0], 0);
+    load(mine, part);
+    if (threadIdx.x <= none) {
 #pragma unroll
-        for (int u = 0; u < AHEAD; ++u) {
-            const int k = k0 + u;
-            if (k < n) {
-                const uint32_t key = skey[1 + k];
-                const float w = sc[k];
+        for (int w = 0; w < W; ++w) cnt[0][w][threadIdx.x] = cnt[1][w][threadIdx.x] = 0;
+    }
+    for (int e = blockIdx.x * 64 * W + threadIdx.x; e < n_tickets; e += gridDim.x * 64 * W) tickets[e] = 0;
+    __syncthreads();
+    const uint32_t mask4 = mask * 0x01010101u, b4 = b * 0x01010101u;  // (lg <= 7: the high bit of each byte is free)
+    uint32_t lower = 0;
 #pragma unroll
-                for (int e = 0; e < VW; ++e) acc[e] += w * g[u][e];
-                if (skey[2 + k] != key) {  // the run ends at position k (the same for all lanes)
-                    if (key < (uint32_t)V) {
-                        if (seg_start == 0 && skey[0] == key) {
-                            float* dst = first + (size_t)pc * d + col;
+    for (int q = 0; q < PARTS; ++q) {
+        if (q + 1 < PARTS) load(id[(q + 1) & 1], q + 1);
+        close(id[q & 1], q);
+        uint32_t* __restrict__ to = cnt[q < part ? 0 : 1][wave];
+        uint32_t seen = 0, times = 0;  // a lane counts an id that follows itself by itself: most of a frequent one's
 #pragma unroll
-                            for (int e = 0; e < VW; ++e) dst[e] = acc[e];
-                        } else {
-                            flush();
-                            pdst = sum_E + (size_t)key * d + col;
+        for (int u = 0; u < Q; u += QUAD) {
+            uint32_t k[4];
 #pragma unroll
-                            for (int e = 0; e < VW; ++e) {
-                                old[e] = pdst[e];
-                                pend[e] = acc[e];
-                            }
-                        }
+            for (int e = 0; e < 4; ++e) k[e] = id[q & 1][u + (e < QUAD ? e : 0)];
+            uint32_t low = (k[0] & 0xFFu) | (k[1] & 0xFFu) << 8 | (k[2] & 0xFFu) << 16 | k[3] << 24;
+            low &= mask4;
+            constexpr uint32_t USED = QUAD == 4 ? 0x80808080u : QUAD == 2 ? 0x8080u : 0x80u;
+            lower += (uint32_t)__popc(~((low | 0x80808080u) - b4) & USED);  // a byte's high bit stays where it is not below b
+            uint32_t eq = ~((low ^ b4) + 0x7F7F7F7Fu) & USED;               // ... where it differs from b
+            while (__builtin_amdgcn_ballot_w64(eq != 0)) {  // each lane's next one
+                if (eq) {
+                    const uint32_t e = __builtin_ctz(eq);
+                    const uint32_t x = e < 16 ? (e < 8 ? k[0] : k[1]) : (e < 24 ? k[2] : k[3]);
+                    if (x != seen && times) {
+                        atomicAdd(&to[digit(seen)], times);
+                        times = 0;
                     }
-#pragma unroll
-                    for (int e = 0; e < VW; ++e) acc[e] = 0.f;
-                    seg_start = k + 1;
+                    seen = x;
+                    ++times;
+                    eq &= eq - 1;
                 }
             }
         }
+        if (times) atomicAdd(&to[digit(seen)], times);
     }
-    if (seg_start < n) {
-        // the last run continues into the next chunk (skey[n+1] equals its key)
-        const uint32_t key = skey[n];
-        if (key < (uint32_t)V) {
-            const bool from_prev = seg_start == 0 && skey[0] == key;
-            float* dst = from_prev ? first + (size_t)pc * d + col : last + (size_t)pc * d + col;
 #pragma unroll
-            for (int e = 0; e < VW; ++e) dst[e] = acc[e];
+    for (int o = 32; o > 0; o >>= 1) lower += (uint32_t)__shfl_xor((int)lower, o, 64);
+    if (lane == 0) below[wave] = lower;
+    __syncthreads();
+    uint32_t total = 0, incl = 0;
+    if (threadIdx.x < GROUP_DIGITS) {
+        uint32_t x[W], y[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            x[w] = threadIdx.x <= none ? cnt[0][w][threadIdx.x] : 0u;
+            y[w] = threadIdx.x <= none ? cnt[1][w][threadIdx.x] : 0u;
+        }
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t t = x[w] + y[w];
+            x[w] += total;  // where the part's positions of this wave begin
+            total += t;
+        }
+        incl = total;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t up = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += up;
+        }
+        if (lane == 63) wtot[wave] = incl;
+#pragma unroll
+        for (int w = 0; w < W; ++w) cnt[1][w][threadIdx.x] = x[w] + incl - total;
+    }
+    __syncthreads();
+    uint32_t base = 0;  // of the bucket; and, in a digit's thread, of the waves of digits before its own
+#pragma unroll
+    for (int w = 0; w < W; ++w) base += below[w];
+    uint32_t* __restrict__ from = cnt[1][wave];
+    uint32_t* __restrict__ keys_b = keys + __builtin_amdgcn_readfirstlane((int)base);
+    uint32_t* __restrict__ rows_b = rows + __builtin_amdgcn_readfirstlane((int)base);
+    // (places inside 64 digits so far: the digits of the waves before are added here)
+    uint32_t pre = 0;
+#pragma unroll
+    for (int w = 0; w < GROUP_DIGITS / 64; ++w) {
+        const uint32_t t = wtot[w];
+        if (lane == w) base = pre;
+        pre += t;
+    }
+    bool bad = false;
+    close(mine, part);
+#pragma unroll
+    for (int u = 0; u < Q; ++u) {
+        const uint32_t k = mine[u], dgt = digit(k);
+        const int p = w0 + (part * Q + u) * 64 + lane;
+        const bool own = (k & mask) == b && p < N;
+        uint64_t rest = __builtin_amdgcn_ballot_w64(own);
+        if (rest == 0) continue;
+        const uint32_t at = own ? from[dgt] : 0u, block = (uint32_t)__shfl((int)base, (int)(dgt >> 6), 64);
+        uint32_t rank = 0, all = 1;
+        if (rest & (rest - 1)) {
+            while (rest) {  // one distinct digit after the other
+                const uint64_t same = __builtin_amdgcn_ballot_w64(own && dgt == (uint32_t)__builtin_amdgcn_readlane((int)dgt, __builtin_ctzll(rest)));
+                if (same >> lane & 1) {
+                    rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+                    all = (uint32_t)__popcll(same);
+                }
+                rest &= ~same;
+            }
+        }
+        if (own) {
+            keys_b[at + block + rank] = dgt == none ? (uint32_t)V : k;
+            rows_b[at + block + rank] = (uint32_t)p;
+            if (rank == 0) from[dgt] = at + all;
+            bad |= dgt == none;
         }
     }
-    flush();
+    if (bad) atomicOr(err, DP_ERRBIT_INDEX);
 }
 
-// Workgroups (pc, column block) for every chunk pc whose last run starts in pc and continues into pc+1: add last[pc],
-// then first[q] for the chunks q = pc+1 .. that the run reaches, and add the total to sum_E[key].  The end of the run is found by
-// bisection of the sorted keys (the most frequent token spans hundreds of chunks); four groups of threads take the pieces
-// q = pc+1+g, pc+5+g, ... in ascending order, eight loads in flight, and their sums are added as (0+1)+(2+3): fixed order.
-// 64 * VW columns a workgroup.  22 -> 12 us (one group, one column a thread, before).
-template <int VW>
-__global__ __launch_bounds__(256) void segment_fixup_kernel(const uint32_t* __restrict__ keys, int N, int d, int V,
-                                                            int nchunks, const float* __restrict__ first,
-                                                            const float* __restrict__ last,
-                                                            float* __restrict__ sum_E) {
-    __shared__ float red[4][64][VW];
-    const int pc = blockIdx.x;
-    const int pend = (pc + 1) * SEG_CHUNK;  // first position of the next chunk
-    if (pend >= N) return;
-    const uint32_t key = keys[pend - 1];
-    if (key >= (uint32_t)V || keys[pend] != key) return;             // no run crosses this boundary
-    const int p0 = pc * SEG_CHUNK;
-    if (p0 > 0 && keys[p0 - 1] == key && keys[p0] == key) return;    // the run started earlier: not its head
-    int lo = pend, hi = N;  // keys[lo] == key; the run ends at the first position in (lo, hi] whose key differs
-    // most runs end in the next chunk: look there before bisecting
-    if (pend + SEG_CHUNK >= N || keys[pend + SEG_CHUNK] != key) hi = pend + 1;
-    while (hi - lo > 1) {
-        const int mid = lo + (hi - lo) / 2;
-        if (keys[mid] == key) lo = mid;
-        else hi = mid;
+// Ordered segment sums over the grouped (id, row) list.  A workgroup owns 4 PW positions and 64 VW columns, a wave PW of the positions in
+// turn: the factors, row addresses and run ends of its positions sit one a lane and are read back as scalars; 8 rows, and the table rows of the
+// runs that end in them, are in flight.  A run that lies inside a wave is added to sum_E there (this wave is its only writer).  What crosses waves is joined in LDS in their order, what crosses workgroups goes to `first`
+// (continues from the workgroup before) or `last` (starts here); the workgroup of such a run that takes its last ticket adds those pieces in order:
+// wave g the pieces h + 1 + g, h + 5 + g, ... of the run from workgroup h on, then the waves in order.  The order is fixed, only who does it is not.
+// Pieces are written and read past the caches of an XCD, and a workgroup's pieces have arrived before it takes its ticket.
+// Bound: HBM where there are many positions, otherwise the chain id - row - piece - ticket - piece.  Us, with the sums of the sort's 32-position chunks and the second
+// launch that joined them before: B * T = 65,536, d = 1,024 48.8 | 41 + 12 (134 MB of rows, 80 MB of the table), 16,384, d = 768 14.8 | 10 + 7, 464, d = 128 7.3 | 12.
+constexpr int SEG_WAVES = 4;
+
+template <int PW, bool BF16, int VW>
+__global__ __launch_bounds__(64 * SEG_WAVES) void segment_sums_kernel(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ rows,
+                                                           const void* __restrict__ G, const float* __restrict__ sqnorms, float C, int N, int T, int d,
+                                                           int V, int ncb, uint32_t* __restrict__ tickets,
+                                                           float* __restrict__ sum_E, float* __restrict__ first, float* __restrict__ last,
+                                                           int* __restrict__ err) {
+    constexpr int WAVES = SEG_WAVES, SEG = WAVES * PW, AHEAD = 8, COLS = 64 * VW;
+    static_assert(PW % AHEAD == 0 && PW < 63, "a wave's positions, the one after them and the one before them sit one a lane");
+    constexpr uint32_t HEAD = 1, WHOLE = 2, TAIL = 4;  // of a wave: its first run continues one, is its only one and goes on; its last run (another) goes on
+    __shared__ float head[WAVES][COLS], tail[WAVES][COLS];
+    __shared__ uint32_t flags[WAVES], wkey[WAVES][2], mine[2];
+    __shared__ int span[3];  // the run that covers the first position: its first and last workgroup; the last one of the run that covers the position behind
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int pc = blockIdx.x / ncb, cb = blockIdx.x - pc * ncb, p0 = pc * SEG, col0 = cb * COLS;
+    const int lo = p0 + wave * PW, n = N - lo < 0 ? 0 : N - lo < PW ? N - lo : PW;  // this wave's positions
+    // The run that covers position k SEG reaches as many workgroups on (STEP 1) or back (-1) as there is its id at their first positions.
+    const int nseg = (N + SEG - 1) / SEG;
+    auto reach = [&](int k, int step) {
+        const uint32_t key = keys[k * SEG];
+        for (;;) {
+            const int j = k + step * (lane + 1);
+            const uint64_t off = __builtin_amdgcn_ballot_w64(j < 0 || j >= nseg || keys[(j < 0 || j >= nseg ? 0 : j) * SEG] != key);
+            if (off) return k + step * __builtin_ctzll(off);
+            k += step * 64;
+        }
+    };
+    if (wave == 0) {
+        const int j = reach(pc, -1);
+        if (lane == 0) span[0] = j > 0 && keys[j * SEG - 1] == keys[j * SEG] ? j - 1 : j;
+    } else if (wave == 1) {
+        const int j = reach(pc, 1);
+        if (lane == 0) span[1] = j;
+    } else if (wave == 2 && pc + 1 < nseg) {
+        const int j = reach(pc + 1, 1);
+        if (lane == 0) span[2] = j;
     }
-    const int qlast = lo / SEG_CHUNK;  // every chunk pc+1 .. qlast starts inside the run, so its first[] holds a piece
-    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int col = (blockIdx.y * 64 + lane) * VW;
-    float acc[VW];
-#pragma unroll
-    for (int e = 0; e < VW; ++e) acc[e] = 0.f;
-    if (col < d) {
-        auto piece = [&](const float* __restrict__ src, int q, float out[VW]) {
-            if constexpr (VW == 4) {
-                const float4 t = *reinterpret_cast<const float4*>(src + (size_t)q * d + col);
-                out[0] = t.x; out[1] = t.y; out[2] = t.z; out[3] = t.w;
-            } else {
-                out[0] = src[(size_t)q * d + col];
-            }
+    uint32_t flag = 0, k_first = 0, k_last = 0;
+    if (n > 0) {
+        constexpr int E = BF16 ? 2 : 4;
+        const int col = col0 + lane * VW;
+        const int p = lane == 63 ? (lo > 0 ? lo - 1 : 0) : lane <= n ? lo + lane : lo;
+        const uint32_t key = keys[p < N ? p : N - 1];
+        const uint32_t row = rows[lane < n ? lo + lane : lo];
+        const float c = dp_clip_factor(sqnorms[row / (uint32_t)T], C);
+        if (c != c) atomicOr(err, DP_ERRBIT_NORM);
+        const uint64_t addr = (uint64_t)G + ((uint64_t)row * (uint64_t)d + col0) * E;
+        const int a_lo = (int)(uint32_t)addr, a_hi = (int)(addr >> 32);
+        const uint32_t at = ((col < d ? col : d - VW) - col0) * E;  // (lanes past the width read its last columns again)
+        const uint32_t next = (uint32_t)__shfl_down((int)key, 1, 64);
+        const uint64_t ends = __builtin_amdgcn_ballot_w64(lane < n && (lo + lane + 1 >= N || next != key));
+        k_first = (uint32_t)__builtin_amdgcn_readlane((int)key, 0);
+        k_last = (uint32_t)__builtin_amdgcn_readlane((int)key, n - 1);
+        const bool from_prev = lo > 0 && (uint32_t)__builtin_amdgcn_readlane((int)key, 63) == k_first;
+        // The table row that the run ending at this lane's position is added to: no bytes where none ends, or where it began before this
+        // wave, or for ids out of range: such an access touches no memory.
+        const bool adds = (ends >> lane & 1) && key < (uint32_t)V && !(from_prev && lane == __builtin_ctzll(ends | 1ull << 63));
+        const uint64_t taddr = (uint64_t)sum_E + ((uint64_t)(adds ? key : 0u) * (uint64_t)d + col0) * 4u;
+        const int t_lo = (int)(uint32_t)taddr, t_hi = (int)(taddr >> 32), t_len = adds ? (d - col0) * 4 : 0;
+        auto table = [&](int k) {
+            const uint64_t r = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(t_hi, k) << 32 | (uint32_t)__builtin_amdgcn_readlane(t_lo, k);
+            return __builtin_amdgcn_make_buffer_rsrc((void*)r, 0, __builtin_amdgcn_readlane(t_len, k), 0x00020000);
         };
-        if (g == 0) piece(last, pc, acc);
-        int q = pc + 1 + g;
-        for (; q + 28 <= qlast; q += 32) {
-            float f[8][VW];
+        float acc[VW];  // the run under way
 #pragma unroll
-            for (int u = 0; u < 8; ++u) piece(first, q + 4 * u, f[u]);
+        for (int e = 0; e < VW; ++e) acc[e] = 0.f;
+        bool begun = from_prev;  // it began before this wave
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
+        for (int k0 = 0; k0 < PW; k0 += AHEAD) {
+            if (k0 >= n) break;
+            RawVec<BF16, VW> g[AHEAD];
+            float old[AHEAD][VW];
 #pragma unroll
-                for (int e = 0; e < VW; ++e) acc[e] += f[u][e];
+            for (int u = 0; u < AHEAD; ++u) {  // (lanes past the last position hold the address of the first)
+                const uint64_t r = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(a_hi, k0 + u) << 32 | (uint32_t)__builtin_amdgcn_readlane(a_lo, k0 + u);
+                g[u] = load_raw<BF16, VW>((rw_global)r, at);
+            }
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                if constexpr (VW == 4) {
+                    const f32x4_t t = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(table(k0 + u), lane * 16, 0, 0));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) old[u][e] = t[e];
+                } else {
+                    old[u][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(table(k0 + u), lane * 4, 0, 0));
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                if (k0 + u >= n) continue;
+                const float w = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(c), k0 + u));
+#pragma unroll
+                for (int e = 0; e < VW; ++e) acc[e] += w * raw_value<BF16, VW>(g[u], e);
+                if (!(ends >> (k0 + u) & 1)) continue;
+                if (begun) {
+                    flag |= HEAD;
+#pragma unroll
+                    for (int e = 0; e < VW; ++e) head[wave][lane * VW + e] = acc[e];
+                } else if constexpr (VW == 4) {
+                    const f32x4_t t = {old[u][0] + acc[0], old[u][1] + acc[1], old[u][2] + acc[2], old[u][3] + acc[3]};
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(rw_u32x4, t), table(k0 + u), lane * 16, 0, 0);
+                } else {
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(old[u][0] + acc[0]), table(k0 + u), lane * 4, 0, 0);
+                }
+                begun = false;
+#pragma unroll
+                for (int e = 0; e < VW; ++e) acc[e] = 0.f;
+            }
         }
-        for (; q <= qlast; q += 4) {
-            float f[VW];
-            piece(first, q, f);
+        if (!(ends >> (n - 1) & 1)) {
+            flag |= begun ? HEAD | WHOLE : TAIL;
 #pragma unroll
-            for (int e = 0; e < VW; ++e) acc[e] += f[e];
+            for (int e = 0; e < VW; ++e) (begun ? head : tail)[wave][lane * VW + e] = acc[e];
         }
     }
-#pragma unroll
-    for (int e = 0; e < VW; ++e) red[g][lane][e] = acc[e];
+    if (lane == 0) {
+        flags[wave] = flag;
+        wkey[wave][0] = k_first;
+        wkey[wave][1] = k_last;
+    }
     __syncthreads();
-    if (g == 0 && col < d) {
-        float* dst = sum_E + (size_t)key * d + col;
+    // Join: a thread per column walks the waves.  First, for all alike, what becomes of each wave's first run: `open`: a run is under way,
+    // `in`: it came from the workgroup before; the table rows of the runs that end are asked for here.
+    const int c = threadIdx.x < COLS ? threadIdx.x : 0, col = col0 + c;
+    const bool on = threadIdx.x < COLS && col < d;
+    uint32_t f[WAVES], ends_in[WAVES];  // ends_in[w]: the id of the run that ends in wave w
+    bool open = false, in = false, in_piece = false;
+    uint32_t open_key = 0;
+    float old[WAVES];
 #pragma unroll
-        for (int e = 0; e < VW; ++e)
-            dst[e] += (red[0][lane][e] + red[1][lane][e]) + (red[2][lane][e] + red[3][lane][e]);
+    for (int w = 0; w < WAVES; ++w) {
+        f[w] = (uint32_t)__builtin_amdgcn_readfirstlane((int)flags[w]);
+        ends_in[w] = (uint32_t)V;
+        old[w] = 0.f;
+        if (f[w] & HEAD) {
+            if (!open) {
+                open = in = true;
+                open_key = (uint32_t)__builtin_amdgcn_readfirstlane((int)wkey[w][0]);
+            }
+            if (!(f[w] & WHOLE)) {
+                if (in) in_piece = open_key < (uint32_t)V;
+                else ends_in[w] = open_key;
+                open = in = false;
+                if (ends_in[w] < (uint32_t)V && on) old[w] = sum_E[(size_t)ends_in[w] * d + col];
+            }
+        }
+        if (f[w] & TAIL) {
+            open = true;
+            open_key = (uint32_t)__builtin_amdgcn_readfirstlane((int)wkey[w][1]);
+        }
+    }
+    const uint32_t in_key = (uint32_t)__builtin_amdgcn_readfirstlane((int)wkey[0][0]);
+    const bool out = open && !in && open_key < (uint32_t)V;  // a run that starts here goes on
+    in_piece = in_piece || (open && in && open_key < (uint32_t)V);
+    {
+        float carry = 0.f;
+        bool from_before = f[0] & HEAD;
+        auto put = [&](float* dst) {
+            if (on) __hip_atomic_store(dst + (size_t)pc * d + col, carry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            if (f[w] & HEAD) {
+                carry += head[w][c];
+                if (!(f[w] & WHOLE)) {
+                    if (from_before && in_piece) put(first);
+                    else if (ends_in[w] < (uint32_t)V && on) sum_E[(size_t)ends_in[w] * d + col] = old[w] + carry;
+                    from_before = false;
+                }
+            }
+            if (f[w] & TAIL) {
+                carry = tail[w][c];
+                from_before = false;
+            }
+        }
+        if (out) put(last);
+        else if (open && in_piece && in) put(first);
+    }
+    if (!in_piece && !out) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0 || threadIdx.x == 64) {
+        const bool take = threadIdx.x == 0 ? in_piece : out;
+        const int h = threadIdx.x == 0 ? span[0] : pc, q = threadIdx.x == 0 ? span[1] : span[2];
+        mine[threadIdx.x >> 6] =
+            take && __hip_atomic_fetch_add(&tickets[h * ncb + cb], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(q - h) ? 1u : 0u;
+    }
+    __syncthreads();
+    for (int s = 0; s < 2; ++s) {
+        if (!__builtin_amdgcn_readfirstlane((int)mine[s])) continue;
+        const int h = s == 0 ? span[0] : pc, qlast = s == 0 ? span[1] : span[2];
+        const uint32_t key = s == 0 ? in_key : open_key;
+        const float was = on ? sum_E[(size_t)key * d + col] : 0.f;
+        const int lcol = col0 + lane * VW;
+        float acc[VW];
+#pragma unroll
+        for (int e = 0; e < VW; ++e) acc[e] = 0.f;
+        if (lcol < d) {
+            constexpr int SC1 = 16;  // past this XCD's caches
+            auto piece = [&](const float* src, int q, float (&x)[VW]) {
+                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)(src + (size_t)q * d), 0, d * 4, 0x00020000);
+                if constexpr (VW == 4) {
+                    const f32x4_t t = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, lcol * 4, 0, SC1));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = t[e];
+                } else {
+                    x[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, lcol * 4, 0, SC1));
+                }
+            };
+            float f0[VW];
+#pragma unroll
+            for (int e = 0; e < VW; ++e) f0[e] = 0.f;
+            if (wave == 0) piece(last, h, f0);
+            constexpr int AT_ONCE = 8;
+            for (int q = h + 1 + wave; q <= qlast; q += AT_ONCE * WAVES) {
+                float x[AT_ONCE][VW];
+#pragma unroll
+                for (int u = 0; u < AT_ONCE; ++u) {
+                    if (q + WAVES * u <= qlast) piece(first, q + WAVES * u, x[u]);
+                    else
+#pragma unroll
+                        for (int e = 0; e < VW; ++e) x[u][e] = 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < AT_ONCE; ++u)
+#pragma unroll
+                    for (int e = 0; e < VW; ++e) acc[e] += x[u][e];
+            }
+#pragma unroll
+            for (int e = 0; e < VW; ++e) acc[e] += f0[e];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < VW; ++e) head[wave][lane * VW + e] = acc[e];
+        __syncthreads();
+        if (on) {
+            float t = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) t += head[w][c];
+            sum_E[(size_t)key * d + col] = was + t;
+        }
     }
 }
 
@@ -1180,54 +1425,73 @@ static dp_status embedding_sums_launch(dp_ctx* ctx, const int32_t* ids, const vo
         return DP_ERR_SHAPE;
     }
     const int N = (int)Nl;
-    const int nsort = (N + SORT_CHUNK - 1) / SORT_CHUNK;
-    const int nseg = (N + SEG_CHUNK - 1) / SEG_CHUNK;
+    const int ncb = (d + 64 * VW - 1) / (64 * VW);
+    // Positions a wave: 8 while that does not fill the chip (B * T = 8,192, d = 768: 29.5 us the call with 8, 31.6 with 16, 34.6 with 32),
+    // 16, and 32 once it does twice over (65,536, d = 1,024: 113 | 102 | 99); 32 also where few ids make long runs, whose pieces
+    // are what the last of their workgroups adds (32,768 of 2 ids: 102 | 68 | 55).
+    const long tiles = Nl * ncb;
+    // (What a choice needs of the workspace is no more than two pairs of lists, a radix sort's counters and two rows per 32 positions.)
+    const bool group = N <= GROUP_MAX_N && V <= GROUP_MAX_V;
+    const int pw = !group || ncb > 64 || tiles > 131072 || Nl >= 256l * V ? 32 : tiles > 32768 ? 16 : 8;
+    const int seg = SEG_WAVES * pw, nseg = (N + seg - 1) / seg;
     dp_ws_alloc ws(ctx);
     uint32_t* k0 = ws.get<uint32_t>(N);
-    uint32_t* k1 = ws.get<uint32_t>(N);
     uint32_t* v0 = ws.get<uint32_t>(N);
-    uint32_t* v1 = ws.get<uint32_t>(N);
-    uint32_t* hist;
-    float *first, *last;
-    const size_t mark = ws.off;
+    uint32_t* tickets = ws.get<uint32_t>((size_t)nseg * ncb);
+    float* first = ws.get<float>((size_t)nseg * d);
+    float* last = ws.get<float>((size_t)nseg * d);
+    uint32_t *k1 = nullptr, *v1 = nullptr, *hist = nullptr;
+    const int nsort = (N + SORT_CHUNK - 1) / SORT_CHUNK;
     int pitch = sort_pitch(nsort);
-    for (;; pitch = nsort) {  // without padding when there is no room for it: the scan takes any pitch
-        ws.off = mark;
+    if (!group) {
+        k1 = ws.get<uint32_t>(N);
+        v1 = ws.get<uint32_t>(N);
         hist = ws.get<uint32_t>((size_t)256 * pitch);
-        first = ws.get<float>((size_t)nseg * d);
-        last = ws.get<float>((size_t)nseg * d);
-        if ((hist && first && last) || pitch == nsort) break;
+        if (!hist) hist = ws.get<uint32_t>((size_t)256 * (pitch = nsort));  // without padding when there is no room for it: the scan takes any pitch
     }
-    if (!k0 || !k1 || !v0 || !v1 || !hist || !first || !last) {
+    if (!k0 || !v0 || !tickets || !first || !last || (!group && (!k1 || !v1 || !hist))) {
         DP_SET_ERR(ctx, "workspace too small for the embedding sort of %d tokens", N);
         return DP_ERR_WORKSPACE;
     }
-    const int bits = bit_length((uint32_t)V);  // the sentinel V itself must be representable
-    const bool scan = nsort > SORT_INLINE || pitch % 4 != 0;
-    const dim3 grid(nsort), block(256);
-    for (int shift = 0; shift < bits; shift += 8) {
-        const uint32_t* kin = shift ? k0 : reinterpret_cast<const uint32_t*>(ids);
-        if (shift) hipLaunchKernelGGL((sort_hist<false>), grid, block, 0, ctx->stream, kin, N, V, shift, hist, nsort, pitch, ctx->err_word);
-        else hipLaunchKernelGGL((sort_hist<true>), grid, block, 0, ctx->stream, kin, N, V, shift, hist, nsort, pitch, ctx->err_word);
-        if (scan) hipLaunchKernelGGL(sort_scan, dim3(1), block, 0, ctx->stream, hist, 256 * pitch);
-        auto scatter = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, ctx->stream, kin, v0, N, V, shift, hist, pitch, k1, v1); };
-        if (shift && scan) scatter(sort_scatter<false, false>);
-        else if (shift) scatter(sort_scatter<false, true>);
-        else if (scan) scatter(sort_scatter<true, false>);
-        else scatter(sort_scatter<true, true>);
-        DP_LAUNCH_CHECK(ctx, "radix sort pass");
-        uint32_t* t = k0; k0 = k1; k1 = t;
-        t = v0; v0 = v1; v1 = t;
+    const dim3 block(256);
+    if (group) {
+        const int lg = group_bits(V);
+        auto launch = [&](auto kernel, int parts) {
+            hipLaunchKernelGGL(kernel, dim3(parts << lg), dim3(64 * GROUP_WAVES), 0, ctx->stream, ids, N, V, lg, k0, v0, tickets, nseg * ncb, ctx->err_word);
+        };
+        if (N <= 64 * GROUP_WAVES) launch(group_ids_kernel<1, 1>, 1);
+        else if (N <= 4 * 64 * GROUP_WAVES) launch(group_ids_kernel<1, 4>, 4);
+        else if (N <= 8 * 64 * GROUP_WAVES) launch(group_ids_kernel<2, 4>, 4);
+        else if (N <= 16 * 64 * GROUP_WAVES) launch(group_ids_kernel<4, 4>, 4);
+        else if (N <= 32 * 64 * GROUP_WAVES) launch(group_ids_kernel<8, 4>, 4);
+        else launch(group_ids_kernel<16, 4>, 4);
+        DP_LAUNCH_CHECK(ctx, "group_ids");
+    } else {
+        const int bits = bit_length((uint32_t)V);  // the sentinel V itself must be representable
+        const bool scan = nsort > SORT_INLINE || pitch % 4 != 0;
+        const dim3 grid(nsort);
+        for (int shift = 0; shift < bits; shift += 8) {
+            const uint32_t* kin = shift ? k0 : reinterpret_cast<const uint32_t*>(ids);
+            if (shift) hipLaunchKernelGGL((sort_hist<false>), grid, block, 0, ctx->stream, kin, N, V, shift, hist, nsort, pitch, tickets, nseg * ncb, ctx->err_word);
+            else hipLaunchKernelGGL((sort_hist<true>), grid, block, 0, ctx->stream, kin, N, V, shift, hist, nsort, pitch, tickets, nseg * ncb, ctx->err_word);
+            if (scan) hipLaunchKernelGGL(sort_scan, dim3(1), block, 0, ctx->stream, hist, 256 * pitch);
+            auto scatter = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, ctx->stream, kin, v0, N, V, shift, hist, pitch, k1, v1); };
+            if (shift && scan) scatter(sort_scatter<false, false>);
+            else if (shift) scatter(sort_scatter<false, true>);
+            else if (scan) scatter(sort_scatter<true, false>);
+            else scatter(sort_scatter<true, true>);
+            DP_LAUNCH_CHECK(ctx, "radix sort pass");
+            uint32_t* t = k0; k0 = k1; k1 = t;
+            t = v0; v0 = v1; v1 = t;
+        }
     }
-    const int J = (d + 256 * VW - 1) / (256 * VW);
-    hipLaunchKernelGGL((segment_sums_kernel<BF16, VW>), dim3(nseg, J), dim3(256), 0, ctx->stream, k0, v0, G, sqnorms, C, N, T, d, V, sum_E, first, last, ctx->err_word);
+    auto sums = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(nseg * ncb)), block, 0, ctx->stream, k0, v0, G, sqnorms, C, N, T, d, V, ncb, tickets, sum_E, first, last, ctx->err_word);
+    };
+    if (pw == 8) sums(segment_sums_kernel<8, BF16, VW>);
+    else if (pw == 16) sums(segment_sums_kernel<16, BF16, VW>);
+    else sums(segment_sums_kernel<32, BF16, VW>);
     DP_LAUNCH_CHECK(ctx, "segment_sums");
-    if (nseg > 1) {
-        const bool v4 = d % 4 == 0;  // the pieces lie in the workspace, aligned
-        if (v4) hipLaunchKernelGGL((segment_fixup_kernel<4>), dim3(nseg - 1, (d + 255) / 256), dim3(256), 0, ctx->stream, k0, N, d, V, nseg, first, last, sum_E);
-        else hipLaunchKernelGGL((segment_fixup_kernel<1>), dim3(nseg - 1, (d + 63) / 64), dim3(256), 0, ctx->stream, k0, N, d, V, nseg, first, last, sum_E);
-        DP_LAUNCH_CHECK(ctx, "segment_fixup");
-    }
     return DP_OK;
 }
 

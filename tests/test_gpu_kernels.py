@@ -783,6 +783,44 @@ def test_many_layernorms_on_a_small_workspace(dp, layers_room):
             np.testing.assert_array_equal(got, want, err_msg=f"layer {l}")
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 264), ("f32", 260), ("f32", 70)])
+@pytest.mark.parametrize("N,V", [(1, 1), (63, 2), (65, 63), (1024, 64), (1025, 65), (4097, 511), (8193, 3), (16385, 32704), (65536, 65408),
+                                 (32769, 65409), (65537, 5)])
+def test_embedding_sums_at_the_edges_of_the_grouping(dp, dtype, d, N, V):
+    """Positions and ids around the sizes where the grouping changes form (64 to 65,536 positions; 64 and 128 buckets of 511 ids, and the
+    radix sort beyond), with frequent ids, ids that occur once and ids out of range: against sums in fp64, and the same bits again.
+    Tolerance: rounding of an fp32 sum of n terms in any order, n 2^-24 of the sum of magnitudes, far above what is seen."""
+    rng = np.random.default_rng(N + V)
+    ids = np.minimum(rng.zipf(1.3, N) - 1, V - 1).astype(np.int32)
+    ids[rng.random(N) < 0.3] = 0
+    some = rng.random(N) < 0.4
+    ids[some] = rng.integers(0, V, int(some.sum()))
+    out = rng.random(N) < 0.01
+    ids[out] = rng.choice(np.array([-1, V, V + 64, -2**31, 2**31 - 1], dtype=np.int64), int(out.sum())).astype(np.int32)
+    G, sq = gen((N, 1, d), 0.1, 863, dtype), syn.synthetic_sqnorms(N, 1.0, 864)
+    ids_d, G_d, sq_d = to_dev(ids.reshape(N, 1)), to_dev(G), f32_dev(sq)
+
+    def sums():
+        E = torch.full((V, d), 0.25, dtype=torch.float32, device=DEV)
+        dp.clip_accumulate_embedding(ids_d, G_d, V, 1.0, sq_d, E)
+        if out.any():
+            with pytest.raises(Exception, match="DP_ERR_INDEX"):
+                dp.sync()
+        else:
+            dp.sync()
+        return E
+
+    got = sums()
+    assert torch.equal(got, sums())
+    keep = torch.from_numpy(np.flatnonzero(~out)).to(DEV)
+    w = G_d.double().view(N, d) * torch.clamp(1.0 / sq_d.double().sqrt(), max=1.0)[:, None]
+    idx = ids_d.view(-1)[keep].long()
+    zero = torch.zeros(V, d, dtype=torch.float64, device=DEV)
+    ref, mag = zero.index_add(0, idx, w[keep]) + 0.25, zero.index_add(0, idx, w[keep].abs()) + 0.25
+    n = torch.bincount(idx, minlength=V)[:, None] + 8
+    assert bool(((got.double() - ref).abs() <= n * 2.0**-24 * mag).all())
+
+
 @pytest.mark.parametrize("B,T,d,V", [(4, 25, 8, 50), (9, 128, 8, 300), (8, 512, 64, 70000)])
 def test_embedding_sums_in_the_least_workspace(dp, B, T, d, V):
     """Room for two pairs of key and row lists, one counter per digit and 1,024 tokens, and two rows per 32 tokens is enough; the
