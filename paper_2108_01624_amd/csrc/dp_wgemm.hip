@@ -916,14 +916,23 @@ static DmaCost dma_cost(int bm, int bn, bool one_stage) {
     if (bm == 128 && bn == 128) return one_stage ? DmaCost{2, 0.9, 0.5, 5.0, 7.0} : DmaCost{2, 0.61, 0.40, 5.0, 7.0};
     return {1, 0.58, 0.58, 6.0, 7.0};
 }
+// The same for launches of several rounds of workgroups, fitted to 170 shapes timed with every tile and row split (2 to 65,536 rows, widths of
+// 64 to 4,096, 1 to 64 layers): the workgroups of later rounds do not run in step, so the bandwidth part is paid by the workgroup, whatever the round holds.
+static DmaCost dma_cost_rounds(int bm, int bn, bool one_stage) {
+    if (bm == 256 && bn == 256) return {1, 0.855, 0.855, 6.9, 16.3};
+    if (bm == 128 && bn == 128) return one_stage ? DmaCost{2, 0.75, 0.365, 3.2, 7.2} : DmaCost{2, 0.61, 0.375, 3.2, 7.2};
+    if (bm == 256) return {1, 0.575, 0.585, 6.5, 5.2};
+    return {1, 0.57, 0.55, 6.5, 5.2};
+}
 
 // Row-split count of one launch over `nl` layers of `ntiles` tiles: the count with the smallest modelled time, in
 // microseconds to *t_out.  An XCD runs 32 * wgs workgroups at a time and gets an eighth of the launch's workgroups, so
 // the launch takes ceil(workgroups / 8 / (32 wgs)) rounds of one workgroup's time; more than one split sends partial sums
 // through memory and costs one reduction launch (which finds most of them in the cache: 4 layers of 768 x 3072 in three
 // splits, 190 MB in 30 us).  `spe`: stages per example
-// (splits start on examples).
-static long choose_nsplit_dma(int nl, int ntiles, long ksteps, long spe, int d_in, int d_out, const DmaCost& c, double* t_out) {
+// (splits start on examples).  ROUNDS: by the costs of several rounds, and only splits that the workspace holds.
+template <bool ROUNDS>
+static long choose_nsplit_dma(int nl, int ntiles, long ksteps, long spe, int d_in, int d_out, const DmaCost& c, size_t ws_bytes, double* t_out) {
     const long max_split = ksteps / 8 < 1 ? 1 : ksteps / 8;
     long best = 1;
     double best_t = 0.0;
@@ -931,12 +940,14 @@ static long choose_nsplit_dma(int nl, int ntiles, long ksteps, long spe, int d_i
         const long steps_per = ((ksteps + s - 1) / s + spe - 1) / spe * spe;
         const long se = (ksteps + steps_per - 1) / steps_per;  // the splits that are not empty
         if (se != s && s > 1) continue;                        // the same plan as a smaller s
+        if (ROUNDS && s > 1 && (size_t)nl * se * d_in * d_out * 4 > ws_bytes) break;
         const long wg = (long)nl * se * ntiles;
         const long per_xcd = (wg + 7) / 8;
         const long rounds = (per_xcd + 32 * c.wgs - 1) / (32 * c.wgs);
-        const double fill = wg >= 256l * c.wgs ? 1.0 : (double)wg / (256.0 * c.wgs);
-        double t = (double)rounds * ((double)steps_per * (wg <= 256 ? c.t_stage_alone : c.t_stage) + c.t_ends + c.t_ends_full * fill);
-        if (se > 1) t += (double)nl * (double)(se + 2) * d_in * d_out * 4.0 / 8.0e6 + 5.0;
+        const double full = (double)wg / (256.0 * c.wgs), stages = (double)steps_per * (wg <= 256 ? c.t_stage_alone : c.t_stage);
+        double t = ROUNDS ? (double)rounds * (stages + c.t_ends) + c.t_ends_full * full
+                          : (double)rounds * (stages + c.t_ends + c.t_ends_full * (full < 1.0 ? full : 1.0));
+        if (se > 1) t += (double)nl * (double)(se + 2) * d_in * d_out * 4.0 / (ROUNDS ? 11.3e6 : 8.0e6) + (ROUNDS ? 3.6 : 5.0);
         if (s == 1 || t < best_t) {
             best = se;
             best_t = t;
@@ -946,55 +957,90 @@ static long choose_nsplit_dma(int nl, int ntiles, long ksteps, long spe, int d_i
     return best;
 }
 
+// Layers per launch in the scaled form: those whose scaled output gradients fit half the workspace, with room for their bias partials besides (one row for up
+// to 32 token rows and no more than 256: a sixteenth of the gradients, but more than they take for a single row).
+static long scaled_layers(long K, int d_out, size_t ws_bytes) {
+    if (ws_bytes / 2 < 1024) return 0;
+    const size_t scaled = (size_t)K * d_out * 2 + 256, bias = (size_t)((K + BK - 1) / BK < 256 ? (K + BK - 1) / BK : 256) * d_out * 4;
+    size_t per = (ws_bytes / 2 - 1024) / scaled;
+    if (per > (ws_bytes - 1024) / (scaled + bias)) per = (ws_bytes - 1024) / (scaled + bias);
+    return per < MAX_BATCH ? (long)per : MAX_BATCH;
+}
+
 // Tile and form for n layers: the smallest modelled time of the whole call.
 static DmaPlan choose_dma_plan(int n, int B, int T, int d_in, int d_out, size_t ws_bytes) {
     DmaPlan best{0, 0, false, 1, 1};
     double best_t = 0.0;
     const long K = (long)B * T;
-    for (int flat = 0; flat < 2; ++flat) {
-        if (flat && T % BK == 0 && T > BK) continue;  // whole stages: nothing to gain
-        if (flat && d_out > 65535 * 256) continue;    // (scale_rows_kernel has a grid row per 256 columns)
-        size_t per_ws = MAX_BATCH;
-        if (flat) {
-            // layers whose scaled output gradients fit half the workspace, with room for their bias partials besides (one row for up
-            // to 32 token rows and no more than 256: a sixteenth of the gradients, but more than they take for a single row)
-            if (ws_bytes / 2 < 1024) continue;
-            const size_t scaled = (size_t)K * d_out * 2 + 256, bias = (size_t)((K + BK - 1) / BK < 256 ? (K + BK - 1) / BK : 256) * d_out * 4;
-            per_ws = (ws_bytes / 2 - 1024) / scaled;
-            if (per_ws > (ws_bytes - 1024) / (scaled + bias)) per_ws = (ws_bytes - 1024) / (scaled + bias);
-            if (per_ws < 1) continue;
-        }
+    // calls f(tile rows, tile columns, stages of one example only, tiles, stages, stages per example, most layers per launch) for the tiles of a form
+    auto tiles = [&](bool flat, auto f) {
+        if (flat && T % BK == 0 && T > BK) return;  // whole stages: nothing to gain
+        if (flat && d_out > 65535 * 256) return;    // (scale_rows_kernel has a grid row per 256 columns)
+        const long most = flat ? scaled_layers(K, d_out, ws_bytes) : MAX_BATCH;
+        if (most < 1) return;
         const long spe = flat ? 1 : (T + BK - 1) / BK;
         const long ksteps = flat ? (K + BK - 1) / BK : (long)B * spe;
         const bool one_stage = !flat && T <= BK;
         for (int bm = one_stage ? 128 : 256; bm >= 128; bm -= 128)
-            for (int bn = one_stage ? 128 : 256; bn >= 128; bn -= 128) {
-                const DmaCost c = dma_cost(bm, bn, one_stage);
-                const int ntiles = ((d_in + bm - 1) / bm) * ((d_out + bn - 1) / bn);
-                // layers per launch: enough to give every CU its workgroups, but no more than one round of them when a
-                // layer has many tiles (workgroups that run at the same time share operands through L2; later rounds do not)
-                long per = 256l * c.wgs / ntiles;
-                if (per < 1) per = 1;
-                if (per > MAX_BATCH) per = MAX_BATCH;
-                if (per > (long)per_ws) per = (long)per_ws;
-                double t = 0.0, tl;
-                const long full = n / per, rest = n % per;
-                long nsplit = 1;
-                if (rest) {
-                    nsplit = choose_nsplit_dma((int)rest, ntiles, ksteps, spe, d_in, d_out, c, &tl);
-                    t += tl + 4.0;
-                }
-                if (full) {
-                    nsplit = choose_nsplit_dma((int)per, ntiles, ksteps, spe, d_in, d_out, c, &tl);
-                    t += full * (tl + 4.0);
-                }
-                if (flat) t += (full + (rest ? 1 : 0)) * 4.0 + 4.0 * (double)K * d_out * n / 4.0e6;
-                if (!best.bm || t < best_t) {
-                    best = DmaPlan{bm, bn, flat != 0, (int)per, nsplit};
-                    best_t = t;
-                }
+            for (int bn = one_stage ? 128 : 256; bn >= 128; bn -= 128)
+                f(bm, bn, one_stage, ((d_in + bm - 1) / bm) * ((d_out + bn - 1) / bn), ksteps, spe, most);
+    };
+    auto scaling = [&](bool flat, long launches, double rate) { return flat ? (double)launches * 4.0 + 4.0 * (double)K * d_out * n / rate : 0.0; };
+    for (const bool flat : {false, true})
+        tiles(flat, [&](int bm, int bn, bool one_stage, int ntiles, long ksteps, long spe, long most) {
+            const DmaCost c = dma_cost(bm, bn, one_stage);
+            // layers per launch: enough to give every CU its workgroups, but no more than one round of them when a layer has many tiles
+            long per = 256l * c.wgs / ntiles;
+            per = per < 1 ? 1 : per > most ? most : per;
+            double t = 0.0, tl;
+            const long full = n / per, rest = n % per;
+            long nsplit = 1;
+            if (rest) {
+                nsplit = choose_nsplit_dma<false>((int)rest, ntiles, ksteps, spe, d_in, d_out, c, ws_bytes, &tl);
+                t += tl + 4.0;
             }
-    }
+            if (full) {
+                nsplit = choose_nsplit_dma<false>((int)per, ntiles, ksteps, spe, d_in, d_out, c, ws_bytes, &tl);
+                t += full * (tl + 4.0);
+            }
+            t += scaling(flat, full + (rest ? 1 : 0), 4.0e6);
+            if (!best.bm || t < best_t) {
+                best = DmaPlan{bm, bn, flat, (int)per, nsplit};
+                best_t = t;
+            }
+        });
+    if (best.per_launch >= n) return best;
+    // Several launches so: the layers together, in one launch of as many rounds as it takes, where that is faster by the costs of such launches.  Short sums
+    // are: 32 stages, 48 layers of 768 x 768 97 us apart, 88 together; 64 of 1024 x 1024 215 | 199; 6 stages, 36 layers of 640 x 640 53 | 44.  Long ones of which a second
+    // round would be partly empty are not: B = 23, T = 375, 6 layers of 832 x 3328 350 | 402.  (In the form chosen above: the scaled one rounds c * g.)
+    const bool scaled = best.flat;
+    double apart = 0.0;
+    tiles(best.flat, [&](int bm, int bn, bool one_stage, int ntiles, long ksteps, long spe, long) {
+        if (bm != best.bm || bn != best.bn) return;
+        const DmaCost c = dma_cost_rounds(bm, bn, one_stage);
+        const long full = n / best.per_launch, rest = n % best.per_launch;
+        double tl = 0.0;
+        if (rest) choose_nsplit_dma<true>((int)rest, ntiles, ksteps, spe, d_in, d_out, c, ws_bytes, &tl);
+        apart = rest ? tl + 7.0 : 0.0;
+        choose_nsplit_dma<true>(best.per_launch, ntiles, ksteps, spe, d_in, d_out, c, ws_bytes, &tl);
+        apart += full * (tl + 7.0) + scaling(best.flat, full + (rest ? 1 : 0), 6.0e6);
+    });
+    best_t = 0.97 * apart;  // (by more than the model is wrong)
+    tiles(scaled, [&](int bm, int bn, bool one_stage, int ntiles, long ksteps, long spe, long most) {
+        const DmaCost c = dma_cost_rounds(bm, bn, one_stage);
+        const long per = n < most ? n : most, full = n / per, rest = n % per;
+        double t = 0.0, tl;
+        if (rest) {
+            choose_nsplit_dma<true>((int)rest, ntiles, ksteps, spe, d_in, d_out, c, ws_bytes, &tl);
+            t += tl + 7.0;
+        }
+        const long nsplit = choose_nsplit_dma<true>((int)per, ntiles, ksteps, spe, d_in, d_out, c, ws_bytes, &tl);
+        t += full * (tl + 7.0) + scaling(scaled, full + (rest ? 1 : 0), 6.0e6);
+        if (t < best_t) {
+            best = DmaPlan{bm, bn, scaled, (int)per, nsplit};
+            best_t = t;
+        }
+    });
     return best;
 }
 
@@ -1041,7 +1087,7 @@ dp_status dpk_weighted_gemm_batched(dp_ctx* ctx, int n, const void* const* A, co
         const int ntiles = a.tiles_m * a.tiles_n;
         double t_model;
         long nsplit = nl == (n < plan.per_launch ? n : plan.per_launch) ? plan.nsplit
-                                                                       : choose_nsplit_dma(nl, ntiles, ksteps, spe, d_in, d_out, cost, &t_model);
+                                                                       : choose_nsplit_dma<false>(nl, ntiles, ksteps, spe, d_in, d_out, cost, ctx->ws_bytes, &t_model);
         bool any_bias = false;
         for (int l = 0; l < nl; ++l)
             if (sum_b && sum_b[l0 + l]) any_bias = true;

@@ -1123,6 +1123,30 @@ def test_clip_accumulate_dense_every_form(dp, tile, form, split, shape):
             assert float((err / (want.abs() + want.square().mean().sqrt())).max()) < m, l
 
 
+@pytest.mark.parametrize("n,B,T,d_in,d_out", [(40, 3, 96, 776, 1032), (36, 18, 18, 640, 640), (12, 6, 38, 2576, 1160), (70, 2, 32, 1024, 520)])
+def test_layers_of_several_rounds_in_one_launch(dp, n, B, T, d_in, d_out):
+    """More workgroups than the chip runs at once, in one launch: each layer's sums are those of a call of its own, up to the order of
+    fp32 additions (K n 2^-24 at most, 1e-5 in the 2-norm)."""
+    import paper_2108_01624_amd as pkg
+
+    plan = pkg.dp_dense_sum_plan(pkg.DP_BF16, n, B, T, d_in, d_out)
+    tiles = -(-d_in // plan["tile_m"]) * -(-d_out // plan["tile_n"]) * plan["layers"]
+    assert tiles > 256 * (2 if plan["tile_m"] == plan["tile_n"] == 128 else 1) and plan["layers"] == min(n, 64), plan
+    g = torch.Generator(device=DEV)
+    g.manual_seed(532)
+    A, G = [[torch.randn(B, T, d, generator=g, device=DEV).to(torch.bfloat16) for _ in range(n)] for d in (d_in, d_out)]
+    sq = f32_dev(syn.synthetic_sqnorms(B, 1.0, 533))
+    W, b = [torch.full((d_in, d_out), 0.25, device=DEV) for _ in range(n)], [torch.full((d_out,), -0.5, device=DEV) for _ in range(n)]
+    dp.clip_accumulate_dense_batched(A, G, 1.0, sq, W, b)
+    for l in range(n):
+        W1, b1 = torch.full((d_in, d_out), 0.25, device=DEV), torch.full((d_out,), -0.5, device=DEV)
+        dp.clip_accumulate_dense(A[l], G[l], 1.0, sq, W1, b1)
+        rel = 1e-5 if pkg.dp_dense_sum_plan(pkg.DP_BF16, 1, B, T, d_in, d_out)["scaled"] == plan["scaled"] else 2.0**-8
+        for got, want in ((W[l], W1), (b[l], b1)):
+            assert float((got - want).norm() / want.norm()) < rel, l
+    dp.sync()
+
+
 @pytest.mark.parametrize("dtype,B,T,d_in,d_out", [("bf16", 5, 50, 72, 136), ("bf16", 3, 64, 256, 264), ("bf16", 600, 20, 512, 512), ("f32", 5, 20, 36, 40)])
 def test_layers_that_share_a_sum_buffer(dp, dtype, B, T, d_in, d_out):
     """Entries of a batched call that name the same sum buffer, or a part of it, add to it one after the other, whatever launches the
