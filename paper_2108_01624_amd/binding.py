@@ -1,5 +1,5 @@
-"""ctypes binding of libdpclip.so: one Python function per C entry point, same names, argument
-marshalling only (tensor -> device pointer, dtype -> enum).  Every step of the path runs in the
+"""Binding of libdpclip.so: one Python function per C entry point (ctypes), same names, argument
+marshalling only (tensor -> device pointer, dtype -> enum); the methods of Context take the extension for the frequent ones.  Every step of the path runs in the
 library's HIP kernels; there is no fallback: if the library is missing, loading raises."""
 from __future__ import annotations
 
@@ -9,6 +9,7 @@ from ctypes import c_char_p, c_float, c_int, c_size_t, c_uint64, c_void_p
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libdpclip.so")
 _lib = None
+_native = None  # the extension module: the same calls with their arguments read in C++ (see csrc/native.cpp)
 _float32 = _bfloat16 = _int32 = None  # torch's dtype objects, bound with the library
 
 DP_F32, DP_BF16 = 0, 1
@@ -85,7 +86,7 @@ class DpError(RuntimeError):
 
 def load_library():
     """dlopen libdpclip.so and declare the prototypes.  Raises if it has not been built."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     # torch ships its own HIP runtime: import it first so that the library binds to the runtime that owns
@@ -100,6 +101,9 @@ def load_library():
         fn = getattr(lib, name)
         fn.argtypes = argtypes
         fn.restype = _RESTYPES.get(name, c_int)
+    from . import _native as native
+
+    _native = native
     _lib = lib
     return lib
 
@@ -549,6 +553,75 @@ class Context:
 
     def __exit__(self, *a):
         self.close()
+
+    # The calls that a step makes many times.  The extension leaves alone (None) what it does not expect: the function above then does the work, or raises.
+    def _finish(self, st, name, *a, **k):
+        if st is None:
+            globals()[name](self.handle, *a, **k)
+        else:
+            _check(self.handle, st, name)
+
+    def zero_f32(self, p, n=None):
+        st = _native.zero_f32(self.handle, p, n)
+        if st != 0:
+            self._finish(st, "dp_zero_f32", p, n)
+
+    def sqnorms_dense(self, A, G, has_bias, path, sqnorms, *, B=None, T=None):
+        st = _native.sqnorms_dense(self.handle, A, G, has_bias, path, sqnorms) if B is None and T is None else None
+        if st != 0:
+            self._finish(st, "dp_sqnorms_dense", A, G, has_bias, path, sqnorms, B=B, T=T)
+
+    def sqnorms_dense_batched(self, As, Gs, has_bias, path, sqnorms):
+        st = _native.sqnorms_dense_batched(self.handle, As, Gs, has_bias, path, sqnorms)
+        if st != 0:
+            self._finish(st, "dp_sqnorms_dense_batched", As, Gs, has_bias, path, sqnorms)
+
+    def clip_accumulate_dense(self, A, G, C, sqnorms, sum_W, sum_b=None):
+        st = _native.clip_accumulate_dense(self.handle, A, G, C, sqnorms, sum_W, sum_b)
+        if st != 0:
+            self._finish(st, "dp_clip_accumulate_dense", A, G, C, sqnorms, sum_W, sum_b)
+
+    def clip_accumulate_dense_batched(self, As, Gs, C, sqnorms, sum_Ws, sum_bs=None):
+        st = _native.clip_accumulate_dense_batched(self.handle, As, Gs, C, sqnorms, sum_Ws, sum_bs)
+        if st != 0:
+            self._finish(st, "dp_clip_accumulate_dense_batched", As, Gs, C, sqnorms, sum_Ws, sum_bs)
+
+    def sqnorms_embedding(self, ids, G, V, distinct_per_example, sqnorms):
+        st = _native.sqnorms_embedding(self.handle, ids, G, V, distinct_per_example, sqnorms)
+        if st != 0:
+            self._finish(st, "dp_sqnorms_embedding", ids, G, V, distinct_per_example, sqnorms)
+
+    def clip_accumulate_embedding(self, ids, G, V, C, sqnorms, sum_E):
+        st = _native.clip_accumulate_embedding(self.handle, ids, G, V, C, sqnorms, sum_E)
+        if st != 0:
+            self._finish(st, "dp_clip_accumulate_embedding", ids, G, V, C, sqnorms, sum_E)
+
+    def sqnorms_tied_embedding(self, ids, dY, H, dL, sqnorms):
+        st = _native.sqnorms_tied_embedding(self.handle, ids, dY, H, dL, sqnorms)
+        if st != 0:
+            self._finish(st, "dp_sqnorms_tied_embedding", ids, dY, H, dL, sqnorms)
+
+    def clip_accumulate_tied_embedding(self, ids, dY, H, dL, C, sqnorms, sum_E):
+        st = _native.clip_accumulate_tied_embedding(self.handle, ids, dY, H, dL, C, sqnorms, sum_E)
+        if st != 0:
+            self._finish(st, "dp_clip_accumulate_tied_embedding", ids, dY, H, dL, C, sqnorms, sum_E)
+
+    def noise_adamw(self, params, m, v, sum_, *, n=None, elem_offset=0, sigma, C, seed, step, batch_size, lr, beta1, beta2, eps=1e-11,
+                    weight_decay, zero_sum=False):
+        st = _native.noise_adamw(self.handle, params, m, v, sum_, n, elem_offset, sigma, C, seed, step, batch_size, lr, beta1, beta2, eps,
+                                 weight_decay, zero_sum)
+        if st != 0:
+            self._finish(st, "dp_noise_adamw", params, m, v, sum_, n=n, elem_offset=elem_offset, sigma=sigma, C=C, seed=seed, step=step,
+                         batch_size=batch_size, lr=lr, beta1=beta1, beta2=beta2, eps=eps, weight_decay=weight_decay, zero_sum=zero_sum)
+
+    def noise_adamw_snr(self, params, m, v, sum_, snr_sq, *, n=None, elem_offset=0, sigma, C, seed, step, batch_size, lr, beta1, beta2,
+                        eps=1e-11, weight_decay, zero_sum=False):
+        st = _native.noise_adamw(self.handle, params, m, v, sum_, n, elem_offset, sigma, C, seed, step, batch_size, lr, beta1, beta2, eps,
+                                 weight_decay, zero_sum, snr_sq)
+        if st != 0:
+            self._finish(st, "dp_noise_adamw_snr", params, m, v, sum_, snr_sq, n=n, elem_offset=elem_offset, sigma=sigma, C=C, seed=seed,
+                         step=step, batch_size=batch_size, lr=lr, beta1=beta1, beta2=beta2, eps=eps, weight_decay=weight_decay,
+                         zero_sum=zero_sum)
 
     def __getattr__(self, name):
         # ctx.sqnorms_dense(...) == dp_sqnorms_dense(ctx.handle, ...)

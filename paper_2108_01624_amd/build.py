@@ -1,15 +1,17 @@
-"""Build libdpclip.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Build libdpclip.so (HIP, gfx950 only) in-tree with hipcc, and the Python extension over it with g++."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 INCLUDE = os.path.join(os.path.dirname(PKG_DIR), "include")
 LIB_PATH = os.path.join(PKG_DIR, "libdpclip.so")
+NATIVE_PATH = os.path.join(PKG_DIR, "_native.so")
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 
 SOURCES = ["dp_api.hip", "dp_update.hip", "dp_rowwise.hip", "dp_gram.hip", "dp_wgemm.hip", "dp_tied.hip"]
@@ -38,17 +40,45 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _run(cmd, what):
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{what} failed:\n{r.stderr}")
+
+
+def _compile_native() -> str:
+    import torch
+
+    obj, top = os.path.join(BUILD_DIR, "native.o"), os.path.dirname(torch.__file__)
+    includes = [INCLUDE, os.path.join(top, "include"), os.path.join(top, "include", "torch", "csrc", "api", "include"),
+                sysconfig.get_paths()["include"]]
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+         + ["-I" + i for i in includes] + ["-c", os.path.join(CSRC, "native.cpp"), "-o", obj], "g++ on native.cpp")
+    return obj
+
+
+def _link_native(obj):
+    """Finds libdpclip.so beside itself; libtorch is in the process before it is imported."""
+    import torch
+
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    _run(["g++", "-shared", "-o", NATIVE_PATH + ".tmp", obj, "-L" + PKG_DIR, "-l:libdpclip.so", "-Wl,-rpath,$ORIGIN", "-L" + lib,
+          "-ltorch_python", "-ltorch_cpu", "-lc10"], "link of _native.so")
+    os.replace(NATIVE_PATH + ".tmp", NATIVE_PATH)
+
+
 def build_library(verbose: bool = False) -> str:
     """Compile every source and link the shared library; always rebuilds."""
     os.makedirs(BUILD_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as ex:
+    with ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, os.cpu_count() or 1)) as ex:
+        native = ex.submit(_compile_native)
         objs = list(ex.map(_compile, SOURCES))
+        native = native.result()
     tmp = LIB_PATH + ".tmp"
-    cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"link failed:\n{r.stderr}")
+    # (the name that whoever links against it finds it by, whatever the file is called while it is written)
+    _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-soname,libdpclip.so", "-o", tmp] + objs, "link")
     os.replace(tmp, LIB_PATH)
+    _link_native(native)
     if verbose:
         print("built", LIB_PATH, file=sys.stderr)
     return LIB_PATH

@@ -6,6 +6,13 @@ from __future__ import annotations
 from . import binding as B_
 
 
+def _elements(shape):
+    n = 1
+    for s in shape:
+        n *= s
+    return n
+
+
 class StepRunner:
     """Owns the flat fp32 state (theta, m, v, clip-weighted sum S) of a manifest and the per-example
     squared-norm buffer.  Tensors of the flat space follow the manifest order (LayerSpec.tensors())."""
@@ -20,16 +27,14 @@ class StepRunner:
         for spec in manifest:
             cur = []
             for _, shp in spec.tensors():
-                n = 1
-                for s in shp:
-                    n *= s
                 off = (off + 3) // 4 * 4  # keep every tensor 16-byte aligned inside the flat buffers
                 cur.append((off, shp))
-                off += n
+                off += _elements(shp)
             self.offsets.append(cur)
         self.P = off
         # byte offsets of the tensors inside a flat buffer: what the batched calls need of a layer's sums
         self._at = [[4 * o for o, _ in cur] for cur in self.offsets]
+        self._spans = [[(4 * o, _elements(shp)) for o, shp in cur] for cur in self.offsets]  # ... and their elements
         self.S = torch.zeros(self.P, dtype=torch.float32, device=device)
         self.theta = torch.zeros(self.P, dtype=torch.float32, device=device)
         self.m = torch.zeros(self.P, dtype=torch.float32, device=device)
@@ -43,10 +48,7 @@ class StepRunner:
 
     def view(self, buf, layer, k):
         off, shp = self.offsets[layer][k]
-        n = 1
-        for s in shp:
-            n *= s
-        return buf[off:off + n].view(*shp)
+        return buf[off:off + _elements(shp)].view(*shp)
 
     def _keep_buffer(self, k, d):
         """[max_batch, 2, d] floats for layer k of the manifest, allocated on first use."""
@@ -79,6 +81,15 @@ class StepRunner:
         nB = layers[0]["G"].shape[0]
         n = self.sqnorms[:nB]
         ctx.zero_f32(n)
+        if batch_dense and path == B_.DP_PATH_AUTO and type(ctx) is B_.Context:
+            # the walk below in C++ (None: something it does not expect, nothing has been called)
+            done = B_._native.pass1(ctx.handle, layers, n, self.ln_keep, self._keep_buffer, self.max_batch)
+            if done is not None:
+                self._kept_for = None
+                if type(done) is tuple:
+                    B_._check(ctx.handle, *done)
+                self._kept_for = done or None
+                return n
         groups, ln_groups = {}, {}
         for k, l in enumerate(layers):
             kind = l["kind"]
@@ -138,6 +149,12 @@ class StepRunner:
         S = B_._f32(self.S)
         if self.S.numel() < self.P or not self.S.is_contiguous():
             raise ValueError("S must be a contiguous buffer of all parameters")
+        if batch_dense and type(ctx) is B_.Context:
+            done = B_._native.pass2(ctx.handle, layers, C, n, self.S, self._spans, self.ln_keep, self._kept_for, self.max_batch)
+            if done is not None:
+                if type(done) is tuple:
+                    B_._check(ctx.handle, *done)
+                return
         groups, ln_groups = {}, {}
         for k, l in enumerate(layers):
             kind = l["kind"]

@@ -243,6 +243,44 @@ def test_privacy_accounting_matches_the_oracle(lib):
             pkg.dp_rdp_noise_multiplier(q, steps, bad[0], 2.89e-9, 32, bad[1])
 
 
+def test_native_calls_leave_alone_what_they_do_not_expect(lib):
+    """Another element type, a shape that does not fit, an address in place of a tensor, a closed context: None, and the library is
+    not called (there is no context behind the handle given here)."""
+    import torch
+
+    from paper_2108_01624_amd import binding
+
+    nat, h = binding._native, 1 << 40
+    f, d, A, G = torch.zeros(4), torch.zeros(4, dtype=torch.float64), torch.zeros(2, 3, 8), torch.zeros(2, 3, 16)
+    ids, E = torch.zeros(2, 3, dtype=torch.int32), torch.zeros(5, 16)
+    H, dL = torch.zeros(2, 4, 16), torch.zeros(2, 4, 5)
+    adam = (0, 0.5, 1.0, 1, 1, 8, 1e-3, 0.9, 0.99, 1e-11, 0.0, True)
+    for args in ((None, f, None), (0, f, None), (h, d, None), (h, 4096, None), (h, f, -1), (h, f, 2.0), (h, f)):
+        assert nat.zero_f32(*args) is None, args
+    for args in ((h, A[0], G, True, 0, f), (h, A, G, True, 0, d), (h, A.half(), G, True, 0, f), (h, A, G, True, "auto", f)):
+        assert nat.sqnorms_dense(*args) is None
+    for a, g in (([A], [G, G]), ([A, A[:1]], [G, G]), ([A], [G[:, :2]]), ([A], [G.bfloat16()]), ((A,), [G]), ([], [])):
+        assert nat.sqnorms_dense_batched(h, a, g, True, 0, f) is None
+        assert nat.clip_accumulate_dense_batched(h, a, g, 1.0, f, [E] * len(a), None) is None
+    assert nat.clip_accumulate_dense_batched(h, [A], [G], 1.0, f, [E.double()], None) is None
+    assert nat.clip_accumulate_dense_batched(h, [A], [G], 1.0, f, [E], [f, f]) is None
+    assert nat.clip_accumulate_dense(h, A, G, "1", f, E, None) is None
+    assert nat.sqnorms_embedding(h, ids.long(), G, 5, False, f) is None
+    assert nat.clip_accumulate_embedding(h, ids, G, 2**31, 1.0, f, E) is None
+    assert nat.sqnorms_tied_embedding(h, ids, G, H[:, :3], dL, f) is None
+    assert nat.clip_accumulate_tied_embedding(h, ids, G, H, dL, 1.0, f, E[:4]) is None
+    assert nat.noise_adamw(h, f, f, f, d, 4, *adam) is None
+    assert nat.noise_adamw(h, f, f, f, f, 4, *adam[:3], -1, *adam[4:]) is None
+    assert nat.noise_adamw(h, f, f, f, f, 4, *adam, f[:1]) is None
+    ok = dict(kind="dense", A=A, G=G, has_bias=True)
+    for bad in ([], [dict(ok, G=G[:, :2])], [dict(ok, A=A[0])], [dict(ok, G=G.bfloat16())], [{k: v for k, v in ok.items() if k != "has_bias"}],
+                [ok, dict(ok, A=A[:1], G=G[:1])], [dict(kind="layernorm", X=A, G=G)], [dict(kind="embedding", ids=ids, G=G, V=5)],
+                [dict(kind="embedding", ids=ids[:, :2], G=G, V=5, distinct=False)], (ok,)):
+        assert nat.pass1(h, bad, f, {}, None, 2) is None
+        assert nat.pass2(h, bad, 1.0, f, E, [[(0, 128), (512, 16)]] * 2, {}, None, 2) is None
+    assert nat.pass2(h, [ok], 1.0, f, E, [[(0, 128)]], {}, None, 2) is None
+
+
 def test_step_runner_refuses_what_the_addresses_cannot_carry():
     """The step driver hands layers over by address: shapes that do not belong together and a sum buffer that cannot hold
     every parameter are refused before the library is called."""

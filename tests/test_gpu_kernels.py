@@ -1123,6 +1123,67 @@ def test_clip_accumulate_dense_every_form(dp, tile, form, split, shape):
             assert float((err / (want.abs() + want.square().mean().sqrt())).max()) < m, l
 
 
+def test_step_driver_in_cpp_is_the_one_in_python(dp):
+    """Both walks over a manifest with every kind of layer, inputs shared by two and by three layers, with and without bias, in two
+    types, make the same calls in the same order: the same bits; then a second micro-batch, and one whose gradients were not kept."""
+    import paper_2108_01624_amd as pkg
+
+    class Walked(pkg.Context):   # (the driver hands only a plain context to the extension)
+        pass
+
+    B, T, h, f, V, M = 6, 24, 64, 128, 96, 5
+    spec = [("embedding", (V, h)), ("embedding", (T + 3, h)), ("layernorm", None), ("dense", (h, h, True, 0)), ("dense", (h, h, True, 0)),
+            ("dense", (h, h, True, 0)), ("dense", (h, f, False, 1)), ("dense", (h, f, False, 1)), ("dense", (f, h, True, 2)), ("layernorm", None),
+            ("dense", (h, h, True, 3)), ("tied_embedding", (V, h)), ("f32", (h, h, True, 4))]
+
+    class Spec:
+        def __init__(self, kind, x):
+            self.kind, self.x = kind, x
+
+        def tensors(self):
+            if self.kind in ("dense", "f32"):
+                return [("W", self.x[:2])] + ([("b", (self.x[1],))] if self.x[2] else [])
+            return [("gamma", (h,)), ("beta", (h,))] if self.kind == "layernorm" else [("E", self.x)]
+
+    man = [Spec(*s) for s in spec]
+
+    def batch(seed):
+        g = torch.Generator(device=DEV)
+        g.manual_seed(seed)
+        rand = lambda *s, dt=torch.bfloat16: torch.randn(s, generator=g, device=DEV).to(dt)
+        ids = lambda v: torch.randint(0, v, (B, T), generator=g, device=DEV, dtype=torch.int32)
+        shared, out = {}, []
+        for k, (kind, x) in enumerate(spec):
+            if kind == "layernorm":
+                out.append(dict(kind=kind, X=rand(B, T, h), G=rand(B, T, h)))
+            elif kind in ("dense", "f32"):
+                dt = torch.float32 if kind == "f32" else torch.bfloat16
+                A = shared.setdefault(x[3], rand(B, T, x[0], dt=dt))
+                out.append(dict(kind="dense", A=A, G=rand(B, T, x[1], dt=dt), has_bias=x[2]))
+            elif kind == "tied_embedding":
+                out.append(dict(kind=kind, ids=ids(V), G=rand(B, T, h), H=rand(B, M, h), dL=rand(B, M, V)))
+            else:
+                pos = k == 1
+                i = torch.arange(T, dtype=torch.int32, device=DEV).expand(B, T).contiguous() if pos else ids(V)
+                out.append(dict(kind="embedding", ids=i, G=rand(B, T, h), V=x[0], distinct=pos))
+        return out
+
+    one, two = batch(1), batch(2)
+    with pkg.Context() as plain, Walked() as walked:
+        got = []
+        for ctx in (plain, walked):
+            run = pkg.StepRunner(ctx, man, B, device=DEV)
+            norms = [run.pass1(one).clone()]
+            run.pass2(one, 1.0)
+            norms.append(run.pass1(two).clone())
+            run.pass2(two, 1.0)
+            run.pass2(one, 1.0)   # (with the norms of the other one, and LayerNorm gradients that are not its own)
+            ctx.sync()
+            got.append((norms, run.S.clone(), bool(run._kept_for)))
+    assert all(torch.equal(a, b) for a, b in zip(got[0][0], got[1][0])) and torch.equal(got[0][1], got[1][1])
+    assert got[0][2] and got[1][2] and bool(got[0][1].any())
+
+
 @pytest.mark.parametrize("n,B,T,d_in,d_out", [(40, 3, 96, 776, 1032), (36, 18, 18, 640, 640), (12, 6, 38, 2576, 1160), (70, 2, 32, 1024, 520)])
 def test_layers_of_several_rounds_in_one_launch(dp, n, B, T, d_in, d_out):
     """More workgroups than the chip runs at once, in one launch: each layer's sums are those of a call of its own, up to the order of
