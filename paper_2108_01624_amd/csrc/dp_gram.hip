@@ -668,7 +668,7 @@ __device__ __forceinline__ float gram_unit_ring(const uint16_t* __restrict__ A, 
     return sum * weight;
 }
 
-// out: partials [B][n_layers * n_units], stored.  Workgroup id g -> XCD g % 8; (layer, example) u = (g / 8 / n_units) * 8 + g % 8,
+// out: partials [B][n_layers * n_units], stored; one unit of one layer: sqnorms, "+=".  Workgroup id g -> XCD g % 8; (layer, example) u = (g / 8 / n_units) * 8 + g % 8,
 // unit = (g / 8) % n_units: the units of one example share an XCD, so that each panel comes from HBM once.
 template <bool RAGGED>
 __global__ __launch_bounds__(512, 1) void gram_units_kernel(GramBatch gb, GramUnits gu, int T, int d_in, int d_out, int has_bias,
@@ -693,7 +693,10 @@ __global__ __launch_bounds__(512, 1) void gram_units_kernel(GramBatch gb, GramUn
     else s = gram_unit_ring<1, false, RAGGED>(A, G, T, d_in, d_out, R, C1, C2, bias_term, ring);
     __syncthreads();  // the ring is free: its first floats serve the reduction
     const float tot = dp_block_sum<512>(s, reinterpret_cast<float*>(&ring[0]));
-    if (threadIdx.x == 0) out[((size_t)i * gb.n_layers + layer) * gu.n_units + unit] = tot;
+    if (threadIdx.x == 0) {
+        if (gb.n_layers * gu.n_units == 1) out[i] += tot;
+        else out[((size_t)i * gb.n_layers + layer) * gu.n_units + unit] = tot;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1068,8 +1071,9 @@ static dp_status gram_units_launch(dp_ctx* ctx, const GramBatch& gb, int T, int 
         DP_SET_ERR(ctx, "dp_sqnorms_dense: B * T^2 too large for one launch");
         return DP_ERR_SHAPE;
     }
+    const bool direct = gb.n_layers * gu.n_units == 1;  // up to 256 rows: nothing to add behind
     dp_ws_alloc ws(ctx);
-    float* part = ws.get<float>((size_t)units * gu.n_units);
+    float* part = direct ? sqnorms : ws.get<float>((size_t)units * gu.n_units);
     if (!part) {
         DP_SET_ERR(ctx, "workspace too small for %ld x %d Gram partials", units, gu.n_units);
         return DP_ERR_WORKSPACE;
@@ -1082,7 +1086,7 @@ static dp_status gram_units_launch(dp_ctx* ctx, const GramBatch& gb, int T, int 
             hipLaunchKernelGGL((gram_units_kernel<true>), dim3((unsigned)nwg), dim3(512), 0, ctx->stream, gb, gu, T, d_in, d_out, has_bias, part);
     }
     DP_LAUNCH_CHECK(ctx, "gram_units");
-    return dpk_finish_partials(ctx, part, gb.B, gu.n_units * gb.n_layers, sqnorms);
+    return direct ? DP_OK : dpk_finish_partials(ctx, part, gb.B, gu.n_units * gb.n_layers, sqnorms);
 }
 
 // One layer on the register-staged kernel: a workgroup per 128 x 128 block of the upper triangle.

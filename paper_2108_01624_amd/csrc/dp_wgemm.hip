@@ -1009,10 +1009,10 @@ static DmaPlan choose_dma_plan(int n, int B, int T, int d_in, int d_out, size_t 
                 best_t = t;
             }
         });
-    if (best.per_launch >= n) return best;
+    if (best.per_launch >= n || K > 64 * BK) return best;
     // Several launches so: the layers together, in one launch of as many rounds as it takes, where that is faster by the costs of such launches.  Short sums
-    // are: 32 stages, 48 layers of 768 x 768 97 us apart, 88 together; 64 of 1024 x 1024 215 | 199; 6 stages, 36 layers of 640 x 640 53 | 44.  Long ones of which a second
-    // round would be partly empty are not: B = 23, T = 375, 6 layers of 832 x 3328 350 | 402.  (In the form chosen above: the scaled one rounds c * g.)
+    // are, up to 64 stages: 32 stages, 48 layers of 768 x 768 97 us apart, 88 together; 64 of 1024 x 1024 215 | 199; 6 stages, 36 layers of 640 x 640 53 | 44.  Long ones of which a second
+    // round would be partly empty are not, and the others gain nothing: B = 23, T = 375, 6 layers of 832 x 3328 350 | 402; B = 128, T = 128, 32 of 1024 x 1024 975 | 972.  (In the form chosen above: the scaled one rounds c * g.)
     const bool scaled = best.flat;
     double apart = 0.0;
     tiles(best.flat, [&](int bm, int bn, bool one_stage, int ntiles, long ksteps, long spe, long) {

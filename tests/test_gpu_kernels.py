@@ -1123,6 +1123,24 @@ def test_clip_accumulate_dense_every_form(dp, tile, form, split, shape):
             assert float((err / (want.abs() + want.square().mean().sqrt())).max()) < m, l
 
 
+@pytest.mark.parametrize("n,B,T,d_in,d_out", [(1, 3, 129, 64, 72), (1, 300, 200, 64, 64), (1, 7, 256, 136, 64), (1, 7, 257, 64, 64), (2, 7, 256, 64, 64)])
+def test_gram_norms_of_one_unit_and_of_several(dp, n, B, T, d_in, d_out):
+    """One layer of up to 256 rows per example is one unit, which adds to the norms itself; further rows and layers leave partial norms.
+    Against fp64, on top of what is there."""
+    import paper_2108_01624_amd as pkg
+
+    g = torch.Generator(device=DEV)
+    g.manual_seed(540)
+    X, Y = ([torch.randn(B, T, d, generator=g, device=DEV).to(torch.bfloat16) for _ in range(n)] for d in (d_in, d_out))
+    want = torch.full((B,), 0.5, dtype=torch.float64, device=DEV)
+    for x, y in zip(X, Y):
+        want += (x.double().transpose(1, 2).contiguous() @ y.double()).square().sum((1, 2)) + y.double().sum(1).square().sum(1)
+    out = torch.full((B,), 0.5, device=DEV)
+    dp.sqnorms_dense_batched(X, Y, True, pkg.DP_PATH_GRAM, out)
+    dp.sync()
+    assert_norms_close(host(out), host(want), 2e-5)
+
+
 def test_step_driver_in_cpp_is_the_one_in_python(dp):
     """Both walks over a manifest with every kind of layer, inputs shared by two and by three layers, with and without bias, in two
     types, make the same calls in the same order: the same bits; then a second micro-batch, and one whose gradients were not kept."""
