@@ -489,8 +489,7 @@ dp_status dp_clip_accumulate_layernorm(dp_ctx* ctx, const void* Xhat, const void
     TRY(check_f32(ctx, "sum_beta", sum_beta));
     TRY(check_clip(ctx, C, B));
     if (B == 0 || T == 0 || d == 0) return DP_OK;
-    TRY(dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf));
-    return dpk_colstat_sums(ctx, Xhat, G, dtype, B, T, d, ctx->cbuf, sum_gamma, sum_beta);
+    return dpk_colstat_sums(ctx, Xhat, G, dtype, B, T, d, sqnorms, C, sum_gamma, sum_beta);
 }
 
 dp_status dp_sqnorms_layernorm_batched(dp_ctx* ctx, int n_layers, const void* const* Xhat, const void* const* G,
@@ -550,8 +549,7 @@ dp_status dp_clip_accumulate_layernorm_kept(dp_ctx* ctx, int n_layers, float* co
     TRY(check_f32(ctx, "sqnorms", sqnorms));
     TRY(check_clip(ctx, C, B));
     if (B == 0 || d == 0) return DP_OK;
-    TRY(dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf));
-    return dpk_kept_sums_batched(ctx, n_layers, grads, B, d, ctx->cbuf, sum_gamma, sum_beta);
+    return dpk_kept_sums_batched(ctx, n_layers, grads, B, d, sqnorms, C, sum_gamma, sum_beta);
 }
 
 dp_status dp_clip_accumulate_layernorm_batched(dp_ctx* ctx, int n_layers, const void* const* Xhat, const void* const* G,
@@ -572,8 +570,7 @@ dp_status dp_clip_accumulate_layernorm_batched(dp_ctx* ctx, int n_layers, const 
     TRY(check_f32(ctx, "sqnorms", sqnorms));
     TRY(check_clip(ctx, C, B));
     if (B == 0 || T == 0 || d == 0) return DP_OK;
-    TRY(dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf));
-    return dpk_colstat_sums_batched(ctx, n_layers, Xhat, G, dtype, B, T, d, ctx->cbuf, sum_gamma, sum_beta);
+    return dpk_colstat_sums_batched(ctx, n_layers, Xhat, G, dtype, B, T, d, sqnorms, C, sum_gamma, sum_beta);
 }
 
 dp_status dp_clip_accumulate_embedding(dp_ctx* ctx, const int32_t* ids, const void* G, dp_dtype dtype, int B, int T,
@@ -603,10 +600,9 @@ dp_status dp_clip_accumulate_positions(dp_ctx* ctx, const void* G, dp_dtype dtyp
     TRY(check_clip(ctx, C, B));
     if (B == 0 || T == 0 || d == 0) return DP_OK;
     if ((long)T * d > 0x7FFFFFFFl) FAIL(ctx, DP_ERR_SHAPE, "T * d too large");
-    TRY(dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf));
     // token t of every example adds to row t: the first T rows of the table, read as one vector of T*d entries,
     // receive sum_i c_i * (example i's gradient read as one row of T*d entries): a weighted column sum over B rows
-    return dpk_colstat_sums(ctx, nullptr, G, dtype, B, 1, T * d, ctx->cbuf, nullptr, sum_E);
+    return dpk_colstat_sums(ctx, nullptr, G, dtype, B, 1, T * d, sqnorms, C, nullptr, sum_E);
 }
 
 static dp_status check_tied(dp_ctx* ctx, const int32_t* ids, const void* dY, const void* H, const void* dL,

@@ -207,15 +207,15 @@ dp_status dpk_weighted_gemm_batched(dp_ctx*, int n, const void* const* A, const 
 //   sums:     out_x[j] += sum_i c_i sum_t g x ; out_1[j] += sum_i c_i sum_t g   (either may be NULL)
 dp_status dpk_colstat_sqnorms(dp_ctx*, const void* X, const void* G, dp_dtype, int B, int T, int d, int use_x,
                               int use_1, float* sqnorms);
-dp_status dpk_colstat_sums(dp_ctx*, const void* X, const void* G, dp_dtype, int B, int T, int d, const float* c,
+dp_status dpk_colstat_sums(dp_ctx*, const void* X, const void* G, dp_dtype, int B, int T, int d, const float* sqnorms, float C,
                            float* out_x, float* out_1);
 
 dp_status dpk_colstat_sqnorms_batched(dp_ctx*, int n, const void* const* X, const void* const* G, dp_dtype, int B, int T, int d,
                                       int use_x, int use_1, float* sqnorms, float* const* keep /* or NULL */);
-dp_status dpk_kept_sums_batched(dp_ctx*, int n, float* const* keep, int B, int d, const float* c, float* const* sum_x,
+dp_status dpk_kept_sums_batched(dp_ctx*, int n, float* const* keep, int B, int d, const float* sqnorms, float C, float* const* sum_x,
                                 float* const* sum_1);
 dp_status dpk_colstat_sums_batched(dp_ctx*, int n, const void* const* X, const void* const* G, dp_dtype, int B, int T, int d,
-                                   const float* c, float* const* out_x, float* const* out_1);
+                                   const float* sqnorms, float C, float* const* out_x, float* const* out_1);
 
 dp_status dpk_embedding_sqnorms(dp_ctx*, const int32_t* ids, const void* G, dp_dtype, int B, int T, int d, int V,
                                 int distinct, float* sqnorms);

@@ -75,6 +75,7 @@ struct ColOut {
     float* out_x[COL_MAX_BATCH];
     float* out_1[COL_MAX_BATCH];
 };
+constexpr int COL_FACTORS = 2048;  // clip factors that a workgroup forms itself
 struct ColKeep {
     float* keep[COL_MAX_BATCH];  // per layer: [B][2][d] fp32, the per-example column statistics themselves
 };
@@ -155,24 +156,37 @@ __global__ __launch_bounds__(256) void colstat_sqnorms_kernel(ColBatch cb, ColKe
 //   grid (R, ceil(d / (64*VW))): WG r reduces rows [r*rows_per, (r+1)*rows_per) of the B*T rows
 //   partial layout: part[layer][r][0][d] = sum c g x,  part[layer][r][1][d] = sum c g   (blockIdx.z = layer)
 // ------------------------------------------------------------------------------------------------
-template <bool BF16, int VW, bool USE_X>
-// (the clip factors come precomputed: forming them here, a square root and a division per row and thread, cost 2 %)
-__global__ __launch_bounds__(256) void colstat_sums_kernel(ColBatch cb, const float* __restrict__ c, int T, int d,
-                                                           long nrows, int rows_per, float* __restrict__ part) {
+// The factors of up to COL_FACTORS examples are formed here, once per workgroup (OWN: `c` holds the squared norms); per row and thread, a square root and a division,
+// they cost 2 %.  One run of rows (DIRECT) is added to the sums themselves.  T x d = 45 x 384 entries of 171 examples: three launches of 4.1, 6.9 and 3.8 us, now two.
+template <bool BF16, int VW, bool USE_X, bool OWN>
+__global__ __launch_bounds__(256) void colstat_sums_kernel(ColBatch cb, ColOut co, const float* __restrict__ c, float C, int T, int d,
+                                                           long nrows, int rows_per, float* __restrict__ part, int direct, int* __restrict__ err) {
     __shared__ float red[4][64][2 * VW];
+    __shared__ float own[OWN ? COL_FACTORS : 1];
     const void* __restrict__ X = cb.X[blockIdx.z];
     const void* __restrict__ G = cb.G[blockIdx.z];
     const int lane = threadIdx.x & 63, tg = threadIdx.x >> 6;
     const int col = (blockIdx.y * 64 + lane) * VW;
     const long r0 = (long)blockIdx.x * rows_per;
     const long r1 = r0 + rows_per < nrows ? r0 + rows_per : nrows;
+    long e0 = 0;  // the example that `c` begins with
+    if constexpr (OWN) {
+        e0 = r0 / T;
+        for (long e = e0 + threadIdx.x; e * T < r1; e += 256) {
+            const float ce = dp_clip_factor(c[e], C);
+            own[e - e0] = ce;
+            if (ce != ce) atomicOr(err, DP_ERRBIT_NORM);
+        }
+        __syncthreads();
+        c = own;
+    }
     float sx[VW], s1[VW];
 #pragma unroll
     for (int k = 0; k < VW; ++k) sx[k] = s1[k] = 0.f;
     if (col < d) {
 #pragma unroll 4
         for (long r = r0 + tg; r < r1; r += 4) {
-            const float w = c[r / T];
+            const float w = c[r / T - e0];
             float g[VW];
             load_vec<BF16, VW>(G, (size_t)r * d + col, g);
             if constexpr (USE_X) {
@@ -191,7 +205,20 @@ __global__ __launch_bounds__(256) void colstat_sums_kernel(ColBatch cb, const fl
         red[tg][lane][VW + k] = s1[k];
     }
     __syncthreads();
-    if (tg == 0 && col < d) {
+    if (tg == 0 && col < d && direct) {
+        float *x = USE_X ? co.out_x[blockIdx.z] : nullptr, *o = co.out_1[blockIdx.z];
+        float ox[VW], oo[VW];
+#pragma unroll
+        for (int k = 0; k < VW; ++k) {
+            ox[k] = x ? x[col + k] : 0.f;
+            oo[k] = o ? o[col + k] : 0.f;
+        }
+#pragma unroll
+        for (int k = 0; k < VW; ++k) {
+            if (x) x[col + k] = ox[k] + ((red[0][lane][k] + red[1][lane][k]) + (red[2][lane][k] + red[3][lane][k]));
+            if (o) o[col + k] = oo[k] + ((red[0][lane][VW + k] + red[1][lane][VW + k]) + (red[2][lane][VW + k] + red[3][lane][VW + k]));
+        }
+    } else if (tg == 0 && col < d) {
         float* p = part + ((size_t)blockIdx.z * gridDim.x + blockIdx.x) * 2 * d;
 #pragma unroll
         for (int k = 0; k < VW; ++k) {
@@ -203,9 +230,21 @@ __global__ __launch_bounds__(256) void colstat_sums_kernel(ColBatch cb, const fl
 
 // Pass 2 from kept per-example statistics: out_x[j] += sum_i c_i keep[i][0][j], out_1[j] += sum_i c_i keep[i][1][j].
 // grid (ceil(2d / 256), layers); 256 threads = 64 float4 columns x 4 example groups; group g adds the examples
-// i = g, g+4, ... in ascending order, the four group sums are added as (0+1)+(2+3): fixed order.
-__global__ __launch_bounds__(256) void kept_sums_kernel(ColKeep ck, ColOut co, const float* __restrict__ c, int B, int d) {
+// i = g, g+4, ... in ascending order, the four group sums are added as (0+1)+(2+3): fixed order.  A workgroup forms the factors itself
+// (OWN: `c` holds the squared norms, up to COL_FACTORS of them): they are a launch that it would wait for otherwise.
+template <bool OWN>
+__global__ __launch_bounds__(256) void kept_sums_kernel(ColKeep ck, ColOut co, const float* __restrict__ c, float C, int B, int d, int* __restrict__ err) {
     __shared__ float4 red[4][64];
+    __shared__ float own[OWN ? COL_FACTORS : 1];
+    if constexpr (OWN) {
+        for (int i = threadIdx.x; i < B; i += 256) {
+            const float ci = dp_clip_factor(c[i], C);
+            own[i] = ci;
+            if (ci != ci) atomicOr(err, DP_ERRBIT_NORM);
+        }
+        __syncthreads();
+        c = own;
+    }
     const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
     const int n4 = 2 * d / 4, d4 = d / 4;
     const int j = blockIdx.x * 64 + lane;
@@ -1258,9 +1297,14 @@ dp_status dpk_colstat_sqnorms(dp_ctx* ctx, const void* X, const void* G, dp_dtyp
 }
 
 // sum_x[l][j] += sum_i c_i keep[l][i][0][j], sum_1[l][j] += sum_i c_i keep[l][i][1][j]; d % 4 == 0, 16-byte aligned buffers
-dp_status dpk_kept_sums_batched(dp_ctx* ctx, int n, float* const* keep, int B, int d, const float* c, float* const* sum_x,
+dp_status dpk_kept_sums_batched(dp_ctx* ctx, int n, float* const* keep, int B, int d, const float* sqnorms, float C, float* const* sum_x,
                                 float* const* sum_1) {
     if (B == 0 || d == 0 || n == 0) return DP_OK;
+    const bool own = B <= COL_FACTORS;
+    if (!own) {
+        const dp_status st = dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf);
+        if (st != DP_OK) return st;
+    }
     int L;
     for (int l0 = 0; l0 < n; l0 += L) {
         L = dp_disjoint_layers(n - l0 < COL_MAX_BATCH ? n - l0 : COL_MAX_BATCH, sum_x + l0, d, sum_1 + l0, d);
@@ -1271,7 +1315,9 @@ dp_status dpk_kept_sums_batched(dp_ctx* ctx, int n, float* const* keep, int B, i
             co.out_x[l] = sum_x[l0 + (l < L ? l : 0)];
             co.out_1[l] = sum_1[l0 + (l < L ? l : 0)];
         }
-        hipLaunchKernelGGL(kept_sums_kernel, dim3((unsigned)((2 * d / 4 + 63) / 64), L), dim3(256), 0, ctx->stream, ck, co, c, B, d);
+        const dim3 grid((unsigned)((2 * d / 4 + 63) / 64), L);
+        if (own) hipLaunchKernelGGL(kept_sums_kernel<true>, grid, dim3(256), 0, ctx->stream, ck, co, sqnorms, C, B, d, ctx->err_word);
+        else hipLaunchKernelGGL(kept_sums_kernel<false>, grid, dim3(256), 0, ctx->stream, ck, co, ctx->cbuf, C, B, d, ctx->err_word);
         DP_LAUNCH_CHECK(ctx, "kept_sums");
     }
     return DP_OK;
@@ -1291,36 +1337,44 @@ static long colstat_runs(long nrows, int d, int vw, int* rows_per) {
 // out_x / out_1: tables of L pointers, or NULL when that statistic is not wanted (the same for every layer of the call)
 template <bool BF16, int VW>
 static dp_status colstat_sums_launch(dp_ctx* ctx, int L, const void* const* X, const void* const* G, int B, int T, int d,
-                                     const float* c, float* const* out_x, float* const* out_1) {
+                                     const float* sqnorms, float C, float* const* out_x, float* const* out_1) {
     const long nrows = (long)B * T;
     const int J = (d + 64 * VW - 1) / (64 * VW);
     int rows_per;
     const long R = colstat_runs(nrows, d, VW, &rows_per);
+    const bool direct = R == 1, own = rows_per / T + 2 <= COL_FACTORS;
+    if (!own) {
+        const dp_status st = dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf);
+        if (st != DP_OK) return st;
+    }
     dp_ws_alloc ws(ctx);
-    float* part = ws.get<float>((size_t)L * R * 2 * d);
-    if (!part) {
+    float* part = direct ? nullptr : ws.get<float>((size_t)L * R * 2 * d);
+    if (!direct && !part) {
         DP_SET_ERR(ctx, "workspace too small for column-sum partials (%d x %ld x 2 x %d floats)", L, R, d);
         return DP_ERR_WORKSPACE;
     }
     ColBatch cb;
+    ColOut co;
     for (int l = 0; l < COL_MAX_BATCH; ++l) {
-        cb.X[l] = out_x ? X[l < L ? l : 0] : nullptr;
-        cb.G[l] = G[l < L ? l : 0];
+        const int src = l < L ? l : 0;
+        cb.X[l] = out_x ? X[src] : nullptr;
+        cb.G[l] = G[src];
+        co.out_x[l] = out_x ? out_x[src] : nullptr;
+        co.out_1[l] = out_1 ? out_1[src] : nullptr;
     }
     dim3 grid((unsigned)R, J, L);
-    if (out_x)
-        hipLaunchKernelGGL((colstat_sums_kernel<BF16, VW, true>), grid, dim3(256), 0, ctx->stream, cb, c, T, d, nrows, rows_per, part);
-    else
-        hipLaunchKernelGGL((colstat_sums_kernel<BF16, VW, false>), grid, dim3(256), 0, ctx->stream, cb, c, T, d, nrows, rows_per, part);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, ctx->stream, cb, co, own ? sqnorms : ctx->cbuf, C, T, d, nrows, rows_per, part, direct ? 1 : 0, ctx->err_word);
+    };
+    if (out_x && own) launch(colstat_sums_kernel<BF16, VW, true, true>);
+    else if (out_x) launch(colstat_sums_kernel<BF16, VW, true, false>);
+    else if (own) launch(colstat_sums_kernel<BF16, VW, false, true>);
+    else launch(colstat_sums_kernel<BF16, VW, false, false>);
     DP_LAUNCH_CHECK(ctx, "colstat_sums");
+    if (direct) return DP_OK;
     bool pair = out_x && out_1 && d % 4 == 0 && R >= 32 && d <= 32768 && ((uintptr_t)part & 15) == 0;
     for (int l = 0; pair && l < L; ++l) pair = (((uintptr_t)out_x[l] | (uintptr_t)out_1[l]) & 15) == 0;
     if (pair) {
-        ColOut co;
-        for (int l = 0; l < COL_MAX_BATCH; ++l) {
-            co.out_x[l] = out_x[l < L ? l : 0];
-            co.out_1[l] = out_1[l < L ? l : 0];
-        }
         const size_t d4 = (size_t)d / 4;
         hipLaunchKernelGGL(reduce_partials_pair_kernel, dim3((unsigned)((2 * d4 + 63) / 64), L), dim3(256), 0, ctx->stream,
                            reinterpret_cast<const float4*>(part), (int)R, d4, co);
@@ -1338,7 +1392,7 @@ static dp_status colstat_sums_launch(dp_ctx* ctx, int L, const void* const* X, c
 }
 
 dp_status dpk_colstat_sums_batched(dp_ctx* ctx, int n, const void* const* X, const void* const* G, dp_dtype dt, int B, int T,
-                                   int d, const float* c, float* const* out_x, float* const* out_1) {
+                                   int d, const float* sqnorms, float C, float* const* out_x, float* const* out_1) {
     if (B == 0 || T == 0 || d == 0 || n == 0 || (!out_x && !out_1)) return DP_OK;
     bool v4 = true;
     for (int l = 0; l < n; ++l) v4 = v4 && vec4_ok(dt, d, out_x ? X[l] : G[l], G[l]);
@@ -1353,17 +1407,17 @@ dp_status dpk_colstat_sums_batched(dp_ctx* ctx, int n, const void* const* X, con
         float* const* o1 = out_1 ? out_1 + l0 : nullptr;
         L = dp_disjoint_layers(n - l0 < (int)per ? n - l0 : (int)per, ox, d, o1, d);
         dp_status st;
-        if (dt == DP_BF16) st = colstat_sums_launch<true, 4>(ctx, L, Xl, G + l0, B, T, d, c, ox, o1);
-        else if (v4) st = colstat_sums_launch<false, 4>(ctx, L, Xl, G + l0, B, T, d, c, ox, o1);
-        else st = colstat_sums_launch<false, 1>(ctx, L, Xl, G + l0, B, T, d, c, ox, o1);
+        if (dt == DP_BF16) st = colstat_sums_launch<true, 4>(ctx, L, Xl, G + l0, B, T, d, sqnorms, C, ox, o1);
+        else if (v4) st = colstat_sums_launch<false, 4>(ctx, L, Xl, G + l0, B, T, d, sqnorms, C, ox, o1);
+        else st = colstat_sums_launch<false, 1>(ctx, L, Xl, G + l0, B, T, d, sqnorms, C, ox, o1);
         if (st != DP_OK) return st;
     }
     return DP_OK;
 }
 
-dp_status dpk_colstat_sums(dp_ctx* ctx, const void* X, const void* G, dp_dtype dt, int B, int T, int d, const float* c,
+dp_status dpk_colstat_sums(dp_ctx* ctx, const void* X, const void* G, dp_dtype dt, int B, int T, int d, const float* sqnorms, float C,
                            float* out_x, float* out_1) {
-    return dpk_colstat_sums_batched(ctx, 1, &X, &G, dt, B, T, d, c, out_x ? &out_x : nullptr, out_1 ? &out_1 : nullptr);
+    return dpk_colstat_sums_batched(ctx, 1, &X, &G, dt, B, T, d, sqnorms, C, out_x ? &out_x : nullptr, out_1 ? &out_1 : nullptr);
 }
 
 template <bool BF16, int VW>

@@ -108,14 +108,15 @@ __device__ __forceinline__ void snr_store(float sig, float noi, float* __restric
     }
 }
 
-// Fast path: elem_offset % 4 == 0 and 16-byte aligned pointers.  Thread i owns local elements 4i .. 4i+3.
+// Fast path: elem_offset % 4 == 0 and 16-byte aligned pointers.  Thread i owns local elements 4i .. 4i+3, the thread behind the last
+// of these the `tail` elements (up to three) that are left: a launch of their own would cost a short update as much as its work.
 // Every byte is touched exactly once per step, so loads and stores carry the non-temporal hint (no reuse to keep
 // in L2, and lines of the 4 x 1.3 GB state do not evict each other's neighbours).
 template <bool NOISE, bool ZERO, bool SNR>
 __global__ __launch_bounds__(256) void noise_adamw_vec4(float* __restrict__ params, float* __restrict__ m,
                                                         float* __restrict__ v, float* __restrict__ sum,
                                                         uint64_t nblocks4, uint64_t block0, uint64_t seed,
-                                                        uint64_t step, AdamArgs a, float* __restrict__ snr_part) {
+                                                        uint64_t step, AdamArgs a, float* __restrict__ snr_part, int tail) {
     const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     float sig = 0.f, noi = 0.f;
     if (i < nblocks4) {
@@ -147,11 +148,31 @@ __global__ __launch_bounds__(256) void noise_adamw_vec4(float* __restrict__ para
                         n3 = a.noise_scale * z[3];
             noi = (n0 * n0 + n1 * n1) + (n2 * n2 + n3 * n3);
         }
+    } else if (i == nblocks4 && tail) {
+        float z[4] = {0.f, 0.f, 0.f, 0.f};
+        if (NOISE) block_normals(block0 + i, seed, step, z);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (k >= tail) continue;
+            const uint64_t j = 4 * i + k;
+            float th = params[j], mk = m[j], vk = v[j];
+            const float sj = sum[j];
+            adam_elem(th, mk, vk, sj, z[k], a);
+            params[j] = th;
+            m[j] = mk;
+            v[j] = vk;
+            if (ZERO) sum[j] = 0.f;
+            if (SNR) {
+                const float nz = a.noise_scale * z[k];
+                sig += sj * sj;
+                noi += nz * nz;
+            }
+        }
     }
     snr_store<SNR>(sig, noi, snr_part, blockIdx.x);
 }
 
-// General path: any offset / alignment, and the ragged tail of the fast path.  Thread i owns the Philox
+// General path: any offset / alignment.  Thread i owns the Philox
 // block first_block + i and touches only those of its four elements that fall inside [e_lo, e_hi).
 // `base_elem` is the global index of params[0].
 template <bool NOISE, bool ZERO, bool SNR>
@@ -278,10 +299,11 @@ __global__ __launch_bounds__(256) void clip_factors_kernel(const float* __restri
     }
 }
 
-// How a slice [off, off + n) is cut into launches: the 16-byte-aligned body in blocks of four elements (vec4 kernel),
-// the rest (or everything, when the slice is not aligned) element by element; one partial pair per workgroup.
+// How a slice [off, off + n) is cut into launches: aligned to 16 bytes, in blocks of four elements and what is left of one (vec4
+// kernel); otherwise, or below four elements, element by element.  One partial pair per workgroup.
 struct AdamPlan {
     uint64_t nb4, grid4, done, first, nblocks, grid1;
+    int tail;
     uint64_t pairs() const { return grid4 + grid1; }
     bool fits() const { return grid4 <= 0x7FFFFFFFull && grid1 <= 0x7FFFFFFFull; }
 };
@@ -289,8 +311,9 @@ AdamPlan plan_adamw(const float* params, const float* m, const float* v, const f
     AdamPlan p{};
     const bool aligned = (off % 4 == 0) && (((uintptr_t)params | (uintptr_t)m | (uintptr_t)v | (uintptr_t)sum) & 15) == 0;
     p.nb4 = (aligned && n >= 4) ? n / 4 : 0;
-    p.grid4 = (p.nb4 + 255) / 256;
-    p.done = p.nb4 * 4;
+    p.tail = p.nb4 ? (int)(n % 4) : 0;
+    p.grid4 = (p.nb4 + (p.tail ? 1 : 0) + 255) / 256;
+    p.done = p.nb4 * 4 + p.tail;
     if (p.done < n) {
         p.first = (off + p.done) / 4;
         p.nblocks = (off + n - 1) / 4 - p.first + 1;
@@ -307,7 +330,7 @@ hipError_t launch_adamw(hipStream_t stream, const AdamPlan& pl, float* params, f
     hipError_t e = hipSuccess;
     if (pl.grid4) {
         hipLaunchKernelGGL((noise_adamw_vec4<NOISE, ZERO, SNR>), dim3((unsigned)pl.grid4), dim3(256), 0, stream, params, m,
-                           v, sum, pl.nb4, off / 4, seed, step, a, part);
+                           v, sum, pl.nb4, off / 4, seed, step, a, part, pl.tail);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (pl.grid1) {

@@ -1304,10 +1304,13 @@ static F32Plan choose_f32_plan(long K, int d_in, int d_out) {
 static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, dp_dtype dt, int B, int T, int d_in, int d_out,
                                      const float* sqnorms, float C, float* sum_W, float* sum_b) {
     if (dt != DP_F32 && !sum_b) return DP_OK;
-    const bool own = d_in > 0 && B <= F32_FACTORS;
+    if (d_in == 0) {
+        if (!sum_b) return dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf);  // (nothing to add; a norm that is no number is still reported)
+        return dpk_colstat_sums(ctx, nullptr, G, dt, B, T, d_out, sqnorms, C, nullptr, sum_b);
+    }
+    const bool own = B <= F32_FACTORS;
     dp_status st = own ? DP_OK : dpk_clip_factors(ctx, sqnorms, B, C, ctx->cbuf);
-    if (st != DP_OK || (d_in == 0 && !sum_b)) return st;
-    if (d_in == 0) return dpk_colstat_sums(ctx, nullptr, G, dt, B, T, d_out, ctx->cbuf, nullptr, sum_b);
+    if (st != DP_OK) return st;
     // (fp32 from here)
     const long K = (long)B * T;
     const F32Plan plan = choose_f32_plan(K, d_in, d_out);

@@ -1141,6 +1141,29 @@ def test_gram_norms_of_one_unit_and_of_several(dp, n, B, T, d_in, d_out):
     assert_norms_close(host(out), host(want), 2e-5)
 
 
+@pytest.mark.parametrize("B,T,d", [(1, 3, 40), (64, 2, 264), (65, 5, 72), (2048, 1, 8), (2049, 1, 8), (4200, 2, 24)])
+def test_column_sums_at_the_edges_of_their_forms(dp, B, T, d):
+    """One run of rows, which is added directly, and several; factors formed in the launch (up to 2,048 examples a workgroup) and before it:
+    positions, LayerNorm sums from kept gradients and from the inputs, against fp64 (n 2^-24 of the sum of magnitudes, n terms)."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(541)
+    X, G = (torch.randn(B, T, d, generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    sq = f32_dev(syn.synthetic_sqnorms(B, 1.0, 542))
+    w = torch.clamp(1.0 / sq.double().sqrt(), max=1.0)[:, None, None]
+    cg, cgx = w * G.double(), w * G.double() * X.double()
+    E = torch.full((T, d), 0.25, device=DEV)
+    dp.clip_accumulate_positions(G, 1.0, sq, E)
+    keep, n = torch.empty(B, 2, d, device=DEV), torch.zeros(B, device=DEV)
+    dp.sqnorms_layernorm_keep([X], [G], n, [keep])
+    gk, bk, gx, bx = (torch.full((d,), 0.25, device=DEV) for _ in range(4))
+    dp.clip_accumulate_layernorm_kept([keep], B, d, 1.0, sq, [gk], [bk])
+    dp.clip_accumulate_layernorm_batched([X], [G], 1.0, sq, [gx], [bx])
+    dp.sync()
+    for got, terms, dims in ((E, cg, 0), (gk, cgx, (0, 1)), (bk, cg, (0, 1)), (gx, cgx, (0, 1)), (bx, cg, (0, 1))):
+        bound = (B * T + 8) * 2.0**-24 * (terms.abs().sum(dims) + 0.25)
+        assert bool(((got.double() - 0.25 - terms.sum(dims)).abs() <= bound).all())
+
+
 def test_step_driver_in_cpp_is_the_one_in_python(dp):
     """Both walks over a manifest with every kind of layer, inputs shared by two and by three layers, with and without bias, in two
     types, make the same calls in the same order: the same bits; then a second micro-batch, and one whose gradients were not kept."""
