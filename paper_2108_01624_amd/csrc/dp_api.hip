@@ -330,6 +330,13 @@ dp_status dp_rdp_noise_multiplier(const double* q, const uint64_t* steps, int n_
     return DP_OK;
 }
 
+// DP_PATH_AUTO: fewer operations, or, where that leaves the chip idle, the path that fills it.
+static dp_path choose_dense_path(const dp_ctx* ctx, int n, int B, int T, int d_in, int d_out, dp_dtype dtype) {
+    dp_path path;
+    dp_choose_path(T, d_in, d_out, dtype, &path);
+    return path == DP_PATH_GRAM && dtype == DP_BF16 && dpk_materialise_sooner(ctx, n, B, T, d_in, d_out) ? DP_PATH_MATERIALISE : path;
+}
+
 dp_status dp_sqnorms_dense(dp_ctx* ctx, const void* A, const void* G, dp_dtype dtype, int B, int T, int d_in,
                            int d_out, int has_bias, dp_path path, float* sqnorms) {
     REQUIRE_CTX(ctx);
@@ -346,7 +353,7 @@ dp_status dp_sqnorms_dense(dp_ctx* ctx, const void* A, const void* G, dp_dtype d
         if (has_bias) return dpk_colstat_sqnorms(ctx, nullptr, G, dtype, B, T, d_out, 0, 1, sqnorms);
         return DP_OK;
     }
-    if (path == DP_PATH_AUTO) dp_choose_path(T, d_in, d_out, dtype, &path);
+    if (path == DP_PATH_AUTO) path = choose_dense_path(ctx, 1, B, T, d_in, d_out, dtype);
     if (path == DP_PATH_GRAM) return dpk_gram_sqnorms(ctx, A, G, dtype, B, T, d_in, d_out, has_bias, sqnorms);
     return dpk_materialise_sqnorms_batched(ctx, 1, &A, &G, dtype, B, T, d_in, d_out, has_bias, sqnorms);
 }
@@ -367,7 +374,7 @@ dp_status dp_sqnorms_dense_batched(dp_ctx* ctx, int n_layers, const void* const*
     }
     TRY(check_f32(ctx, "sqnorms", sqnorms));
     if (B == 0 || T == 0 || d_out == 0) return DP_OK;
-    if (path == DP_PATH_AUTO && d_in > 0) dp_choose_path(T, d_in, d_out, dtype, &path);
+    if (path == DP_PATH_AUTO && d_in > 0) path = choose_dense_path(ctx, n_layers, B, T, d_in, d_out, dtype);
     if (path == DP_PATH_GRAM && d_in > 0)
         return dpk_gram_sqnorms_batched(ctx, n_layers, A, G, dtype, B, T, d_in, d_out, has_bias, sqnorms);
     if (path == DP_PATH_MATERIALISE && d_in > 0)
@@ -630,8 +637,9 @@ dp_status dp_sqnorms_tied_embedding(dp_ctx* ctx, const int32_t* ids, const void*
     if (T > 0) TRY(dpk_embedding_sqnorms(ctx, ids, dY, dtype, B, T, d, V, 0, sqnorms));
     if (M == 0) return DP_OK;
     // the output projection as a dense layer with weight E: "input" dL_i [M, V], "output gradient" H_i [M, d];
-    // M is far below both widths, so the Gram form <dL dL^T, H H^T> is the cheap one
-    TRY(dpk_gram_sqnorms(ctx, dL, H, dtype, B, M, V, d, 0, sqnorms));
+    // M is far below both widths, so the Gram form <dL dL^T, H H^T> is the cheap one, if not always the quick one
+    if (dtype == DP_BF16 && dpk_materialise_sooner(ctx, 1, B, M, V, d)) TRY(dpk_materialise_sqnorms_batched(ctx, 1, &dL, &H, dtype, B, M, V, d, 0, sqnorms));
+    else TRY(dpk_gram_sqnorms(ctx, dL, H, dtype, B, M, V, d, 0, sqnorms));
     return dpk_tied_cross_sqnorms(ctx, ids, dY, H, dL, dtype, B, T, M, d, V, sqnorms);
 }
 

@@ -1379,9 +1379,46 @@ dp_status dpk_dense_sum_plan(dp_dtype dt, int n, int B, int T, int d_in, int d_o
     return DP_OK;
 }
 
+// The tile of n layers' norms by materialisation, and the modelled time of their launch: the stage costs above (a workgroup without a sum to
+// add to takes about 3 us besides its stages).
+static double materialise_tile(int n, int B, int T, int d_in, int d_out, int* bm, int* bn) {
+    double best_t = 0.0;
+    *bm = *bn = 0;
+    for (int m = 256; m >= 128; m -= 128)
+        for (int k = 256; k >= 128; k -= 128) {
+            const long wgs = (long)n * B * ((d_in + m - 1) / m) * ((d_out + k - 1) / k);
+            const DmaCost c = dma_cost(m, k, false);
+            const double t = (double)((wgs + 256 * c.wgs - 1) / (256 * c.wgs)) * ((T + BK - 1) / BK * (wgs <= 256 ? c.t_stage_alone : c.t_stage) + 3.0);
+            if (!*bm || t < best_t) {
+                *bm = m;
+                *bn = k;
+                best_t = t;
+            }
+        }
+    return best_t;
+}
+
+// Whether bf16 norms that take fewer operations from Gram matrices are there sooner by materialisation: with few examples the Gram kernels run one workgroup to an
+// example (and unit), a chain of chunks of 64 columns on a chip that is mostly idle, while the gradient's tiles fill it.  Microseconds a chunk, measured:
+// 0.68 above 128 rows, 0.41 (chunks of 128 columns in pairs) and 0.54 from 65, 0.15 and 0.22 from 33; shorter examples split their chunks over waves.
+// Of 205 shapes 23 change by it; us, Gram | materialised: B = 3, T = 98, 1024 x 4096 38 | 11; B = 17, T = 80, 3664 x 296 40 | 16; three layers of 896 x 3584, B = 3,
+// T = 164 53 | 21; B = 9, T = 330, 1920 x 640 34 | 16; B = 32, T = 64, 27168 x 256 100 | 78.  The entries of a materialised gradient are squared and added: no cancellation,
+// the error is no larger.
+bool dpk_materialise_sooner(const dp_ctx* ctx, int n, int B, int T, int d_in, int d_out) {
+    uint32_t words[70];
+    int units = 1, bm, bn;
+    if (T <= 32 || n > MAX_BATCH || !dp_sum_width_ok(DP_BF16, d_in, d_out)) return false;
+    if (T > 128 && dpk_gram_unit_plan(T, words, 70, &units) != DP_OK) return false;
+    if ((long)n * B * units > 256) return false;
+    const bool wide = d_in % 128 == 0 && d_out % 128 == 0;
+    const double chunk = T > 128 ? 0.68 : T > 64 ? (wide ? 0.41 : 0.54) : (wide ? 0.15 : 0.22);
+    const double gram = 4.0 + chunk * ((d_in + 63) / 64 + (d_out + 63) / 64), sooner = 4.0 + materialise_tile(n, B, T, d_in, d_out, &bm, &bn);
+    if ((size_t)B * n * ((d_in + bm - 1) / bm) * ((d_out + bn - 1) / bn) * sizeof(float) > ctx->ws_bytes) return false;
+    return sooner < 0.85 * gram;
+}
+
 // Norms by materialisation: a unit of the kernel is one example, its tiles of A_i^T G_i are squared and summed as they leave the
-// accumulators; partial norms [B][layers * tiles] through the workspace.  Tile: the smallest time of a launch by the stage
-// costs above (a workgroup without a sum to add to takes about 3 us besides its stages).
+// accumulators; partial norms [B][layers * tiles] through the workspace.
 dp_status dpk_materialise_sqnorms_batched(dp_ctx* ctx, int n, const void* const* A, const void* const* G, dp_dtype dt, int B, int T,
                                           int d_in, int d_out, int has_bias, float* sqnorms) {
     dp_status st = DP_OK;
@@ -1398,18 +1435,7 @@ dp_status dpk_materialise_sqnorms_batched(dp_ctx* ctx, int n, const void* const*
         int nl = n - l0 < MAX_BATCH ? n - l0 : MAX_BATCH, bm = 0, bn = 0;
         float* part = nullptr;
         for (;; nl = (nl + 1) / 2) {  // fewer layers, and at last the largest tile, until the partial norms fit
-            double best_t = 0.0;
-            for (int m = 256; m >= 128; m -= 128)
-                for (int k = 256; k >= 128; k -= 128) {
-                    const long wgs = (long)nl * B * ((d_in + m - 1) / m) * ((d_out + k - 1) / k);
-                    const DmaCost c = dma_cost(m, k, false);
-                    const double t = (double)((wgs + 256 * c.wgs - 1) / (256 * c.wgs)) * ((T + BK - 1) / BK * (wgs <= 256 ? c.t_stage_alone : c.t_stage) + 3.0);
-                    if (!bm || t < best_t) {
-                        bm = m;
-                        bn = k;
-                        best_t = t;
-                    }
-                }
+            materialise_tile(nl, B, T, d_in, d_out, &bm, &bn);
             dp_ws_alloc ws(ctx);
             part = ws.get<float>((size_t)B * nl * ((d_in + bm - 1) / bm) * ((d_out + bn - 1) / bn));
             if (!part && nl == 1) {
@@ -1418,7 +1444,6 @@ dp_status dpk_materialise_sqnorms_batched(dp_ctx* ctx, int n, const void* const*
                 part = ws.get<float>((size_t)B * ((d_in + bm - 1) / bm) * ((d_out + bn - 1) / bn));
             }
             if ((part && (long)nl * B * ((d_in + bm - 1) / bm) * ((d_out + bn - 1) / bn) < 0x7FFFFFF0l) || nl == 1) break;
-            bm = 0;
         }
         WgemmBatchArgs b;
         WgemmArgs& a = b.base;

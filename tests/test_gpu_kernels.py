@@ -1164,6 +1164,29 @@ def test_column_sums_at_the_edges_of_their_forms(dp, B, T, d):
         assert bool(((got.double() - 0.25 - terms.sum(dims)).abs() <= bound).all())
 
 
+@pytest.mark.parametrize("n,B,T,d_in,d_out,few", [(1, 3, 98, 1024, 4096, True), (3, 3, 164, 896, 3592, True), (1, 9, 330, 1920, 640, True),
+                                                  (1, 34, 45, 6504, 64, True), (1, 40, 33, 6504, 64, True), (1, 40, 32, 6504, 64, False),
+                                                  (1, 257, 98, 1024, 256, False), (2, 128, 129, 256, 1024, False), (1, 3, 98, 256, 256, False)])
+def test_norms_of_few_examples_are_materialised(dp, n, B, T, d_in, d_out, few):
+    """DP_PATH_AUTO on shapes of fewer operations by Gram: the bits of the path that it takes, and both paths against fp64."""
+    import paper_2108_01624_amd as pkg
+
+    assert pkg.dp_choose_path(T, d_in, d_out) == pkg.DP_PATH_GRAM
+    g = torch.Generator(device=DEV)
+    g.manual_seed(543)
+    A, G = ([torch.randn(B, T, d, generator=g, device=DEV).to(torch.bfloat16) for _ in range(n)] for d in (d_in, d_out))
+    want = sum((((a.double() @ a.double().transpose(1, 2).contiguous()) + 1) * (b.double() @ b.double().transpose(1, 2).contiguous())).sum((1, 2))
+               for a, b in zip(A, G))
+    got = {}
+    for path in (pkg.DP_PATH_AUTO, pkg.DP_PATH_GRAM, pkg.DP_PATH_MATERIALISE):
+        got[path] = torch.zeros(B, device=DEV)
+        dp.sqnorms_dense_batched(A, G, True, path, got[path])
+    dp.sync()
+    assert torch.equal(got[pkg.DP_PATH_AUTO], got[pkg.DP_PATH_MATERIALISE if few else pkg.DP_PATH_GRAM])
+    for out in got.values():
+        assert_norms_close(host(out), host(want), 2e-5)
+
+
 def test_step_driver_in_cpp_is_the_one_in_python(dp):
     """Both walks over a manifest with every kind of layer, inputs shared by two and by three layers, with and without bias, in two
     types, make the same calls in the same order: the same bits; then a second micro-batch, and one whose gradients were not kept."""
