@@ -411,12 +411,16 @@ __global__ __launch_bounds__(256) void reduce_partials_pair_kernel(const float4*
 // d = 2,048, B = 514 62 -> 56 us; T = 64, B = 400 26 -> 22).  Runs that are complete inside a wave are squared there; the sums of
 // a wave's first and last run go to LDS, where they are joined across the waves, column by column.
 // One wave walking all positions of its columns was a chain of T / 8 round trips: B = 23, T = 375, d = 832: 61 -> 23 us;
-// B = 512, T = 128, d = 1024 (134 MB): 31 + 5 -> 28.  Waves without positions would only make the joining of the parts longer: T = 16,
+// B = 512, T = 128, d = 1024 (134 MB): 31 + 5 -> 28.  Where there are two waves and more to 64 positions they share the comparisons of the ranking, and the
+// joining finds out which parts continue one another for all parts at once (B = 74, T = 295, d = 128, norms and sums 37.7 -> 35.6 us; B = 23, T = 375, d = 832 40.9 -> 38.6).
+// (32 rows in flight instead of 16: 5 to 8 % slower throughout.)  Waves without positions would only make the joining of the parts longer: T = 16,
 // d = 256, B = 4 12 us with 16 waves, 6 with 1; B = 514 16 | 7.
 // ------------------------------------------------------------------------------------------------
 // Rows in flight of a wave; without runs to form, position rows of B = 256, T = 128, d = 1,024 take 12.6 us with 8 and 11.4 with 16.
 constexpr int emb_ahead(bool distinct) { return distinct ? 16 : 8; }
 constexpr int EMB_PIECE = 16;  // positions that are worth a wave
+constexpr int EMB_SHARED = 512;  // positions up to which 16 waves are two and more to 64 of them
+__host__ __device__ constexpr int emb_shared_ranks(int T) { return T <= EMB_SHARED ? (T + 3) / 4 * 4 : 0; }
 
 // EMB_WAVES: the most waves that a launch may have; it has ncb * parts.
 template <bool BF16, int VW, bool DISTINCT, int EMB_WAVES>
@@ -429,7 +433,8 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
     __shared__ uint32_t whole[EMB_WAVES];                                 // the wave saw one run only: it is in head
     __shared__ float wred[EMB_WAVES];
     uint32_t* sid = lds;        // [T rounded up to 4] ids of this example
-    uint16_t* order = reinterpret_cast<uint16_t*>(lds + (T + 3) / 4 * 4);  // [T] row index at each sorted position (T <= 4096)
+    uint32_t* part_rank = lds + (T + 3) / 4 * 4;  // [T up to EMB_SHARED, otherwise none] ranks that several waves add up
+    uint16_t* order = reinterpret_cast<uint16_t*>(part_rank + emb_shared_ranks(T));  // [T] row index at each sorted position (T <= 4096)
     constexpr int AHEAD = emb_ahead(DISTINCT);
     const int i = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nt = 64 * ncb * parts;
@@ -438,34 +443,49 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
         const int32_t v = t < T ? ids[(size_t)i * T + t] : 0;
         if (t < T && (v < 0 || v >= V)) bad = true;
         sid[t] = t >= T ? 0xFFFFFFFFu : v == -1 ? 0xFFFFFFFEu : (uint32_t)v;  // (the padding ranks behind everything, also behind -1)
+        if (T <= EMB_SHARED) part_rank[t] = 0;
     }
     if (bad) atomicOr(err, 1);
     __syncthreads();
     if constexpr (!DISTINCT) {
         const uint4* s4 = reinterpret_cast<const uint4*>(sid);
-        const int n4 = (T + 3) / 4;
-        for (int t0 = wave * 64; t0 < T; t0 += nt) {  // (the same bounds for all lanes: the reads stay in flight)
-            const int t = t0 + lane, mid = t0 / 4 + 16 < n4 ? t0 / 4 + 16 : n4;
+        const int n4 = (T + 3) / 4, waves = ncb * parts, chunks = (T + 63) / 64;
+        // keys are unique as (id, position): before position t an equal id ranks lower, after it higher; against the positions 4 from .. 4 to
+        auto rank_of = [&](int t0, int from, int to) {
+            const int t = t0 + lane, mid = t0 / 4 + 16;
             const uint32_t v = sid[t < T ? t : T - 1];
-            // keys are unique as (id, position): before position t an equal id ranks lower, after it higher
             int rank = 0;
 #pragma unroll 4
-            for (int s = 0; s < t0 / 4; ++s) {
+            for (int s = from; s < (t0 / 4 < to ? t0 / 4 : to); ++s) {
                 const uint4 u = s4[s];
                 rank += (u.x <= v) + (u.y <= v) + (u.z <= v) + (u.w <= v);
             }
 #pragma unroll 4
-            for (int s = t0 / 4; s < mid; ++s) {
+            for (int s = from > t0 / 4 ? from : t0 / 4; s < (mid < to ? mid : to); ++s) {
                 const uint4 u = s4[s];
                 const int e = t - 4 * s;
                 rank += (u.x < v + (e > 0)) + (u.y < v + (e > 1)) + (u.z < v + (e > 2)) + (u.w < v + (e > 3));
             }
 #pragma unroll 4
-            for (int s = mid; s < n4; ++s) {
+            for (int s = from > mid ? from : mid; s < to; ++s) {
                 const uint4 u = s4[s];
                 rank += (u.x < v) + (u.y < v) + (u.z < v) + (u.w < v);
             }
-            if (t < T) order[rank] = (uint16_t)t;
+            return rank;
+        };
+        if (waves >= 2 * chunks) {  // (then T <= EMB_SHARED) several waves to 64 positions, each against its share of all
+            const int split = waves / chunks, chunk = wave % chunks, share = wave / chunks, t = chunk * 64 + lane;
+            if (share < split) {
+                const int rank = rank_of(chunk * 64, n4 * share / split, n4 * (share + 1) / split);
+                if (t < T) atomicAdd(&part_rank[t], (uint32_t)rank);
+            }
+            __syncthreads();
+            for (int t = threadIdx.x; t < T; t += nt) order[part_rank[t]] = (uint16_t)t;
+        } else {
+            for (int t0 = wave * 64; t0 < T; t0 += nt) {  // (the same bounds for all lanes: the reads stay in flight)
+                const int rank = rank_of(t0, 0, n4);
+                if (t0 + lane < T) order[rank] = (uint16_t)(t0 + lane);
+            }
         }
         __syncthreads();
     }
@@ -539,26 +559,28 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
         }
         if (lane == 0) whole[wave] = one ? 1u : 0u;
         __syncthreads();
-        if (part == 0 && col < d) {
+        if (part == 0) {
             // the parts of this column block in order of position: a part's first run continues the one before it when the ids agree
+            // (a part a lane: read one after the other, ids through the order, they are a chain of LDS reads)
+            const int q0 = lane < parts ? lane : 0, p0 = q0 * per;
+            const uint64_t joins = __ballot(q0 > 0 && p0 < T && sid[order[p0 < T ? p0 : 0]] == sid[order[p0 < T && p0 > 0 ? p0 - 1 : 0]]);
+            const uint64_t single = __ballot(lane < parts && whole[q0 * ncb + cb] != 0u);
             float carry[VW];
 #pragma unroll
             for (int k = 0; k < VW; ++k) carry[k] = 0.f;
-            uint32_t carry_id = 0;
-            for (int q = 0; q < parts && q * per < T; ++q) {
-                const int w = q * ncb + cb, end = (q + 1) * per < T ? (q + 1) * per : T;
-                const bool joins = q > 0 && sid[order[q * per]] == carry_id, single = whole[w] != 0u;
+            for (int q = 0; q < parts && q * per < T && col < d; ++q) {
+                const int w = q * ncb + cb;
+                const bool join = joins >> q & 1;
 #pragma unroll
                 for (int k = 0; k < VW; ++k) {
-                    const float h = head[w][lane * VW + k];
-                    tot += joins ? 0.f : carry[k] * carry[k];
-                    carry[k] = joins ? carry[k] + h : h;
-                    if (!single) {
+                    const float h = head[w][lane * VW + k], l = tail[w][lane * VW + k];
+                    tot += join ? 0.f : carry[k] * carry[k];
+                    carry[k] = join ? carry[k] + h : h;
+                    if (!(single >> q & 1)) {
                         tot += carry[k] * carry[k];
-                        carry[k] = tail[w][lane * VW + k];
+                        carry[k] = l;
                     }
                 }
-                carry_id = sid[order[end - 1]];
             }
 #pragma unroll
             for (int k = 0; k < VW; ++k) tot += carry[k] * carry[k];
@@ -1443,7 +1465,7 @@ static dp_status embedding_sqnorms_launch(dp_ctx* ctx, const int32_t* ids, const
         direct = 0;
     }
     dim3 grid(B, J);
-    const size_t lds = ((size_t)T + 3) / 4 * 4 * sizeof(uint32_t) + (size_t)T * sizeof(uint16_t);
+    const size_t lds = (((size_t)T + 3) / 4 * 4 + emb_shared_ranks(T)) * sizeof(uint32_t) + (size_t)T * sizeof(uint16_t);
     const long per_cu = ((long)B * J + 255) / 256;
     const int room = 16 / ncb / per_cu < 1 ? 1 : (int)(16 / ncb / per_cu), parts = pieces < room ? pieces : room, waves = ncb * parts;
     auto launch = [&](auto kernel) {

@@ -1187,6 +1187,24 @@ def test_norms_of_few_examples_are_materialised(dp, n, B, T, d_in, d_out, few):
         assert_norms_close(host(out), host(want), 2e-5)
 
 
+@pytest.mark.parametrize("T", [1, 15, 64, 65, 127, 128, 129, 300, 449, 511, 512, 513, 1100])
+@pytest.mark.parametrize("B,d", [(2, 8), (3, 264), (300, 72)])
+def test_embedding_norms_are_exact_whatever_shares_the_ranking(dp, B, T, d):
+    """Whole numbers: every sum below 2^24 is exact.  Few ids (long runs over several waves) and many."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(544)
+    ids = torch.randint(0, 400, (B, T), generator=g, device=DEV, dtype=torch.int32)
+    ids = torch.where(torch.rand(B, T, generator=g, device=DEV) < 0.4, ids % 3, ids)
+    G = torch.randint(-1, 2, (B, T, d), generator=g, device=DEV).to(torch.bfloat16)
+    n = torch.zeros(B, device=DEV)
+    dp.sqnorms_embedding(ids, G, 400, False, n)
+    dp.sync()
+    rows = torch.zeros(B * 400, d, device=DEV).index_add_(0, (ids.long() + 400 * torch.arange(B, device=DEV)[:, None]).view(-1), G.float().view(-1, d))
+    want = rows.view(B, -1).square().sum(1)
+    assert float(want.max()) < 2**24
+    assert torch.equal(n, want)
+
+
 def test_step_driver_in_cpp_is_the_one_in_python(dp):
     """Both walks over a manifest with every kind of layer, inputs shared by two and by three layers, with and without bias, in two
     types, make the same calls in the same order: the same bits; then a second micro-batch, and one whose gradients were not kept."""
