@@ -598,9 +598,9 @@ __global__ __launch_bounds__(64 * EMB_WAVES) void embedding_sqnorms_kernel(const
 }
 
 // ------------------------------------------------------------------------------------------------
-// embedding, clip-weighted scatter (pass 2): stable LSD radix sort of (id, row) + ordered segment sums
+// embedding, clip-weighted scatter (pass 2): the positions grouped by id (group_ids_kernel, or a stable LSD radix sort of (id, row)) + ordered segment sums
 // ------------------------------------------------------------------------------------------------
-// Launches: a histogram and a scatter per 8-bit digit (the first pair reads the ids themselves), segment sums, fix-up; up to
+// Launches of the sort: a histogram and a scatter per 8-bit digit (the first pair reads the ids themselves); up to
 // SORT_INLINE chunks a scatter forms its own bases from the histogram, beyond that a scan does.  Every launch of a few
 // microseconds of work costs about five: B * T = 65,536, V = 30,522: 46 -> 24 us for the sort (7 launches, now 4).
 // ------------------------------------------------------------------------------------------------

@@ -608,7 +608,7 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(ScaleBatch sb, const fl
 // fp32 inputs, on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: products and sums in fp32).  The contraction index is
 // the slow index of both operands in memory and the MFMA wants one k per half-wave: a lane's operand is simply the element
 // (row k + lane / 32, column lane % 32), 128 contiguous bytes a half-wave, straight from global memory into registers.  A
-// workgroup owns a tile of 32 TM x 32 TN; its 8 waves take the row pairs in turn (16 flop per byte of L2 at 2 x 2, 12 at 3 x 1: 10 and
+// workgroup owns a tile of 32 TM x 32 TN; its 8 waves take the row pairs in turn (24 flop per byte of L2 at 3 x 3, 16 at 2 x 2, 12 at 3 x 1: 6, 10 and
 // 13 TB/s at the full matrix rate) and their accumulators meet in LDS.  c_i multiplies G on the way in; the workgroups of tile row
 // 0 also add up the columns of c * G for the bias.
 // A block of rows is addressed by 32-bit offsets into one buffer resource; where a layer is so wide that a block's bytes do not
@@ -620,7 +620,7 @@ constexpr int F32_WAVES = 8;
 constexpr int F32_FACTORS = 1024;  // clip factors a workgroup forms itself; with more examples in its rows they come precomputed
 
 // Row pairs a wave of a TM x TN tile has in flight beside those it multiplies, and the rows of a workgroup's block of them.
-constexpr int f32_pairs(int tm, int tn) { return tm + tn < 3 ? 16 : 8; }
+constexpr int f32_pairs(int tm, int tn) { return tm + tn < 3 ? 16 : tm + tn > 4 ? 4 : 8; }
 constexpr int f32_block(int tm, int tn) { return 2 * F32_WAVES * f32_pairs(tm, tn); }
 
 template <int TM, int TN, bool OWN, bool WIDE>
@@ -889,6 +889,17 @@ __global__ __launch_bounds__(256) void finish_layers_kernel(FinishArgs f, int R,
     }
 }
 }  // namespace
+
+// R = 1: no partial sums of the weights, nb = 0: none of the biases.
+static dp_status finish_layers(dp_ctx* ctx, const FinishArgs& f, int nl, int R, size_t n4, const float* bias_part, int nb, int d_out) {
+    const bool tall = R >= 16 && n4 * nl <= 16384;  // too few columns to fill the chip one a thread
+    const long w_blocks = R > 1 ? (long)((n4 + (tall ? 63 : 255)) / (tall ? 64 : 256)) : 0, b_blocks = nb ? (d_out + 63) / 64 : 0;
+    const dim3 grid((unsigned)(w_blocks + b_blocks), nl);
+    if (tall) hipLaunchKernelGGL(finish_layers_kernel<true>, grid, dim3(256), 0, ctx->stream, f, R, n4, (int)w_blocks, bias_part, nb, d_out);
+    else hipLaunchKernelGGL(finish_layers_kernel<false>, grid, dim3(256), 0, ctx->stream, f, R, n4, (int)w_blocks, bias_part, nb, d_out);
+    DP_LAUNCH_CHECK(ctx, "finish_layers");
+    return DP_OK;
+}
 
 static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, dp_dtype dt, int B, int T, int d_in, int d_out,
                                      const float* sqnorms, float C, float* sum_W, float* sum_b);
@@ -1213,12 +1224,8 @@ dp_status dpk_weighted_gemm_batched(dp_ctx* ctx, int n, const void* const* A, co
                 f.sum_b[l] = nb ? sum_b[l0 + l] : nullptr;
             }
             const size_t n4 = (size_t)d_in * d_out / 4;  // d_out is a multiple of 8
-            const bool tall = nsplit >= 16 && n4 * nl <= 16384;  // too few columns to fill the chip one a thread
-            const long w_blocks = nsplit > 1 ? (long)((n4 + (tall ? 63 : 255)) / (tall ? 64 : 256)) : 0, b_blocks = nb ? (d_out + 63) / 64 : 0;
-            const dim3 grid((unsigned)(w_blocks + b_blocks), nl);
-            if (tall) hipLaunchKernelGGL(finish_layers_kernel<true>, grid, dim3(256), 0, ctx->stream, f, (int)nsplit, n4, (int)w_blocks, bias_part, nb, d_out);
-            else hipLaunchKernelGGL(finish_layers_kernel<false>, grid, dim3(256), 0, ctx->stream, f, (int)nsplit, n4, (int)w_blocks, bias_part, nb, d_out);
-            DP_LAUNCH_CHECK(ctx, "finish_layers");
+            const dp_status st = finish_layers(ctx, f, nl, (int)nsplit, n4, bias_part, nb, d_out);
+            if (st != DP_OK) return st;
         }
     }
     return DP_OK;
@@ -1272,30 +1279,35 @@ struct F32Plan {
     bool wide;
 };
 
-// The tile with the smallest time of a launch: rounds of the 256 workgroups that run at once, at 4 us and, by
-// tile, 7.0 (1 x 1), 10.7 (2 x 1), 14.8 (3 x 1) or 18.5 ns (2 x 2) a row.  Where one round is not filled the rows are
-// split, at 1,024 and more each (partial sums through the workspace as far as it goes; the two reduction launches take 6 us).
-// 2,048 rows: 768 x 768 (144 tiles of 2 x 2, 192 of 3 x 1) 46 -> 38 us; 512 x 512: 19 with 1 x 1, 28 with 2 x 2; 1024 x 1024: 43 with
-// 2 x 2, 51 with 2 x 1; 768 x 3072: 128 -> 104 with 3 x 1.
-// A tile whose block of rows does not fit a 32-bit buffer resource is no candidate; without any, 2 x 2 with 64-bit addresses.
-static F32Plan choose_f32_plan(long K, int d_in, int d_out) {
+// The tile and row splits with the smallest modelled time: rounds of the 256 workgroups that run at once, each a tile's microseconds at its ends and its
+// nanoseconds a row (of whole pairs of blocks), measured alone and on a full chip; where one round is not filled the rows are split as often as it takes, or half
+// as often, if the workspace holds the partial sums, which cost a launch, of 3.8 us, and their bytes.  3 x 3 has the fewest loads to a product (87 % of the matrix rate, 3 x 1 70 %)
+// and the longest ends, 144 registers a lane through LDS.  Us, the best of the other tiles, in splits of 1,024 rows and more as they were | 3 x 3: 768 x 768, 8,192 rows 120 | 88 (2,048: 34.5 | 33.8, not taken);
+// 768 x 3072, 2,048 rows 100 | 84, 150 rows 25 | 20.6.  Shorter splits: 256 x 256, 2,048 rows 13.4 | 10.7 (2 x 1, eight of 256).
+// A tile whose block of rows (of 128, where it has fewer) does not fit a 32-bit buffer resource is no candidate; without any, 2 x 2 with 64-bit addresses.
+static F32Plan choose_f32_plan(long K, int d_in, int d_out, size_t ws_bytes) {
     static constexpr struct {
         int m, n;
-        double ns_row;
-    } kTiles[] = {{2, 2, 18.5}, {3, 1, 14.8}, {2, 1, 10.7}, {1, 1, 7.0}};
+        double ns_row, us_ends;
+    } kTiles[] = {{2, 2, 17.5, 7.0}, {3, 1, 14.0, 5.6}, {2, 1, 10.2, 5.0}, {1, 1, 6.5, 4.6}, {3, 3, 34.6, 12.5}};
     const uint64_t width = d_in > d_out ? d_in : d_out;
+    const size_t n = (size_t)d_in * d_out;
     F32Plan plan{0, 0, 1, false};
     double best = 0.0;
     for (const auto& t : kTiles) {
-        const long a = (d_in + 32l * t.m - 1) / (32 * t.m), b = (d_out + 32l * t.n - 1) / (32 * t.n);
-        const bool wide = (uint64_t)f32_block(t.m, t.n) * 4u * width > 0xFFFFFFFFu;
-        long ns = 256 / (a * b);
-        if (ns > K / 1024) ns = K / 1024;
-        if (ns < 1) ns = 1;
-        const double us = (double)((a * b * ns + 255) / 256) * ((double)((K + ns - 1) / ns) * t.ns_row * 1e-3 + 4.0) + (ns > 1 ? 6.0 : 0.0);
-        if (plan.m32 && (us >= best || a > 65535 || wide)) continue;  // (a launch has at most 65,535 tile rows)
-        best = us;
-        plan = F32Plan{t.m, t.n, ns, wide};
+        const long a = (d_in + 32l * t.m - 1) / (32 * t.m), b = (d_out + 32l * t.n - 1) / (32 * t.n), pair = 2 * f32_block(t.m, t.n);
+        const bool wide = (uint64_t)(pair < 256 ? 128 : pair / 2) * 4u * width > 0xFFFFFFFFu;
+        long most = 256 / (a * b);
+        if (most > K / 128) most = K / 128;
+        for (int k = 0; k < 3; ++k) {
+            const long ns = k == 0 ? 1 : k == 1 ? most : most / 2;
+            if (k > 0 && (ns < 2 || (size_t)ns * (n + d_out) * sizeof(float) + 1024 > ws_bytes)) continue;
+            const long rows = ((K + ns - 1) / ns + pair - 1) / pair * pair;
+            const double us = (double)((a * b * ns + 255) / 256) * ((double)rows * t.ns_row * 1e-3 + t.us_ends) + (ns > 1 ? 3.8 + (double)(ns + 2) * n * 4.0 / 8e6 : 0.0);
+            if (plan.m32 && (us >= best || a > 65535 || wide)) continue;  // (a launch has at most 65,535 tile rows)
+            best = us;
+            plan = F32Plan{t.m, t.n, ns, wide};
+        }
     }
     return plan;
 }
@@ -1313,7 +1325,7 @@ static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, 
     if (st != DP_OK) return st;
     // (fp32 from here)
     const long K = (long)B * T;
-    const F32Plan plan = choose_f32_plan(K, d_in, d_out);
+    const F32Plan plan = choose_f32_plan(K, d_in, d_out, ctx->ws_bytes);
     long nsplit = plan.nsplit;
     float *part = nullptr, *bpart = nullptr;
     if (nsplit > 1) {
@@ -1345,12 +1357,21 @@ static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, 
     using three = std::integral_constant<int, 3>;
     if (plan.wide) launch(two{}, two{}, std::true_type{});
     else if (plan.m32 == 2 && plan.n32 == 2) launch(two{}, two{}, std::false_type{});
+    else if (plan.m32 == 3 && plan.n32 == 3) launch(three{}, three{}, std::false_type{});
     else if (plan.m32 == 3) launch(three{}, one{}, std::false_type{});
     else if (plan.m32 == 2) launch(two{}, one{}, std::false_type{});
     else launch(one{}, one{}, std::false_type{});
     DP_LAUNCH_CHECK(ctx, "wgemm_f32");
     if (add) return DP_OK;
-    st = dpk_reduce_partials(ctx, part, (int)nsplit, (size_t)d_in * d_out, (size_t)d_in * d_out, sum_W);
+    const size_t n = (size_t)d_in * d_out;
+    if (n % 4 == 0 && (((uintptr_t)part | (uintptr_t)sum_W) & 15) == 0) {
+        FinishArgs f;
+        f.part[0] = reinterpret_cast<const float4*>(part);
+        f.out[0] = reinterpret_cast<float4*>(sum_W);
+        f.sum_b[0] = sum_b;
+        return finish_layers(ctx, f, 1, (int)nsplit, n / 4, bpart, sum_b ? (int)nsplit : 0, d_out);
+    }
+    st = dpk_reduce_partials(ctx, part, (int)nsplit, n, n, sum_W);
     if (st == DP_OK && sum_b) st = dpk_reduce_partials(ctx, bpart, (int)nsplit, (size_t)d_out, (size_t)d_out, sum_b);
     return st;
 }
@@ -1360,7 +1381,7 @@ static dp_status weighted_sum_single(dp_ctx* ctx, const void* A, const void* G, 
 dp_status dpk_dense_sum_plan(dp_dtype dt, int n, int B, int T, int d_in, int d_out, size_t ws_bytes, int32_t* out) {
     const long K = (long)B * T;
     if (dt == DP_F32) {
-        const F32Plan p = choose_f32_plan(K, d_in, d_out);
+        const F32Plan p = choose_f32_plan(K, d_in, d_out, ws_bytes);
         out[0] = 32 * p.m32;
         out[1] = 32 * p.n32;
         out[2] = 0;

@@ -1187,6 +1187,28 @@ def test_norms_of_few_examples_are_materialised(dp, n, B, T, d_in, d_out, few):
         assert_norms_close(host(out), host(want), 2e-5)
 
 
+@pytest.mark.parametrize("B,T,d_in,d_out,tile,splits", [(32, 255, 767, 761, (96, 96), 4), (19, 217, 672, 761, (96, 96), 4), (8, 256, 768, 768, (96, 32), 1),
+                                                        (3, 50, 768, 3072, (96, 96), 1), (16, 128, 256, 256, (64, 32), 8), (7, 293, 253, 255, (96, 32), 10)])
+def test_fp32_sums_by_every_tile_and_in_short_splits(dp, B, T, d_in, d_out, tile, splits):
+    """Whole numbers and factors of one: exact in any order.  Sums of a multiple of 4 entries and not, an address of 16 bytes and of 4, rows that fill no pair of blocks."""
+    import paper_2108_01624_amd as pkg
+
+    plan = pkg.dp_dense_sum_plan(pkg.DP_F32, 1, B, T, d_in, d_out)
+    assert (plan["tile_m"], plan["tile_n"], plan["splits"]) == (*tile, splits), plan
+    g = torch.Generator(device=DEV)
+    g.manual_seed(545)
+    A = torch.randint(-2, 3, (B, T, d_in), generator=g, device=DEV).float()
+    G = torch.randint(-2, 3, (B, T, d_out), generator=g, device=DEV).float()
+    norms = torch.rand(B, generator=g, device=DEV)
+    for shift in (0, 1):
+        W = torch.ones(d_in * d_out + shift, device=DEV)[shift:].view(d_in, d_out)
+        b = torch.ones(d_out, device=DEV)
+        dp.clip_accumulate_dense(A, G, 1.0, norms, W, b)
+        dp.sync()
+        assert torch.equal(W.double(), A.view(-1, d_in).double().T @ G.view(-1, d_out).double() + 1)
+        assert torch.equal(b.double(), G.view(-1, d_out).double().sum(0) + 1)
+
+
 @pytest.mark.parametrize("T", [1, 15, 64, 65, 127, 128, 129, 300, 449, 511, 512, 513, 1100])
 @pytest.mark.parametrize("B,d", [(2, 8), (3, 264), (300, 72)])
 def test_embedding_norms_are_exact_whatever_shares_the_ranking(dp, B, T, d):
