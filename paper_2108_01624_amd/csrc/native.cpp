@@ -328,6 +328,9 @@ bool parse(PyObject* list, std::vector<Layer>& out) {
     return true;
 }
 
+// Whether there are norms, and room for kept LayerNorm gradients, for as many examples as the layers (all the same) have.
+bool holds(const std::vector<Layer>& layers, const Arr& sqnorms, int64_t max_batch) { return layers[0].G.s[0] <= max_batch && layers[0].G.s[0] <= sqnorms.numel; }
+
 // The groups of same-shaped layers of a kind, in order of their first layer.
 std::vector<std::vector<int>> group(const std::vector<Layer>& layers, Kind kind, bool by_bias) {
     std::vector<std::vector<int>> out;
@@ -397,7 +400,7 @@ PyObject* pass1(PyObject*, Args a, Py_ssize_t n) {
     Arr sq;
     int64_t max_batch;
     ARGS(6);
-    NEED(context(a[0], ctx) && get_f32(a[2], sq) && PyDict_CheckExact(a[3]) && num(a[5], max_batch) && parse(a[1], layers));
+    NEED(context(a[0], ctx) && get_f32(a[2], sq) && PyDict_CheckExact(a[3]) && num(a[5], max_batch) && parse(a[1], layers) && holds(layers, sq, max_batch));
     float* const out = (float*)sq.p;
     const auto norms = group(layers, LAYERNORM, false), dense = group(layers, DENSE, true);
     std::vector<std::vector<float*>> kept(norms.size());
@@ -478,7 +481,7 @@ PyObject* pass2(PyObject*, Args a, Py_ssize_t n) {
     float C;
     int64_t max_batch;
     ARGS(9);
-    NEED(context(a[0], ctx) && num(a[2], C) && get_f32(a[3], sq) && get_f32(a[4], S) && PyList_CheckExact(a[5]) && PyDict_CheckExact(a[6]) && num(a[8], max_batch) && parse(a[1], layers));
+    NEED(context(a[0], ctx) && num(a[2], C) && get_f32(a[3], sq) && get_f32(a[4], S) && PyList_CheckExact(a[5]) && PyDict_CheckExact(a[6]) && num(a[8], max_batch) && parse(a[1], layers) && holds(layers, sq, max_batch));
     const float* const norms = (float*)sq.p;
     // where the layers' sums lie
     NEED(PyList_GET_SIZE(a[5]) >= (Py_ssize_t)layers.size());

@@ -73,13 +73,25 @@ class StepRunner:
             raise ValueError("A [B,T,d_in] and G [B,T,d_out] expected")
         return B, T, d_in, sG[-1]
 
+    def _norms(self, layers):
+        """(B, the norms of a micro-batch of B examples).  Refuses more examples than there are norms, and kept LayerNorm gradients, for."""
+        nB, most = layers[0]["G"].shape[0], min(self.max_batch, self.sqnorms.shape[0])
+        if nB > most:
+            raise ValueError(f"a micro-batch of {nB} examples: the buffers hold {most}")
+        return nB, self.sqnorms[:nB]
+
+    def _check_layers(self, layers):
+        """The same for every layer (the extension takes layers of one batch size only)."""
+        most = max(l["G"].shape[0] for l in layers)
+        if most > min(self.max_batch, self.sqnorms.shape[0]):
+            raise ValueError(f"a layer of {most} examples: the buffers hold {min(self.max_batch, self.sqnorms.shape[0])}")
+
     def pass1(self, layers, path=B_.DP_PATH_AUTO, batch_dense=True):
         """Per-example squared global norms of one micro-batch: sqnorms[:B] = sum over all layers.  The norm is a sum
         over layers, so dense layers of one shape, and LayerNorms of one shape, are handed over together (by address: a small
         micro-batch is over on the GPU before Python has looked at 96 tensors twice)."""
         ctx = self.ctx
-        nB = layers[0]["G"].shape[0]
-        n = self.sqnorms[:nB]
+        nB, n = self._norms(layers)
         ctx.zero_f32(n)
         if batch_dense and path == B_.DP_PATH_AUTO and type(ctx) is B_.Context:
             # the walk below in C++ (None: something it does not expect, nothing has been called)
@@ -90,6 +102,7 @@ class StepRunner:
                     B_._check(ctx.handle, *done)
                 self._kept_for = done or None
                 return n
+        self._check_layers(layers)
         groups, ln_groups = {}, {}
         for k, l in enumerate(layers):
             kind = l["kind"]
@@ -144,8 +157,7 @@ class StepRunner:
         """S += sum_i clip(grad_i, C) for one micro-batch, using the norms left by pass1.  The sums of different
         layers are independent, so dense layers of one shape are handed over together (the library cuts them into launches that fill the chip)."""
         ctx = self.ctx
-        nB = layers[0]["G"].shape[0]
-        n = self.sqnorms[:nB]
+        nB, n = self._norms(layers)
         S = B_._f32(self.S)
         if self.S.numel() < self.P or not self.S.is_contiguous():
             raise ValueError("S must be a contiguous buffer of all parameters")
@@ -155,6 +167,7 @@ class StepRunner:
                 if type(done) is tuple:
                     B_._check(ctx.handle, *done)
                 return
+        self._check_layers(layers)
         groups, ln_groups = {}, {}
         for k, l in enumerate(layers):
             kind = l["kind"]

@@ -1,0 +1,140 @@
+"""The calls that the step driver and the methods of Context make, on the CPU: a library that only writes its calls down stands in
+for libdpclip.so (in a process of its own: the extension is bound to whatever library of that name is in the process)."""
+import ctypes
+import os
+import re
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = "paper_2108_01624_amd"
+
+
+def _stub_source():
+    """Every entry point of the header: name and arguments, pointer tables by what they hold, appended to a text; the status `stub_status`."""
+    head = re.sub(r"/\*.*?\*/", "", open(os.path.join(ROOT, "include", "dpclip.h")).read(), flags=re.S)
+    out = ['#include <stdio.h>\n#include <string>\n#include "dpclip.h"\nstatic std::string text;\nextern "C" {\nint stub_status = 0;',
+           "const char* stub_log() { return text.c_str(); }\nvoid stub_clear() { text.clear(); }",
+           "static void num(double v) { char b[40]; snprintf(b, 40, \" %.17g\", v); text += b; }",
+           "static void ptr(const void* p) { char b[40]; snprintf(b, 40, \" %p\", p); text += b; }",
+           "static void table(const void* const* t, int n) { text += \" [\"; if (!t) n = 0; for (int k = 0; k < n; ++k) ptr(t[k]); text += \"]\"; }"]
+    for ret, name, args in re.findall(r"^(\w[\w\s\*]*?)\b(dp_\w+)\s*\(([^)]*)\)\s*;", head, flags=re.M):
+        args = [re.match(r"(.*?)(\w+)$", " ".join(a.split())).groups() for a in args.split(",")]
+        body = [f'text += "{name}";']
+        for kind, arg in args:
+            if kind.count("*") == 2 and "const*" in kind.replace("const *", "const*"):
+                length = "n_groups * n_out" if name == "dp_sqnorms_dense_shared" and arg == "G" else "n_groups" if "shared" in name else "n_layers"
+                body.append(f"table((const void* const*){arg}, {length});")
+            elif "*" in kind:
+                body.append(f"ptr((const void*){arg});")
+            else:
+                body.append(f"num((double){arg});")
+        tail = 'return "";' if "char" in ret else "return (dp_status)stub_status;"
+        params = ", ".join(k + a for k, a in args)
+        out.append(f"{ret.strip()} {name}({params}) {{ {' '.join(body)} text += \"\\n\"; {tail} }}")
+    return "\n".join(out) + "\n}\n"
+
+
+@pytest.fixture(scope="module")
+def stubbed(tmp_path_factory):
+    """-> run(name): the function of that name, below, in a process whose package stands on the stub."""
+    from paper_2108_01624_amd import build
+
+    if not os.path.exists(build.LIB_PATH) or not os.path.exists(build.NATIVE_PATH):
+        build.build_library()
+    top = tmp_path_factory.mktemp("stub")
+    (top / PKG).mkdir()
+    for f in os.listdir(build.PKG_DIR):
+        if f.endswith(".py"):
+            shutil.copy(os.path.join(build.PKG_DIR, f), top / PKG / f)
+    shutil.copy(build.NATIVE_PATH, top / PKG / "_native.so")
+    (top / "stub.cpp").write_text(_stub_source())
+    r = subprocess.run(["g++", "-shared", "-fPIC", "-O1", "-std=c++17", "-I" + build.INCLUDE, "-Wl,-soname,libdpclip.so", str(top / "stub.cpp"),
+                        "-o", str(top / PKG / "libdpclip.so")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+
+    def run(name):
+        r = subprocess.run([sys.executable, os.path.abspath(__file__), name], capture_output=True, text=True, cwd=top, timeout=600,
+                           env=dict(os.environ, PYTHONPATH=str(top)))
+        assert r.returncode == 0, (r.stdout + r.stderr)[-4000:]
+
+    return run
+
+
+# ---- in the process on the stub ---------------------------------------------------------------------------------------------
+class Spec:
+    def __init__(self, *tensors):
+        self.shapes = tensors
+
+    def tensors(self):
+        return [(str(k), s) for k, s in enumerate(self.shapes)]
+
+
+def _package():
+    """(package, context on the stub, lines): lines() are the calls since the last time it was asked."""
+    import paper_2108_01624_amd as pkg
+
+    lib = pkg.load_library()
+    lib.stub_log.restype = ctypes.c_char_p
+
+    def lines():
+        got = lib.stub_log().decode().splitlines()
+        lib.stub_clear()
+        return got
+
+    def context(cls=pkg.Context):
+        ctx = object.__new__(cls)   # (its constructor needs a GPU; the stub does not look at the handle)
+        ctx.handle = 1 << 40
+        return ctx
+
+    return pkg, context, lines
+
+
+def over_large_batches():
+    import torch
+
+    pkg, context, lines = _package()
+
+    class Walked(pkg.Context):   # (the driver hands only a plain context to the extension)
+        pass
+
+    d = 8
+    ln = lambda B: dict(kind="layernorm", X=torch.zeros(B, 3, d), G=torch.zeros(B, 3, d))
+    dense = lambda B: dict(kind="dense", A=torch.zeros(B, 3, d), G=torch.zeros(B, 3, d), has_bias=False)
+    for cls in (pkg.Context, Walked):
+        for make, spec in ((ln, Spec((d,), (d,))), (dense, Spec((d, d)))):
+            run = pkg.StepRunner(context(cls), [spec], 4, device="cpu")
+            for B in (4, 3):   # (the keep buffers are there from the first on)
+                run.pass1([make(B)])
+                run.pass2([make(B)], 1.0)
+            assert len(lines()) == 6
+            for B in (5, 8):
+                for call in (lambda: run.pass1([make(B)]), lambda: run.pass2([make(B)], 1.0)):
+                    try:
+                        call()
+                    except ValueError:
+                        assert not lines()
+                        continue
+                    raise AssertionError(f"{cls.__name__}: a micro-batch of {B} went through: {lines()}")
+        # another layer of the micro-batch has more examples than the buffers hold
+        run = pkg.StepRunner(context(cls), [Spec((d, d)), Spec((d, d))], 4, device="cpu")
+        for call in (lambda: run.pass1([dense(4), dense(5)]), lambda: run.pass2([dense(4), dense(5)], 1.0)):
+            try:
+                call()
+            except ValueError:
+                assert all(x.startswith("dp_zero_f32 ") for x in lines())
+                continue
+            raise AssertionError(lines())
+
+
+def test_micro_batches_larger_than_the_runners_buffers_are_refused(stubbed):
+    """... by both walks, whether or not the keep buffers are there already: norms and kept LayerNorm gradients have room for
+    max_batch examples."""
+    stubbed("over_large_batches")
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[1]]()
