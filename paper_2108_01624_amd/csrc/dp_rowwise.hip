@@ -834,11 +834,13 @@ __global__ __launch_bounds__(64 * GROUP_WAVES) void group_ids_kernel(const int32
     const int part = blockIdx.x >> lg;
     const uint32_t mask = (1u << lg) - 1u, b = blockIdx.x & mask, none = ((uint32_t)(V - 1) >> lg) + 1u;  // none: the digit of ids out of range
     const int w0 = wave * (Q * PARTS * 64);
-    // Places past the last position hold an id out of range of the last bucket: they come behind everything and are not written.
-    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc((void*)ids, 0, N * 4, 0x00020000);
+    // Places past the last position hold an id out of range of the last bucket: they come behind everything and are not written.  A wave's
+    // resource is its own positions (none: no bytes), all of its offsets lie in the range-checked part: the scalar offset is not checked.
+    const int first = w0 < N ? w0 : N;
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc((void*)(ids + first), 0, (N - first) * 4, 0x00020000);
     auto load = [&](uint32_t (&id)[Q], int q) {
 #pragma unroll
-        for (int u = 0; u < Q; ++u) id[u] = __builtin_amdgcn_raw_buffer_load_b32(src, lane * 4 + (q * Q + u) * 256, w0 * 4, 0);
+        for (int u = 0; u < Q; ++u) id[u] = __builtin_amdgcn_raw_buffer_load_b32(src, lane * 4 + (q * Q + u) * 256, 0, 0);
     };
     auto close = [&](uint32_t (&id)[Q], int q) {
         if (w0 + (q * Q + Q) * 64 <= N) return;

@@ -63,3 +63,15 @@ def test_lds_filling_kernels_keep_descriptors_scalar_and_use_no_scratch(src, hot
             assert vaddr.startswith("v") and rsrc.startswith("s[") and soff.startswith("s"), (name, vaddr, rsrc, soff)
         assert "v_pk_mul_f32" not in body and "v_pk_fma_f32" not in body and "v_pk_add_f32" not in body, name
     assert seen >= len(hot) and all(any(h in name for name in kernels) for h in hot)
+
+
+def test_range_checked_accesses_have_no_scalar_offset(tmp_path):
+    """The grouping of the ids and the segment sums leave what lies past an array to the range check of its buffer resource, which
+    covers the vector and the immediate offset of an access and not the scalar one."""
+    kernels = _kernels(_isa("dp_rowwise.hip", tmp_path))
+    for hot in ("group_ids_kernel", "segment_sums_kernel"):
+        bodies = {name: body for name, (body, _) in kernels.items() if hot in name}
+        assert bodies
+        for name, body in bodies.items():
+            accesses = re.findall(r"buffer_(?:load|store)_\w+ [^,]+, [^,]+, s\[\d+:\d+\], (\S+)", body)
+            assert accesses and set(accesses) == {"0"}, (name, sorted(set(accesses)))
