@@ -821,6 +821,27 @@ def test_embedding_sums_at_the_edges_of_the_grouping(dp, dtype, d, N, V):
     assert bool(((got.double() - ref).abs() <= n * 2.0**-24 * mag).all())
 
 
+@pytest.mark.parametrize("V,counts", [(3, (1, 128 * 4161 + 1, 5)), (2, (128 * 64, 128 * 65)), (6, (128 * 63 + 1, 128 * 64 - 1, 128 * 129, 128 * 4160, 7, 128 * 66 + 127)),
+                                      (70000, (32 * 300, 0, 128 * 500 + 64)), (1000, (32 * 900, 3, 32 * 65)), (1, (128 * 700,))])
+def test_embedding_sums_of_runs_over_many_workgroups(dp, V, counts):
+    """Ids so frequent that their positions fill 64 workgroups and more, up to thousands: ends of runs at and beside the distances at which
+    they are looked for; one id in fifty out of range.  Whole numbers and factors of one: exact."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(866)
+    ids = torch.repeat_interleave(torch.arange(len(counts), device=DEV), torch.tensor(counts, device=DEV))
+    ids = torch.cat([ids, torch.randint(0, V, (333,), generator=g, device=DEV), torch.full((ids.numel() // 50,), -1, device=DEV)])
+    ids = ids[torch.randperm(ids.numel(), generator=g, device=DEV)].to(torch.int32).view(-1, 1)
+    N, d = ids.numel(), 8
+    G = torch.randint(-1, 2, (N, 1, d), generator=g, device=DEV).to(torch.bfloat16)
+    sq, E = torch.rand(N, generator=g, device=DEV), torch.ones(V, d, device=DEV)
+    dp.clip_accumulate_embedding(ids, G, V, 1.0, sq, E)
+    with pytest.raises(Exception, match="DP_ERR_INDEX"):
+        dp.sync()
+    keep = (ids.view(-1) >= 0).nonzero().view(-1)
+    want = torch.ones(V, d, dtype=torch.float64, device=DEV).index_add_(0, ids.view(-1)[keep].long(), G.view(N, d)[keep].double())
+    assert float(want.abs().max()) < 2**24 and torch.equal(E.double(), want)
+
+
 @pytest.mark.parametrize("B,T,d,V", [(4, 25, 8, 50), (9, 128, 8, 300), (8, 512, 64, 70000)])
 def test_embedding_sums_in_the_least_workspace(dp, B, T, d, V):
     """Room for two pairs of key and row lists, one counter per digit and 1,024 tokens, and two rows per 32 tokens is enough; the
