@@ -158,8 +158,10 @@ def _dtype_code(dt) -> int:
     raise TypeError(f"unsupported tensor dtype {dt}")
 
 
-def _table(ptrs):
-    """HOST array of device pointers."""
+def _table(ptrs, n):
+    """HOST array of device pointers, of which the library reads n."""
+    if len(ptrs) < n:
+        raise ValueError(f"{len(ptrs)} tensors for {n} layers")
     return (c_void_p * len(ptrs))(*ptrs)
 
 
@@ -205,31 +207,34 @@ def dp_sqnorms_dense(ctx, A, G, has_bias, path, sqnorms, *, B=None, T=None):
 # Pointer-level forms of the batched calls: the caller has checked that all layers share one shape and dtype (`shape` is
 # (B, T, d_in, d_out) or (B, T, d), `dtype` a DP_* code) and hands over device addresses; one per layer, no tensor is touched again.
 def _sqnorms_dense_ptrs(ctx, As, Gs, dtype, shape, has_bias, path, sqnorms):
-    st = load_library().dp_sqnorms_dense_batched(ctx, len(As), _table(As), _table(Gs), dtype, *shape, int(has_bias), int(path),
+    st = load_library().dp_sqnorms_dense_batched(ctx, len(As), _table(As, len(As)), _table(Gs, len(As)), dtype, *shape, int(has_bias), int(path),
                                                  _f32(sqnorms))
     _check(ctx, st, "dp_sqnorms_dense_batched")
 
 
 def _sqnorms_dense_shared_ptrs(ctx, As, n_out, Gs, dtype, shape, has_bias, sqnorms):
-    st = load_library().dp_sqnorms_dense_shared(ctx, len(As), _table(As), n_out, _table(Gs), dtype, *shape, int(has_bias),
+    st = load_library().dp_sqnorms_dense_shared(ctx, len(As), _table(As, len(As)), n_out, _table(Gs, n_out * len(As)), dtype, *shape, int(has_bias),
                                                 _f32(sqnorms))
     _check(ctx, st, "dp_sqnorms_dense_shared")
 
 
 def _clip_accumulate_dense_ptrs(ctx, As, Gs, dtype, shape, C, sqnorms, sum_Ws, sum_bs):
-    st = load_library().dp_clip_accumulate_dense_batched(ctx, len(As), _table(As), _table(Gs), dtype, *shape, float(C), _f32(sqnorms),
-                                                         _table(sum_Ws), _table(sum_bs) if sum_bs is not None else None)
+    n = len(As)
+    st = load_library().dp_clip_accumulate_dense_batched(ctx, n, _table(As, n), _table(Gs, n), dtype, *shape, float(C), _f32(sqnorms),
+                                                         _table(sum_Ws, n), _table(sum_bs, n) if sum_bs is not None else None)
     _check(ctx, st, "dp_clip_accumulate_dense_batched")
 
 
 def _sqnorms_layernorm_keep_ptrs(ctx, Xhats, Gs, dtype, shape, sqnorms, grads):
-    st = load_library().dp_sqnorms_layernorm_keep(ctx, len(Xhats), _table(Xhats), _table(Gs), dtype, *shape, _f32(sqnorms), _table(grads))
+    n = len(Xhats)
+    st = load_library().dp_sqnorms_layernorm_keep(ctx, n, _table(Xhats, n), _table(Gs, n), dtype, *shape, _f32(sqnorms), _table(grads, n))
     _check(ctx, st, "dp_sqnorms_layernorm_keep")
 
 
 def _clip_accumulate_layernorm_kept_ptrs(ctx, grads, B, d, C, sqnorms, sum_gammas, sum_betas):
-    st = load_library().dp_clip_accumulate_layernorm_kept(ctx, len(grads), _table(grads), int(B), int(d), float(C), _f32(sqnorms),
-                                                          _table(sum_gammas), _table(sum_betas))
+    n = len(grads)
+    st = load_library().dp_clip_accumulate_layernorm_kept(ctx, n, _table(grads, n), int(B), int(d), float(C), _f32(sqnorms),
+                                                          _table(sum_gammas, n), _table(sum_betas, n))
     _check(ctx, st, "dp_clip_accumulate_layernorm_kept")
 
 

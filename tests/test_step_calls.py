@@ -136,5 +136,35 @@ def test_micro_batches_larger_than_the_runners_buffers_are_refused(stubbed):
     stubbed("over_large_batches")
 
 
+def short_lists():
+    import torch
+
+    pkg, context, lines = _package()
+    ctx, f = context(), torch.zeros
+    A, G, n, W, v = [f(2, 3, 8)] * 3, [f(2, 3, 16)] * 3, f(2), [f(8, 16)] * 3, [f(8)] * 3
+    keep, b = [f(2, 2, 8)] * 3, [f(16)] * 3
+    calls = [(ctx.sqnorms_dense_batched, [A, G, True, 0, n]), (ctx.sqnorms_dense_shared, [A, [[g, g] for g in G], True, n]),
+             (ctx.clip_accumulate_dense_batched, [A, G, 1.0, n, W, b]), (ctx.sqnorms_layernorm_batched, [A, A, n]),
+             (ctx.clip_accumulate_layernorm_batched, [A, A, 1.0, n, v, v]), (ctx.sqnorms_layernorm_keep, [A, A, n, keep]),
+             (ctx.clip_accumulate_layernorm_kept, [keep, 2, 8, 1.0, n, v, v])]
+    for fn, args in calls:
+        fn(*args)
+        assert len(lines()) == 1
+        at = [k for k, x in enumerate(args) if isinstance(x, list)]
+        for k in at[1:]:
+            try:
+                fn(*(x[:2] if j == k else x for j, x in enumerate(args)))
+            except ValueError:
+                assert not lines()
+                continue
+            got = lines()
+            assert len(got) == 1 and "(nil)" in got[0], (k, got)   # (an entry that the library refuses by itself)
+
+
+def test_lists_shorter_than_the_layers_are_refused(stubbed):
+    """The library reads as many entries of every list as there are layers: a list with fewer is refused, or filled up with nulls, which it refuses."""
+    stubbed("short_lists")
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]]()
