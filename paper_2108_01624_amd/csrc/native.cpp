@@ -88,10 +88,11 @@ bool num(PyObject* o, float& v) {
     v = (float)d;
     return true;
 }
+// A flag: True, False, 1 or 0 (whatever else has a truth value need not be a number to Python's int()).
 bool truth(PyObject* o, bool& v) {
-    const int t = PyObject_IsTrue(o);
-    if (t < 0) return PyErr_Clear(), false;
-    v = t != 0;
+    int64_t x;
+    if (!num(o, x) || (x != 0 && x != 1)) return false;
+    v = x != 0;
     return true;
 }
 bool context(PyObject* o, dp_ctx*& ctx) {
@@ -147,7 +148,7 @@ PyObject* clip_accumulate_dense(PyObject*, Args a, Py_ssize_t n) {  // ctx, A, G
     STATUS(dp_clip_accumulate_dense(ctx, A.p, G.p, (dp_dtype)A.type, (int)A.s[0], (int)A.s[1], (int)A.s[2], (int)G.s[G.dim - 1], C, (float*)sq.p, (float*)W.p, (float*)b.p));
 }
 
-// A list of tensors; `like`: of this type and shape (where given).
+// A list of tensors.
 bool list_of(PyObject* o, std::vector<Arr>& out) {
     if (!PyList_CheckExact(o)) return false;
     out.resize((size_t)PyList_GET_SIZE(o));

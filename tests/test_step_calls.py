@@ -59,7 +59,7 @@ def stubbed(tmp_path_factory):
     def run(name):
         r = subprocess.run([sys.executable, os.path.abspath(__file__), name], capture_output=True, text=True, cwd=top, timeout=600,
                            env=dict(os.environ, PYTHONPATH=str(top)))
-        assert r.returncode == 0, (r.stdout + r.stderr)[-4000:]
+        assert r.returncode == 0, (r.stdout + r.stderr)[-8000:]
 
     return run
 
@@ -164,6 +164,89 @@ def short_lists():
 def test_lists_shorter_than_the_layers_are_refused(stubbed):
     """The library reads as many entries of every list as there are layers: a list with fewer is refused, or filled up with nulls, which it refuses."""
     stubbed("short_lists")
+
+
+def _outcome(f, lines):
+    """The calls that f makes, or the type of what it raises."""
+    try:
+        f()
+    except Exception as e:
+        return type(e).__name__, lines()
+    return "", lines()
+
+
+def _odd_values(x):
+    """Values in place of an argument, most of which no program should pass."""
+    import numpy as np
+    import torch
+
+    if isinstance(x, torch.Tensor):
+        return [None, 4096, 0, "x", 1.5, x.double(), x.bfloat16(), x.int(), x[0], x[None], x[None, None, None], x[:, :0] if x.dim() > 1 else x[:0], x[..., ::2],
+                x.to("meta"), torch.nn.Parameter(x) if x.is_floating_point() else x, x.float().numpy(), [x]]
+    if isinstance(x, list):
+        t = x[-1]
+        return [None, [], tuple(x), x * 70, x[:-1], [None] * len(x), [4096] * len(x), [t.double()] * len(x), x + [t[:1]], x[:-1] + [t[..., :8]]]
+    return [None, True, False, 0, 1, 2, -1, 1 << 31, 1 << 32, 1 << 40, 1 << 64, 0.5, 1e300, float("nan"), np.float32(0.5), np.float64(0.5), np.int64(3), np.bool_(True),
+            "1", "", [], torch.tensor(1), torch.tensor(1.0)]
+
+
+def frequent_calls():
+    import torch
+
+    pkg, context, lines = _package()
+    from paper_2108_01624_amd import binding
+
+    ctx, native = context(), binding._native
+    accepted = []
+
+    class Seen:
+        def __getattr__(self, name):
+            def call(*a):
+                st = getattr(native, name)(*a)
+                accepted.append(st is not None)
+                return st
+
+            return call
+
+    binding._native = Seen()
+    f = torch.zeros
+    A, G, W, b, n = f(2, 3, 8), f(2, 3, 16), f(8, 16), f(16), f(2)
+    ids, H, dL, E = f(2, 3, dtype=torch.int32), f(2, 4, 16), f(2, 4, 5), f(5, 16)
+    adam = dict(sigma=0.5, C=1.0, seed=1, step=2, batch_size=8, lr=1e-3, beta1=0.9, beta2=0.99, weight_decay=0.1)
+    calls = [("zero_f32", (n,), {}), ("zero_f32", (n, 1), {}),
+             ("sqnorms_dense", (A, G, True, 0, n), {}), ("sqnorms_dense", (A.bfloat16(), G.bfloat16(), False, 1, n), {}),
+             ("sqnorms_dense_batched", ([A, A + 1], [G, G + 1], True, 0, n), {}),
+             ("clip_accumulate_dense", (A, G, 1.0, n, W, b), {}), ("clip_accumulate_dense", (A, G, 1, n, W), {}),
+             ("clip_accumulate_dense_batched", ([A, A + 1], [G, G + 1], 1.0, n, [W, W + 1], [b, b + 1]), {}),
+             ("clip_accumulate_dense_batched", ([A, A + 1], [G, G + 1], 1.0, n, [W, W + 1], [None, b]), {}),
+             ("clip_accumulate_dense_batched", ([A], [G], 1.0, n, [W]), {}),
+             ("sqnorms_embedding", (ids, G, 5, False, n), {}), ("clip_accumulate_embedding", (ids, G, 5, 1.0, n, E), {}),
+             ("sqnorms_tied_embedding", (ids, G, H, dL, n), {}), ("clip_accumulate_tied_embedding", (ids, G, H, dL, 1.0, n, E), {}),
+             ("noise_adamw", (W, W + 1, W + 2, W + 3), adam), ("noise_adamw", (W, W + 1, W + 2, W + 3), dict(adam, n=7, elem_offset=1 << 33, eps=1e-8, zero_sum=True)),
+             ("noise_adamw_snr", (W, W + 1, W + 2, W + 3, n), dict(adam, n=None, zero_sum=False))]
+    tried, wrong = 0, []
+    for name, args, kw in calls:
+        both = [lambda *a, **k: getattr(ctx, name)(*a, **k), lambda *a, **k: getattr(binding, "dp_" + name)(ctx.handle, *a, **k)]
+        accepted.clear()
+        got, want = (_outcome(lambda: g(*args, **kw), lines) for g in both)
+        assert got == want and got[0] == "" and len(got[1]) == 1, (name, got, want)
+        assert accepted == [True], name   # (the extension did it, and not the function behind it)
+        for at in list(range(len(args))) + sorted(kw):
+            for odd in _odd_values(args[at] if isinstance(at, int) else kw[at]):
+                a = args if not isinstance(at, int) else args[:at] + (odd,) + args[at + 1:]
+                k = kw if isinstance(at, int) else dict(kw, **{at: odd})
+                got, want = (_outcome(lambda: g(*a, **k), lines) for g in both)
+                tried += 1
+                if got != want:
+                    wrong.append(f"{name}, argument {at} = {str(odd)[:60]!r}: {got}, not {want}")
+    assert tried > 800
+    assert not wrong, "\n".join(wrong)
+
+
+def test_frequent_calls_are_those_of_the_functions_behind_them(stubbed):
+    """Every method that has a form in the extension: an ordinary call is accepted there and is, argument for argument, the call that the
+    Python function makes; with odd values in place of each argument in turn, too, or it is refused in the same way."""
+    stubbed("frequent_calls")
 
 
 if __name__ == "__main__":
