@@ -1248,10 +1248,22 @@ def test_embedding_norms_are_exact_whatever_shares_the_ranking(dp, B, T, d):
     assert torch.equal(n, want)
 
 
-def test_step_driver_in_cpp_is_the_one_in_python(dp):
+def test_step_driver_in_cpp_is_the_one_in_python(dp, monkeypatch):
     """Both walks over a manifest with every kind of layer, inputs shared by two and by three layers, with and without bias, in two
-    types, make the same calls in the same order: the same bits; then a second micro-batch, and one whose gradients were not kept."""
+    types: the same bits; then a second micro-batch, and one whose gradients were not kept.  The extension does all of the first walk."""
     import paper_2108_01624_amd as pkg
+    from paper_2108_01624_amd import binding
+
+    taken, native = [], binding._native
+
+    class Seen:
+        def __getattr__(self, name):
+            def call(*a):
+                got = getattr(native, name)(*a)
+                taken.append((name, got is not None))
+                return got
+
+            return call
 
     class Walked(pkg.Context):   # (the driver hands only a plain context to the extension)
         pass
@@ -1294,6 +1306,7 @@ def test_step_driver_in_cpp_is_the_one_in_python(dp):
         return out
 
     one, two = batch(1), batch(2)
+    monkeypatch.setattr(binding, "_native", Seen())
     with pkg.Context() as plain, Walked() as walked:
         got = []
         for ctx in (plain, walked):
@@ -1304,9 +1317,11 @@ def test_step_driver_in_cpp_is_the_one_in_python(dp):
             run.pass2(two, 1.0)
             run.pass2(one, 1.0)   # (with the norms of the other one, and LayerNorm gradients that are not its own)
             ctx.sync()
-            got.append((norms, run.S.clone(), bool(run._kept_for)))
+            got.append((norms, run.S.clone(), type(run._kept_for), [x for x in taken if x[0] in ("pass1", "pass2")]))
+            taken.clear()
     assert all(torch.equal(a, b) for a, b in zip(got[0][0], got[1][0])) and torch.equal(got[0][1], got[1][1])
-    assert got[0][2] and got[1][2] and bool(got[0][1].any())
+    assert got[0][2] is bytes and got[1][2] is tuple and bool(got[0][1].any())
+    assert got[0][3] == [("pass1", True), ("pass2", True)] * 2 + [("pass2", True)] and got[1][3] == []
 
 
 @pytest.mark.parametrize("n,B,T,d_in,d_out", [(40, 3, 96, 776, 1032), (36, 18, 18, 640, 640), (12, 6, 38, 2576, 1160), (70, 2, 32, 1024, 520)])

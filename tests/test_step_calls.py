@@ -249,5 +249,102 @@ def test_frequent_calls_are_those_of_the_functions_behind_them(stubbed):
     stubbed("frequent_calls")
 
 
+def both_walks():
+    import random
+
+    import torch
+
+    pkg, context, lines = _package()
+    from paper_2108_01624_amd import binding
+
+    native, taken = binding._native, []
+
+    class Seen:
+        def __getattr__(self, name):
+            def call(*a):
+                got = getattr(native, name)(*a)
+                if name in ("pass1", "pass2"):
+                    taken.append(got is not None)
+                return got
+
+            return call
+
+    binding._native = Seen()
+
+    class Walked(pkg.Context):   # (the driver hands only a plain context to the extension)
+        pass
+
+    rng = random.Random(5)
+    B, T, M = 4, 6, 3
+
+    def layer(pool):
+        """(manifest entry, layer of a batch of B) of any kind, now and then reading an input that another layer reads."""
+        dt = rng.choice([torch.bfloat16, torch.float32])
+        h, o = rng.choice([8, 16]), rng.choice([8, 24])
+        z = lambda *s: torch.zeros(*s).to(dt)
+        kind = rng.choice(["dense"] * 4 + ["layernorm", "embedding", "position", "tied_embedding"])
+        if kind == "dense":
+            A, bias = rng.choice(pool.setdefault((h, dt), []) + [z(B, T, h)]), rng.random() < 0.6
+            pool[h, dt].append(A)
+            return Spec((h, o), *([(o,)] if bias or rng.random() < 0.2 else [])), dict(kind=kind, A=A, G=z(B, T, o), has_bias=rng.choice([bias, int(bias)]))
+        if kind == "layernorm":
+            w = rng.choice([8, 8, 16, 6])
+            return Spec((w,), (w,)), dict(kind=kind, X=z(B, T, w), G=z(B, T, w))
+        ids = torch.zeros(B, T, dtype=torch.int32)
+        if kind == "tied_embedding":
+            return Spec((9, h)), dict(kind=kind, ids=ids, G=z(B, T, h), H=z(B, M, h), dL=z(B, M, 9))
+        return Spec((T + 1, h)), dict(kind="embedding", ids=ids, G=z(B, T, h), V=T + 1, distinct=kind == "position")
+
+    def walks(man, calls):
+        """The outcomes of the calls on a runner of each kind; buffers of the two by their place in it."""
+        out = []
+        for cls in (pkg.Context, Walked):
+            run = pkg.StepRunner(context(cls), man, B, device="cpu")
+            place = lambda: {hex(p.data_ptr() + 4 * k): f"{n}+{k}" for n, p in
+                             [("S", run.S), ("sq", run.sqnorms)] + [(f"keep{j}", x) for j, x in sorted(run.ln_keep.items())] for k in (range(p.numel()) if n == "S" else [0])}
+            got = []
+            for c in calls:
+                name, text = _outcome(lambda: c(run), lines)
+                at = place()
+                got.append((name, [re.sub(r"0x[0-9a-f]+", lambda m: at.get(m.group(), m.group()), x) for x in text]))
+            out.append(got)
+        return out
+
+    wrong = []
+    for trial in range(150):
+        pool, man, one, two = {}, [], [], []
+        for _ in range(rng.choice([1, 2, 3, 8, 20])):
+            spec, l = layer(pool)
+            man.append(spec)
+            one.append(l)
+        two = [{k: v.clone() if isinstance(v, torch.Tensor) else v for k, v in l.items()} for l in one]
+        short = [{k: v[:2] if isinstance(v, torch.Tensor) else v for k, v in l.items()} for l in one]
+        taken.clear()
+        got, want = walks(man, [lambda r: r.pass1(one), lambda r: r.pass2(one, 1.0), lambda r: r.pass1(two), lambda r: r.pass2(two, 0.5), lambda r: r.pass2(one, 1.0),
+                                lambda r: r.pass1(short), lambda r: r.pass2(short, 2), lambda r: r.pass1(one), lambda r: r.pass2(one, 1.0)])
+        assert got == want, next((i, a, b) for i, (a, b) in enumerate(zip(got, want)) if a != b)
+        assert taken == [True] * 9 and all(name == "" and text for name, text in got), (taken, got)
+        # one value of one layer is another: accepted or refused by both
+        for _ in range(12):
+            k = rng.randrange(len(one))
+            key = rng.choice(sorted(one[k]))
+            bad = rng.choice(_odd_values(one[k][key]))
+            if key == "kind":
+                bad = rng.choice(["dense", "layernorm", "tied_embedding", "embedding", "", None, 3])
+            other = one[:k] + [dict(one[k], **{key: bad})] + one[k + 1:]
+            if rng.random() < 0.1:
+                other = one[:k] + [{x: v for x, v in one[k].items() if x != key}] + one[k + 1:]
+            for a, b, which in zip(*walks(man, [lambda r: r.pass1(other), lambda r: r.pass2(other, 1.0)]), ("pass1", "pass2")):
+                if a != b:
+                    wrong.append(f"{which}, {key} of {one[k]['kind']} = {str(bad)[:60]!r}: {a}, not {b}")
+    assert not wrong, "\n".join(wrong)
+
+
+def test_both_walks_make_the_same_calls(stubbed):
+    """Manifests of layers of every kind, widths, types, shared inputs and biases: the extension takes them and makes the calls that the walk in Python
+    makes, in the same order (kept LayerNorm gradients included); layers with an odd value are refused, or taken, by both."""
+    stubbed("both_walks")
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]]()
