@@ -8,6 +8,7 @@ import os
 from ctypes import c_char_p, c_float, c_int, c_size_t, c_uint64, c_void_p
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libdpclip.so")
+_NATIVE_PATH = os.path.join(os.path.dirname(_LIB_PATH), "_native.so")
 _lib = None
 _native = None  # the extension module: the same calls with their arguments read in C++ (see csrc/native.cpp)
 _float32 = _bfloat16 = _int32 = None  # torch's dtype objects, bound with the library
@@ -85,7 +86,7 @@ class DpError(RuntimeError):
 
 
 def load_library():
-    """dlopen libdpclip.so and declare the prototypes.  Raises if it has not been built."""
+    """dlopen libdpclip.so, declare the prototypes and import the extension over it.  Raises if either has not been built."""
     global _lib, _native
     if _lib is not None:
         return _lib
@@ -93,16 +94,19 @@ def load_library():
     # the tensors' memory and streams instead of pulling in a second copy.
     _bind_types()
 
-    if not os.path.exists(_LIB_PATH):
-        raise RuntimeError(f"{_LIB_PATH} is missing: build it with `python -m paper_2108_01624_amd.build` "
-                           "(there is no fallback path)")
+    build = "build it with `python -m paper_2108_01624_amd.build` (hipcc, g++ and the headers of torch and Python; there is no fallback path)"
+    for path in (_LIB_PATH, _NATIVE_PATH):
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is missing: {build}")
     lib = ctypes.CDLL(_LIB_PATH)
     for name, argtypes in SIGNATURES.items():
         fn = getattr(lib, name)
         fn.argtypes = argtypes
         fn.restype = _RESTYPES.get(name, c_int)
-    from . import _native as native
-
+    try:
+        from . import _native as native
+    except ImportError as e:
+        raise RuntimeError(f"{_NATIVE_PATH} does not load beside this torch, Python and libdpclip.so: {build}") from e
     _native = native
     _lib = lib
     return lib

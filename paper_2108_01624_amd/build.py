@@ -57,30 +57,31 @@ def _compile_native() -> str:
     return obj
 
 
-def _link_native(obj):
-    """Finds libdpclip.so beside itself; libtorch is in the process before it is imported."""
+def _link_native(obj, lib, out):
+    """Finds libdpclip.so (here `lib`, which bears that name inside) beside itself; libtorch is in the process before it is imported."""
     import torch
 
-    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    _run(["g++", "-shared", "-o", NATIVE_PATH + ".tmp", obj, "-L" + PKG_DIR, "-l:libdpclip.so", "-Wl,-rpath,$ORIGIN", "-L" + lib,
-          "-ltorch_python", "-ltorch_cpu", "-lc10"], "link of _native.so")
-    os.replace(NATIVE_PATH + ".tmp", NATIVE_PATH)
+    top = os.path.join(os.path.dirname(torch.__file__), "lib")
+    _run(["g++", "-shared", "-o", out, obj, lib, "-Wl,-rpath,$ORIGIN", "-L" + top, "-ltorch_python", "-ltorch_cpu", "-lc10"],
+         "link of _native.so")
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compile every source and link the shared library; always rebuilds."""
+    """Compile every source and link the shared library and the extension; always rebuilds.  Neither file is replaced before both are
+    linked: the extension has the library's argument lists compiled in."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, os.cpu_count() or 1)) as ex:
         native = ex.submit(_compile_native)
         objs = list(ex.map(_compile, SOURCES))
         native = native.result()
-    tmp = LIB_PATH + ".tmp"
+    lib, ext = LIB_PATH + ".tmp", NATIVE_PATH + ".tmp"
     # (the name that whoever links against it finds it by, whatever the file is called while it is written)
-    _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-soname,libdpclip.so", "-o", tmp] + objs, "link")
-    os.replace(tmp, LIB_PATH)
-    _link_native(native)
+    _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-soname,libdpclip.so", "-o", lib] + objs, "link")
+    _link_native(native, lib, ext)
+    os.replace(lib, LIB_PATH)
+    os.replace(ext, NATIVE_PATH)
     if verbose:
-        print("built", LIB_PATH, file=sys.stderr)
+        print("built", LIB_PATH, "and", NATIVE_PATH, file=sys.stderr)
     return LIB_PATH
 
 

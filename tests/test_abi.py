@@ -13,7 +13,7 @@ def lib():
     import paper_2108_01624_amd as pkg
     from paper_2108_01624_amd import build
 
-    if not os.path.exists(build.LIB_PATH):
+    if not os.path.exists(build.LIB_PATH) or not os.path.exists(build.NATIVE_PATH):
         build.build_library()
     return pkg.load_library()
 
@@ -312,3 +312,56 @@ def test_step_runner_refuses_what_the_addresses_cannot_carry():
     run.S = full.double()
     with pytest.raises(TypeError):
         run.pass2(layer(A, G), 1.0)
+
+
+@pytest.mark.parametrize("native", ["missing", "unreadable"])
+def test_loading_without_the_extension_says_how_to_build_it(lib, tmp_path, native):
+    """A library whose extension is not there, or cannot be loaded, is refused with the instruction that a missing library gets."""
+    import shutil
+    import subprocess
+    import sys
+
+    from paper_2108_01624_amd import build
+
+    top = tmp_path / "paper_2108_01624_amd"
+    top.mkdir()
+    for f in os.listdir(build.PKG_DIR):
+        if f.endswith(".py"):
+            shutil.copy(os.path.join(build.PKG_DIR, f), top / f)
+    shutil.copy(build.LIB_PATH, top / "libdpclip.so")
+    if native == "unreadable":
+        (top / "_native.so").write_text("not a library")
+    code = ("import paper_2108_01624_amd as pkg\n"
+            "try:\n    pkg.load_library()\n"
+            "except RuntimeError as e:\n    print('REFUSED', e, type(e.__cause__).__name__)\n")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=tmp_path, timeout=600, env=dict(os.environ, PYTHONPATH=str(tmp_path)))
+    assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
+    assert "REFUSED" in r.stdout and "_native.so" in r.stdout and "python -m paper_2108_01624_amd.build" in r.stdout, r.stdout
+    assert r.stdout.rstrip().endswith("ImportError" if native == "unreadable" else "NoneType")
+
+
+@pytest.mark.parametrize("step", ["link of _native.so", "link"])
+def test_a_build_that_fails_replaces_neither_file(monkeypatch, tmp_path, step):
+    """A link that fails leaves the library and the extension of the last build, which fit one another."""
+    from paper_2108_01624_amd import build
+
+    for name in ("LIB_PATH", "NATIVE_PATH"):
+        path = str(tmp_path / os.path.basename(getattr(build, name)))
+        open(path, "w").write("old")
+        monkeypatch.setattr(build, name, path)
+    monkeypatch.setattr(build, "BUILD_DIR", str(tmp_path / "_build"))
+    monkeypatch.setattr(build, "_compile", lambda src: src)
+    monkeypatch.setattr(build, "_compile_native", lambda: "native.o")
+
+    def run(cmd, what):
+        if what == step:
+            raise RuntimeError(f"{what} failed")
+        open(cmd[cmd.index("-o") + 1], "w").write("new")
+
+    monkeypatch.setattr(build, "_run", run)
+    with pytest.raises(RuntimeError, match="failed"):
+        build.build_library()
+    assert open(build.LIB_PATH).read() == open(build.NATIVE_PATH).read() == "old"
+    step = "none"
+    build.build_library()
+    assert open(build.LIB_PATH).read() == open(build.NATIVE_PATH).read() == "new"
