@@ -93,7 +93,8 @@ const char* dp_last_error(const dp_ctx* ctx);
  * DP_PATH_GRAM evaluates sum_{t,s} (a_t.a_s)(g_t.g_s) from the two T x T Gram matrices;
  * DP_PATH_MATERIALISE forms A_i^T G_i tile by tile and sums the squares; DP_PATH_AUTO picks by
  * dp_choose_path, but materialises bf16 layers of so few examples that the Gram kernels would leave the chip idle.  Both give the same
- * value up to fp32 rounding order. */
+ * value up to fp32 rounding order.  The choice looks at all sizes of a call, examples and layers among them, so that an example's norm
+ * may be rounded differently in a short last micro-batch than in a full one (the same call gives the same bits). */
 dp_status dp_sqnorms_dense(dp_ctx* ctx, const void* A, const void* G, dp_dtype dtype, int B, int T, int d_in,
                            int d_out, int has_bias, dp_path path, float* sqnorms);
 
@@ -288,7 +289,8 @@ dp_status dp_zero_f32(dp_ctx* ctx, float* p, uint64_t n);
 dp_status dp_philox_u32(dp_ctx* ctx, uint32_t* out, uint64_t n, uint64_t elem_offset, uint64_t seed, uint64_t step);
 /* The standard normals z that dp_noise_adamw draws for elements [elem_offset, elem_offset + n). */
 dp_status dp_normal_f32(dp_ctx* ctx, float* out, uint64_t n, uint64_t elem_offset, uint64_t seed, uint64_t step);
-/* Host-only, pure: the path of fewer operations for this shape, which DP_PATH_AUTO takes unless examples are few (HOST pointer out). */
+/* Host-only, pure: the path of fewer operations for this shape, which DP_PATH_AUTO takes unless the examples of a bf16 call are few
+ * (see dp_sqnorms_dense; the number of examples and layers is not among these arguments).  HOST pointer out. */
 dp_status dp_choose_path(int T, int d_in, int d_out, dp_dtype dtype, dp_path* out);
 /* Host-only, pure: how the Gram path cuts the T x T plane of an example (128 < T <= 2048) into the units its workgroups
  * take.  The plane is nblk x nblk cells of 128 x 128, nblk = ceil(T / 128); only cells (r, c) with r <= c are formed.

@@ -413,8 +413,7 @@ __global__ __launch_bounds__(256) void reduce_partials_pair_kernel(const float4*
 // One wave walking all positions of its columns was a chain of T / 8 round trips: B = 23, T = 375, d = 832: 61 -> 23 us;
 // B = 512, T = 128, d = 1024 (134 MB): 31 + 5 -> 28.  Where there are two waves and more to 64 positions they share the comparisons of the ranking, and the
 // joining finds out which parts continue one another for all parts at once (B = 74, T = 295, d = 128, norms and sums 37.7 -> 35.6 us; B = 23, T = 375, d = 832 40.9 -> 38.6).
-// (32 rows in flight instead of 16: 5 to 8 % slower throughout.)  Waves without positions would only make the joining of the parts longer: T = 16,
-// d = 256, B = 4 12 us with 16 waves, 6 with 1; B = 514 16 | 7.
+// Waves without positions would only make the joining of the parts longer: T = 16, d = 256, B = 4 12 us with 16 waves, 6 with 1; B = 514 16 | 7.
 // ------------------------------------------------------------------------------------------------
 // Rows in flight of a wave; without runs to form, position rows of B = 256, T = 128, d = 1,024 take 12.6 us with 8 and 11.4 with 16.
 constexpr int emb_ahead(bool distinct) { return distinct ? 16 : 8; }
