@@ -326,10 +326,17 @@ __global__ __launch_bounds__(64 * WAVES, WGS_PER_CU * WAVES / 4) void gram_dma_k
                 gram_dma16<!RAGGED>(rs, __builtin_amdgcn_readfirstlane(ldsoff[j] + ibuf * (STAGE * 2)), v, so);
             }
         };
+        const bool past = !EXACT && st >= nch;
         if (isA) run(rA, voffA, soff);
-        else if (!EXACT && st >= nch) run(rG, voffG, 0x7FFFFFF0);  // past the end: reads zeros, keeps the load count uniform
-        else if (which == 0) run(rG, voffG, soff);
-        else if (which == 1) run(rG2, voffG, soff);
+        else if (past || which == 0) {
+            if constexpr (EXACT) {
+                run(rG, voffG, soff);
+            } else {  // past the end: a resource of no bytes reads zeros and keeps the load count uniform (a scalar offset is not range-checked)
+                gram_i32x4 rg = rG;
+                rg[2] = past ? 0 : rG[2];
+                run(rg, voffG, soff);
+            }
+        } else if (which == 1) run(rG2, voffG, soff);
         else run(rG3, voffG, soff);
         ibuf = ibuf + 1 == NS ? 0 : ibuf + 1;
     };
